@@ -70,7 +70,7 @@ __device__ long long g_tail_fine[8 * 64];
 
 // One tile: rows row0 .. row0 + 32*PB - 1 of the compact list of active pixels (M rows exist).
 template <int NCT, int PB, bool CS>  // NCT column tiles of 256 output channels (cout = 256 * NCT); CS: channel mask
-__device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, const int M) {
+__device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, const int M, const unsigned touched) {
   using namespace tail;
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int COUT = 256 * NCT;
@@ -234,6 +234,7 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
 
   // ---- the 3x3 -----------------------------------------------------------------------------------------------
   vm_wait<0>();  // everything issued so far (weights 0-2, activations 0-2 of this wave) has landed
+  l2_touched(touched);
   lds_wait();    // the tables written above
   wg_barrier();  // ... and everybody else's
   TAIL_STAMP(1);
@@ -439,6 +440,8 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
 template <int NCT, bool CS>
 __global__ __launch_bounds__(tail::kThreads) void k_tail(const TailArgs a) {
   using namespace tail;
+  // (a body's blocks bring cold weights: 43.3 -> 36.5 us per launch in a ResNet-101 body, batch 128, ratio 0.5)
+  const unsigned touched = l2_touch(a.wpacked, (kSl2 + NCT * kKch) * kSliceChunks * 16, kThreads);
   const int SS = a.S * a.S, b32 = blockIdx.x * 32;
   const int M = *a.count * SS;
   const int t32 = (M + 31) >> 5;
@@ -455,11 +458,15 @@ __global__ __launch_bounds__(tail::kThreads) void k_tail(const TailArgs a) {
     }
   }
   const int row0 = b32 * pb;
-  if (row0 >= M) return;
+  if (row0 >= M) {
+    vm_wait<0>();
+    l2_touched(touched);
+    return;
+  }
   switch (pb) {
-    case 1: tail_tile<NCT, 1, CS>(a, row0, M); break;
-    case 2: tail_tile<NCT, 2, CS>(a, row0, M); break;
-    default: tail_tile<NCT, 3, CS>(a, row0, M); break;
+    case 1: tail_tile<NCT, 1, CS>(a, row0, M, touched); break;
+    case 2: tail_tile<NCT, 2, CS>(a, row0, M, touched); break;
+    default: tail_tile<NCT, 3, CS>(a, row0, M, touched); break;
   }
 }
 

@@ -26,6 +26,20 @@ __device__ __forceinline__ void vm_wait() {
 __device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "memory"); }
 __device__ __forceinline__ void lds_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// Requests one 128-byte line per thread of the weights a launch streams, so that they are on their way into this XCD's
+// L2 before the tiles ask for them slice by slice: workgroups go round-robin over the eight XCDs, so
+// workgroup b takes piece b/8 (kThreads lines) of the range.  In a model every block brings weights of its own, which no
+// earlier launch has left in the L2.  Returns the register the load writes: it must stay reserved -- l2_touched() -- until
+// a wait that covers it.
+__device__ __forceinline__ unsigned l2_touch(const void* base, int bytes, int threads) {
+  unsigned r = 0;
+  const int line = (int)(blockIdx.x >> 3) * threads + (int)threadIdx.x;
+  if (line * 128 < bytes)
+    asm volatile("global_load_dword %0, %1, off" : "=v"(r) : "v"((const char*)base + (size_t)line * 128) : "memory");
+  return r;
+}
+__device__ __forceinline__ void l2_touched(unsigned r) { asm volatile("" ::"v"(r)); }
+
 __device__ __forceinline__ f32x16 mma_bf16(const u32x4& first, const uint4& second, f32x16 acc) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, first), __builtin_bit_cast(bf16x8, second),
                                                  acc, 0, 0, 0);
