@@ -33,20 +33,13 @@
 //
 // Accumulation is float32 (bf16: v_mfma_f32_32x32x16_bf16, fp32: v_mfma_f32_32x32x2_f32).
 #include "laud_common.h"
+#include "laud_gemm.h"
 #include "laud_tail_pack.h"
 
 #include <algorithm>
 #include <atomic>
 
 namespace laud {
-
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef const __attribute__((address_space(1))) u32x4* gptr16;  // 16-byte chunk in global memory
-
-enum { M_CONV1 = 0, M_CONV2 = 1, M_CONV3 = 2, M_CS1 = 3, M_CS2 = 4, M_CS3 = 5, M_DENSE1 = 6, M_U1 = 7, M_U2 = 8, M_U3 = 9,
-       M_SD1 = 10, M_SD2 = 11, M_SD3 = 12, M_G2 = 13 };
 
 // 256 bytes of zeros in device memory: the source of the zero chunks of the pointer-based weight gather
 // of channel skipping (every other load gets its zeros from the buffer descriptor's range check).  Not
@@ -55,52 +48,6 @@ enum { M_CONV1 = 0, M_CONV2 = 1, M_CONV3 = 2, M_CS1 = 3, M_CS2 = 4, M_CS3 = 5, M
 __device__ uint4 g_zero_page[16];
 
 constexpr int kMaxGroups = 1024;  // channel-skip decisions per sample the kernels can hold in LDS
-
-struct GemmArgs {
-  const void* A;         // activations the rows are gathered from
-  const void* Wt;        // weights [Ncols][ldw]
-  const float* scale;    // per-output-channel affine
-  const float* shift;
-  void* Out;
-  const void* Res;       // residual (CONV3 / CS3); may alias Out
-  const int32_t* count;  // device: number of units (pixels for CONV1, patches for CONV2/3)
-  const int32_t* list;   // device: pixel ids (CONV1) or active patch ids (CONV2/3)
-  const uint8_t* cmask;  // CS: [N][D]
-  int K;                 // reduction length per tap (full width)
-  int ldw;               // weight row stride, elements
-  int Ncols;             // output channels (full width)
-  int H, W, S;
-  int lda;               // A row stride, elements
-  int ldo;               // Out/Res row stride, elements
-  int relu;
-  int D, G;              // CS: groups per sample, channels per group
-  int row_tiles, col_tiles;
-  int group_rows, tiles_per_group;  // CONV1: pixel lists are kept per group of samples
-  int m_rows;            // DENSE1, SD1..3: number of rows (all output pixels), known on the host
-  int stride, Ho, Wo;    // SD1, SD2: spatial stride and output size (H, W are the input size)
-  int gw;                // G2: channels per group of the 3x3
-  // Workgroups past the tiles (CONV1 / DENSE1 launches only) copy the block's w2 / w3 into the fused tail kernel's
-  // streaming order while the first 1x1 runs; pk_out == null: none.
-  const void* pk_w2; const void* pk_w3; void* pk_out; int pk_chunks; int pk_first_block;
-  const float* wmask;    // DENSE1: masker weights [K] or null
-  float* proj;           // DENSE1: per-pixel masker projection sum_c w[c]*x[pixel][c], [m_rows]
-};
-
-// ---- one 16-byte fragment pair -> MFMA ------------------------------------------------------
-template <typename ET>
-__device__ __forceinline__ void mma16(f32x16& acc, const uint4& a, const uint4& b) {
-  if constexpr (sizeof(ET) == 2) {
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc,
-                                                  0, 0, 0);
-  } else {
-    // Four k-steps of the 32x32x2 fp32 MFMA; lane group l/32 holds k-slots {4h..4h+3} of this
-    // 8-wide K group for A and B alike, so the pairing of A and B elements is consistent.
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
-  }
-}
 
 // Element-wise form of the kept-channel gather for group widths that do not fill a 16-byte chunk: the
 // elements at offsets eoff[] of a weight row; every load is issued (an element that must read as zero has a valid
@@ -136,16 +83,6 @@ __device__ __forceinline__ uint4 mask_tail(uint4 v, int nvalid) {
     if (e >= nvalid) tmp[e] = (ET)0;
   __builtin_memcpy(&v, tmp, 16);
   return v;
-}
-
-// first position of a sorted list whose value is not below `key`
-__device__ __forceinline__ int lower_bound_dev(const int32_t* v, int n, int key) {
-  int lo = 0, hi = n;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (v[mid] < key) lo = mid + 1; else hi = mid;
-  }
-  return lo;
 }
 
 template <int MODE, typename ET, int BM, int BN, int WGN>
@@ -186,7 +123,6 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
   const int HW = a.H * a.W, SS = a.S * a.S;
   // Dynamic blocks with a spatial stride (a.stride > 1) keep their mask on the output grid Ho x Wo;
   // everywhere else the output grid is the input grid.
-  const int sy = a.stride > 1 ? a.stride : 1;
   const int oH = a.stride > 1 ? a.Ho : a.H, oW = a.stride > 1 ? a.Wo : a.W;
   const int Hp = oH / a.S, Wp = oW / a.S;
   const ET* __restrict__ Ap = (const ET*)a.A;
@@ -284,40 +220,8 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
     voffA[i] = 0;
     amask[i] = 0;
     if (rho < M) {
-      size_t pixrow;  // row of A (pixel id or compact row)
-      int y = 0, x = 0;
-      if constexpr (MODE == M_CONV1) {
-        pixrow = (size_t)listp[rho];
-      } else if constexpr (MODE == M_CONV3 || MODE == M_DENSE1 || MODE == M_U1 || MODE == M_U3) {
-        pixrow = (size_t)rho;
-      } else if constexpr (MODE == M_SD3) {
-        pixrow = (size_t)rho;
-      } else if constexpr (MODE == M_SD1 || MODE == M_SD2) {
-        // row = output pixel (n, yo, xo); the input pixel under it (centre of the 3x3) is (yo*stride, xo*stride)
-        const int n = rho / (a.Ho * a.Wo), r2 = rho - n * (a.Ho * a.Wo);
-        y = (r2 / a.Wo) * a.stride;
-        x = (r2 % a.Wo) * a.stride;
-        pixrow = (size_t)n * HW + (size_t)y * a.W + x;
-      } else if constexpr (MODE == M_U2) {
-        // row = (patch p, pixel j of the patch); its centre inside the gathered (S+2) x (S+2) tile
-        const int E = a.S + 2;
-        const int p = rho / SS, j = rho - p * SS;
-        pixrow = (size_t)p * E * E + (size_t)(j / a.S + 1) * E + (j % a.S + 1);
-      } else if constexpr (MODE == M_CONV2 || MODE == M_G2) {
-        const int p = rho / SS, j = rho - p * SS;
-        const int q = a.list[p];
-        const int n = q / (Hp * Wp), r2 = q - n * (Hp * Wp);
-        const int py = r2 / Wp, px = r2 - py * Wp;
-        y = (py * a.S + j / a.S) * sy;  // centre of the 3x3 on the input grid
-        x = (px * a.S + j % a.S) * sy;
-        pixrow = (size_t)n * HW + (size_t)y * a.W + x;
-      } else if constexpr (MODE == M_CS2) {
-        y = rho / a.W;
-        x = rho - y * a.W;
-        pixrow = (size_t)sample * HW + rho;
-      } else {  // CS1, CS3
-        pixrow = (size_t)sample * HW + rho;
-      }
+      int y, x;
+      const size_t pixrow = source_row<MODE>(a, rho, listp, sample, Hp, Wp, y, x);
       voffA[i] = (unsigned)((pixrow * a.lda + cc * EPC + (MODE == M_G2 ? col0 : 0)) * sizeof(ET));
       if constexpr (MODE == M_U2) {
         amask[i] = 0x1ffu;  // every tap lies inside the gathered tile
@@ -336,30 +240,7 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
   }
   if (tid < BM) {
     const int rho = row0 + tid;
-    int o = -1;
-    if (rho < M) {
-      if constexpr (MODE == M_CONV1) {
-        o = listp[rho];
-      } else if constexpr (MODE == M_CONV2 || MODE == M_DENSE1 || MODE == M_U2 || MODE == M_U3 || MODE >= M_SD1) {
-        o = rho;  // (G2 included)
-      } else if constexpr (MODE == M_U1) {
-        // gathered position (p, e): inside the image -> row rho, outside -> -2 - rho (stored as zeros)
-        const int E = a.S + 2;
-        const int p = rho / (E * E), e = rho - p * (E * E);
-        const int q = a.list[p];
-        const int r2 = q % (Hp * Wp);
-        const int yy = (r2 / Wp) * a.S - 1 + e / E, xx = (r2 % Wp) * a.S - 1 + e % E;
-        o = (yy >= 0 && yy < a.H && xx >= 0 && xx < a.W) ? rho : -2 - rho;
-      } else if constexpr (MODE == M_CONV3) {
-        const int p = rho / SS, j = rho - p * SS;
-        const int q = a.list[p];
-        const int n = q / (Hp * Wp), r2 = q - n * (Hp * Wp);
-        const int py = r2 / Wp, px = r2 - py * Wp;
-        o = n * (oH * oW) + (py * a.S + j / a.S) * oW + (px * a.S + j % a.S);
-      } else {
-        o = sample * HW + rho;
-      }
-    }
+    const int o = rho < M ? output_row<MODE>(a, rho, listp, sample, Hp, Wp) : -1;
     s_row[tid] = o;
     if constexpr (MODE == M_SD1) {
       // shortcut of a dynamic first block: the activation is applied here only where the branch will
@@ -889,6 +770,9 @@ static int launch_gemm(int dtype, const GemmArgs& a, long long cap_rows, int nsa
                               LAUD_STAGE_CS3,   LAUD_STAGE_CONV1, LAUD_STAGE_CONV1, LAUD_STAGE_CONV2, LAUD_STAGE_CONV3,
                               LAUD_STAGE_CONV1, LAUD_STAGE_CONV2, LAUD_STAGE_CONV3, LAUD_STAGE_CONV2};
   StageScope scope(kStage[MODE], st);
+  if constexpr (MODE == M_CONV2 || MODE == M_CONV3 || MODE == M_DENSE1 || (MODE >= M_SD1 && MODE <= M_SD3)) {
+    if (skinny_wanted(MODE, dtype, a, cap_rows)) return launch_skinny(MODE, dtype, a, cap_rows, st);
+  }
   return dtype == LAUD_BF16 ? launch_gemm_e<MODE, bf16_t>(a, cap_rows, nsamples, st)
                             : launch_gemm_e<MODE, float>(a, cap_rows, nsamples, st);
 }
@@ -1084,6 +968,7 @@ static int launch_conv2(int dtype, GemmArgs a, const laud_group_se* e, long long
   a.gw = e->group_width;
   a.ldw = 9 * e->group_width;
   StageScope scope(LAUD_STAGE_CONV2, st);
+  if (skinny_wanted(M_G2, dtype, a, cap_rows)) return launch_skinny(M_G2, dtype, a, cap_rows, st);
   return dtype == LAUD_BF16 ? launch_gemm_t<M_G2, bf16_t, 64, 64, 2>(a, cap_rows, 1, st)
                             : launch_gemm_t<M_G2, float, 64, 64, 2>(a, cap_rows, 1, st);
 }
@@ -1101,6 +986,16 @@ static bool head_wanted(int dtype, const laud_bottleneck* p) {
   return false;
 #endif
   return head_supported(dtype, p->c_in, p->c_mid);
+}
+// ... for a launch of (at most) `rows` rows: a workgroup of these kernels streams all weights, which takes 11 / 25 us however
+// few rows there are; up to kWideRows the small tiles of laud_skinny.hip are faster (stage-3 block: 46 against 27 us at one
+// image, 50 against 39 us at 16, equal at about 22).
+constexpr long long kWideRows = 4096;
+static bool tail_used(int dtype, const laud_bottleneck* p, const laud_group_se* e, long long rows) {
+  return tail_wanted(dtype, p, e) && rows > kWideRows;
+}
+static bool head_used(int dtype, const laud_bottleneck* p, long long rows) {
+  return head_wanted(dtype, p) && rows > kWideRows;
 }
 // Where the two parts lie in a block's packed weights (laud_pack_weights, or the workspace copy of a call).
 struct PackedLayout { size_t head, tail, bytes; };
@@ -1120,9 +1015,10 @@ static int pack_weights_into(int dtype, const laud_bottleneck* p, void* packed, 
   return rc;
 }
 // ... and then the first 1x1's launch carries the re-ordering of w2 / w3 for it in spare workgroups.
-static void attach_tail_pack(GemmArgs& a, int dtype, const laud_bottleneck* p, const laud_group_se* e, void* wpack) {
+static void attach_tail_pack(GemmArgs& a, int dtype, const laud_bottleneck* p, const laud_group_se* e, long long rows,
+                             void* wpack) {
   a.pk_out = nullptr;
-  if (!tail_wanted(dtype, p, e) || p->packed) return;
+  if (!tail_used(dtype, p, e, rows) || p->packed) return;
   a.pk_w2 = p->w2; a.pk_w3 = p->w3; a.pk_out = (char*)wpack + packed_layout(dtype, p).tail;
   a.pk_chunks = tail::packed_slices(p->c_out) * tail::kSliceChunks;
 }
@@ -1140,12 +1036,30 @@ static int launch_sparse_head(int dtype, const laud_bottleneck* p, const void* x
   return launch_head(h, st);
 }
 
+// Whether a dynamic block's first 1x1 runs on every pixel of the map instead of on the dilated active set: where the small
+// tiles take it, the launch is bound by its latency and not by its rows, and the pixel lists would cost a launch of
+// their own.
+static bool dense_conv1_wanted(int dtype, const laud_bottleneck* p, long long npix) {
+  GemmArgs a{};
+  a.K = p->c_in; a.Ncols = p->c_mid;
+  return skinny_wanted(M_SD1, dtype, a, npix);
+}
+static int run_dense_conv1(const laud_fmap& fx, const laud_bottleneck* p, const void* x, void* h1, hipStream_t st) {
+  GemmArgs a{};
+  a.H = fx.H; a.W = fx.W; a.S = 1; a.D = 1; a.G = 1; a.stride = 1; a.Ho = fx.H; a.Wo = fx.W;
+  a.A = x; a.Wt = p->w1; a.scale = p->s1; a.shift = p->t1; a.Out = h1; a.K = p->c_in; a.ldw = p->c_in;
+  a.Ncols = p->c_mid; a.lda = p->c_in; a.ldo = p->c_mid; a.relu = 1;
+  const long long npix = (long long)fx.N * fx.H * fx.W;
+  a.m_rows = (int)npix;
+  return launch_gemm<M_SD1>(fx.dtype, a, npix, 1, st);
+}
+
 // conv2 -> conv3 -> residual add as one kernel where laud_tail.hip covers the shape (h2 stays in LDS).
 // Returns 1 when that kernel was launched (*rc = its status), 0 when the caller has to run the two GEMMs.
 static int try_tail(int dtype, const laud_bottleneck* p, const laud_group_se* e, const void* h1, const void* res,
                     void* out, const int32_t* idx, const int32_t* count, int H, int W, int S, int stride, int Ho, int Wo,
                     long long cap_rows, void* wpack, hipStream_t st, int* rc) {
-  if (!tail_wanted(dtype, p, e)) return 0;
+  if (!tail_used(dtype, p, e, cap_rows)) return 0;
   TailArgs t{};
   t.h1 = h1; t.wpacked = (const char*)(p->packed ? p->packed : wpack) + packed_layout(dtype, p).tail; t.s2 = p->s2; t.t2 = p->t2; t.s3 = p->s3; t.t3 = p->t3;
   t.res = res; t.out = out; t.count = count; t.list = idx; t.H = H; t.W = W; t.S = S; t.stride = stride;
@@ -1183,32 +1097,35 @@ static int run_dyn_block(const void* x, laud_fmap fx, const laud_bottleneck* p, 
                        (uint4*)out, fx.H, fx.W, S, cpp, idx, count);
     if (check_launch() != LAUD_OK) return LAUD_ERR_HIP;
   }
-  // samples per group of the dilated pixel lists: about 1.5k pixels, so that a group's ragged last
-  // conv1 tile wastes little, and its patch masks fit in LDS
-  const int hw = fx.H * fx.W, pps = Hp * Wp;
-  int gs = (1536 + hw - 1) / hw;
-  if (gs > fx.N) gs = fx.N;
-  while (gs > 1 && (size_t)gs * pps > 60000) --gs;
-  const int ngroups = (fx.N + gs - 1) / gs;
-  {
-    StageScope scope(LAUD_STAGE_NEED, st);
-    hipLaunchKernelGGL(k_need, dim3(ngroups), dim3(kNeedThreads), align_up((size_t)gs * pps, 16), st, idx, count,
-                       fx.N, fx.H, fx.W, S, 1, fx.H, fx.W, gs, need_counts, pix);
-  }
-  if (check_launch() != LAUD_OK) return LAUD_ERR_HIP;
-
   GemmArgs a{};
   a.H = fx.H; a.W = fx.W; a.S = S; a.D = 1; a.G = 1; a.cmask = nullptr;
-  // conv1: gathered 1x1 over the dilated active set -> h1 at pixel positions
-  a.A = x; a.Wt = p->w1; a.scale = p->s1; a.shift = p->t1; a.Out = h1; a.Res = nullptr;
-  a.count = need_counts; a.list = pix; a.group_rows = gs * hw; a.K = p->c_in; a.ldw = p->c_in; a.Ncols = p->c_mid;
-  a.lda = p->c_in; a.ldo = p->c_mid; a.relu = 1;
-  if (!e && head_wanted(fx.dtype, p)) {
-    if ((rc = launch_sparse_head(fx.dtype, p, x, h1, pix, need_counts, gs * hw, ngroups, wsb + L.wpack, st)) != LAUD_OK) return rc;
+  if (dense_conv1_wanted(fx.dtype, p, npix) && !head_used(fx.dtype, p, npix)) {
+    if ((rc = run_dense_conv1(fx, p, x, h1, st)) != LAUD_OK) return rc;
   } else {
-    attach_tail_pack(a, fx.dtype, p, e, wsb + L.wpack);
-    if ((rc = launch_gemm<M_CONV1>(fx.dtype, a, (long long)gs * hw, ngroups, st)) != LAUD_OK) return rc;
-    a.pk_out = nullptr;
+    // samples per group of the dilated pixel lists: about 1.5k pixels, so that a group's ragged last
+    // conv1 tile wastes little, and its patch masks fit in LDS
+    const int hw = fx.H * fx.W, pps = Hp * Wp;
+    int gs = (1536 + hw - 1) / hw;
+    if (gs > fx.N) gs = fx.N;
+    while (gs > 1 && (size_t)gs * pps > 60000) --gs;
+    const int ngroups = (fx.N + gs - 1) / gs;
+    {
+      StageScope scope(LAUD_STAGE_NEED, st);
+      hipLaunchKernelGGL(k_need, dim3(ngroups), dim3(kNeedThreads), align_up((size_t)gs * pps, 16), st, idx, count,
+                         fx.N, fx.H, fx.W, S, 1, fx.H, fx.W, gs, need_counts, pix);
+    }
+    if (check_launch() != LAUD_OK) return LAUD_ERR_HIP;
+    // conv1: gathered 1x1 over the dilated active set -> h1 at pixel positions
+    a.A = x; a.Wt = p->w1; a.scale = p->s1; a.shift = p->t1; a.Out = h1; a.Res = nullptr;
+    a.count = need_counts; a.list = pix; a.group_rows = gs * hw; a.K = p->c_in; a.ldw = p->c_in; a.Ncols = p->c_mid;
+    a.lda = p->c_in; a.ldo = p->c_mid; a.relu = 1;
+    if (!e && head_used(fx.dtype, p, npix)) {
+      if ((rc = launch_sparse_head(fx.dtype, p, x, h1, pix, need_counts, gs * hw, ngroups, wsb + L.wpack, st)) != LAUD_OK) return rc;
+    } else {
+      attach_tail_pack(a, fx.dtype, p, e, npix, wsb + L.wpack);
+      if ((rc = launch_gemm<M_CONV1>(fx.dtype, a, (long long)gs * hw, ngroups, st)) != LAUD_OK) return rc;
+      a.pk_out = nullptr;
+    }
   }
   if (try_tail(fx.dtype, p, e, h1, x, out, idx, count, fx.H, fx.W, S, 1, fx.H, fx.W, npix, wsb + L.wpack, st, &rc)) return rc;
   // conv2: 3x3 over active patches, A rows fetched from h1 by index -> dense h2
@@ -1264,7 +1181,7 @@ extern "C" int laud_masker_dyn_bottleneck(const void* x, laud_fmap fx, const lau
   a.A = x; a.Wt = p->w1; a.scale = p->s1; a.shift = p->t1; a.Out = h1; a.Res = nullptr;
   a.count = nullptr; a.list = nullptr; a.K = p->c_in; a.ldw = p->c_in; a.Ncols = p->c_mid;
   a.lda = p->c_in; a.ldo = p->c_mid; a.relu = 1; a.m_rows = (int)npix; a.wmask = w; a.proj = proj;
-  if (head_wanted(fx.dtype, p)) {
+  if (head_used(fx.dtype, p, npix)) {
     // register-weight kernel; without caller-packed weights both parts are re-ordered here, ahead of it
     if (!p->packed && (rc = pack_weights_into(fx.dtype, p, wsb + L.wpack, true, true, st)) != LAUD_OK) return rc;
     HeadArgs h{};
@@ -1280,7 +1197,7 @@ extern "C" int laud_masker_dyn_bottleneck(const void* x, laud_fmap fx, const lau
     }
     if ((rc = launch_head(h, st)) != LAUD_OK) return rc;
   } else {
-    attach_tail_pack(a, fx.dtype, p, nullptr, wsb + L.wpack);
+    attach_tail_pack(a, fx.dtype, p, nullptr, npix, wsb + L.wpack);
     if ((rc = launch_gemm<M_DENSE1>(fx.dtype, a, npix, 1, st)) != LAUD_OK) return rc;
     a.pk_out = nullptr;
   }
@@ -1531,27 +1448,31 @@ static int run_dyn_projection(const void* x, laud_fmap fx, const laud_bottleneck
   a.list = idx; a.count = count;
   if ((rc = launch_gemm<M_SD1>(fx.dtype, a, nout, 1, st)) != LAUD_OK) return rc;
 
-  // input pixels the branch reads: the 3x3 windows (at the block's stride) of the active output pixels
-  const int hw = fx.H * fx.W, pps = Hp * Wp;
-  int gs = (1536 + hw - 1) / hw;
-  if (gs > fx.N) gs = fx.N;
-  while (gs > 1 && (size_t)gs * pps > 60000) --gs;
-  const int ngroups = (fx.N + gs - 1) / gs;
-  {
-    StageScope scope(LAUD_STAGE_NEED, st);
-    hipLaunchKernelGGL(k_need, dim3(ngroups), dim3(kNeedThreads), align_up((size_t)gs * pps, 16), st, idx, count,
-                       fx.N, fx.H, fx.W, S, stride, Ho, Wo, gs, need_counts, pix);
-  }
-  if (check_launch() != LAUD_OK) return LAUD_ERR_HIP;
-  // conv1 over that set -> h1 at input pixel positions
-  a.Wt = p->w1; a.scale = p->s1; a.shift = p->t1; a.Out = h1; a.Res = nullptr;
-  a.count = need_counts; a.list = pix; a.group_rows = gs * hw; a.Ncols = p->c_mid; a.ldo = p->c_mid; a.relu = 1;
-  if (!e && head_wanted(fx.dtype, p)) {
-    if ((rc = launch_sparse_head(fx.dtype, p, x, h1, pix, need_counts, gs * hw, ngroups, wsb + L.wpack, st)) != LAUD_OK) return rc;
+  if (dense_conv1_wanted(fx.dtype, p, npix) && !head_used(fx.dtype, p, npix)) {
+    if ((rc = run_dense_conv1(fx, p, x, h1, st)) != LAUD_OK) return rc;
   } else {
-    attach_tail_pack(a, fx.dtype, p, e, wsb + L.wpack);
-    if ((rc = launch_gemm<M_CONV1>(fx.dtype, a, (long long)gs * hw, ngroups, st)) != LAUD_OK) return rc;
-    a.pk_out = nullptr;
+    // input pixels the branch reads: the 3x3 windows (at the block's stride) of the active output pixels
+    const int hw = fx.H * fx.W, pps = Hp * Wp;
+    int gs = (1536 + hw - 1) / hw;
+    if (gs > fx.N) gs = fx.N;
+    while (gs > 1 && (size_t)gs * pps > 60000) --gs;
+    const int ngroups = (fx.N + gs - 1) / gs;
+    {
+      StageScope scope(LAUD_STAGE_NEED, st);
+      hipLaunchKernelGGL(k_need, dim3(ngroups), dim3(kNeedThreads), align_up((size_t)gs * pps, 16), st, idx, count,
+                         fx.N, fx.H, fx.W, S, stride, Ho, Wo, gs, need_counts, pix);
+    }
+    if (check_launch() != LAUD_OK) return LAUD_ERR_HIP;
+    // conv1 over that set -> h1 at input pixel positions
+    a.Wt = p->w1; a.scale = p->s1; a.shift = p->t1; a.Out = h1; a.Res = nullptr;
+    a.count = need_counts; a.list = pix; a.group_rows = gs * hw; a.Ncols = p->c_mid; a.ldo = p->c_mid; a.relu = 1;
+    if (!e && head_used(fx.dtype, p, npix)) {
+      if ((rc = launch_sparse_head(fx.dtype, p, x, h1, pix, need_counts, gs * hw, ngroups, wsb + L.wpack, st)) != LAUD_OK) return rc;
+    } else {
+      attach_tail_pack(a, fx.dtype, p, e, nout, wsb + L.wpack);
+      if ((rc = launch_gemm<M_CONV1>(fx.dtype, a, (long long)gs * hw, ngroups, st)) != LAUD_OK) return rc;
+      a.pk_out = nullptr;
+    }
   }
   if (try_tail(fx.dtype, p, e, h1, out, out, idx, count, fx.H, fx.W, S, stride, Ho, Wo, nout, wsb + L.wpack, st, &rc)) return rc;
   // conv2: strided 3x3 at the active output pixels -> dense h2
@@ -1560,7 +1481,7 @@ static int run_dyn_projection(const void* x, laud_fmap fx, const laud_bottleneck
   a.lda = p->c_mid; a.ldo = p->c_mid;
   if ((rc = launch_conv2(fx.dtype, a, e, nout, st)) != LAUD_OK) return rc;
   if (e && e->se_width > 0 &&
-      (rc = launch_se(fx.dtype, fx.N, pps, S * S, p->c_mid, e, h2, idx, count, (float*)h1, nout, st)) != LAUD_OK)
+      (rc = launch_se(fx.dtype, fx.N, Hp * Wp, S * S, p->c_mid, e, h2, idx, count, (float*)h1, nout, st)) != LAUD_OK)
     return rc;
   // conv3 added onto the shortcut already in `out`, at the active output pixels
   a.A = h2; a.Wt = p->w3; a.scale = p->s3; a.shift = p->t3; a.Out = out; a.Res = out;
@@ -1679,6 +1600,7 @@ extern "C" int laud_init(void) {
   if (rc != LAUD_OK) return rc;
   rc = gemm_init_device();
   if (rc != LAUD_OK) return rc;
+  if ((rc = skinny_init_device()) != LAUD_OK) return rc;
   if ((rc = tail_init_device()) != LAUD_OK) return rc;
   return head_init_device();
 }

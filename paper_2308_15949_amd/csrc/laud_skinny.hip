@@ -1,0 +1,463 @@
+// The convolutions of a block when there are few rows (small batches, single images): same modes and arguments as the
+// tiled kernel of laud_gemm.hip, built for latency instead of throughput.
+//
+// With a few hundred rows a 64- or 128-row tile leaves most of the chip idle while each workgroup walks its whole reduction
+// alone, slice after slice: what bounds such a launch is that serial chain (a 3x3 over 512 channels on one 7 x 7 image:
+// 13 x 4 tiles, 72 slices each, 29 us).  Here a workgroup takes a small output tile (32*TM rows x 32*TN columns) and its
+// NW waves SPLIT THE REDUCTION: wave w multiplies slices w, w+NW, ... (a slice: 128 bytes of every row of both operands) with
+// the loads of D slices in flight in registers and no barrier in the loop; the NW partial tiles meet in LDS once, are added
+// in wave order (fixed order: reproducible), and go through affine / residual / activation / rounding.
+//   A lane loads 16 bytes so that eight consecutive lanes take one row's 128 bytes (a wave instruction: 8 rows), and the
+// slice goes through a piece of LDS private to its wave into MFMA order.  Loading MFMA fragments straight from row-major
+// memory puts consecutive lanes into different rows, and the CU then takes 16 bytes per cycle instead of 45 to 64 (measured
+// 38 against 105 GB/s per CU).
+// The MFMA computes the transposed tile (weights first), so a lane holds 4 x 4 consecutive channels of one row.
+#include "laud_common.h"
+#include "laud_gemm.h"
+
+#include <atomic>
+
+namespace laud {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+// One 16-byte fragment pair: 16x16x32 bf16, or four k-steps of the 16x16x4 fp32 MFMA (lane group l/16 holds k-slots
+// 4q .. 4q+3 of the 16-wide K group for both operands, so their pairing is consistent).
+template <typename ET>
+__device__ __forceinline__ void mma4(f32x4& acc, const uint4& a, const uint4& b) {
+  if constexpr (sizeof(ET) == 2) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+  } else {
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
+  }
+}
+
+// A launch of this kind lives for a few microseconds, of which the instructions ahead of the first load are a good part
+// (sixteen waves of a workgroup share four SIMDs), so divisions by run-time values are multiplications with reciprocals made
+// on the host: exact for the row numbers launch_skinny admits (below 2^20; (n + 1/2) / d is at least 1 / 2d away from an
+// integer, the product's error is below n / d * 2^-22).
+struct SkinnyArgs {
+  GemmArgs g;
+  int cap_rows;               // rows (dense) or their upper bound (count on the device)
+  int kch, KT;                // slices per tap, slices
+  unsigned kmul;              // ceil(2^32 / kch), 0 for kch = 1
+  float inv_ss, inv_s, inv_pps, inv_wp, inv_howo, inv_wo, inv_rt;
+};
+__device__ __forceinline__ int fdiv(int n, float inv) { return (int)(((float)n + 0.5f) * inv); }
+
+template <int TM, int TN, int NW>
+__host__ __device__ constexpr int skinny_lds() {
+  constexpr int part = NW * 16 * TM * (16 * TN + 4) * 4, slices = NW * (16 * TM + 16 * TN) * 128;
+  return part > slices ? part : slices;
+}
+
+template <int MODE, typename ET, int TM, int TN, int NW, int D>
+__global__ __launch_bounds__(64 * NW) void k_skinny(const SkinnyArgs ka) {
+  const GemmArgs& a = ka.g;
+  constexpr int BM = 16 * TM, BN = 16 * TN, NT = 64 * NW;
+  constexpr int EPC = elem<ET>::per16, ES = (int)sizeof(ET), BKE = 8 * EPC;
+  constexpr bool TAPS = (MODE == M_CONV2 || MODE == M_SD2 || MODE == M_G2);
+  constexpr bool RES = (MODE == M_CONV3 || MODE == M_SD3);
+  constexpr bool LISTED = (MODE == M_CONV2 || MODE == M_CONV3 || MODE == M_G2);
+  constexpr int PSTR = BN + 4;  // floats per row of a partial tile
+  extern __shared__ __align__(16) unsigned char smem[];
+  // partial tiles [NW][BM][PSTR]; during the loop the same bytes are the waves' private slices [NW][(BM + BN) * 128 bytes]
+  float* const part = reinterpret_cast<float*>(smem);
+  float* const s_wm = reinterpret_cast<float*>(smem + skinny_lds<TM, TN, NW>());  // DENSE1: masker weights [K]
+  __shared__ unsigned s_voff[BM], s_bad[BM];
+  __shared__ int s_row[BM];
+  __shared__ unsigned char s_inact[MODE == M_SD1 ? BM : 1];
+  __shared__ float s_proj[MODE == M_DENSE1 ? NW * BM : 1];
+
+  const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, lq = lane >> 4, l8 = lane >> 3, l7 = lane & 7;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // which tile: with eight or more column tiles the tiles of a column (same weights) stay on one XCD
+  int rt, ct;
+  {
+    const int L = blockIdx.x;
+    if ((a.col_tiles & 7) == 0) {
+      const int s = L >> 3, c8 = fdiv(s, ka.inv_rt);
+      ct = c8 * 8 + (L & 7);
+      rt = s - c8 * a.row_tiles;
+    } else {
+      ct = fdiv(L, ka.inv_rt);
+      rt = L - ct * a.row_tiles;
+    }
+  }
+  const int row0 = rt * BM, col0 = ct * BN;
+
+  constexpr unsigned kOob = 0x80000000u;
+  const long long ashift = TAPS ? (long long)(a.W + 1) * a.lda * ES : 0;
+  const __amdgpu_buffer_rsrc_t arsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<char*>(reinterpret_cast<const char*>(a.A)) - ashift, 0, (int)kOob, 0x00020000);
+  const __amdgpu_buffer_rsrc_t wrsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.Wt), 0, (int)kOob, 0x00020000);
+
+  // ---- the row this thread looks up for the workgroup (first BM threads); its list entry is requested first (entries past
+  // the count are dropped later) ------------------------------------------------------------------------------------------
+  const int rrow = row0 + min(tid, BM - 1);
+  int entry = 0;
+  if constexpr (LISTED) entry = a.list[fdiv(min(rrow, ka.cap_rows - 1), ka.inv_ss)];
+
+  // ---- the weights of the first D slices: they depend on nothing but the tile ------------------------------------------
+  // Every load is unconditional; a chunk that must read as zero (past K, past the wave's last slice, outside the image) gets
+  // the top bit of its offset set, which lies outside the descriptor.  The bit is put together from sign bits: written as
+  // conditions, the compiler branches around the loads and drains the counter where the paths meet.
+  const int keff = MODE == M_G2 ? min(BN, a.K - col0) : a.K;  // group convolution: the tile's own input channels
+  const int KT = ka.KT;
+  unsigned voffA[2 * TM], abad[2 * TM], voffW[2 * TN];  // abad: bit t set = tap t reads as zero (bit 0 outside the tap modes)
+  int wrel[2 * TN];
+#pragma unroll
+  for (int j = 0; j < 2 * TN; ++j) {
+    const int c = min(col0 + 8 * j + l8, a.Ncols - 1);  // a column past the end re-reads the last one; its result is dropped
+    voffW[j] = (unsigned)((c * a.ldw + (MODE == M_G2 ? 0 : l7 * EPC)) * ES);
+    wrel[j] = 0;
+    if constexpr (MODE == M_G2) wrel[j] = col0 + l7 * EPC - (c & ~(a.gw - 1));  // (group widths are powers of two)
+  }
+  u32x4 ra[D][2 * TM], rb[D][2 * TN];
+  int kcs[D];
+  auto tap_of = [&](int s) __attribute__((always_inline)) -> int {
+    if constexpr (!TAPS) return 0;
+    return ka.kmul ? (int)__umulhi((unsigned)s, ka.kmul) : s;
+  };
+  auto load_w = [&](int d, int i) __attribute__((always_inline)) {
+    const int s = wave + i * NW, tap = tap_of(s), kc = s - tap * ka.kch;
+    const int soff = (tap * (MODE == M_G2 ? a.gw : a.K) + (MODE == M_G2 ? 0 : kc * BKE)) * ES;
+    const int bad = (KT - 1 - s) | (keff - 1 - kc * BKE - l7 * EPC);
+#pragma unroll
+    for (int j = 0; j < 2 * TN; ++j) {
+      unsigned v = voffW[j] | ((unsigned)bad & kOob);
+      if constexpr (MODE == M_G2) {
+        const int rel = wrel[j] + kc * BKE;
+        v = (voffW[j] + (unsigned)(rel * ES)) | ((unsigned)(bad | rel | (a.gw - 1 - rel)) & kOob);
+      }
+      rb[d][j] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, v, soff, 0);
+    }
+  };
+  auto load_a = [&](int d, int i) __attribute__((always_inline)) {
+    const int s = wave + i * NW, tap = tap_of(s), kc = s - tap * ka.kch;
+    const int ky = (tap * 11) >> 5, kx = tap - ky * 3;  // (tap / 3 for the nine taps)
+    const int soff = ((TAPS ? (ky * a.W + kx) * a.lda : 0) + kc * BKE) * ES;
+    const int bad = (KT - 1 - s) | (keff - 1 - kc * BKE - l7 * EPC);
+    kcs[d] = kc;
+#pragma unroll
+    for (int t = 0; t < 2 * TM; ++t)
+      ra[d][t] = __builtin_amdgcn_raw_buffer_load_b128(
+          arsrc, voffA[t] | ((unsigned)(bad | (int)(abad[t] << (31 - tap))) & kOob), soff, 0);
+  };
+  const int rounds = (KT + NW - 1) / NW;  // slices of the wave with the most
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (d < rounds) load_w(d, d);
+
+  // ---- rows ----------------------------------------------------------------------------------------------------------
+  const int sy = a.stride > 1 ? a.stride : 1;
+  const int oH = a.stride > 1 ? a.Ho : a.H, oW = a.stride > 1 ? a.Wo : a.W;
+  const int SS = a.S * a.S;
+  auto patch_pixel = [&](int rho, int q, int& n, int& yo, int& xo) __attribute__((always_inline)) {
+    const int Wp = fdiv(oW, ka.inv_s), pps = fdiv(oH, ka.inv_s) * Wp;
+    const int j = rho - fdiv(rho, ka.inv_ss) * SS;
+    n = fdiv(q, ka.inv_pps);
+    const int r2 = q - n * pps, py = fdiv(r2, ka.inv_wp), px = r2 - py * Wp, jy = fdiv(j, ka.inv_s);
+    yo = py * a.S + jy;
+    xo = px * a.S + j - jy * a.S;
+  };
+  const int M = LISTED ? *a.count * SS : ka.cap_rows;
+  if (row0 >= M) return;
+  if (tid < BM) {
+    int pix = rrow, y = 0, x = 0, o = rrow;
+    if constexpr (LISTED) {
+      int n, yo, xo;
+      patch_pixel(rrow, entry, n, yo, xo);
+      if constexpr (MODE == M_CONV3) {
+        o = (n * oH + yo) * oW + xo;
+      } else {
+        y = yo * sy; x = xo * sy;
+        pix = (n * a.H + y) * a.W + x;
+      }
+    } else if constexpr (MODE == M_SD1 || MODE == M_SD2) {
+      const int n = fdiv(rrow, ka.inv_howo), r2 = rrow - n * (a.Ho * a.Wo), yo = fdiv(r2, ka.inv_wo);
+      y = yo * a.stride;
+      x = (r2 - yo * a.Wo) * a.stride;
+      pix = (n * a.H + y) * a.W + x;
+    }
+    unsigned mk = ~0u;
+    if constexpr (TAPS)
+      mk = ((y > 0 ? 0x7u : 0u) | 0x38u | (y < a.H - 1 ? 0x1c0u : 0u)) & ((x > 0 ? 0x49u : 0u) | 0x92u | (x < a.W - 1 ? 0x124u : 0u));
+    const bool live = rrow < M;
+    s_voff[tid] = ((unsigned)pix * (unsigned)a.lda + (unsigned)(MODE == M_G2 ? col0 : 0)) * (unsigned)ES;
+    s_bad[tid] = live ? ~mk : ~0u;
+    s_row[tid] = live ? o : -1;
+    if constexpr (MODE == M_SD1) {
+      // shortcut of a dynamic first block: the activation is applied here only where the branch will not be added
+      bool inact = true;
+      if (a.list != nullptr && live) {
+        const int Hp = oH / a.S, Wp = oW / a.S;
+        const int n = fdiv(rrow, ka.inv_howo), r2 = rrow - n * (a.Ho * a.Wo), yo = fdiv(r2, ka.inv_wo);
+        const int q = (n * Hp + yo / a.S) * Wp + (r2 - yo * a.Wo) / a.S;
+        const int cnt = *a.count;
+        const int pos = lower_bound_dev(a.list, cnt, q);
+        inact = !(pos < cnt && a.list[pos] == q);
+      }
+      s_inact[tid] = inact ? 1 : 0;
+    }
+  }
+  const bool do_proj = MODE == M_DENSE1 && ct == 0 && a.wmask != nullptr;
+  if (do_proj)
+    for (int k = tid; k < a.K; k += NT) s_wm[k] = a.wmask[k];
+  // (LDS only: the weight loads stay in flight across this barrier)
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#endif
+#pragma unroll
+  for (int t = 0; t < 2 * TM; ++t) {
+    voffA[t] = s_voff[8 * t + l8] + (unsigned)(l7 * 16);
+    abad[t] = s_bad[8 * t + l8];
+  }
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (d < rounds) load_a(d, d);
+
+  // ---- while those are on their way: affine and residual of this thread's share -------------------------------------
+  constexpr int UPR = BN / 4;                        // units of four channels per row
+  constexpr int UN = (BM * UPR + NT - 1) / NT;       // units per thread
+  struct alignas(4 * ES) R4 { ET v[4]; };
+  float4 sc[UN], sh[UN];
+  R4 res[UN];
+#pragma unroll
+  for (int q = 0; q < UN; ++q) {
+    // units past the tile and columns past the end read valid addresses; their results are dropped
+    const int u = min(tid + q * NT, BM * UPR - 1), r = u / UPR, col = min(col0 + (u - r * UPR) * 4, a.Ncols - 4);
+    __builtin_memcpy(&sc[q], a.scale + col, 16);
+    __builtin_memcpy(&sh[q], a.shift + col, 16);
+    if constexpr (RES) res[q] = *reinterpret_cast<const R4*>((const ET*)a.Res + (size_t)max(s_row[r], 0) * a.ldo + col);
+  }
+
+  f32x4 acc[TM][TN];
+  float psum[TM];
+#pragma unroll
+  for (int t = 0; t < TM; ++t) {
+    psum[t] = 0.f;
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[t][j][e] = 0.f;
+  }
+  // this wave's slice in LDS: row r keeps chunk c at position c ^ (r & 7) (rows of A, then rows of the weights)
+  unsigned char* const mine = smem + wave * (BM + BN) * 128;
+  const unsigned wpos = (unsigned)(l8 * 128 + ((l7 ^ l8) << 4));
+  auto multiply = [&](int d) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < 2 * TM; ++t) *reinterpret_cast<u32x4*>(mine + t * 1024 + wpos) = ra[d][t];
+#pragma unroll
+    for (int j = 0; j < 2 * TN; ++j) *reinterpret_cast<u32x4*>(mine + BM * 128 + j * 1024 + wpos) = rb[d][j];
+#pragma unroll
+    for (int kg = 0; kg < 2; ++kg) {
+      const unsigned rpos = (unsigned)(l15 * 128 + (((4 * kg + lq) ^ (l15 & 7)) << 4));
+      uint4 av[TM], bv[TN];
+#pragma unroll
+      for (int t = 0; t < TM; ++t) av[t] = *reinterpret_cast<const uint4*>(mine + t * 2048 + rpos);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) bv[j] = *reinterpret_cast<const uint4*>(mine + BM * 128 + j * 2048 + rpos);
+#pragma unroll
+      for (int t = 0; t < TM; ++t) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) mma4<ET>(acc[t][j], bv[j], av[t]);
+        if constexpr (MODE == M_DENSE1) {
+          if (do_proj) {
+            const int k = min(kcs[d] * BKE + (4 * kg + lq) * EPC, a.K - EPC);  // (past K the activation reads as zero)
+            ET xe[EPC];
+            __builtin_memcpy(xe, &av[t], 16);
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) psum[t] += elem<ET>::load(&xe[e]) * s_wm[k + e];
+          }
+        }
+      }
+    }
+  };
+  int i0 = 0;
+  for (; i0 + D < rounds; i0 += D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      multiply(d);
+      load_w(d, i0 + d + D);
+      load_a(d, i0 + d + D);
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (i0 + d < rounds) multiply(d);
+
+  // ---- the partial tiles meet (in the bytes of the slices: every wave is done with its own, and only with its own) ------
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < TM; ++t)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+      *reinterpret_cast<float4*>(part + (wave * BM + 16 * t + l15) * PSTR + 16 * j + 4 * lq) =
+          make_float4(acc[t][j][0], acc[t][j][1], acc[t][j][2], acc[t][j][3]);
+  if constexpr (MODE == M_DENSE1) {
+    if (do_proj) {
+#pragma unroll
+      for (int t = 0; t < TM; ++t) {
+        float p = psum[t];
+        p += __shfl_xor(p, 16, kWave);
+        p += __shfl_xor(p, 32, kWave);
+        if (lq == 0) s_proj[wave * BM + 16 * t + l15] = p;
+      }
+    }
+  }
+  __syncthreads();
+  if constexpr (MODE == M_DENSE1) {
+    if (do_proj && tid < BM && row0 + tid < M) {
+      float p = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) p += s_proj[w * BM + tid];
+      a.proj[row0 + tid] = p;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < UN; ++q) {
+    const int u = tid + q * NT, r = u / UPR, c4 = (u - r * UPR) * 4, col = col0 + c4;
+    if (u >= BM * UPR || col >= a.Ncols) continue;
+    const int orow = s_row[r];
+    if (orow < 0) continue;
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float4 p = *reinterpret_cast<const float4*>(part + (w * BM + r) * PSTR + c4);
+      v[0] += p.x; v[1] += p.y; v[2] += p.z; v[3] += p.w;
+    }
+    const float scv[4] = {sc[q].x, sc[q].y, sc[q].z, sc[q].w}, shv[4] = {sh[q].x, sh[q].y, sh[q].z, sh[q].w};
+    R4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = v[e] * scv[e] + shv[e];
+      if constexpr (RES) {
+        v[e] += elem<ET>::load(&res[q].v[e]);
+        if (a.relu) v[e] = fmaxf(v[e], 0.f);
+      } else if constexpr (MODE == M_SD1) {
+        if (a.relu && s_inact[r]) v[e] = fmaxf(v[e], 0.f);
+      } else {
+        v[e] = fmaxf(v[e], 0.f);
+      }
+      elem<ET>::store(&o.v[e], v[e]);
+    }
+    *reinterpret_cast<R4*>((ET*)a.Out + (size_t)orow * a.ldo + col) = o;
+  }
+}
+
+// ---- host side ------------------------------------------------------------------------------------------------------
+// More than 64 KB of dynamic LDS has to be requested once per kernel and device (idempotent; see gemm_request_lds).
+template <int MODE, typename ET, int TM, int TN, int NW, int D>
+static int skinny_request_lds() {
+  static std::atomic<unsigned> done{0};  // one bit per device ordinal (ordinals >= 32 repeat the request)
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return LAUD_ERR_HIP;
+  const unsigned bit = dev >= 0 && dev < 32 ? 1u << dev : 0u;
+  if (bit && (done.load(std::memory_order_acquire) & bit)) return LAUD_OK;
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_skinny<MODE, ET, TM, TN, NW, D>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize,
+                          skinny_lds<TM, TN, NW>() + (MODE == M_DENSE1 ? 4096 * 4 : 0)) != hipSuccess)
+    return LAUD_ERR_HIP;
+  done.fetch_or(bit, std::memory_order_release);
+  return LAUD_OK;
+}
+
+// rows < 0: only make the request (laud_init)
+template <int MODE, typename ET, int TM, int TN, int NW, int D>
+static int launch_skinny_t(GemmArgs a, long long cap_rows, hipStream_t st) {
+  const int rc = skinny_request_lds<MODE, ET, TM, TN, NW, D>();
+  if (rc != LAUD_OK || cap_rows < 0) return rc;
+  constexpr bool TAPS = (MODE == M_CONV2 || MODE == M_SD2 || MODE == M_G2);
+  constexpr int BKE = 8 * elem<ET>::per16;
+  a.row_tiles = (int)((cap_rows + 16 * TM - 1) / (16 * TM));
+  a.col_tiles = (a.Ncols + 16 * TN - 1) / (16 * TN);
+  SkinnyArgs k{};
+  k.g = a;
+  k.cap_rows = (int)cap_rows;
+  k.kch = ((MODE == M_G2 ? 16 * TN : a.K) + BKE - 1) / BKE;
+  k.KT = (TAPS ? 9 : 1) * k.kch;
+  k.kmul = k.kch > 1 ? (unsigned)((0x100000000ull + k.kch - 1) / k.kch) : 0u;
+  const int oH = a.stride > 1 ? a.Ho : a.H, oW = a.stride > 1 ? a.Wo : a.W;
+  k.inv_s = 1.f / a.S; k.inv_ss = 1.f / (a.S * a.S);
+  k.inv_wp = 1.f / (oW / a.S); k.inv_pps = 1.f / ((oH / a.S) * (oW / a.S));
+  k.inv_howo = a.Ho > 0 ? 1.f / (a.Ho * a.Wo) : 0.f; k.inv_wo = a.Wo > 0 ? 1.f / a.Wo : 0.f;
+  k.inv_rt = 1.f / a.row_tiles;
+  const int lds = skinny_lds<TM, TN, NW>() + (MODE == M_DENSE1 && a.wmask ? a.K * 4 : 0);
+  hipLaunchKernelGGL((k_skinny<MODE, ET, TM, TN, NW, D>), dim3((unsigned)(a.row_tiles * a.col_tiles)), dim3(64 * NW), lds, st, k);
+  return check_launch();
+}
+
+template <int MODE, typename ET>
+static int launch_skinny_e(const GemmArgs& a, long long cap_rows, hipStream_t st) {
+  constexpr int BKE = 8 * elem<ET>::per16;
+  constexpr bool TAPS = (MODE == M_CONV2 || MODE == M_SD2 || MODE == M_G2);
+  if constexpr (MODE == M_G2) {  // 64-channel column tiles: they hold whole groups
+    if (cap_rows < 0) {
+      const int rc = launch_skinny_t<MODE, ET, 1, 4, 8, 2>(a, -1, st);
+      return rc == LAUD_OK ? launch_skinny_t<MODE, ET, 4, 4, 4, 2>(a, -1, st) : rc;
+    }
+    if (((cap_rows + 63) / 64) * ((a.Ncols + 63) / 64) < 192) return launch_skinny_t<MODE, ET, 1, 4, 8, 2>(a, cap_rows, st);
+    return launch_skinny_t<MODE, ET, 4, 4, 4, 2>(a, cap_rows, st);
+  } else {
+    if (cap_rows < 0) {
+      int rc = launch_skinny_t<MODE, ET, 1, 1, 8, 8>(a, -1, st);
+      if (rc == LAUD_OK) rc = launch_skinny_t<MODE, ET, 1, 1, 4, 4>(a, -1, st);
+      if (rc == LAUD_OK) rc = launch_skinny_t<MODE, ET, 2, 2, 8, 4>(a, -1, st);
+      if (rc == LAUD_OK) rc = launch_skinny_t<MODE, ET, 2, 2, 4, 4>(a, -1, st);
+      if (rc == LAUD_OK) rc = launch_skinny_t<MODE, ET, 2, 4, 4, 3>(a, -1, st);
+      if (rc == LAUD_OK) rc = launch_skinny_t<MODE, ET, 4, 4, 4, 2>(a, -1, st);
+      return rc;
+    }
+    // the largest tile that still gives most compute units a workgroup (float32: one and a half; its MFMAs, sixteen times
+    // slower, are then what a workgroup's time is made of); eight waves where a wave of four would walk many slices
+    const int kt = (TAPS ? 9 : 1) * ((a.K + BKE - 1) / BKE);
+    auto tiles = [&](int tm, int tn) { return ((cap_rows + 16 * tm - 1) / (16 * tm)) * ((a.Ncols + 16 * tn - 1) / (16 * tn)); };
+    constexpr int fill = sizeof(ET) == 2 ? 192 : 384;
+    if (tiles(4, 4) >= fill) return launch_skinny_t<MODE, ET, 4, 4, 4, 2>(a, cap_rows, st);
+    if (tiles(2, 4) >= fill) return launch_skinny_t<MODE, ET, 2, 4, 4, 3>(a, cap_rows, st);
+    const bool small = tiles(2, 2) < fill;
+    if (kt > 8) return small ? launch_skinny_t<MODE, ET, 1, 1, 8, 8>(a, cap_rows, st) : launch_skinny_t<MODE, ET, 2, 2, 8, 4>(a, cap_rows, st);
+    return small ? launch_skinny_t<MODE, ET, 1, 1, 4, 4>(a, cap_rows, st) : launch_skinny_t<MODE, ET, 2, 2, 4, 4>(a, cap_rows, st);
+  }
+}
+
+int launch_skinny(int mode, int dtype, const GemmArgs& a, long long cap_rows, hipStream_t st) {
+  switch (mode) {
+#define LAUD_SKINNY_MODE(M) case M: return dtype == LAUD_BF16 ? launch_skinny_e<M, bf16_t>(a, cap_rows, st) : launch_skinny_e<M, float>(a, cap_rows, st)
+    LAUD_SKINNY_MODE(M_CONV2);
+    LAUD_SKINNY_MODE(M_CONV3);
+    LAUD_SKINNY_MODE(M_DENSE1);
+    LAUD_SKINNY_MODE(M_SD1);
+    LAUD_SKINNY_MODE(M_SD2);
+    LAUD_SKINNY_MODE(M_SD3);
+    LAUD_SKINNY_MODE(M_G2);
+#undef LAUD_SKINNY_MODE
+    default: return LAUD_ERR_UNSUPPORTED;
+  }
+}
+
+// The line lies where the tiled kernel of laud_gemm.hip gets the chip filled: counted in 64 x 64 output tiles, the longer the
+// reduction the later (measured on the four ResNet stages at 1 to 64 images: with a reduction of up to 8 slices the two meet
+// at about 256 tiles, with 9 to 16 at 320, with more at 512 and above).
+bool skinny_wanted(int mode, int dtype, const GemmArgs& a, long long cap_rows) {
+  const bool taps = mode == M_CONV2 || mode == M_SD2 || mode == M_G2;
+  const int bke = dtype == LAUD_BF16 ? 64 : 32;
+  const int kt = (taps ? 9 : 1) * (((mode == M_G2 ? 64 : a.K) + bke - 1) / bke);
+  const long long t = ((cap_rows + 63) / 64) * ((a.Ncols + 63) / 64);
+  return cap_rows < (1 << 20) && t <= (kt <= 8 ? 256 : kt <= 16 ? 320 : 512);
+}
+
+int skinny_init_device() {
+  const GemmArgs none{};
+  for (int mode : {M_CONV2, M_CONV3, M_DENSE1, M_SD1, M_SD2, M_SD3, M_G2})
+    for (int dtype : {LAUD_BF16, LAUD_F32})
+      if (launch_skinny(mode, dtype, none, -1, nullptr) != LAUD_OK) return LAUD_ERR_HIP;
+  return LAUD_OK;
+}
+
+}  // namespace laud
