@@ -140,6 +140,60 @@ constexpr int kSeMaxC = 4096, kSeMaxHidden = 1024;  // widest layer / SE hidden 
 int launch_se(int dtype, int N, int pps, int SS, int C, const laud_group_se* e, void* h2, const int32_t* idx,
               const int32_t* count, float* scratch, long long cap_rows, hipStream_t stream);
 
+// Out-of-place calls: pixels of inactive patches keep their value, so they are copied from x to out, bit for bit.  The copy
+// rides in extra workgroups of the block's last launch (nblocks of them, from workgroup id `first` on): it has nothing to
+// wait for but the index list, and the compute units that launch leaves idle carry it.  (As a launch of its own it took 4 us
+// on one image and 14 us on 128 images of the stage-3 map.)
+struct InactiveCopy {
+  const uint4* x;
+  uint4* out;
+  const int32_t* idx;    // ascending active patch ids
+  const int32_t* count;
+  int npatch, Hp, Wp;    // patches, patch grid
+  int S, W, H;           // patch size, map size
+  int cpp;               // 16-byte chunks per pixel
+  int first, nblocks;
+};
+constexpr int kCopyPatches = 1024;  // most patches one workgroup takes at a time
+InactiveCopy inactive_copy(const void* x, void* out, const laud_fmap& fx, int S, const int32_t* idx, const int32_t* count);
+
+// Workgroup `part` of the copy; flags: kCopyPatches bytes of LDS.
+template <int NT>
+__device__ __forceinline__ void copy_inactive_part(const InactiveCopy& c, int part, unsigned char* flags) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int cnt = *c.count;
+  const int per = (c.npatch + c.nblocks - 1) / c.nblocks;
+  const int p0 = part * per, p1 = min(p0 + per, c.npatch);
+  const int rowc = c.S * c.cpp;  // chunks in one pixel row of a patch
+  for (int q0 = p0; q0 < p1; q0 += kCopyPatches) {
+    const int n = min(kCopyPatches, p1 - q0);
+    for (int i = tid; i < n; i += NT) flags[i] = 0;
+    const int lo = wave_lower_bound(c.idx, cnt, q0);
+    __syncthreads();
+    for (int i = tid; i < n && lo + i < cnt; i += NT) {  // at most n entries of the sorted list fall into the range
+      const int q = c.idx[lo + i] - q0;
+      if (q < n) flags[q] = 1;
+    }
+    __syncthreads();
+    for (int r = wave; r < n * c.S; r += NT / kWave) {  // one wave per pixel row of a patch
+      const int k = r / c.S, q = q0 + k;
+      if (flags[k]) continue;
+      const int s = q / (c.Hp * c.Wp), g = q - s * (c.Hp * c.Wp), py = g / c.Wp, px = g - py * c.Wp;
+      const size_t off = (((size_t)s * c.H + py * c.S + (r - k * c.S)) * c.W + px * c.S) * c.cpp;
+      int i = lane;
+      for (; i + 3 * kWave < rowc; i += 4 * kWave) {
+        uint4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = c.x[off + i + u * kWave];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) c.out[off + i + u * kWave] = v[u];
+      }
+      for (; i < rowc; i += kWave) c.out[off + i] = c.x[off + i];
+    }
+    __syncthreads();
+  }
+}
+
 // conv2 -> conv3 -> residual add in one kernel (laud_tail.hip), for the shapes tail_supported() names.
 struct TailArgs {
   const void* h1;        // [pixels of the input grid][MID] bf16, conv1's output at pixel positions
@@ -163,6 +217,7 @@ struct TailArgs {
   // groups a row drops.  Null: no channel mask.
   const uint8_t* sbits;
   int cs_group;
+  InactiveCopy cp;       // nblocks 0: in place
   int wg_target;         // workgroups that fill the device once (its compute units; set by launch_tail)
 };
 

@@ -42,6 +42,7 @@ struct GemmArgs {
   const void* pk_w2; const void* pk_w3; void* pk_out; int pk_chunks; int pk_first_block;
   const float* wmask;    // DENSE1: masker weights [K] or null
   float* proj;           // DENSE1: per-pixel masker projection sum_c w[c]*x[pixel][c], [m_rows]
+  InactiveCopy cp;       // CONV3: copy of the inactive patches in extra workgroups (nblocks 0: none)
 };
 
 // Few rows: small tiles, the reduction split over the waves of a workgroup (laud_skinny.hip).  cap_rows: number of rows, or

@@ -119,6 +119,12 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
       return;
     }
   }
+  if constexpr (MODE == M_CONV3) {
+    if (a.cp.nblocks && (int)blockIdx.x >= a.cp.first) {
+      copy_inactive_part<NT>(a.cp, blockIdx.x - a.cp.first, smem);
+      return;
+    }
+  }
   const int wm = wave / WGN, wn = wave % WGN;
   const int HW = a.H * a.W, SS = a.S * a.S;
   // Dynamic blocks with a spatial stride (a.stride > 1) keep their mask on the output grid Ho x Wo;
@@ -649,7 +655,7 @@ __global__ __launch_bounds__(kNeedThreads) void k_need(const int32_t* __restrict
   if (tid == 0) need_counts[g] = running;
 }
 
-// Out-of-place call: pixels of inactive patches are copied bit for bit.  One block per patch.
+// The same for the unfused schedule, as a launch of its own: one block per patch.
 __global__ __launch_bounds__(256) void k_copy_inactive(const uint4* __restrict__ x, uint4* __restrict__ out, int H,
                                                        int W, int S, int cpp, const int32_t* __restrict__ idx,
                                                        const int32_t* __restrict__ count) {
@@ -670,6 +676,18 @@ __global__ __launch_bounds__(256) void k_copy_inactive(const uint4* __restrict__
 // ------------------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------------------
+InactiveCopy inactive_copy(const void* x, void* out, const laud_fmap& fx, int S, const int32_t* idx, const int32_t* count) {
+  InactiveCopy c{};
+  if (x == out) return c;
+  c.x = (const uint4*)x; c.out = (uint4*)out; c.idx = idx; c.count = count;
+  c.Hp = fx.H / S; c.Wp = fx.W / S; c.npatch = fx.N * c.Hp * c.Wp; c.S = S; c.W = fx.W; c.H = fx.H;
+  c.cpp = (int)((size_t)fx.C * elem_bytes(fx.dtype) / 16);
+  // about 64 KB of map per workgroup, at most four workgroups per compute unit
+  const long long bytes = (long long)fx.N * fx.H * fx.W * c.cpp * 16;
+  c.nblocks = (int)std::min<long long>(std::min<long long>(c.npatch, (bytes + 65535) / 65536), 1024);
+  return c;
+}
+
 struct Tile { int bm, bn, waves; };
 
 // Tile choice: a function of the shapes alone.
@@ -718,6 +736,10 @@ static int launch_gemm_t(GemmArgs a, long long cap_rows, int nsamples, hipStream
     }
   } else {
     a.pk_out = nullptr;
+  }
+  if constexpr (MODE == M_CONV3) {
+    a.cp.first = (int)grid.x;
+    grid.x += (unsigned)a.cp.nblocks;
   }
   constexpr int kStages = 2 * (BM + BN) * 144;  // two pipeline stages of 144-byte rows
   constexpr int kStaging = BM * (BN * 4 + 32);  // fp32 tile the epilogue transposes through
@@ -1058,13 +1080,14 @@ static int run_dense_conv1(const laud_fmap& fx, const laud_bottleneck* p, const 
 // Returns 1 when that kernel was launched (*rc = its status), 0 when the caller has to run the two GEMMs.
 static int try_tail(int dtype, const laud_bottleneck* p, const laud_group_se* e, const void* h1, const void* res,
                     void* out, const int32_t* idx, const int32_t* count, int H, int W, int S, int stride, int Ho, int Wo,
-                    long long cap_rows, void* wpack, hipStream_t st, int* rc) {
+                    long long cap_rows, void* wpack, const InactiveCopy& copy, hipStream_t st, int* rc) {
   if (!tail_used(dtype, p, e, cap_rows)) return 0;
   TailArgs t{};
   t.h1 = h1; t.wpacked = (const char*)(p->packed ? p->packed : wpack) + packed_layout(dtype, p).tail; t.s2 = p->s2; t.t2 = p->t2; t.s3 = p->s3; t.t3 = p->t3;
   t.res = res; t.out = out; t.count = count; t.list = idx; t.H = H; t.W = W; t.S = S; t.stride = stride;
   t.Ho = Ho; t.Wo = Wo; t.cout = p->c_out; t.relu = p->relu_out ? 1 : 0;
   t.cap_patches = (int)(cap_rows / ((long long)S * S));
+  t.cp = copy;
   *rc = launch_tail(t, cap_rows, st);
   return 1;
 }
@@ -1089,14 +1112,8 @@ static int run_dyn_block(const void* x, laud_fmap fx, const laud_bottleneck* p, 
   void* h1 = wsb + L.h1;
   void* h2 = wsb + L.h2;
   const long long npix = (long long)fx.N * fx.H * fx.W;
-  const int cpp = (int)((size_t)fx.C * elem_bytes(fx.dtype) / 16);
 
-  if (x != out) {
-    StageScope scope(LAUD_STAGE_COPY_INACTIVE, st);
-    hipLaunchKernelGGL(k_copy_inactive, dim3((unsigned)(fx.N * Hp * Wp)), dim3(256), 0, st, (const uint4*)x,
-                       (uint4*)out, fx.H, fx.W, S, cpp, idx, count);
-    if (check_launch() != LAUD_OK) return LAUD_ERR_HIP;
-  }
+  const InactiveCopy copy = inactive_copy(x, out, fx, S, idx, count);
   GemmArgs a{};
   a.H = fx.H; a.W = fx.W; a.S = S; a.D = 1; a.G = 1; a.cmask = nullptr;
   if (dense_conv1_wanted(fx.dtype, p, npix) && !head_used(fx.dtype, p, npix)) {
@@ -1127,7 +1144,7 @@ static int run_dyn_block(const void* x, laud_fmap fx, const laud_bottleneck* p, 
       a.pk_out = nullptr;
     }
   }
-  if (try_tail(fx.dtype, p, e, h1, x, out, idx, count, fx.H, fx.W, S, 1, fx.H, fx.W, npix, wsb + L.wpack, st, &rc)) return rc;
+  if (try_tail(fx.dtype, p, e, h1, x, out, idx, count, fx.H, fx.W, S, 1, fx.H, fx.W, npix, wsb + L.wpack, copy, st, &rc)) return rc;
   // conv2: 3x3 over active patches, A rows fetched from h1 by index -> dense h2
   a.A = h1; a.Wt = p->w2; a.scale = p->s2; a.shift = p->t2; a.Out = h2;
   a.count = count; a.list = idx; a.K = p->c_mid; a.ldw = 9 * p->c_mid; a.Ncols = p->c_mid;
@@ -1140,6 +1157,7 @@ static int run_dyn_block(const void* x, laud_fmap fx, const laud_bottleneck* p, 
   a.A = h2; a.Wt = p->w3; a.scale = p->s3; a.shift = p->t3; a.Out = out; a.Res = x;
   a.K = p->c_mid; a.ldw = p->c_mid; a.Ncols = p->c_out; a.lda = p->c_mid; a.ldo = p->c_out;
   a.relu = p->relu_out ? 1 : 0;
+  a.cp = copy;
   return launch_gemm<M_CONV3>(fx.dtype, a, npix, 1, st);
 }
 
@@ -1173,7 +1191,6 @@ extern "C" int laud_masker_dyn_bottleneck(const void* x, laud_fmap fx, const lau
   void* h1 = wsb + L.h1;
   void* h2 = wsb + L.h2;
   const long long npix = (long long)fx.N * fx.H * fx.W;
-  const int cpp = (int)((size_t)fx.C * elem_bytes(fx.dtype) / 16);
 
   GemmArgs a{};
   a.H = fx.H; a.W = fx.W; a.S = S; a.D = 1; a.G = 1; a.cmask = nullptr;
@@ -1205,14 +1222,9 @@ extern "C" int laud_masker_dyn_bottleneck(const void* x, laud_fmap fx, const lau
   if ((rc = launch_pool_compact(proj, fx.N, fx.H, fx.W, S, bias, keep, mask, logits, idx, count, sample_offsets,
                                 (int32_t*)(wsb + L.blocks), st)) != LAUD_OK)
     return rc;
-  if (x != out) {
-    StageScope scope(LAUD_STAGE_COPY_INACTIVE, st);
-    hipLaunchKernelGGL(k_copy_inactive, dim3((unsigned)(fx.N * Hp * Wp)), dim3(256), 0, st, (const uint4*)x,
-                       (uint4*)out, fx.H, fx.W, S, cpp, idx, count);
-    if (check_launch() != LAUD_OK) return LAUD_ERR_HIP;
-  }
   a.wmask = nullptr; a.proj = nullptr;
-  if (try_tail(fx.dtype, p, nullptr, h1, x, out, idx, count, fx.H, fx.W, S, 1, fx.H, fx.W, npix, wsb + L.wpack, st, &rc)) return rc;
+  const InactiveCopy copy = inactive_copy(x, out, fx, S, idx, count);
+  if (try_tail(fx.dtype, p, nullptr, h1, x, out, idx, count, fx.H, fx.W, S, 1, fx.H, fx.W, npix, wsb + L.wpack, copy, st, &rc)) return rc;
   // conv2 and conv3 exactly as in laud_dyn_bottleneck
   a.A = h1; a.Wt = p->w2; a.scale = p->s2; a.shift = p->t2; a.Out = h2;
   a.count = count; a.list = idx; a.K = p->c_mid; a.ldw = 9 * p->c_mid; a.Ncols = p->c_mid;
@@ -1221,6 +1233,7 @@ extern "C" int laud_masker_dyn_bottleneck(const void* x, laud_fmap fx, const lau
   a.A = h2; a.Wt = p->w3; a.scale = p->s3; a.shift = p->t3; a.Out = out; a.Res = x;
   a.K = p->c_mid; a.ldw = p->c_mid; a.Ncols = p->c_out; a.lda = p->c_mid; a.ldo = p->c_out;
   a.relu = p->relu_out ? 1 : 0;
+  a.cp = copy;
   return launch_gemm<M_CONV3>(fx.dtype, a, npix, 1, st);
 }
 
@@ -1474,7 +1487,7 @@ static int run_dyn_projection(const void* x, laud_fmap fx, const laud_bottleneck
       a.pk_out = nullptr;
     }
   }
-  if (try_tail(fx.dtype, p, e, h1, out, out, idx, count, fx.H, fx.W, S, stride, Ho, Wo, nout, wsb + L.wpack, st, &rc)) return rc;
+  if (try_tail(fx.dtype, p, e, h1, out, out, idx, count, fx.H, fx.W, S, stride, Ho, Wo, nout, wsb + L.wpack, InactiveCopy{}, st, &rc)) return rc;
   // conv2: strided 3x3 at the active output pixels -> dense h2
   a.A = h1; a.Wt = p->w2; a.scale = p->s2; a.shift = p->t2; a.Out = h2;
   a.count = count; a.list = idx; a.K = p->c_mid; a.ldw = 9 * p->c_mid; a.Ncols = p->c_mid;

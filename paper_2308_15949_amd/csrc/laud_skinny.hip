@@ -74,6 +74,12 @@ __global__ __launch_bounds__(64 * NW) void k_skinny(const SkinnyArgs ka) {
 
   const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, lq = lane >> 4, l8 = lane >> 3, l7 = lane & 7;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if constexpr (MODE == M_CONV3) {
+    if (a.cp.nblocks && (int)blockIdx.x >= a.cp.first) {
+      copy_inactive_part<NT>(a.cp, blockIdx.x - a.cp.first, smem);
+      return;
+    }
+  }
   // which tile: with eight or more column tiles the tiles of a column (same weights) stay on one XCD
   int rt, ct;
   {
@@ -388,7 +394,12 @@ static int launch_skinny_t(GemmArgs a, long long cap_rows, hipStream_t st) {
   k.inv_howo = a.Ho > 0 ? 1.f / (a.Ho * a.Wo) : 0.f; k.inv_wo = a.Wo > 0 ? 1.f / a.Wo : 0.f;
   k.inv_rt = 1.f / a.row_tiles;
   const int lds = skinny_lds<TM, TN, NW>() + (MODE == M_DENSE1 && a.wmask ? a.K * 4 : 0);
-  hipLaunchKernelGGL((k_skinny<MODE, ET, TM, TN, NW, D>), dim3((unsigned)(a.row_tiles * a.col_tiles)), dim3(64 * NW), lds, st, k);
+  unsigned grid = (unsigned)(a.row_tiles * a.col_tiles);
+  if constexpr (MODE == M_CONV3) {
+    k.g.cp.first = (int)grid;
+    grid += (unsigned)a.cp.nblocks;
+  }
+  hipLaunchKernelGGL((k_skinny<MODE, ET, TM, TN, NW, D>), dim3(grid), dim3(64 * NW), lds, st, k);
   return check_launch();
 }
 

@@ -440,6 +440,11 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
 template <int NCT, bool CS>
 __global__ __launch_bounds__(tail::kThreads) void k_tail(const TailArgs a) {
   using namespace tail;
+  if ((int)blockIdx.x >= a.cp.first && a.cp.nblocks) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    copy_inactive_part<kThreads>(a.cp, blockIdx.x - a.cp.first, smem);
+    return;
+  }
   // (a body's blocks bring cold weights: 43.3 -> 36.5 us per launch in a ResNet-101 body, batch 128, ratio 0.5)
   const unsigned touched = l2_touch(a.wpacked, (kSl2 + NCT * kKch) * kSliceChunks * 16, kThreads);
   const int SS = a.S * a.S, b32 = blockIdx.x * 32;
@@ -522,7 +527,9 @@ int launch_tail(const TailArgs& args, long long cap_rows, hipStream_t st) {
   a.wg_target = g_tail_cus[dev];
   // one workgroup per 32 rows of the capacity: enough for the smallest tile height; workgroups past the last tile
   // of the height chosen on the device leave at once
-  const unsigned grid = (unsigned)((cap_rows + 31) / 32);
+  unsigned grid = (unsigned)((cap_rows + 31) / 32);
+  a.cp.first = (int)grid;
+  grid += (unsigned)a.cp.nblocks;
   StageScope scope(LAUD_STAGE_CONV2, st);
   if (a.sbits)
     hipLaunchKernelGGL((k_tail<4, true>), dim3(grid), dim3(tail::kThreads), tail::lds_bytes(tail::kMaxPB, 1024), st, a);
