@@ -157,12 +157,12 @@ struct InactiveCopy {
 constexpr int kCopyPatches = 1024;  // most patches one workgroup takes at a time
 InactiveCopy inactive_copy(const void* x, void* out, const laud_fmap& fx, int S, const int32_t* idx, const int32_t* count);
 
-// Workgroup `part` of the copy; flags: kCopyPatches bytes of LDS.
+// Share `part` of `nparts` of the copy; flags: kCopyPatches bytes of LDS.
 template <int NT>
-__device__ __forceinline__ void copy_inactive_part(const InactiveCopy& c, int part, unsigned char* flags) {
+__device__ __forceinline__ void copy_inactive_part(const InactiveCopy& c, int part, int nparts, unsigned char* flags) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int cnt = *c.count;
-  const int per = (c.npatch + c.nblocks - 1) / c.nblocks;
+  const int per = (c.npatch + nparts - 1) / nparts;
   const int p0 = part * per, p1 = min(p0 + per, c.npatch);
   const int rowc = c.S * c.cpp;  // chunks in one pixel row of a patch
   for (int q0 = p0; q0 < p1; q0 += kCopyPatches) {

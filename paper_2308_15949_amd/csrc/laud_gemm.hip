@@ -121,7 +121,7 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
   }
   if constexpr (MODE == M_CONV3) {
     if (a.cp.nblocks && (int)blockIdx.x >= a.cp.first) {
-      copy_inactive_part<NT>(a.cp, blockIdx.x - a.cp.first, smem);
+      copy_inactive_part<NT>(a.cp, blockIdx.x - a.cp.first, a.cp.nblocks, smem);
       return;
     }
   }

@@ -76,7 +76,7 @@ __global__ __launch_bounds__(64 * NW) void k_skinny(const SkinnyArgs ka) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if constexpr (MODE == M_CONV3) {
     if (a.cp.nblocks && (int)blockIdx.x >= a.cp.first) {
-      copy_inactive_part<NT>(a.cp, blockIdx.x - a.cp.first, smem);
+      copy_inactive_part<NT>(a.cp, blockIdx.x - a.cp.first, a.cp.nblocks, smem);
       return;
     }
   }

@@ -41,6 +41,7 @@ namespace tail {
 // A workgroup takes PB blocks of 32 pixels (PB = 1 .. 3, chosen per launch on the device from the number of active
 // pixels, see k_tail); the LDS layout depends on it.
 constexpr int kMaxPB = 3;
+constexpr int kCopyExtra = 128;               // workgroups beyond the tiles' capacity where inactive patches have to be copied
 constexpr int kARing = 4;
 constexpr int kWRing = 3;                     // weight slices held / in flight in registers (4 without a channel mask)
 constexpr unsigned kOob = 0x80000000u;        // offset outside every descriptor: reads as zero
@@ -440,11 +441,6 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
 template <int NCT, bool CS>
 __global__ __launch_bounds__(tail::kThreads) void k_tail(const TailArgs a) {
   using namespace tail;
-  if ((int)blockIdx.x >= a.cp.first && a.cp.nblocks) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    copy_inactive_part<kThreads>(a.cp, blockIdx.x - a.cp.first, smem);
-    return;
-  }
   // (a body's blocks bring cold weights: 43.3 -> 36.5 us per launch in a ResNet-101 body, batch 128, ratio 0.5)
   const unsigned touched = l2_touch(a.wpacked, (kSl2 + NCT * kKch) * kSliceChunks * 16, kThreads);
   const int SS = a.S * a.S, b32 = blockIdx.x * 32;
@@ -466,6 +462,14 @@ __global__ __launch_bounds__(tail::kThreads) void k_tail(const TailArgs a) {
   if (row0 >= M) {
     vm_wait<0>();
     l2_touched(touched);
+    if (a.cp.nblocks) {
+      // the first workgroups past the tiles copy the inactive patches: eight for each compute unit the last round of tiles
+      // leaves idle (each has a chain of four round trips ahead of its share; two, four and sixteen measured 2 to 4 us slower)
+      extern __shared__ __align__(16) unsigned char smem[];
+      const int tiles = (t32 + pb - 1) / pb, idle = a.wg_target - tiles % a.wg_target;
+      const int nparts = min((int)gridDim.x - tiles, max(8 * idle, kCopyExtra));
+      if ((int)blockIdx.x - tiles < nparts) copy_inactive_part<kThreads>(a.cp, blockIdx.x - tiles, nparts, smem);
+    }
     return;
   }
   switch (pb) {
@@ -528,8 +532,7 @@ int launch_tail(const TailArgs& args, long long cap_rows, hipStream_t st) {
   // one workgroup per 32 rows of the capacity: enough for the smallest tile height; workgroups past the last tile
   // of the height chosen on the device leave at once
   unsigned grid = (unsigned)((cap_rows + 31) / 32);
-  a.cp.first = (int)grid;
-  grid += (unsigned)a.cp.nblocks;
+  if (a.cp.nblocks) grid += tail::kCopyExtra;
   StageScope scope(LAUD_STAGE_CONV2, st);
   if (a.sbits)
     hipLaunchKernelGGL((k_tail<4, true>), dim3(grid), dim3(tail::kThreads), tail::lds_bytes(tail::kMaxPB, 1024), st, a);
