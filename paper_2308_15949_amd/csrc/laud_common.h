@@ -88,6 +88,38 @@ __device__ __forceinline__ int wave_lower_bound(const int32_t* v, int n, int key
   return lo;
 }
 
+// The same for two keys at once (their round trips overlap).
+__device__ __forceinline__ void wave_lower_bound2(const int32_t* v, int n, int key0, int key1, int& r0, int& r1) {
+  const int lane = lane_id();
+  int lo[2] = {0, 0}, hi[2] = {n, n};
+  const int key[2] = {key0, key1};
+  while (hi[0] > lo[0] || hi[1] > lo[1]) {
+    int step[2], val[2];
+    bool in[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      step[i] = (hi[i] - lo[i] + kWave - 1) / kWave;
+      const int pos = lo[i] + lane * step[i];
+      in[i] = pos < hi[i];
+      val[i] = v[in[i] ? pos : 0];
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      if (hi[i] <= lo[i]) continue;
+      const int c = __popcll(__ballot(in[i] && val[i] < key[i]));
+      if (c == 0) {
+        hi[i] = lo[i];
+      } else {
+        const int nhi = min(lo[i] + c * step[i], hi[i]);
+        lo[i] = lo[i] + (c - 1) * step[i] + 1;
+        hi[i] = nhi;
+      }
+    }
+  }
+  r0 = lo[0];
+  r1 = lo[1];
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
@@ -135,10 +167,10 @@ int launch_dense_affine(int dtype, const void* A, const void* Wt, const float* s
                         long long rows, int K, int ncols, int relu, hipStream_t stream);
 
 // The SE module on the compact rows h2 [rows][C] of the active patches (pps patches per sample, SS pixels per
-// patch, at most cap_rows rows); see laud_se.hip.  `scratch` holds N*(2*C + se_width) floats.
-constexpr int kSeMaxC = 4096, kSeMaxHidden = 1024;  // widest layer / SE hidden layer the kernels keep in LDS
+// patch); see laud_se.hip.
+constexpr int kSeMaxC = 4096, kSeMaxHidden = 1024;  // widest layer / SE hidden layer the kernel keeps in LDS
 int launch_se(int dtype, int N, int pps, int SS, int C, const laud_group_se* e, void* h2, const int32_t* idx,
-              const int32_t* count, float* scratch, long long cap_rows, hipStream_t stream);
+              const int32_t* count, hipStream_t stream);
 
 // Out-of-place calls: pixels of inactive patches keep their value, so they are copied from x to out, bit for bit.  The copy
 // rides in extra workgroups of the block's last launch (nblocks of them, from workgroup id `first` on): it has nothing to

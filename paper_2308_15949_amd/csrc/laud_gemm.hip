@@ -976,7 +976,7 @@ static int validate_group_se(const laud_bottleneck* p, const laud_group_se* e, c
   if (!(g == 8 || g == 16 || g == 32 || g == 64)) return LAUD_ERR_UNSUPPORTED;
   if (e->se_width > kSeMaxHidden || (e->se_width > 0 && p->c_mid > kSeMaxC)) return LAUD_ERR_UNSUPPORTED;
   if (e->se_width > 0 && fx.N > 65535) return LAUD_ERR_UNSUPPORTED;  // one grid row of the squeeze per sample
-  // the SE module's means, gates and hidden units are kept in the scratch region of h1 (N*H*W*c_mid elements)
+  // (the entry points' documented range: means, gates and hidden units fit the scratch activations of one sample)
   if (e->se_width > 0 && 4 * (2 * (size_t)p->c_mid + e->se_width) > (size_t)fx.H * fx.W * p->c_mid * elem_bytes(fx.dtype))
     return LAUD_ERR_UNSUPPORTED;
   return LAUD_OK;
@@ -1059,12 +1059,16 @@ static int launch_sparse_head(int dtype, const laud_bottleneck* p, const void* x
 }
 
 // Whether a dynamic block's first 1x1 runs on every pixel of the map instead of on the dilated active set: where the small
-// tiles take it, the launch is bound by its latency and not by its rows, and the pixel lists would cost a launch of
-// their own.
+// tiles take it the launch is bound by its latency and not by its rows, and on narrow maps (up to kDenseConv1Bytes of input
+// and output, kDenseConv1Flops) all rows take about 16 us, of which the rows outside the dilated set (a tenth to a half) are
+// less than the launch that writes the pixel lists (7 us).
+constexpr double kDenseConv1Bytes = 40e6, kDenseConv1Flops = 4e9;
 static bool dense_conv1_wanted(int dtype, const laud_bottleneck* p, long long npix) {
   GemmArgs a{};
   a.K = p->c_in; a.Ncols = p->c_mid;
-  return skinny_wanted(M_SD1, dtype, a, npix);
+  if (skinny_wanted(M_SD1, dtype, a, npix)) return true;
+  return dtype == LAUD_BF16 && (double)npix * (p->c_in + p->c_mid) * 2 <= kDenseConv1Bytes &&
+         2.0 * npix * p->c_in * p->c_mid <= kDenseConv1Flops;
 }
 static int run_dense_conv1(const laud_fmap& fx, const laud_bottleneck* p, const void* x, void* h1, hipStream_t st) {
   GemmArgs a{};
@@ -1151,7 +1155,7 @@ static int run_dyn_block(const void* x, laud_fmap fx, const laud_bottleneck* p, 
   a.lda = p->c_mid; a.ldo = p->c_mid;
   if ((rc = launch_conv2(fx.dtype, a, e, npix, st)) != LAUD_OK) return rc;
   if (e && e->se_width > 0 &&
-      (rc = launch_se(fx.dtype, fx.N, Hp * Wp, S * S, p->c_mid, e, h2, idx, count, (float*)h1, npix, st)) != LAUD_OK)
+      (rc = launch_se(fx.dtype, fx.N, Hp * Wp, S * S, p->c_mid, e, h2, idx, count, st)) != LAUD_OK)
     return rc;
   // conv3: 1x1 on dense h2 with the scatter-add epilogue
   a.A = h2; a.Wt = p->w3; a.scale = p->s3; a.shift = p->t3; a.Out = out; a.Res = x;
@@ -1494,7 +1498,7 @@ static int run_dyn_projection(const void* x, laud_fmap fx, const laud_bottleneck
   a.lda = p->c_mid; a.ldo = p->c_mid;
   if ((rc = launch_conv2(fx.dtype, a, e, nout, st)) != LAUD_OK) return rc;
   if (e && e->se_width > 0 &&
-      (rc = launch_se(fx.dtype, fx.N, Hp * Wp, S * S, p->c_mid, e, h2, idx, count, (float*)h1, nout, st)) != LAUD_OK)
+      (rc = launch_se(fx.dtype, fx.N, Hp * Wp, S * S, p->c_mid, e, h2, idx, count, st)) != LAUD_OK)
     return rc;
   // conv3 added onto the shortcut already in `out`, at the active output pixels
   a.A = h2; a.Wt = p->w3; a.scale = p->s3; a.shift = p->t3; a.Out = out; a.Res = out;
