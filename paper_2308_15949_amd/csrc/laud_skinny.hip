@@ -44,7 +44,8 @@ struct SkinnyArgs {
   int cap_rows;               // rows (dense) or their upper bound (count on the device)
   int kch, KT;                // slices per tap, slices
   unsigned kmul;              // ceil(2^32 / kch), 0 for kch = 1
-  float inv_ss, inv_s, inv_pps, inv_wp, inv_howo, inv_wo, inv_rt;
+  int deal;                   // tiles to XCDs: 1 by row tile, 2 by column tile (a multiple of eight of them), 0 as they come
+  float inv_ss, inv_s, inv_pps, inv_wp, inv_howo, inv_wo, inv_rt, inv_ct;
 };
 __device__ __forceinline__ int fdiv(int n, float inv) { return (int)(((float)n + 0.5f) * inv); }
 
@@ -80,11 +81,17 @@ __global__ __launch_bounds__(64 * NW) void k_skinny(const SkinnyArgs ka) {
       return;
     }
   }
-  // which tile: with eight or more column tiles the tiles of a column (same weights) stay on one XCD
+  // which tile (consecutive workgroups go round-robin over the XCDs): the larger operand is read by one XCD only -- row tiles
+  // dealt to the XCDs as in the tiled kernel, so that the next launch finds its rows in the same L2, or column tiles
   int rt, ct;
   {
     const int L = blockIdx.x;
-    if ((a.col_tiles & 7) == 0) {
+    if (ka.deal == 1) {
+      const int s = L >> 3, r8 = fdiv(s, ka.inv_ct);
+      rt = r8 * 8 + (L & 7);
+      ct = s - r8 * a.col_tiles;
+      if (rt >= a.row_tiles) return;
+    } else if (ka.deal == 2) {
       const int s = L >> 3, c8 = fdiv(s, ka.inv_rt);
       ct = c8 * 8 + (L & 7);
       rt = s - c8 * a.row_tiles;
@@ -392,9 +399,11 @@ static int launch_skinny_t(GemmArgs a, long long cap_rows, hipStream_t st) {
   k.inv_s = 1.f / a.S; k.inv_ss = 1.f / (a.S * a.S);
   k.inv_wp = 1.f / (oW / a.S); k.inv_pps = 1.f / ((oH / a.S) * (oW / a.S));
   k.inv_howo = a.Ho > 0 ? 1.f / (a.Ho * a.Wo) : 0.f; k.inv_wo = a.Wo > 0 ? 1.f / a.Wo : 0.f;
-  k.inv_rt = 1.f / a.row_tiles;
+  k.inv_rt = 1.f / a.row_tiles; k.inv_ct = 1.f / a.col_tiles;
+  const bool by_row = cap_rows > (long long)a.Ncols * (TAPS ? 9 : 1) && a.row_tiles >= 64;
+  k.deal = by_row ? 1 : (a.col_tiles & 7) == 0 ? 2 : 0;
   const int lds = skinny_lds<TM, TN, NW>() + (MODE == M_DENSE1 && a.wmask ? a.K * 4 : 0);
-  unsigned grid = (unsigned)(a.row_tiles * a.col_tiles);
+  unsigned grid = (unsigned)((by_row ? (a.row_tiles + 7) / 8 * 8 : a.row_tiles) * a.col_tiles);
   if constexpr (MODE == M_CONV3) {
     k.g.cp.first = (int)grid;
     grid += (unsigned)a.cp.nblocks;
@@ -431,7 +440,7 @@ static int launch_skinny_e(const GemmArgs& a, long long cap_rows, hipStream_t st
     constexpr int fill = sizeof(ET) == 2 ? 192 : 384;
     if (tiles(4, 4) >= fill) return launch_skinny_t<MODE, ET, 4, 4, 4, 2>(a, cap_rows, st);
     if (tiles(2, 4) >= fill) return launch_skinny_t<MODE, ET, 2, 4, 4, 3>(a, cap_rows, st);
-    const bool small = tiles(2, 2) < fill;
+    const bool small = tiles(2, 2) < 192;
     if (kt > 8) return small ? launch_skinny_t<MODE, ET, 1, 1, 8, 8>(a, cap_rows, st) : launch_skinny_t<MODE, ET, 2, 2, 8, 4>(a, cap_rows, st);
     return small ? launch_skinny_t<MODE, ET, 1, 1, 4, 4>(a, cap_rows, st) : launch_skinny_t<MODE, ET, 2, 2, 4, 4>(a, cap_rows, st);
   }
@@ -452,15 +461,19 @@ int launch_skinny(int mode, int dtype, const GemmArgs& a, long long cap_rows, hi
   }
 }
 
-// The line lies where the tiled kernel of laud_gemm.hip gets the chip filled: counted in 64 x 64 output tiles, the longer the
-// reduction the later (measured on the four ResNet stages at 1 to 64 images: with a reduction of up to 8 slices the two meet
-// at about 256 tiles, with 9 to 16 at 320, with more at 512 and above).
+// The line lies where the tiled kernel of laud_gemm.hip gets the chip filled, counted in 64 x 64 output tiles: there this
+// kernel's 64 x 64 tiles stop fitting the chip in one round.  Measured on the four ResNet stages at 1 to 64 images and
+// activation ratios 0.5 and 0.86 (bf16): the 3x3 wins up to about 260 tiles with 18 slices or more (stage 4, 42 images: 25
+// against 33 us) and to 220 with nine; the 1x1s meet the tiled kernel at 250 tiles with up to 8 slices, at 200 with more,
+// and at 200 where a residual is read.  In float32 the tiled kernel is bound by its MFMAs on few workgroups much longer.
 bool skinny_wanted(int mode, int dtype, const GemmArgs& a, long long cap_rows) {
-  const bool taps = mode == M_CONV2 || mode == M_SD2 || mode == M_G2;
+  const bool taps = mode == M_CONV2 || mode == M_SD2 || mode == M_G2, res = mode == M_CONV3 || mode == M_SD3;
   const int bke = dtype == LAUD_BF16 ? 64 : 32;
   const int kt = (taps ? 9 : 1) * (((mode == M_G2 ? 64 : a.K) + bke - 1) / bke);
   const long long t = ((cap_rows + 63) / 64) * ((a.Ncols + 63) / 64);
-  return cap_rows < (1 << 20) && t <= (kt <= 8 ? 256 : kt <= 16 ? 320 : 512);
+  int most = taps ? (kt > 9 ? 288 : 224) : (kt > 8 || res ? 208 : 256);
+  if (dtype == LAUD_F32 && kt > 8) most = 512;
+  return cap_rows < (1 << 20) && t <= most;
 }
 
 int skinny_init_device() {
