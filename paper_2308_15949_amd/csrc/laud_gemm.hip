@@ -87,6 +87,7 @@ __device__ __forceinline__ uint4 mask_tail(uint4 v, int nvalid) {
 
 template <int MODE, typename ET, int BM, int BN, int WGN>
 __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
+  prefetch_args<sizeof(GemmArgs)>();
   // 2 x WGN waves; each wave owns a (BM/2) x (BN/WGN) sub-tile of 32x32 MFMA tiles.
   constexpr int NT = 128 * WGN;          // threads per workgroup
   constexpr int RPP = NT / 8;            // tile rows covered by one pass of the loading threads

@@ -245,6 +245,7 @@ __device__ __forceinline__ void head_tile(const HeadArgs& a, const int row0, con
 template <bool PROJ>
 __global__ __launch_bounds__(head::kThreads) void k_head(const HeadArgs a) {
   using namespace head;
+  prefetch_args<sizeof(HeadArgs)>();
   int pb = a.pb;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, l8 = lane >> 3;
   if (a.slist != nullptr) {

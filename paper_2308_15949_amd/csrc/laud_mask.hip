@@ -215,6 +215,7 @@ __global__ __launch_bounds__(kCompactThreads) void k_pool_compact_s2(PoolArgs pa
                                                                      int32_t* __restrict__ sample_offsets,
                                                                      int per_sample) {
   __shared__ int scan[2][kCompactThreads / kWave];
+  prefetch_args<sizeof(PoolArgs) + 48>();
   const int Hp = pa.H / 2, Wp = pa.W / 2;
   const int b = blockIdx.x, tid = threadIdx.x;
   float2 top[kPoolFusedBlocks], bot[kPoolFusedBlocks];
@@ -270,6 +271,7 @@ __global__ __launch_bounds__(kCompactThreads) void k_pool_compact_one_block(Pool
                                                                             int32_t* __restrict__ sample_offsets,
                                                                             int per_sample) {
   __shared__ int scan[kCompactThreads / kWave];
+  prefetch_args<sizeof(PoolArgs) + 48>();
   const int q = threadIdx.x;
   const bool on = q < n ? pooled_decision(pa, q, mask) : false;
   const unsigned long long bal = __ballot(on);
@@ -380,7 +382,7 @@ int launch_pool_compact(const float* proj, int N, int H, int W, int S, float bia
                         hipStream_t stream) {
   const int pps = (H / S) * (W / S), npatch = N * pps;
   PoolArgs pa{proj, keep, logits, H, W, S, bias};
-  if (S == 2 && npatch > 0 && npatch <= kPoolFusedMax) {
+  if (S == 2 && npatch > kCompactThreads && npatch <= kPoolFusedMax) {
     StageScope scope(LAUD_STAGE_COMPACT, stream);
     hipLaunchKernelGGL(k_pool_compact_s2, dim3((npatch + kCompactThreads - 1) / kCompactThreads), dim3(kCompactThreads), 0,
                        stream, pa, npatch, mask, idx, count, sample_offsets, pps);

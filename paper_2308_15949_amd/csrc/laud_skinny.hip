@@ -57,6 +57,7 @@ __host__ __device__ constexpr int skinny_lds() {
 
 template <int MODE, typename ET, int TM, int TN, int NW, int D>
 __global__ __launch_bounds__(64 * NW) void k_skinny(const SkinnyArgs ka) {
+  prefetch_args<sizeof(SkinnyArgs)>();
   const GemmArgs& a = ka.g;
   constexpr int BM = 16 * TM, BN = 16 * TN, NT = 64 * NW;
   constexpr int EPC = elem<ET>::per16, ES = (int)sizeof(ET), BKE = 8 * EPC;
