@@ -309,6 +309,27 @@ size_t head_packed_bytes(int c_in);
 int launch_head_pack(const void* w1, int c_in, void* packed, hipStream_t stream);
 int launch_head(const HeadArgs& a, hipStream_t stream);
 
+// 3x3 -> last 1x1 -> residual add / projection shortcut of the 64-wide bf16 blocks in one kernel (laud_narrow.hip), for
+// narrow_supported() shapes and row counts.
+struct NarrowArgs {
+  const void* h1;        // [input pixels][64]
+  const void* w2; const void* w3;  // [64][3][3][64], [256][64]
+  const float* s2; const float* t2; const float* s3; const float* t3;
+  const void* res;       // residual [output pixels][256]; may alias out
+  void* out;
+  const int32_t* count;  // active patches (device) and their ascending ids; null with a shortcut (every output pixel)
+  const int32_t* list;
+  int m_rows;            // rows, or their upper bound where the count is on the device
+  int H, W, S, stride, Ho, Wo, relu;
+  // projection shortcut instead of a residual (static first block): x [input pixels][64] read at the 3x3's centre
+  const void* x; const void* wsc; const float* ssc; const float* tsc;
+  InactiveCopy cp;
+  float inv_s, inv_ss, inv_wp, inv_pps, inv_howo, inv_wo;  // set by launch_narrow
+};
+bool narrow_supported(int dtype, int c_mid, int c_out, long long rows);
+int narrow_init_device();
+int launch_narrow(const NarrowArgs& a, hipStream_t stream);
+
 // Stage timing (see laud_stage_timing_enable): RAII bracket around the launches of one stage.
 extern bool g_stage_timing_on;
 void stage_mark(int stage, hipStream_t stream, bool begin);

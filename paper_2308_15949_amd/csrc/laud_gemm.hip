@@ -1097,6 +1097,20 @@ static int try_tail(int dtype, const laud_bottleneck* p, const laud_group_se* e,
   return 1;
 }
 
+// The same for the 64-wide blocks (laud_narrow.hip).
+static int try_narrow(int dtype, const laud_bottleneck* p, const laud_group_se* e, const void* h1, const void* res,
+                      void* out, const int32_t* idx, const int32_t* count, int H, int W, int S, int stride, int Ho, int Wo,
+                      long long cap_rows, const InactiveCopy& copy, hipStream_t st, int* rc) {
+  if (e || !narrow_supported(dtype, p->c_mid, p->c_out, cap_rows)) return 0;
+  NarrowArgs t{};
+  t.h1 = h1; t.w2 = p->w2; t.w3 = p->w3; t.s2 = p->s2; t.t2 = p->t2; t.s3 = p->s3; t.t3 = p->t3;
+  t.res = res; t.out = out; t.count = count; t.list = idx; t.m_rows = (int)cap_rows;
+  t.H = H; t.W = W; t.S = S; t.stride = stride; t.Ho = Ho; t.Wo = Wo; t.relu = p->relu_out ? 1 : 0;
+  t.cp = copy;
+  *rc = launch_narrow(t, st);
+  return 1;
+}
+
 // The spatially adaptive block on an index list; `e` adds the group convolution / SE variant (or is null).
 static int run_dyn_block(const void* x, laud_fmap fx, const laud_bottleneck* p, const laud_group_se* e, int S,
                          const int32_t* idx, const int32_t* count, void* out, void* ws, size_t ws_bytes,
@@ -1150,6 +1164,7 @@ static int run_dyn_block(const void* x, laud_fmap fx, const laud_bottleneck* p, 
     }
   }
   if (try_tail(fx.dtype, p, e, h1, x, out, idx, count, fx.H, fx.W, S, 1, fx.H, fx.W, npix, wsb + L.wpack, copy, st, &rc)) return rc;
+  if (try_narrow(fx.dtype, p, e, h1, x, out, idx, count, fx.H, fx.W, S, 1, fx.H, fx.W, npix, copy, st, &rc)) return rc;
   // conv2: 3x3 over active patches, A rows fetched from h1 by index -> dense h2
   a.A = h1; a.Wt = p->w2; a.scale = p->s2; a.shift = p->t2; a.Out = h2;
   a.count = count; a.list = idx; a.K = p->c_mid; a.ldw = 9 * p->c_mid; a.Ncols = p->c_mid;
@@ -1230,6 +1245,7 @@ extern "C" int laud_masker_dyn_bottleneck(const void* x, laud_fmap fx, const lau
   a.wmask = nullptr; a.proj = nullptr;
   const InactiveCopy copy = inactive_copy(x, out, fx, S, idx, count);
   if (try_tail(fx.dtype, p, nullptr, h1, x, out, idx, count, fx.H, fx.W, S, 1, fx.H, fx.W, npix, wsb + L.wpack, copy, st, &rc)) return rc;
+  if (try_narrow(fx.dtype, p, nullptr, h1, x, out, idx, count, fx.H, fx.W, S, 1, fx.H, fx.W, npix, copy, st, &rc)) return rc;
   // conv2 and conv3 exactly as in laud_dyn_bottleneck
   a.A = h1; a.Wt = p->w2; a.scale = p->s2; a.shift = p->t2; a.Out = h2;
   a.count = count; a.list = idx; a.K = p->c_mid; a.ldw = 9 * p->c_mid; a.Ncols = p->c_mid;
@@ -1382,6 +1398,15 @@ extern "C" int laud_static_bottleneck(const void* x, laud_fmap fx, const laud_bo
   int rc;
   GemmArgs a{};
   a.H = fx.H; a.W = fx.W; a.S = 1; a.D = 1; a.G = 1; a.Ho = Ho; a.Wo = Wo;
+  if (p->c_in == 64 && narrow_supported(fx.dtype, p->c_mid, p->c_out, nout)) {
+    // conv1 on every input pixel; 3x3, last 1x1 and shortcut in one kernel
+    if ((rc = run_dense_conv1(fx, p, x, h1, st)) != LAUD_OK) return rc;
+    NarrowArgs t{};
+    t.h1 = h1; t.w2 = p->w2; t.w3 = p->w3; t.s2 = p->s2; t.t2 = p->t2; t.s3 = p->s3; t.t3 = p->t3;
+    t.out = out; t.m_rows = (int)nout; t.H = fx.H; t.W = fx.W; t.S = 1; t.stride = stride; t.Ho = Ho; t.Wo = Wo; t.relu = 1;
+    t.x = x; t.wsc = w_sc; t.ssc = s_sc; t.tsc = t_sc;
+    return launch_narrow(t, st);
+  }
   // shortcut: strided 1x1 + affine, straight into the output buffer
   a.A = x; a.Wt = w_sc; a.scale = s_sc; a.shift = t_sc; a.Out = out; a.K = p->c_in; a.ldw = p->c_in;
   a.Ncols = p->c_out; a.lda = p->c_in; a.ldo = p->c_out; a.relu = 0; a.stride = stride; a.m_rows = (int)nout;
@@ -1493,6 +1518,7 @@ static int run_dyn_projection(const void* x, laud_fmap fx, const laud_bottleneck
     }
   }
   if (try_tail(fx.dtype, p, e, h1, out, out, idx, count, fx.H, fx.W, S, stride, Ho, Wo, nout, wsb + L.wpack, InactiveCopy{}, st, &rc)) return rc;
+  if (try_narrow(fx.dtype, p, e, h1, out, out, idx, count, fx.H, fx.W, S, stride, Ho, Wo, nout, InactiveCopy{}, st, &rc)) return rc;
   // conv2: strided 3x3 at the active output pixels -> dense h2
   a.A = h1; a.Wt = p->w2; a.scale = p->s2; a.shift = p->t2; a.Out = h2;
   a.count = count; a.list = idx; a.K = p->c_mid; a.ldw = 9 * p->c_mid; a.Ncols = p->c_mid;
@@ -1619,6 +1645,7 @@ extern "C" int laud_init(void) {
   rc = gemm_init_device();
   if (rc != LAUD_OK) return rc;
   if ((rc = skinny_init_device()) != LAUD_OK) return rc;
+  if ((rc = narrow_init_device()) != LAUD_OK) return rc;
   if ((rc = tail_init_device()) != LAUD_OK) return rc;
   return head_init_device();
 }
