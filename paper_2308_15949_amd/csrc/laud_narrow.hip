@@ -3,12 +3,12 @@
 //
 // These blocks are bound by memory traffic (dense 136 FLOP per byte), and as separate launches h2, and in a first block the
 // shortcut, make a round trip through it: at 128 images 42 + 55 us for the two convolutions of a dynamic block at ratio 0.5,
-// 72 + 121 + 100 us for those of a static first block with its shortcut.  All weights of such a block fit a compute unit's
-// registers, so here a workgroup keeps them there for its whole life and walks over its tiles:
+// 72 + 121 + 100 us for those of a static first block with its shortcut.  All weights of such a block fit a compute unit, so
+// here a workgroup keeps them there for its whole life and walks over its tiles:
 //
 //   * one workgroup = 128 rows (active pixels of the index list, or all output pixels) x all channels, 8 waves.  In the
-//     3x3 wave (wn, wm) owns mid channels 32 wn .. +31 of rows 32 wm .. +31, its weights (9 taps x 64 channels) in 128
-//     registers per lane (the ninth tap's in LDS: 144 registers leave too few); in the last 1x1 wave w owns output channels 32 w .. +31 of all rows, its weights in 16.
+//     3x3 wave (wn, wm) owns mid channels 32 wn .. +31 of rows 32 wm .. +31, its weights (9 taps x 64 channels) in
+//     registers as far as these go (seven taps, four with a shortcut), the rest in LDS; in the last 1x1 wave w owns output channels 32 w .. +31 of all rows.
 //   * a tap's rows of h1 (64 channels = one 128-byte slice) come with LDS-direct loads into a ring of four slices, swizzled
 //     as in the fused kernel of the 256-wide blocks; one barrier per tap.  h2 goes through LDS once.  The rows of a
 //     projection shortcut (64 input channels) are one more slice.
@@ -26,17 +26,37 @@ namespace laud {
 
 namespace narrow {
 constexpr int kMid = 64, kOut = 256, kBM = 128, kThreads = 512;
-constexpr int kStage = kBM * 128, kRing = 4;
+constexpr int kStage = kBM * 128, kRing = 4, kAhead = kRing - 1;  // slices requested ahead of the one in use
 constexpr int kH2 = kRing * kStage, kX = kH2 + kStage, kTab = kX + kStage;
 constexpr int kTabFloats = 2 * kMid + 4 * kOut;         // s2 t2 | s3 t3 | s_sc t_sc
 constexpr int kRows = kTab + kTabFloats * 4;            // output rows of two tiles
-constexpr int kW8 = kRows + 2 * kBM * 4;                // the ninth tap's weights, in MFMA order [wn][kg][lane]
-constexpr int kLds = kW8 + 2 * 4 * 64 * 16;
+// taps whose weights stay in registers; the others' lie in LDS in MFMA order
+template <bool SC> constexpr int reg_taps() { return SC ? 4 : 7; }
+constexpr int kW2 = kRows + 2 * kBM * 4;                // [tap - reg_taps][wn][kg][lane] 16 bytes
+template <bool SC> constexpr int lds_bytes() { return kW2 + (9 - reg_taps<SC>()) * 8192; }
 constexpr unsigned kOob = 0x80000000u;
+static_assert(lds_bytes<false>() <= 160 * 1024 && lds_bytes<true>() <= 160 * 1024, "LDS");
 static_assert(kMid * 9 * kMid * 2 <= kTab, "w2 passes through the ring, h2 and shortcut regions on its way into registers");
 }  // namespace narrow
 
 __device__ __forceinline__ int fdivn(int n, float inv) { return (int)(((float)n + 0.5f) * inv); }
+
+// vm_wait with a count that is a constant once the loop around it is unrolled
+__device__ __forceinline__ void vm_wait_n(int n) {
+  switch (n) {
+    case 0: vm_wait<0>(); break;
+    case 2: vm_wait<2>(); break;
+    case 4: vm_wait<4>(); break;
+    case 6: vm_wait<6>(); break;
+    case 8: vm_wait<8>(); break;
+    case 10: vm_wait<10>(); break;
+    case 12: vm_wait<12>(); break;
+    case 14: vm_wait<14>(); break;
+    case 16: vm_wait<16>(); break;
+    case 18: vm_wait<18>(); break;
+    default: vm_wait<0>(); break;
+  }
+}
 
 template <bool SC>
 __global__ __launch_bounds__(narrow::kThreads) void k_narrow(const NarrowArgs a) {
@@ -84,18 +104,18 @@ __global__ __launch_bounds__(narrow::kThreads) void k_narrow(const NarrowArgs a)
   vm_wait<0>();
   lds_wait();
   wg_barrier();
-  u32x4 w2r[8][4], w3r[4], wsr[4];
+  constexpr int RT = reg_taps<SC>();
+  u32x4 w2r[RT][4], w3r[4], wsr[4];
 #pragma unroll
-  for (int t = 0; t < 8; ++t)
+  for (int t = 0; t < 9; ++t)
 #pragma unroll
-    for (int kg = 0; kg < 4; ++kg)
-      w2r[t][kg] = *reinterpret_cast<const u32x4*>(smem + (32 * wn + l31) * (9 * kMid * 2) + t * 128 + kg * 32 + lhi * 16);
-  if (wm == 0) {
-#pragma unroll
-    for (int kg = 0; kg < 4; ++kg)
-      *reinterpret_cast<u32x4*>(smem + kW8 + ((wn * 4 + kg) * 64 + lane) * 16) =
-          *reinterpret_cast<const u32x4*>(smem + (32 * wn + l31) * (9 * kMid * 2) + 8 * 128 + kg * 32 + lhi * 16);
-  }
+    for (int kg = 0; kg < 4; ++kg) {
+      if (t < RT || wm == 0) {
+        const u32x4 v = *reinterpret_cast<const u32x4*>(smem + (32 * wn + l31) * (9 * kMid * 2) + t * 128 + kg * 32 + lhi * 16);
+        if (t < RT) w2r[t < RT ? t : 0][kg] = v;
+        else *reinterpret_cast<u32x4*>(smem + kW2 + (t - RT) * 8192 + ((wn * 4 + kg) * 64 + lane) * 16) = v;
+      }
+    }
   lds_wait();
   wg_barrier();
   for (int i = wave; i < kW3KB; i += 8) dma16(w3rs, lane * 16u, (unsigned)i * 1024u, (unsigned)i * 1024u);
@@ -156,7 +176,7 @@ __global__ __launch_bounds__(narrow::kThreads) void k_narrow(const NarrowArgs a)
   constexpr int NS = SC ? 10 : 9;  // slices of a tile; slice 9: the shortcut's input rows
   auto issue_A = [&](int s) __attribute__((always_inline)) {
     const unsigned soff = s < 9 ? (unsigned)((s / 3) * a.W + s % 3) * 128u : 0u;
-    const unsigned base = (s < 9 ? (unsigned)(s & (kRing - 1)) * kStage : (unsigned)kX) + wave * 1024u;
+    const unsigned base = (s < 9 ? (unsigned)(s % kRing) * kStage : (unsigned)kX) + wave * 1024u;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const unsigned v = ((amask[i] >> (s < 9 ? s : 4)) & 1u) ? voffA[i] : kOob;  // (the centre tap is inside for every live row)
@@ -171,9 +191,8 @@ __global__ __launch_bounds__(narrow::kThreads) void k_narrow(const NarrowArgs a)
 
   request_entries(tile);
   describe(tile, 0);
-  issue_A(0);
-  issue_A(1);
-  issue_A(2);
+#pragma unroll
+  for (int s = 0; s < kAhead; ++s) issue_A(s);
   int buf = 0;
   lds_wait();
   wg_barrier();  // the output rows of the first tile
@@ -193,25 +212,22 @@ __global__ __launch_bounds__(narrow::kThreads) void k_narrow(const NarrowArgs a)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0.f;
     // ---- the 3x3 -------------------------------------------------------------------------------------------------
-    constexpr int kR = SC ? 0 : 10;  // residual and list loads, between the first three slices and the fourth
+    constexpr int kR = SC ? 0 : 10;  // residual and list loads, between slices kAhead - 1 and kAhead
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      // loads younger than slice s: the two slices behind it (as far as there are any), and the residual while s < 3
-      constexpr int kAfter[3] = {4, 2, 0};
-      if (s < 3) vm_wait<4 + kR>();
-      else if (s < NS - 2) vm_wait<4>();
-      else if (s == NS - 2) vm_wait<kAfter[1]>();
-      else vm_wait<kAfter[2]>();
+      // loads younger than slice s: the slices behind it that have been requested, and the residual where it is
+      vm_wait_n(2 * ((s + kAhead - 1 < NS - 1 ? s + kAhead - 1 : NS - 1) - s) + (s < kAhead ? kR : 0));
       wg_barrier();  // everyone's part of slice s is there, and everyone is done with slice s - 1
-      if (s + 3 < NS) issue_A(s + 3);
+      if (s + kAhead < NS) issue_A(s + kAhead);
       if (s < 9) {
-        const unsigned char* pa = smem + (unsigned)(s & (kRing - 1)) * kStage + wm * 4096u;
+        const unsigned char* pa = smem + (unsigned)(s % kRing) * kStage + wm * 4096u;
         uint4 fa[4];
 #pragma unroll
         for (int kg = 0; kg < 4; ++kg) fa[kg] = *reinterpret_cast<const uint4*>(pa + (swz ^ (kg << 5)));
 #pragma unroll
         for (int kg = 0; kg < 4; ++kg) {
-          const u32x4 w = s < 8 ? w2r[s < 8 ? s : 0][kg] : *reinterpret_cast<const u32x4*>(smem + kW8 + ((wn * 4 + kg) * 64 + lane) * 16);
+          const u32x4 w = s < RT ? w2r[s < RT ? s : 0][kg]
+                                 : *reinterpret_cast<const u32x4*>(smem + kW2 + (s - RT) * 8192 + ((wn * 4 + kg) * 64 + lane) * 16);
           acc = mma_bf16(w, fa[kg], acc);
         }
       }
@@ -239,10 +255,21 @@ __global__ __launch_bounds__(narrow::kThreads) void k_narrow(const NarrowArgs a)
     describe(tile + step, buf ^ 1);  // (past the last tile: no live rows, nothing is fetched)
     lds_wait();
     wg_barrier();  // h2 complete; everyone is done with the slices
-    issue_A(0);
-    issue_A(1);
-    issue_A(2);
-    // ---- the last 1x1 (and the shortcut), one 32-row block at a time ------------------------------------------------
+#pragma unroll
+    for (int s = 0; s < kAhead; ++s) issue_A(s);
+    // ---- the last 1x1 (and the shortcut), one 32-row block at a time; the affine of this wave's channels is read
+    // once per tile (per block it took as much LDS time as the fragments) -------------------------------
+    float4 sc[4], sh[4], s4[4], t4[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int c = 32 * wave + 8 * g + 4 * lhi;
+      sc[g] = *reinterpret_cast<const float4*>(s_s3 + c);
+      sh[g] = *reinterpret_cast<const float4*>(s_t3 + c);
+      if constexpr (SC) {
+        s4[g] = *reinterpret_cast<const float4*>(s_ss + c);
+        t4[g] = *reinterpret_cast<const float4*>(s_ts + c);
+      }
+    }
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       f32x16 o, os;
@@ -261,23 +288,19 @@ __global__ __launch_bounds__(narrow::kThreads) void k_narrow(const NarrowArgs a)
           o = mma_bf16(w3r[k2 + k], fh[k], o);
           if constexpr (SC) os = mma_bf16(wsr[k2 + k], fx[k], os);
         }
-        __builtin_amdgcn_sched_barrier(0);
       }
       float v[16];
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const int c = 32 * wave + 8 * g + 4 * lhi;
-        const float4 sc = *reinterpret_cast<const float4*>(s_s3 + c), sh = *reinterpret_cast<const float4*>(s_t3 + c);
-        v[4 * g + 0] = o[4 * g + 0] * sc.x + sh.x;
-        v[4 * g + 1] = o[4 * g + 1] * sc.y + sh.y;
-        v[4 * g + 2] = o[4 * g + 2] * sc.z + sh.z;
-        v[4 * g + 3] = o[4 * g + 3] * sc.w + sh.w;
+        v[4 * g + 0] = o[4 * g + 0] * sc[g].x + sh[g].x;
+        v[4 * g + 1] = o[4 * g + 1] * sc[g].y + sh[g].y;
+        v[4 * g + 2] = o[4 * g + 2] * sc[g].z + sh[g].z;
+        v[4 * g + 3] = o[4 * g + 3] * sc[g].w + sh[g].w;
         if constexpr (SC) {
-          const float4 s4 = *reinterpret_cast<const float4*>(s_ss + c), t4 = *reinterpret_cast<const float4*>(s_ts + c);
-          v[4 * g + 0] += os[4 * g + 0] * s4.x + t4.x;
-          v[4 * g + 1] += os[4 * g + 1] * s4.y + t4.y;
-          v[4 * g + 2] += os[4 * g + 2] * s4.z + t4.z;
-          v[4 * g + 3] += os[4 * g + 3] * s4.w + t4.w;
+          v[4 * g + 0] += os[4 * g + 0] * s4[g].x + t4[g].x;
+          v[4 * g + 1] += os[4 * g + 1] * s4[g].y + t4[g].y;
+          v[4 * g + 2] += os[4 * g + 2] * s4[g].z + t4[g].z;
+          v[4 * g + 3] += os[4 * g + 3] * s4[g].w + t4[g].w;
         }
       }
       to_consecutive_channels(v);  // 0-3, 8-11, 4-7, 12-15: channels 32 wave + 16 lhi + 0 .. 15
@@ -318,9 +341,11 @@ int narrow_init_device() {
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 32) return LAUD_ERR_HIP;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return LAUD_ERR_HIP;
   g_narrow_cus[dev] = cus / 8 * 8;
-  for (const void* f : {reinterpret_cast<const void*>(&k_narrow<false>), reinterpret_cast<const void*>(&k_narrow<true>)})
-    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, narrow::kLds) != hipSuccess) return LAUD_ERR_HIP;
-  return LAUD_OK;
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_narrow<false>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          narrow::lds_bytes<false>()) != hipSuccess)
+    return LAUD_ERR_HIP;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_narrow<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             narrow::lds_bytes<true>()) == hipSuccess ? LAUD_OK : LAUD_ERR_HIP;
 }
 
 int launch_narrow(const NarrowArgs& args, hipStream_t st) {
@@ -341,10 +366,10 @@ int launch_narrow(const NarrowArgs& args, hipStream_t st) {
   a.cp.first = (int)grid;
   StageScope scope(LAUD_STAGE_CONV2, st);
   if (a.x) {
-    hipLaunchKernelGGL((k_narrow<true>), dim3(grid), dim3(narrow::kThreads), narrow::kLds, st, a);
+    hipLaunchKernelGGL((k_narrow<true>), dim3(grid), dim3(narrow::kThreads), narrow::lds_bytes<true>(), st, a);
   } else {
     grid += (unsigned)a.cp.nblocks;
-    hipLaunchKernelGGL((k_narrow<false>), dim3(grid), dim3(narrow::kThreads), narrow::kLds, st, a);
+    hipLaunchKernelGGL((k_narrow<false>), dim3(grid), dim3(narrow::kThreads), narrow::lds_bytes<false>(), st, a);
   }
   return check_launch();
 }
