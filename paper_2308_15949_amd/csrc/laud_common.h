@@ -330,6 +330,8 @@ bool narrow_supported(int dtype, int c_mid, int c_out, long long rows);
 int narrow_init_device();
 int launch_narrow(const NarrowArgs& a, hipStream_t stream);
 
+int stem_init_device(int* cus_out);
+
 // Stage timing (see laud_stage_timing_enable): RAII bracket around the launches of one stage.
 extern bool g_stage_timing_on;
 void stage_mark(int stage, hipStream_t stream, bool begin);

@@ -1646,6 +1646,7 @@ extern "C" int laud_init(void) {
   if (rc != LAUD_OK) return rc;
   if ((rc = skinny_init_device()) != LAUD_OK) return rc;
   if ((rc = narrow_init_device()) != LAUD_OK) return rc;
+  if ((rc = stem_init_device(nullptr)) != LAUD_OK) return rc;
   if ((rc = tail_init_device()) != LAUD_OK) return rc;
   return head_init_device();
 }

@@ -1,9 +1,13 @@
 // Static stem of the ResNet body (the whole-body workload): 7x7 stride-2 conv on the 3-channel image with
 // folded-BN affine and ReLU, then 3x3 stride-2 max pooling.  Outside the dynamic hot path (it runs once
-// per image and is not masked): the usual shape (bf16, 64 channels) is an implicit GEMM straight from the
-// image, other shapes go through an im2col kernel and the dense MFMA GEMM of laud_gemm.hip; a plain kernel
-// pools.
+// per image and is not masked): the usual shape (bf16, 64 channels) is one kernel straight from the image to the
+// pooled map, other shapes go through an im2col kernel and the dense MFMA GEMM of laud_gemm.hip, and a plain
+// kernel pools.
 #include "laud_common.h"
+#include "laud_tile_util.h"
+
+#include <algorithm>
+#include <atomic>
 
 namespace laud {
 
@@ -40,90 +44,162 @@ __global__ __launch_bounds__(256) void k_stem_im2col(const ET* __restrict__ x, i
   for (int q = 0; q < (int)(sizeof(v) / 16); ++q) dst[q] = raw[q];
 }
 
-// ---- fused stem conv for the usual shape (bf16, 64 output channels) -----------------------------
-// The 7x7 stride-2 conv as an implicit GEMM straight from the image: no im2col buffer in HBM (it is
-// 13 times the image).  A block walks the 8 x 16-pixel output tiles of one band of 8 output rows; per tile
-// it puts the 21 x 38 input pixels the tile's windows cover into LDS, four bf16 per pixel (the fourth is
-// zero), and runs 32x32x16 MFMAs whose 8-element A fragments are two neighbouring pixels of one window
-// row: K = 7 rows x 8 taps x 4 channels = 224 with zero weights at the eighth tap and the fourth channel.
-// The weights are rearranged into that K order in LDS once per block.  Folded-BN affine and ReLU in the
-// accumulators, output rows through LDS so that stores are 16 bytes.
 typedef __attribute__((ext_vector_type(16))) float stem_f32x16;
-typedef __attribute__((ext_vector_type(8))) __bf16 stem_bf16x8;
-constexpr int kSTY = 8, kSTX = 16;                    // output tile: 128 GEMM rows
-constexpr int kSPY = 2 * kSTY + 5, kSPW = 2 * kSTX + 6;  // 21 x 38 input pixels (38 is even and holds the padded 8th tap)
-constexpr int kSK = 7 * 32;                           // reduction length in the padded order
-constexpr int kSWS = kSK * 2 + 16;                    // LDS weight row stride in bytes
-constexpr int kSOS = 64 * 2 + 16;                     // LDS output row stride in bytes
-__global__ __launch_bounds__(256) void k_stem_conv_bf16(const bf16_t* __restrict__ x, int N, int Hin, int Win, int Hc,
-                                                        int Wc, const bf16_t* __restrict__ w7,
-                                                        const float* __restrict__ s, const float* __restrict__ t,
-                                                        bf16_t* __restrict__ out) {
-  __shared__ __align__(16) unsigned char s_w[64 * kSWS];
-  __shared__ __align__(16) unsigned char s_p[kSPY * kSPW * 8];
-  __shared__ __align__(16) unsigned char s_o[kSTY * kSTX * kSOS];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
-  const int r = lane & 31, h = lane >> 5;
-  for (int i = tid; i < 64 * kSK; i += 256) {
-    const int col = i / kSK, k = i - col * kSK;
-    const int ky = k >> 5, kx = (k & 31) >> 2, c = k & 3;
-    bf16_t v = 0;
-    if (kx < 7 && c < 3) v = w7[col * kStemK + (ky * 7 + kx) * 3 + c];
-    *reinterpret_cast<bf16_t*>(s_w + col * kSWS + k * 2) = v;
+
+// ---- the usual stem (bf16, 64 output channels) in one kernel: 7x7 stride-2 conv, affine, ReLU, 3x3 stride-2 max pooling ----
+// As two kernels the conv's output (four times the image, eight times the result) makes a round trip through memory: 190 + 60
+// us at 128 images of 224 x 224.  Here it stays in LDS.
+//   * A workgroup takes strips of 7 pooled rows (16 conv rows, one of them to spare) and walks along x in steps of 16 conv
+//     columns = 8 pooled columns; the conv columns of two steps lie in LDS (slot = column mod 32), so the pooling windows
+//     that reach one column back find it there.
+//   * Implicit GEMM per step: 256 rows (conv pixels) x 64 channels.  A window row is 21 consecutive values of the image
+//     (7 pixels x 3 channels), padded to 24 = three 16-byte fragments: K = 7 x 24 (+ 8) = 176 in eleven 32x32x16 steps.  A
+//     fragment starts 12 * column bytes into the image row, so each image row is kept in LDS four times, shifted by 0, 12,
+//     24 and 36 bytes: column x reads copy x % 4, where its fragments are 16-byte aligned.
+//   * 8 waves: wave (wm, wn) computes rows 64 wm .. +63, channels 32 wn .. +31, weights in 44 registers per lane for the
+//     workgroup's whole life.  The next step's image rows are on their way in registers meanwhile.
+//   * ReLU leaves bf16 values whose bit patterns order like 16-bit integers: pooling is a packed integer maximum, and
+//     positions outside the conv's output count as zeros.
+constexpr int kSpRows = 7, kSpCols = 8;               // pooled rows of a strip, pooled columns of a step
+constexpr int kSpIn = 37;                             // image rows of a strip: 2 * 15 + 7
+constexpr int kSpDw = 57;                             // dwords of an image row a step reads: 12 * 15 + 48 bytes
+constexpr int kSpCopy = 240, kSpRowB = 4 * kSpCopy;   // LDS bytes of one copy / of the four copies of an image row
+constexpr int kSpConv = (kSpIn * kSpRowB + 255) / 256 * 256;
+constexpr int kSpLds = kSpConv + 16 * 32 * 128;       // conv values [16 rows][32 columns][64 channels]
+constexpr int kSpThreads = 512, kSpLoads = (kSpIn * kSpDw + kSpThreads - 1) / kSpThreads;
+__global__ __launch_bounds__(kSpThreads) void k_stem_pool_bf16(const bf16_t* __restrict__ x, int N, int Hin, int Win, int Hc, int Wc,
+                                                               int Hp, int Wp, int strips, int chunks, int chunk_steps,
+                                                               const bf16_t* __restrict__ w7, const float* __restrict__ s,
+                                                               const float* __restrict__ t, bf16_t* __restrict__ out) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l31 = lane & 31, lhi = lane >> 5, wm = wave >> 1, wn = wave & 1;
+  // weights into registers, through LDS: K step st of this lane is window row f / 3, values 8 (f % 3) .. +7, f = 2 st + lhi
+  {
+    unsigned* d = reinterpret_cast<unsigned*>(smem);
+    for (int i = tid; i < 64 * kStemK / 2; i += kSpThreads) d[i] = reinterpret_cast<const unsigned*>(w7)[i];
   }
-  const int nbands = (Hc + kSTY - 1) / kSTY;
-  const int n = blockIdx.x / nbands, y0 = (blockIdx.x - n * nbands) * kSTY;
-  const int col = wn * 32 + r;
-  const float sc = s[col], sh = t[col];
-  for (int x0 = 0; x0 < Wc; x0 += kSTX) {
-    __syncthreads();  // the previous tile's reads of s_p and s_o are over (first pass: the weights are in place)
-    for (int p = tid; p < kSPY * kSPW; p += 256) {
-      const int py = p / kSPW, px = p - py * kSPW;
-      const int iy = 2 * y0 - 3 + py, ix = 2 * x0 - 3 + px;
-      bf16_t v0 = 0, v1 = 0, v2 = 0;
-      if (iy >= 0 && iy < Hin && ix >= 0 && ix < Win) {
-        const bf16_t* src = x + (((size_t)n * Hin + iy) * Win + ix) * 3;
-        v0 = src[0]; v1 = src[1]; v2 = src[2];
+  __syncthreads();
+  u32x4 wr[11];
+#pragma unroll
+  for (int st = 0; st < 11; ++st) {
+    const int f = 2 * st + lhi, ky = f / 3, j = f - ky * 3;
+    const bf16_t* src = reinterpret_cast<const bf16_t*>(smem) + (32 * wn + l31) * kStemK + ky * 21 + 8 * j;
+    unsigned e[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) e[k] = ky < 7 && 8 * j + k < 21 ? (unsigned)src[k] : 0u;
+    wr[st] = u32x4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+  }
+  float4 sc[4], sh[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    __builtin_memcpy(&sc[g], s + 32 * wn + 8 * g + 4 * lhi, 16);
+    __builtin_memcpy(&sh[g], t + 32 * wn + 8 * g + 4 * lhi, 16);
+  }
+  // fragment addresses of this lane's two 32-row blocks (two conv rows each), without the K step's part
+  unsigned abase[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int rr = wm * 64 + i * 32 + l31, r = rr >> 4, xo = rr & 15;
+    abase[i] = (unsigned)(2 * r * kSpRowB + (xo & 3) * kSpCopy + (xo >> 2) * 48);
+  }
+  const int units = N * strips * chunks, nsteps = (Wp + kSpCols - 1) / kSpCols;
+  for (int u = blockIdx.x; u < units; u += gridDim.x) {
+    const int c = u % chunks, ns = u / chunks, n = ns / strips, p0 = (ns - n * strips) * kSpRows;
+    const int first = c * chunk_steps, stop = min(first + chunk_steps, nsteps);
+    const int iy0 = 4 * p0 - 5, cy0 = 2 * p0 - 1;  // first image row, first conv row
+    const int s0 = first > 0 ? first - 1 : 0;      // the step before supplies the conv column to the left
+    unsigned pre[kSpLoads];
+    // dword k of image row r: values e, e + 1 of the row's 3 Win, outside the image zero
+    auto request = [&](int step) __attribute__((always_inline)) {
+      const int e0 = (32 * step - 3) * 3;
+#pragma unroll
+      for (int i = 0; i < kSpLoads; ++i) {
+        const int k = tid + i * kSpThreads, r = k / kSpDw, e = e0 + 2 * (k - r * kSpDw), iy = iy0 + r;
+        unsigned v = 0;
+        if (r < kSpIn && iy >= 0 && iy < Hin) {
+          const bf16_t* row = x + ((size_t)n * Hin + iy) * Win * 3;
+          if (e >= 0 && e + 1 < 3 * Win) __builtin_memcpy(&v, row + e, 4);
+          else if (e + 1 == 0) v = (unsigned)row[0] << 16;
+          else if (e + 1 == 3 * Win) v = row[e];
+        }
+        pre[i] = v;
       }
-      uint2 pk;
-      pk.x = (unsigned)v0 | ((unsigned)v1 << 16);
-      pk.y = (unsigned)v2;
-      *reinterpret_cast<uint2*>(s_p + p * 8) = pk;
-    }
-    __syncthreads();
-    stem_f32x16 acc[2];
+    };
+    auto store_rows = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < kSpLoads; ++i) {
+        const int k = tid + i * kSpThreads, r = k / kSpDw, d = k - r * kSpDw;
+        if (r < kSpIn) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+          for (int q = 0; q < 4; ++q)
+            if (d >= 3 * q) *reinterpret_cast<unsigned*>(smem + r * kSpRowB + q * kSpCopy + (d - 3 * q) * 4) = pre[i];
+        }
+      }
+    };
+    request(s0);
+    __syncthreads();  // the weights, or the previous unit's last reads
+    for (int step = s0; step < stop; ++step) {
+      store_rows();
+      __syncthreads();
+      if (step + 1 < stop) request(step + 1);
+      stem_f32x16 acc[2];
 #pragma unroll
-    for (int st = 0; st < kSK / 16; ++st) {
-      const int f = 2 * st + h, ky = f >> 2, j = f & 3;  // this lane's fragment: window row ky, taps 2j and 2j+1
-      const uint4 b = *reinterpret_cast<const uint4*>(s_w + col * kSWS + (st * 16 + h * 8) * 2);
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+#pragma unroll
+      for (int st = 0; st < 11; ++st) {
+        // lane half h: fragment f = 2 st + h; the last one (f = 21) has zero weights and reads fragment 20
+        const int f0 = 2 * st, f1 = 2 * st + 1 < 21 ? 2 * st + 1 : 20;
+        const unsigned o0 = (unsigned)(f0 / 3 * kSpRowB + f0 % 3 * 16), o1 = (unsigned)(f1 / 3 * kSpRowB + f1 % 3 * 16);
+        const unsigned off = lhi ? o1 : o0;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const uint4 a = *reinterpret_cast<const uint4*>(smem + abase[i] + off);
+          acc[i] = mma_bf16(wr[st], a, acc[i]);
+        }
+      }
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const int rr = wm * 64 + i * 32 + r, yo = rr >> 4, xo = rr & 15;
-        const uint4 a = *reinterpret_cast<const uint4*>(s_p + ((2 * yo + ky) * kSPW + 2 * xo + 2 * j) * 8);
-        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(stem_bf16x8, a),
-                                                         __builtin_bit_cast(stem_bf16x8, b), acc[i], 0, 0, 0);
+        const int rr = wm * 64 + i * 32 + l31, r = rr >> 4, X = 16 * step + (rr & 15), Y = cy0 + r;
+        const bool live = Y >= 0 && Y < Hc && X < Wc;
+        float v[16];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          v[4 * g + 0] = fmaxf(acc[i][4 * g + 0] * sc[g].x + sh[g].x, 0.f);
+          v[4 * g + 1] = fmaxf(acc[i][4 * g + 1] * sc[g].y + sh[g].y, 0.f);
+          v[4 * g + 2] = fmaxf(acc[i][4 * g + 2] * sc[g].z + sh[g].z, 0.f);
+          v[4 * g + 3] = fmaxf(acc[i][4 * g + 3] * sc[g].w + sh[g].w, 0.f);
+        }
+        to_consecutive_channels(v);
+        uint4 c0 = make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[8], v[9]), pack_bf16(v[10], v[11]));
+        uint4 c1 = make_uint4(pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]), pack_bf16(v[12], v[13]), pack_bf16(v[14], v[15]));
+        if (!live) c0 = c1 = make_uint4(0, 0, 0, 0);
+        // 16-byte chunk ch of a conv pixel at ch ^ (column & 7)
+        const unsigned slot = (unsigned)(r * 32 + (X & 31)) * 128u, ch = wn * 4u + lhi * 2u;
+        *reinterpret_cast<uint4*>(smem + kSpConv + slot + ((ch ^ (X & 7u)) << 4)) = c0;
+        *reinterpret_cast<uint4*>(smem + kSpConv + slot + (((ch + 1u) ^ (X & 7u)) << 4)) = c1;
+      }
+      __syncthreads();
+      if (step >= first && tid < kSpRows * kSpCols * 8) {
+        const unsigned ch = tid & 7u;
+        const int q = (tid >> 3) & (kSpCols - 1), p = tid >> 6, P = p0 + p, X = step * kSpCols + q;
+        typedef __attribute__((ext_vector_type(8))) short s16x8;
+        s16x8 m = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int dx = -1; dx < 2; ++dx) {
+          const int cx = 2 * X + dx;
+          if (cx < 0) continue;
+#pragma unroll
+          for (int dy = 0; dy < 3; ++dy)
+            m = __builtin_elementwise_max(m, *reinterpret_cast<const s16x8*>(smem + kSpConv + ((2 * p + dy) * 32 + (cx & 31)) * 128 +
+                                                                             ((ch ^ ((unsigned)cx & 7u)) << 4)));
+        }
+        if (P < Hp && X < Wp) *reinterpret_cast<s16x8*>(out + (((size_t)n * Hp + P) * Wp + X) * 64 + ch * 8) = m;
       }
     }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int row = wm * 64 + i * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
-        *reinterpret_cast<bf16_t*>(s_o + row * kSOS + col * 2) = f32_to_bf16(fmaxf(acc[i][e] * sc + sh, 0.f));
-      }
     __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int id = tid + q * 256, row = id >> 3, ch = id & 7;
-      const int Y = y0 + (row >> 4), X = x0 + (row & 15);
-      if (Y < Hc && X < Wc)
-        *reinterpret_cast<uint4*>(out + (((size_t)n * Hc + Y) * Wc + X) * 64 + ch * 8) =
-            *reinterpret_cast<const uint4*>(s_o + row * kSOS + ch * 16);
-    }
   }
 }
 
@@ -253,6 +329,25 @@ extern "C" int laud_stem3x3(const void* x, int N, int Hin, int Win, int dtype, c
   return check_launch();
 }
 
+namespace laud {
+// Requests the stem kernel's LDS once per device; the device's compute units.
+int stem_init_device(int* cus_out) {
+  static std::atomic<int> cus_of[32];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 32) return LAUD_ERR_HIP;
+  int cus = cus_of[dev].load(std::memory_order_acquire);
+  if (cus == 0) {
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return LAUD_ERR_HIP;
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_stem_pool_bf16), hipFuncAttributeMaxDynamicSharedMemorySize, kSpLds) !=
+        hipSuccess)
+      return LAUD_ERR_HIP;
+    cus_of[dev].store(cus, std::memory_order_release);
+  }
+  if (cus_out) *cus_out = cus;
+  return LAUD_OK;
+}
+}  // namespace laud
+
 namespace {
 struct StemWs { size_t cols, wp, conv, bytes; };
 StemWs stem_ws_layout(int N, int Hin, int Win, int c_out, int dtype) {
@@ -287,14 +382,17 @@ extern "C" int laud_stem(const void* x, int N, int Hin, int Win, int dtype, cons
   const StemWs L = stem_ws_layout(N, Hin, Win, c_out, dtype);
   char* wsb = (char*)ws;
   void *cols = wsb + L.cols, *wp = wsb + L.wp, *conv = wsb + L.conv;
-  const unsigned pblocks0 = (unsigned)(((long long)N * Hp * Wp * (c_out / 8) + 255) / 256);
-  if (dtype == LAUD_BF16 && c_out == 64) {  // the usual stem: conv straight from the image, then the pooling kernel
-    const unsigned bands = (unsigned)(N * ((Hc + kSTY - 1) / kSTY));
-    hipLaunchKernelGGL(k_stem_conv_bf16, dim3(bands), dim3(256), 0, st, (const bf16_t*)x, N, Hin, Win, Hc, Wc,
-                       (const bf16_t*)w7, s, t, (bf16_t*)conv);
-    if (check_launch() != LAUD_OK) return LAUD_ERR_HIP;
-    hipLaunchKernelGGL((k_maxpool3x3s2<bf16_t>), dim3(pblocks0), dim3(256), 0, st, (const bf16_t*)conv, N, Hc, Wc, c_out,
-                       Hp, Wp, (bf16_t*)out);
+  if (dtype == LAUD_BF16 && c_out == 64 && (reinterpret_cast<uintptr_t>(w7) & 3u) == 0) {
+    int cus;
+    if (stem_init_device(&cus) != LAUD_OK) return LAUD_ERR_HIP;
+    // with fewer strips than compute units a strip is cut along x (each cut repeats one step)
+    const int strips = (Hp + kSpRows - 1) / kSpRows, nsteps = (Wp + kSpCols - 1) / kSpCols;
+    const long long ns = (long long)N * strips;
+    const int chunks = (int)std::min<long long>(nsteps, std::max<long long>(1, cus / ns));
+    const int chunk_steps = (nsteps + chunks - 1) / chunks;
+    hipLaunchKernelGGL(k_stem_pool_bf16, dim3((unsigned)std::min<long long>(ns * chunks, cus)), dim3(kSpThreads), kSpLds, st,
+                       (const bf16_t*)x, N, Hin, Win, Hc, Wc, Hp, Wp, strips, chunks, chunk_steps, (const bf16_t*)w7, s, t,
+                       (bf16_t*)out);
     return check_launch();
   }
   const unsigned iblocks = (unsigned)((rows * (kStemKp / 8) + 255) / 256);
