@@ -145,18 +145,28 @@ def abi_version() -> int:
 
 
 # ----- marshalling helpers ---------------------------------------------------------------
+# (A single image's block is a handful of launches of 4 us each, so the microseconds of the binding count: pointers go to
+# ctypes as plain integers, and the stream comes from the raw getter instead of through a Stream object.)
 def _ptr(t):
     """Device (or raw integer) pointer of a tensor; None -> NULL."""
-    if t is None:
-        return None
-    if isinstance(t, int):
-        return C.c_void_p(t)
-    return C.c_void_p(t.data_ptr())
+    return t if t is None or isinstance(t, int) else t.data_ptr()
+
+
+_raw_stream = None
 
 
 def _stream():
-    import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """torch's current stream on the current device, as an integer."""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        get_stream, get_device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if get_stream is not None and get_device is not None:
+            torch.cuda.current_stream()  # initialises torch's device state, which the raw getters take for granted
+            _raw_stream = lambda: get_stream(get_device())  # noqa: E731
+        else:
+            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+    return _raw_stream()
 
 
 def _check(status: int, where: str) -> None:
