@@ -1492,6 +1492,11 @@ static int run_dyn_projection(const void* x, laud_fmap fx, const laud_bottleneck
   if ((rc = launch_gemm<M_SD1>(fx.dtype, a, nout, 1, st)) != LAUD_OK) return rc;
 
   if (dense_conv1_wanted(fx.dtype, p, npix) && !head_used(fx.dtype, p, npix)) {
+    // (input widths the register-weight first 1x1 does not take, in front of the fused 3x3 -> 1x1 kernel: the dense launch
+    // carries no re-ordering of its weights)
+    if (tail_used(fx.dtype, p, e, nout) && !p->packed &&
+        (rc = pack_weights_into(fx.dtype, p, wsb + L.wpack, false, true, st)) != LAUD_OK)
+      return rc;
     if ((rc = run_dense_conv1(fx, p, x, h1, st)) != LAUD_OK) return rc;
   } else {
     // input pixels the branch reads: the 3x3 windows (at the block's stride) of the active output pixels

@@ -4,6 +4,7 @@ kernels."""
 import numpy as np
 import pytest
 
+import test_gpu_body as body
 from oracle import laud_oracle as O
 from paper_2308_15949_amd import inputs as I
 from test_gpu_parity import G, TOL, assert_close, check_dyn, oracle_params, run_dyn  # noqa: F401
@@ -68,3 +69,11 @@ def test_few_rows_fused_masker(G, case, use_keep):  # noqa: F811
     if not use_keep:
         assert_close(lg.cpu().numpy().reshape(ref0.shape), ref0 + bias, 2e-5, "logits")
     check_dyn(D.to_host(xd), x, hb, S, mask)
+
+
+@pytest.mark.parametrize("case", [(22, 14, 14, 320, 256, 1024, 1, 2, I.BF16, True, "bern"),
+                                  (17, 32, 32, 40, 256, 1024, 2, 4, I.BF16, True, "bern")])
+def test_dense_first_conv_before_fused_kernel(case):
+    """A dynamic first block whose input width the register-weight first 1x1 does not take, with enough rows for the fused
+    3x3 -> 1x1 kernel and no caller-packed weights: the call re-orders them itself, whichever way its first 1x1 runs."""
+    body.test_dyn_projection_block(case)
