@@ -209,6 +209,11 @@ InactiveCopy inactive_copy(const void* x, void* out, const laud_fmap& fx, int S,
 // Share `part` of `nparts` of the copy; flags: kCopyPatches bytes of LDS.
 template <int NT>
 __device__ __forceinline__ void copy_inactive_part(const InactiveCopy& c, int part, int nparts, unsigned char* flags) {
+  // (a vector type of the compiler's own: an array of the uint4 struct went to scratch memory, 80 bytes a lane that every
+  // wave of the launch was given, tiles included)
+  typedef __attribute__((ext_vector_type(4))) unsigned chunk;
+  const chunk* const x = reinterpret_cast<const chunk*>(c.x);
+  chunk* const out = reinterpret_cast<chunk*>(c.out);
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int cnt = *c.count;
   const int per = (c.npatch + nparts - 1) / nparts;
@@ -231,13 +236,13 @@ __device__ __forceinline__ void copy_inactive_part(const InactiveCopy& c, int pa
       const size_t off = (((size_t)s * c.H + py * c.S + (r - k * c.S)) * c.W + px * c.S) * c.cpp;
       int i = lane;
       for (; i + 3 * kWave < rowc; i += 4 * kWave) {
-        uint4 v[4];
+        chunk v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = c.x[off + i + u * kWave];
+        for (int u = 0; u < 4; ++u) v[u] = x[off + i + u * kWave];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) c.out[off + i + u * kWave] = v[u];
+        for (int u = 0; u < 4; ++u) out[off + i + u * kWave] = v[u];
       }
-      for (; i < rowc; i += kWave) c.out[off + i] = c.x[off + i];
+      for (; i < rowc; i += kWave) out[off + i] = x[off + i];
     }
     __syncthreads();
   }
