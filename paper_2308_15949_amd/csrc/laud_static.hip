@@ -245,7 +245,7 @@ __global__ __launch_bounds__(256) void k_maxpool3x3s2(const ET* __restrict__ in,
 // Stem of the RegNet backbones: 3x3 stride-2 pad-1 conv from the 3-channel image, affine, ReLU.  One thread per
 // output pixel: the 27 inputs of its window are read once into registers, then the output channels are produced
 // eight at a time from the 27 x c_out float32 weights in LDS (all lanes read the same weight: a broadcast).
-// HBM-bound: the image is read once (neighbouring windows overlap in cache) and the output written once.
+// Takes what the matrix-core kernel below does not.
 template <typename ET>
 __global__ __launch_bounds__(256) void k_stem3x3(const ET* __restrict__ in, int N, int H, int W, int Ho, int Wo,
                                                  const ET* __restrict__ w, const float* __restrict__ s,
@@ -304,6 +304,86 @@ __global__ __launch_bounds__(256) void k_stem3x3(const ET* __restrict__ in, int 
   }
 }
 
+// The same on the matrix cores, for bf16 images of even width and c_out a multiple of 32.  One wave makes 32 output pixels of
+// one row x 32 channels: a window row is nine consecutive values of the image; with the value ahead of them (zeroed here: it
+// may be anything) they start at a 4-byte boundary, ten values = five dwords.  K = 32: four fragments of eight, the first eight
+// values of each of the three window rows and the last pairs of all three together.  Fragments are loaded from the image as
+// they are (neighbouring windows overlap in the cache); rows outside the image lie outside the descriptor and read as zero.
+// The vector-ALU kernel reads 27 x c_out weights from LDS per wave of 64 pixels, which is what bounds it: about 105 us at 128
+// images of 224 x 224 and 32 channels; this one takes 42 (142 MB read and written: 3.4 TB/s of a copy's 4.3).
+constexpr int kS3Waves = 4, kS3Blocks = 2048;  // eight workgroups per compute unit, each wave walking over its tiles
+__global__ __launch_bounds__(64 * kS3Waves) void k_stem3x3_mfma(const bf16_t* __restrict__ in, unsigned in_bytes, int rows, int H, int W,
+                                                                int Ho, int Wo, int xtiles, const bf16_t* __restrict__ w,
+                                                                const float* __restrict__ s, const float* __restrict__ t, int C,
+                                                                bf16_t* __restrict__ out) {
+  const int lane = threadIdx.x & 63, l31 = lane & 31, lhi = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int c0 = 32 * blockIdx.y;
+  constexpr unsigned kOob = 0x80000000u;
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(in), 0, (int)in_bytes, 0x00020000);
+  // weights of channel c0 + l31: fragment lhi, then fragment 2 + lhi
+  u32x4 wr[2];
+  {
+    const bf16_t* wc = w + (size_t)(c0 + l31) * 27;
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+      const int f = 2 * st + lhi;
+      unsigned e[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int i = f < 3 ? f * 9 + k - 1 : (k >> 1) * 9 + 7 + (k & 1);
+        const bool none = f < 3 ? k == 0 : k > 5;
+        e[k] = none ? 0u : (unsigned)wc[none ? 0 : i];
+      }
+      wr[st] = u32x4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+    }
+  }
+  float4 sc[4], sh[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    __builtin_memcpy(&sc[g], s + c0 + 8 * g + 4 * lhi, 16);
+    __builtin_memcpy(&sh[g], t + c0 + 8 * g + 4 * lhi, 16);
+  }
+  const int units = rows * xtiles;
+  for (int u = blockIdx.x * kS3Waves + wave; u < units; u += gridDim.x * kS3Waves) {
+    const int R = u / xtiles, x0 = (u - R * xtiles) * 32, n = R / Ho, yo = R - n * Ho;
+    const int xo = min(x0 + l31, Wo - 1), yc = 2 * yo;  // (pixels past the row's end repeat the last one; not stored)
+    const unsigned rowb = (unsigned)W * 6u, mid = (unsigned)(n * H + yc) * rowb;
+    const unsigned top = yc > 0 ? mid - rowb : kOob, bot = yc + 1 < H ? mid + rowb : kOob;
+    // (the leftmost window starts outside the image: its load starts at the row and is moved up below)
+    const unsigned lead = 12u * xo - (xo > 0 ? 8u : 0u), tail = lhi ? 12u * xo + 8u : kOob;
+    u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(rs, (lhi ? mid : top) + lead, 0, 0);
+    u32x4 b = __builtin_amdgcn_raw_buffer_load_b128(rs, (lhi ? kOob : bot) + lead, 0, 0);
+    const unsigned d0 = __builtin_amdgcn_raw_buffer_load_b32(rs, (top + tail) | (tail & kOob) | (top & kOob), 0, 0);
+    const unsigned d1 = __builtin_amdgcn_raw_buffer_load_b32(rs, mid + tail, 0, 0);
+    const unsigned d2 = __builtin_amdgcn_raw_buffer_load_b32(rs, (bot + tail) | (tail & kOob) | (bot & kOob), 0, 0);
+    auto window = [&](const u32x4& v) __attribute__((always_inline)) {
+      return xo > 0 ? make_uint4(v.x & 0xffff0000u, v.y, v.z, v.w) : make_uint4(0u, 0u, v.x, v.y);
+    };
+    const uint4 fa = window(a), wb = window(b);
+    const uint4 fb = make_uint4(lhi ? d0 : wb.x, lhi ? d1 : wb.y, lhi ? d2 : wb.z, lhi ? 0u : wb.w);
+    stem_f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    acc = mma_bf16(wr[0], fa, acc);
+    acc = mma_bf16(wr[1], fb, acc);
+    float v[16];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      v[4 * g + 0] = fmaxf(acc[4 * g + 0] * sc[g].x + sh[g].x, 0.f);
+      v[4 * g + 1] = fmaxf(acc[4 * g + 1] * sc[g].y + sh[g].y, 0.f);
+      v[4 * g + 2] = fmaxf(acc[4 * g + 2] * sc[g].z + sh[g].z, 0.f);
+      v[4 * g + 3] = fmaxf(acc[4 * g + 3] * sc[g].w + sh[g].w, 0.f);
+    }
+    to_consecutive_channels(v);
+    if (x0 + l31 < Wo) {
+      uint4* po = reinterpret_cast<uint4*>(out + ((size_t)R * Wo + xo) * C + c0 + 16 * lhi);
+      po[0] = make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[8], v[9]), pack_bf16(v[10], v[11]));
+      po[1] = make_uint4(pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]), pack_bf16(v[12], v[13]), pack_bf16(v[14], v[15]));
+    }
+  }
+}
+
 }  // namespace laud
 
 using namespace laud;
@@ -318,6 +398,15 @@ extern "C" int laud_stem3x3(const void* x, int N, int Hin, int Win, int dtype, c
   if ((work + 255) / 256 > 0x7fffffffLL) return LAUD_ERR_UNSUPPORTED;
   hipStream_t st = (hipStream_t)stream;
   clear_stale_error();
+  const long long in_bytes = (long long)N * Hin * Win * 6;
+  if (dtype == LAUD_BF16 && c_out % 32 == 0 && Win % 2 == 0 && Win >= 4 && in_bytes < 0x7fffffffLL && (reinterpret_cast<uintptr_t>(x) & 3u) == 0) {
+    const int xtiles = (Wo + 31) / 32;
+    const long long units = (long long)N * Ho * xtiles;
+    const long long wgs = std::min<long long>((units + kS3Waves - 1) / kS3Waves, kS3Blocks);
+    hipLaunchKernelGGL(k_stem3x3_mfma, dim3((unsigned)wgs, (unsigned)(c_out / 32)), dim3(64 * kS3Waves), 0, st, (const bf16_t*)x,
+                       (unsigned)in_bytes, N * Ho, Hin, Win, Ho, Wo, xtiles, (const bf16_t*)w3, s, t, c_out, (bf16_t*)out);
+    return check_launch();
+  }
   const unsigned blocks = (unsigned)((work + 255) / 256);
   const size_t lds = (size_t)29 * c_out * sizeof(float);
   if (dtype == LAUD_BF16)

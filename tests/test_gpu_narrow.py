@@ -93,3 +93,22 @@ def test_stem_one_kernel(G, case):  # noqa: F811
                 64, out, D.workspace(L.stem_workspace(N, H, W, 64, I.BF16)))
     t.cuda.synchronize()
     close(D.to_host(out), ref, TOL[I.BF16])
+
+
+@pytest.mark.parametrize("case", [
+    # N, H, W, c_out: edges of the matrix-core 3x3 stem (even width from 4 on, channels in 32s, 32 output pixels a tile)
+    (1, 1, 4, 32), (2, 2, 2, 32), (1, 3, 6, 32), (2, 5, 62, 32), (2, 6, 64, 64), (3, 7, 66, 32), (2, 9, 65, 32), (2, 8, 66, 40),
+    (70, 240, 4, 32),  # more tiles than waves
+])
+def test_stem3x3_matrix_cores(G, case):  # noqa: F811
+    t, L, D = G.torch, G.L, G.D
+    N, H, W, co = case
+    g = np.random.default_rng(5700 + W)
+    x = I.round_to(g.standard_normal((N, H, W, 3), dtype=np.float32), I.BF16)
+    w3 = I.round_to(g.standard_normal((co, 3, 3, 3), dtype=np.float32) * np.float32(np.sqrt(2.0 / 27)), I.BF16)
+    s, b = (1 + 0.1 * g.standard_normal(co)).astype(np.float32), (0.1 * g.standard_normal(co)).astype(np.float32)
+    ref = O.stem3x3(x, w3, s, b)
+    out = t.full(ref.shape, 7.0, dtype=t.bfloat16, device="cuda")
+    L.laud_stem3x3(D.to_device(x, I.BF16), N, H, W, I.BF16, D.to_device(w3, I.BF16), t.from_numpy(s).cuda(), t.from_numpy(b).cuda(), co, out)
+    t.cuda.synchronize()
+    close(D.to_host(out), ref, TOL[I.BF16])
