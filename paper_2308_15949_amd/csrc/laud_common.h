@@ -137,6 +137,16 @@ __device__ __forceinline__ void wave_lower_bound2(const int32_t* v, int n, int k
   r1 = lo[1];
 }
 
+// n / d by the reciprocal 1 / d, exact for n below 2^21: (n + 1/2) / d is at least 1 / 2d away from an integer, the product's
+// error is below (n + 1) / d * 2^-23.
+__host__ __device__ __forceinline__ int fdiv(int n, float inv) { return (int)(((float)n + 0.5f) * inv); }
+
+// Entry of an index list that row `rho` of a launch over `rows` >= 1 rows (entries * S * S) belongs to.  Rows past the last one
+// repeat its entry: a caller's list may end, and its memory with it, at the last of its *count entries.
+__host__ __device__ __forceinline__ int list_entry(int rho, int rows, float inv_ss) {
+  return fdiv(rho < rows ? rho : rows - 1, inv_ss);
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
@@ -258,7 +268,6 @@ struct TailArgs {
   void* out;             // [output pixels][cout]; may alias res
   const int32_t* count;  // device: number of active patches
   const int32_t* list;   // device: ascending active patch ids
-  int cap_patches;       // capacity of `list` (number of patches of the grid), > 0
   int H, W;              // input grid of h1
   int S;                 // patch size on the output grid
   int stride, Ho, Wo;    // spatial stride of the 3x3 and the output grid (stride 1: Ho = H, Wo = W)

@@ -1091,7 +1091,6 @@ static int try_tail(int dtype, const laud_bottleneck* p, const laud_group_se* e,
   t.h1 = h1; t.wpacked = (const char*)(p->packed ? p->packed : wpack) + packed_layout(dtype, p).tail; t.s2 = p->s2; t.t2 = p->t2; t.s3 = p->s3; t.t3 = p->t3;
   t.res = res; t.out = out; t.count = count; t.list = idx; t.H = H; t.W = W; t.S = S; t.stride = stride;
   t.Ho = Ho; t.Wo = Wo; t.cout = p->c_out; t.relu = p->relu_out ? 1 : 0;
-  t.cap_patches = (int)(cap_rows / ((long long)S * S));
   t.cp = copy;
   *rc = launch_tail(t, cap_rows, st);
   return 1;
@@ -1591,7 +1590,7 @@ extern "C" int laud_channel_skip_conv(const void* x, laud_fmap fx, const laud_bo
     if ((rc = launch_head(h, st)) != LAUD_OK) return rc;  // (stage timing books the two kernels as conv1 / conv2)
     TailArgs t{};
     t.h1 = h1; t.wpacked = packed + PL.tail; t.s2 = p->s2; t.t2 = p->t2; t.s3 = p->s3; t.t3 = p->t3;
-    t.res = x; t.out = out; t.count = cnt; t.list = perm; t.cap_patches = fx.N;
+    t.res = x; t.out = out; t.count = cnt; t.list = perm;
     t.H = fx.H; t.W = fx.W; t.S = fx.H; t.stride = 1; t.Ho = fx.H; t.Wo = fx.W; t.cout = p->c_out;
     t.relu = p->relu_out ? 1 : 0; t.sbits = sbits; t.cs_group = G;
     return launch_tail(t, fx.N * hw, st);

@@ -39,8 +39,6 @@ static_assert(lds_bytes<false>() <= 160 * 1024 && lds_bytes<true>() <= 160 * 102
 static_assert(kMid * 9 * kMid * 2 <= kTab, "w2 passes through the ring, h2 and shortcut regions on its way into registers");
 }  // namespace narrow
 
-__device__ __forceinline__ int fdivn(int n, float inv) { return (int)(((float)n + 0.5f) * inv); }
-
 // vm_wait with a count that is a constant once the loop around it is unrolled
 __device__ __forceinline__ void vm_wait_n(int n) {
   switch (n) {
@@ -141,7 +139,7 @@ __global__ __launch_bounds__(narrow::kThreads) void k_narrow(const NarrowArgs a)
   auto request_entries = [&](int t) __attribute__((always_inline)) {
     if constexpr (!SC) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) entry[i] = a.list[fdivn(min(t * kBM + 64 * i + 8 * wave + l8, a.m_rows - 1), a.inv_ss)];
+      for (int i = 0; i < 2; ++i) entry[i] = a.list[list_entry(t * kBM + 64 * i + 8 * wave + l8, M, a.inv_ss)];
     }
   };
   auto describe = [&](int t, int buf) __attribute__((always_inline)) {
@@ -150,14 +148,14 @@ __global__ __launch_bounds__(narrow::kThreads) void k_narrow(const NarrowArgs a)
       const int r = 64 * i + 8 * wave + l8, rho = t * kBM + r;
       int n, yo, xo;
       if constexpr (SC) {
-        n = fdivn(rho, a.inv_howo);
+        n = fdiv(rho, a.inv_howo);
         const int r2 = rho - n * (a.Ho * a.Wo);
-        yo = fdivn(r2, a.inv_wo);
+        yo = fdiv(r2, a.inv_wo);
         xo = r2 - yo * a.Wo;
       } else {
-        const int q = entry[i], j = rho - fdivn(rho, a.inv_ss) * SS;
-        n = fdivn(q, a.inv_pps);
-        const int r2 = q - n * (Hp * Wp), py = fdivn(r2, a.inv_wp), px = r2 - py * Wp, jy = fdivn(j, a.inv_s);
+        const int q = entry[i], j = rho - fdiv(rho, a.inv_ss) * SS;
+        n = fdiv(q, a.inv_pps);
+        const int r2 = q - n * (Hp * Wp), py = fdiv(r2, a.inv_wp), px = r2 - py * Wp, jy = fdiv(j, a.inv_s);
         yo = py * a.S + jy;
         xo = px * a.S + j - jy * a.S;
       }

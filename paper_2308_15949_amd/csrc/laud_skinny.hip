@@ -37,8 +37,7 @@ __device__ __forceinline__ void mma4(f32x4& acc, const uint4& a, const uint4& b)
 
 // A launch of this kind lives for a few microseconds, of which the instructions ahead of the first load are a good part
 // (sixteen waves of a workgroup share four SIMDs), so divisions by run-time values are multiplications with reciprocals made
-// on the host: exact for the row numbers launch_skinny admits (below 2^20; (n + 1/2) / d is at least 1 / 2d away from an
-// integer, the product's error is below n / d * 2^-22).
+// on the host (fdiv; launch_skinny admits row numbers below 2^20).
 struct SkinnyArgs {
   GemmArgs g;
   int cap_rows;               // rows (dense) or their upper bound (count on the device)
@@ -47,7 +46,6 @@ struct SkinnyArgs {
   int deal;                   // tiles to XCDs: 1 by row tile, 2 by column tile (a multiple of eight of them), 0 as they come
   float inv_ss, inv_s, inv_pps, inv_wp, inv_howo, inv_wo, inv_rt, inv_ct;
 };
-__device__ __forceinline__ int fdiv(int n, float inv) { return (int)(((float)n + 0.5f) * inv); }
 
 template <int TM, int TN, int NW>
 __host__ __device__ constexpr int skinny_lds() {
@@ -102,6 +100,9 @@ __global__ __launch_bounds__(64 * NW) void k_skinny(const SkinnyArgs ka) {
     }
   }
   const int row0 = rt * BM, col0 = ct * BN;
+  const int SS = a.S * a.S;
+  const int M = LISTED ? *a.count * SS : ka.cap_rows;
+  if (row0 >= M) return;
 
   constexpr unsigned kOob = 0x80000000u;
   const long long ashift = TAPS ? (long long)(a.W + 1) * a.lda * ES : 0;
@@ -110,11 +111,10 @@ __global__ __launch_bounds__(64 * NW) void k_skinny(const SkinnyArgs ka) {
   const __amdgpu_buffer_rsrc_t wrsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.Wt), 0, (int)kOob, 0x00020000);
 
-  // ---- the row this thread looks up for the workgroup (first BM threads); its list entry is requested first (entries past
-  // the count are dropped later) ------------------------------------------------------------------------------------------
+  // ---- the row this thread looks up for the workgroup (first BM threads); its list entry is requested first -------------
   const int rrow = row0 + min(tid, BM - 1);
   int entry = 0;
-  if constexpr (LISTED) entry = a.list[fdiv(min(rrow, ka.cap_rows - 1), ka.inv_ss)];
+  if constexpr (LISTED) entry = a.list[list_entry(rrow, M, ka.inv_ss)];
 
   // ---- the weights of the first D slices: they depend on nothing but the tile ------------------------------------------
   // Every load is unconditional; a chunk that must read as zero (past K, past the wave's last slice, outside the image) gets
@@ -170,7 +170,6 @@ __global__ __launch_bounds__(64 * NW) void k_skinny(const SkinnyArgs ka) {
   // ---- rows ----------------------------------------------------------------------------------------------------------
   const int sy = a.stride > 1 ? a.stride : 1;
   const int oH = a.stride > 1 ? a.Ho : a.H, oW = a.stride > 1 ? a.Wo : a.W;
-  const int SS = a.S * a.S;
   auto patch_pixel = [&](int rho, int q, int& n, int& yo, int& xo) __attribute__((always_inline)) {
     const int Wp = fdiv(oW, ka.inv_s), pps = fdiv(oH, ka.inv_s) * Wp;
     const int j = rho - fdiv(rho, ka.inv_ss) * SS;
@@ -179,8 +178,6 @@ __global__ __launch_bounds__(64 * NW) void k_skinny(const SkinnyArgs ka) {
     yo = py * a.S + jy;
     xo = px * a.S + j - jy * a.S;
   };
-  const int M = LISTED ? *a.count * SS : ka.cap_rows;
-  if (row0 >= M) return;
   if (tid < BM) {
     int pix = rrow, y = 0, x = 0, o = rrow;
     if constexpr (LISTED) {

@@ -99,7 +99,7 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
   const int SS = a.S * a.S;
   int qsp[(PB + 1) / 2];
 #pragma unroll
-  for (int i = 0; i < (PB + 1) / 2; ++i) qsp[i] = a.list[min((row0 + 64 * i + 8 * wave + l8) / SS, a.cap_patches - 1)];
+  for (int i = 0; i < (PB + 1) / 2; ++i) qsp[i] = a.list[min(row0 + 64 * i + 8 * wave + l8, M - 1) / SS];  // (see list_entry)
   // ---- channel skipping: which input slices of the 3x3 this tile needs ---------------------------------------------
   // The tile's rows belong to the list entries (samples) row0/SS .. (row0+kBM-1)/SS; a K chunk (64 input channels) is
   // needed if any of them keeps the chunk's group.  n2 = slices of the 3x3 that are multiplied (9 taps x kept

@@ -1,0 +1,63 @@
+"""GPU parity of routes through the entry points that the per-kernel files do not take: index lists that end with their last
+entry, on every kernel that reads one."""
+import numpy as np
+import pytest
+
+from oracle import laud_oracle as O
+from paper_2308_15949_amd import inputs as I
+from test_gpu_body import close, oparams, shortcut_params
+from test_gpu_parity import G, TOL, check_dyn  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def exact_list(t, mask):
+    """The ascending ids of the active patches in a tensor of exactly that many entries, and their number."""
+    ids = np.flatnonzero(mask).astype(np.int32)
+    return t.from_numpy(ids).cuda(), t.tensor([len(ids)], dtype=t.int32, device="cuda")
+
+
+@pytest.mark.parametrize("case", [
+    # N, H, W, C, m, S, dtype
+    (1, 56, 56, 256, 64, 4, I.F32),       # small tiles
+    (2, 7, 7, 2048, 512, 1, I.BF16),
+    (5, 56, 56, 256, 64, 4, I.BF16),      # 64-wide kernel
+    (22, 14, 14, 1024, 256, 2, I.BF16),   # register-weight first 1x1, fused 3x3 -> 1x1
+    (40, 28, 28, 512, 128, 4, I.BF16),    # tiled kernels
+])
+@pytest.mark.parametrize("active", [1, 0.3])
+def test_list_of_exact_length(G, case, active):  # noqa: F811
+    t, L, D = G.torch, G.L, G.D
+    N, H, W, C, m, S, dt = case
+    x = I.feature_map(7000 + C, N, H, W, C, dt)
+    hb = I.bottleneck_params(7100 + C, C, m, C, dt, relu_out=True)
+    if active == 1:  # one entry, the grid's last patch
+        mask = np.zeros((N, H // S, W // S), np.uint8)
+        mask[-1, -1, -1] = 1
+    else:
+        mask = I.bernoulli_mask(7200 + H, (N, H // S, W // S), active)
+    idx, cnt = exact_list(t, mask)
+    xd, db = D.to_device(x, dt), D.DeviceBottleneck(hb)
+    fx = L.fmap_of(xd)
+    L.laud_dyn_bottleneck(xd, fx, db.desc, S, idx, cnt, xd, D.workspace(L.workspace_size(L.binding.OP_DYN_BOTTLENECK, fx, db.desc, S)))
+    t.cuda.synchronize()
+    check_dyn(D.to_host(xd), x, hb, S, mask)
+
+
+@pytest.mark.parametrize("case", [(3, 16, 16, 64, 64, 256, 2, 4), (8, 112, 112, 64, 64, 256, 2, 8)])
+def test_projection_list_of_exact_length(G, case):  # noqa: F811
+    t, L, D = G.torch, G.L, G.D
+    N, H, W, ci, m, co, stride, S = case
+    x = I.feature_map(7300 + H, N, H, W, ci, I.BF16)
+    hb = I.bottleneck_params(7400 + H, ci, m, co, I.BF16, relu_out=True, s3_gain=0.5)
+    wsc, ssc, tsc = shortcut_params(7500 + H, ci, co, I.BF16)
+    Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
+    mask = I.bernoulli_mask(7600 + H, (N, Ho // S, Wo // S), 0.4)
+    ref = O.dyn_projection_bottleneck(x, oparams(hb), wsc, ssc, tsc, stride, S, mask)
+    idx, cnt = exact_list(t, mask)
+    xd, db = D.to_device(x, I.BF16), D.DeviceBottleneck(hb)
+    fx, out = L.fmap_of(xd), t.full(ref.shape, 7.0, dtype=t.bfloat16, device="cuda")
+    L.laud_dyn_projection_bottleneck(xd, fx, db.desc, D.to_device(wsc, I.BF16), t.from_numpy(ssc).cuda(), t.from_numpy(tsc).cuda(),
+                                     stride, S, idx, cnt, out, D.workspace(L.dyn_projection_workspace(fx, db.desc, stride)))
+    t.cuda.synchronize()
+    close(D.to_host(out), ref, TOL[I.BF16])

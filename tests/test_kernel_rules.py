@@ -1,0 +1,37 @@
+"""CPU checks of rules the kernels rely on, on the code itself: small host functions compiled from the kernels' headers."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2308_15949_amd import build as B
+
+
+def hipcc(*args):
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *B.FLAGS, *args], check=True, capture_output=True, text=True)
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.hip").write_text('#include "laud_common.h"\n'
+                                 'extern "C" void entries(const int* rho, int n, int rows, int ss, int* out) {\n'
+                                 '  for (int i = 0; i < n; ++i) out[i] = laud::list_entry(rho[i], rows, 1.f / ss);\n}\n')
+    hipcc("--cuda-host-only", "-shared", str(d / "rules.hip"), "-o", str(d / "rules.so"))
+    return C.CDLL(str(d / "rules.so"))
+
+
+@pytest.mark.parametrize("S", [1, 2, 3, 4, 7, 8, 14, 56])
+@pytest.mark.parametrize("count", [1, 2, 3, 63, 64, 65, 1000, 18725])
+def test_rows_past_the_end_of_an_index_list_stay_inside_it(rules, S, count):
+    """A list of exactly `count` entries: the rows of the last tiles (up to 128 rows, one tile looked ahead) read none past it."""
+    rows = min(count * S * S, 1 << 21) // (S * S) * S * S
+    if rows == 0:
+        pytest.skip("more rows than the kernels take")
+    rho = np.unique(np.concatenate([np.arange(min(rows, 5000)), np.arange(max(rows - 5000, 0), rows + 256), np.arange(0, rows, 997)])).astype(np.int32)
+    out = np.empty_like(rho)
+    ptr = lambda a: a.ctypes.data_as(C.c_void_p)  # noqa: E731
+    rules.entries(ptr(rho), len(rho), rows, S * S, ptr(out))
+    assert np.array_equal(out, np.minimum(rho, rows - 1) // (S * S))
