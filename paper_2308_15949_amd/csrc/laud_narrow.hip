@@ -215,6 +215,7 @@ __global__ __launch_bounds__(narrow::kThreads) void k_narrow(const NarrowArgs a)
     for (int s = 0; s < NS; ++s) {
       // loads younger than slice s: the slices behind it that have been requested, and the residual where it is
       vm_wait_n(2 * ((s + kAhead - 1 < NS - 1 ? s + kAhead - 1 : NS - 1) - s) + (s < kAhead ? kR : 0));
+      lds_wait();    // (this wave's reads of slice s - 1: its MFMAs, and their wait, may stand behind the barrier)
       wg_barrier();  // everyone's part of slice s is there, and everyone is done with slice s - 1
       if (s + kAhead < NS) issue_A(s + kAhead);
       if (s < 9) {

@@ -35,3 +35,24 @@ def test_rows_past_the_end_of_an_index_list_stay_inside_it(rules, S, count):
     ptr = lambda a: a.ctypes.data_as(C.c_void_p)  # noqa: E731
     rules.entries(ptr(rho), len(rho), rows, S * S, ptr(out))
     assert np.array_equal(out, np.minimum(rho, rows - 1) // (S * S))
+
+
+def test_lds_reads_have_landed_at_the_barriers_of_the_64_wide_kernel(tmp_path):
+    """A stage of the ring is refilled by another wave's LDS-direct loads right behind a barrier, so no wave may pass a barrier
+    with LDS reads under way: in the generated code every ds_read is waited for (lgkmcnt counts down in order) before the next
+    s_barrier."""
+    hipcc("--cuda-device-only", "-S", os.path.join(B.CSRC, "laud_narrow.hip"), "-o", str(tmp_path / "narrow.s"))
+    barriers, pending = 0, []
+    for line in (tmp_path / "narrow.s").read_text().splitlines():
+        op = line.split()[:1]
+        if not op:
+            continue
+        if op[0].startswith("ds_read") or op[0].startswith("ds_load"):
+            pending.append(line.strip())
+        elif op[0] == "s_waitcnt" and "lgkmcnt(" in line:
+            left = int(line.split("lgkmcnt(")[1].split(")")[0])
+            pending = pending[-left:] if left else []
+        elif op[0] == "s_barrier":
+            barriers += 1
+            assert not pending, f"barrier {barriers} is passed with {pending} under way"
+    assert barriers >= 2 * 12
