@@ -183,7 +183,7 @@ __global__ __launch_bounds__(narrow::kThreads) void k_narrow(const NarrowArgs a)
   };
   // fragment address of K step kg inside 32 rows of a slice: swz ^ (kg << 5)
   const unsigned swz = (unsigned)l31 * 128u + (((unsigned)lhi ^ (unsigned)(l31 & 7) ^ ((unsigned)(l31 >> 3) & 1u)) << 4);
-  const float floor_ = SC || a.relu ? 0.f : -__builtin_inff();
+  const float floor_ = act_floor(SC || a.relu);
   const __bf16* const resp = reinterpret_cast<const __bf16*>(a.res);
   __bf16* const outp = reinterpret_cast<__bf16*>(a.out);
 

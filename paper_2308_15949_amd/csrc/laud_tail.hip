@@ -332,7 +332,7 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
     for (int t = 0; t < PB; ++t)
       fa[buf][t] = *reinterpret_cast<const uint4*>(smem + hrow + t * (32 * 512) + ((c ^ hx) << 4));
   };
-  const float floor_ = a.relu ? 0.f : -__builtin_inff();  // the activation after the add as one max (NaN passes through)
+  const float floor_ = act_floor(a.relu);
   const __bf16* const resp = reinterpret_cast<const __bf16*>(a.res);
   __bf16* const outp = reinterpret_cast<__bf16*>(a.out);
   f32x16 acc2[DUAL ? PB : 1];  // the second accumulator set (odd column tiles)

@@ -49,6 +49,10 @@ __device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
 }
 
+// The activation after the residual add as one maximum, fmaxf(v, act_floor(relu)): of a number and a quiet NaN the maximum is
+// the number, so without a ReLU every sum, NaN included, stays what it is.  (With one a NaN becomes 0, as in every kernel.)
+__device__ __forceinline__ float act_floor(bool relu) { return relu ? 0.f : __builtin_nanf(""); }
+
 // Accumulator e of a lane belongs to channel 8*(e/4) + 4*(lane/32) + e%4 of the wave's 32.  After these eight
 // swaps v[] holds, in the order 0-3, 8-11, 4-7, 12-15, the sixteen consecutive channels 16*(lane/32) .. +15.
 __device__ __forceinline__ void to_consecutive_channels(float (&v)[16]) {

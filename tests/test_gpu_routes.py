@@ -61,3 +61,31 @@ def test_projection_list_of_exact_length(G, case):  # noqa: F811
                                      stride, S, idx, cnt, out, D.workspace(L.dyn_projection_workspace(fx, db.desc, stride)))
     t.cuda.synchronize()
     close(D.to_host(out), ref, TOL[I.BF16])
+
+
+@pytest.mark.parametrize("case", [
+    # N, H, W, C, m, S, dtype
+    (1, 56, 56, 256, 64, 4, I.BF16),      # small tiles
+    (5, 56, 56, 256, 64, 4, I.BF16),      # 64-wide kernel
+    (2, 14, 14, 1024, 256, 2, I.BF16),    # small tiles
+    (22, 14, 14, 1024, 256, 2, I.BF16),   # fused 3x3 -> 1x1
+    (40, 28, 28, 512, 128, 4, I.BF16),    # tiled kernels
+])
+def test_nan_stays_nan_without_output_relu(G, case):  # noqa: F811
+    """One NaN in an active pixel, whatever kernel the batch size selects: the first 1x1's ReLU makes that pixel's h1 zero, the
+    residual add gives NaN at that one value of the output, and without an output ReLU it stays NaN."""
+    t, L, D = G.torch, G.L, G.D
+    N, H, W, C, m, S, dt = case
+    x = I.feature_map(7700 + C, N, H, W, C, dt)
+    x[N - 1, H - 2, 3, 5] = np.nan
+    hb = I.bottleneck_params(7800 + C, C, m, C, dt, relu_out=False)
+    mask = I.bernoulli_mask(7900 + H, (N, H // S, W // S), 0.5)
+    mask[N - 1, (H - 2) // S, 3 // S] = 1
+    idx, cnt = exact_list(t, mask)
+    xd, db = D.to_device(x, dt), D.DeviceBottleneck(hb)
+    assert int(t.isnan(xd).sum()) == 1
+    fx = L.fmap_of(xd)
+    L.laud_dyn_bottleneck(xd, fx, db.desc, S, idx, cnt, xd, D.workspace(L.workspace_size(L.binding.OP_DYN_BOTTLENECK, fx, db.desc, S)))
+    t.cuda.synchronize()
+    got = xd.float().cpu().numpy()
+    assert np.argwhere(~np.isfinite(got)).tolist() == [[N - 1, H - 2, 3, 5]] and np.isnan(got[N - 1, H - 2, 3, 5])
