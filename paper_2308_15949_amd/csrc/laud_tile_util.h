@@ -29,14 +29,12 @@ __device__ __forceinline__ void lds_wait() { asm volatile("s_waitcnt lgkmcnt(0)"
 // Requests one 128-byte line per thread of the weights a launch streams, so that they are on their way into this XCD's
 // L2 before the tiles ask for them slice by slice: workgroups go round-robin over the eight XCDs, so
 // workgroup b takes piece b/8 (kThreads lines) of the range.  In a model every block brings weights of its own, which no
-// earlier launch has left in the L2.  Returns the register the load writes: it must stay reserved -- l2_touched() -- until
-// a wait that covers it.
+// earlier launch has left in the L2.  Returns the value loaded, for l2_touched() to consume behind the first wait that drains
+// the loads anyway (so that the request is not dropped and nobody waits for it alone).
 __device__ __forceinline__ unsigned l2_touch(const void* base, int bytes, int threads) {
-  unsigned r = 0;
-  const int line = (int)(blockIdx.x >> 3) * threads + (int)threadIdx.x;
-  if (line * 128 < bytes)
-    asm volatile("global_load_dword %0, %1, off" : "=v"(r) : "v"((const char*)base + (size_t)line * 128) : "memory");
-  return r;
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+  const unsigned line = (blockIdx.x >> 3) * (unsigned)threads + threadIdx.x;
+  return __builtin_amdgcn_raw_buffer_load_b32(rs, min(line, 0x1000000u) * 128u, 0, 0);  // (past the end: no request, zero)
 }
 __device__ __forceinline__ void l2_touched(unsigned r) { asm volatile("" ::"v"(r)); }
 

@@ -1,6 +1,7 @@
 """CPU checks of rules the kernels rely on, on the code itself: small host functions compiled from the kernels' headers."""
 import ctypes as C
 import os
+import re
 import subprocess
 
 import numpy as np
@@ -56,3 +57,17 @@ def test_lds_reads_have_landed_at_the_barriers_of_the_64_wide_kernel(tmp_path):
             barriers += 1
             assert not pending, f"barrier {barriers} is passed with {pending} under way"
     assert barriers >= 2 * 12
+
+
+def test_no_inline_assembly_load_writes_a_register():
+    """The compiler takes an asm statement's outputs as written when it ends and may copy or re-use them while the load is still
+    under way.  Loads into registers are builtins, whose waits it places itself; asm loads go to LDS (no output operand)."""
+    for name in sorted(os.listdir(B.CSRC)):
+        if not name.endswith((".h", ".hip")):
+            continue
+        with open(os.path.join(B.CSRC, name)) as f:
+            text = f.read()
+        for at in re.finditer(r"\basm\b[^;]*?\(", text):
+            body = text[at.end():text.index(");", at.end())]
+            outputs = body.split(":")[1] if ":" in body else ""
+            assert not ("load" in body and "=" in outputs), (name, body)
