@@ -160,7 +160,7 @@ __global__ __launch_bounds__(narrow::kThreads) void k_narrow(const NarrowArgs a)
         xo = px * a.S + j - jy * a.S;
       }
       const int y = yo * sy, x = xo * sy;  // centre of the 3x3 on the input grid
-      const bool live = rho < M;
+      const bool live = t < last && rho < M;  // (tiles from `last` on belong to another XCD's workgroups)
       voffA[i] = (unsigned)((n * a.H + y) * a.W + x) * 128u + (((unsigned)l7 ^ (unsigned)l8 ^ (wave & 1u)) << 4);
       const unsigned mk = ((y > 0 ? 0x7u : 0u) | 0x38u | (y < a.H - 1 ? 0x1c0u : 0u)) &
                           ((x > 0 ? 0x49u : 0u) | 0x92u | (x < a.W - 1 ? 0x124u : 0u));
@@ -251,7 +251,7 @@ __global__ __launch_bounds__(narrow::kThreads) void k_narrow(const NarrowArgs a)
       *reinterpret_cast<uint4*>(row + (((ch + 1u) ^ f) << 4)) =
           make_uint4(pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]), pack_bf16(v[12], v[13]), pack_bf16(v[14], v[15]));
     }
-    describe(tile + step, buf ^ 1);  // (past the last tile: no live rows, nothing is fetched)
+    describe(tile + step, buf ^ 1);  // (past this workgroup's last tile: no live rows, nothing is fetched)
     lds_wait();
     wg_barrier();  // h2 complete; everyone is done with the slices
 #pragma unroll
