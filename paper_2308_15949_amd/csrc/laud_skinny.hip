@@ -414,13 +414,12 @@ template <int MODE, typename ET>
 static int launch_skinny_e(const GemmArgs& a, long long cap_rows, hipStream_t st) {
   constexpr int BKE = 8 * elem<ET>::per16;
   constexpr bool TAPS = (MODE == M_CONV2 || MODE == M_SD2 || MODE == M_G2);
-  if constexpr (MODE == M_G2) {  // 64-channel column tiles: they hold whole groups
-    if (cap_rows < 0) {
-      const int rc = launch_skinny_t<MODE, ET, 1, 4, 8, 2>(a, -1, st);
-      return rc == LAUD_OK ? launch_skinny_t<MODE, ET, 4, 4, 4, 2>(a, -1, st) : rc;
-    }
-    if (((cap_rows + 63) / 64) * ((a.Ncols + 63) / 64) < 192) return launch_skinny_t<MODE, ET, 1, 4, 8, 2>(a, cap_rows, st);
-    return launch_skinny_t<MODE, ET, 4, 4, 4, 2>(a, cap_rows, st);
+  if constexpr (MODE == M_G2) {
+    // 64-channel column tiles: they hold whole groups.  bf16: nine slices on three waves, all of a wave's under way at once, so
+    // that a compute unit holds two workgroups (on eight waves their LDS let it hold one, and a second round took 10.6 us where
+    // the tiled kernel takes 8.6).  float32: eighteen slices, MFMAs as long as loads: eight waves.
+    if constexpr (sizeof(ET) == 2) return launch_skinny_t<MODE, ET, 1, 4, 3, 3>(a, cap_rows, st);
+    else return launch_skinny_t<MODE, ET, 1, 4, 8, 2>(a, cap_rows, st);
   } else {
     if (cap_rows < 0) {
       int rc = launch_skinny_t<MODE, ET, 1, 1, 8, 8>(a, -1, st);
@@ -464,6 +463,9 @@ int launch_skinny(int mode, int dtype, const GemmArgs& a, long long cap_rows, hi
 // activation ratios 0.5 and 0.86 (bf16): the 3x3 wins up to about 260 tiles with 18 slices or more (stage 4, 42 images: 25
 // against 33 us) and to 220 with nine; the 1x1s meet the tiled kernel at 250 tiles with up to 8 slices, at 200 with more,
 // and at 200 where a residual is read.  In float32 the tiled kernel is bound by its MFMAs on few workgroups much longer.
+// The group 3x3 wins while its 16-row workgroups fit the chip in one round at any activation ratio, up to 128 tiles (bf16, the
+// two RegNetY backbones at ratios 0.3 / 0.95: 5.5 / 6.9 us against 8.6 / 9.0 at 112 tiles, 5.6 / 9.7 against 8.8 / 9.0 at 160;
+// float32: 8.7 / 15.7 against 16.8 / 17.5 at 112, 8.4 / 22.8 against 16.9 / 17.8 at 160).
 bool skinny_wanted(int mode, int dtype, const GemmArgs& a, long long cap_rows) {
   const bool taps = mode == M_CONV2 || mode == M_SD2 || mode == M_G2, res = mode == M_CONV3 || mode == M_SD3;
   const int bke = dtype == LAUD_BF16 ? 64 : 32;
@@ -471,6 +473,7 @@ bool skinny_wanted(int mode, int dtype, const GemmArgs& a, long long cap_rows) {
   const long long t = ((cap_rows + 63) / 64) * ((a.Ncols + 63) / 64);
   int most = taps ? (kt > 9 ? 288 : 224) : (kt > 8 || res ? 208 : 256);
   if (dtype == LAUD_F32 && kt > 8) most = 512;
+  if (mode == M_G2) most = 128;
   return cap_rows < (1 << 20) && t <= most;
 }
 

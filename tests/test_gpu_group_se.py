@@ -54,6 +54,10 @@ CASES = [
     (2, 12, 12, 128, 64, 16, 2, I.F32, True, 0.5),
     (2, 8, 8, 64, 64, 16, 2, I.BF16, True, 0.5),     # one group as wide as the layer
     (40, 14, 14, 320, 16, 80, 2, I.BF16, True, 0.5),  # many row tiles
+    (2, 64, 64, 64, 16, 8, 4, I.BF16, True, 0.9),    # 128 tiles of 64 x 64: the last size of the small tiles of the group 3x3
+    (2, 64, 66, 64, 16, 8, 2, I.BF16, True, 0.9),    # 132: the tiled kernel
+    (2, 64, 64, 64, 16, 8, 4, I.F32, True, 0.9),
+    (2, 64, 66, 64, 16, 8, 2, I.F32, True, 0.9),
 ]
 
 
