@@ -55,7 +55,9 @@ typedef __attribute__((ext_vector_type(16))) float stem_f32x16;
 //   * Implicit GEMM per step: 256 rows (conv pixels) x 64 channels.  A window row is 21 consecutive values of the image
 //     (7 pixels x 3 channels), padded to 24 = three 16-byte fragments: K = 7 x 24 (+ 8) = 176 in eleven 32x32x16 steps.  A
 //     fragment starts 12 * column bytes into the image row, so each image row is kept in LDS four times, shifted by 0, 12,
-//     24 and 36 bytes: column x reads copy x % 4, where its fragments are 16-byte aligned.
+//     24 and 36 bytes: column x reads copy x % 4, where its fragments are 16-byte aligned.  The 48 bytes of a window in its copy
+//     are no other window's, so the padding is stored as zeros (the pixel beside the window, met by zero weights, would
+//     make a NaN of an infinity).
 //   * 8 waves: wave (wm, wn) computes rows 64 wm .. +63, channels 32 wn .. +31, weights in 44 registers per lane for the
 //     workgroup's whole life.  The next step's image rows are on their way in registers meanwhile.
 //   * ReLU leaves bf16 values whose bit patterns order like 16-bit integers: pooling is a packed integer maximum, and
@@ -64,7 +66,8 @@ constexpr int kSpRows = 7, kSpCols = 8;               // pooled rows of a strip,
 constexpr int kSpIn = 37;                             // image rows of a strip: 2 * 15 + 7
 constexpr int kSpDw = 57;                             // dwords of an image row a step reads: 12 * 15 + 48 bytes
 constexpr int kSpCopy = 240, kSpRowB = 4 * kSpCopy;   // LDS bytes of one copy / of the four copies of an image row
-constexpr int kSpConv = (kSpIn * kSpRowB + 255) / 256 * 256;
+constexpr int kSpZero = kSpIn * kSpRowB;              // 16 bytes of zeros
+constexpr int kSpConv = (kSpZero + 16 + 255) / 256 * 256;
 constexpr int kSpLds = kSpConv + 16 * 32 * 128;       // conv values [16 rows][32 columns][64 channels]
 constexpr int kSpThreads = 512, kSpLoads = (kSpIn * kSpDw + kSpThreads - 1) / kSpThreads;
 __global__ __launch_bounds__(kSpThreads) void k_stem_pool_bf16(const bf16_t* __restrict__ x, int N, int Hin, int Win, int Hc, int Wc,
@@ -74,6 +77,7 @@ __global__ __launch_bounds__(kSpThreads) void k_stem_pool_bf16(const bf16_t* __r
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l31 = lane & 31, lhi = lane >> 5, wm = wave >> 1, wn = wave & 1;
+  if (tid < 4) reinterpret_cast<unsigned*>(smem + kSpZero)[tid] = 0u;
   // weights into registers, through LDS: K step st of this lane is window row f / 3, values 8 (f % 3) .. +7, f = 2 st + lhi
   {
     unsigned* d = reinterpret_cast<unsigned*>(smem);
@@ -102,6 +106,20 @@ __global__ __launch_bounds__(kSpThreads) void k_stem_pool_bf16(const bf16_t* __r
   for (int i = 0; i < 2; ++i) {
     const int rr = wm * 64 + i * 32 + l31, r = rr >> 4, xo = rr & 15;
     abase[i] = (unsigned)(2 * r * kSpRowB + (xo & 3) * kSpCopy + (xo >> 2) * 48);
+  }
+  // which bits of this thread's dword i of a step lie inside the window it belongs to in copy q (dwords 10 and 11 of a window's
+  // twelve: its last value and the padding)
+  unsigned inside[kSpLoads][4];
+#pragma unroll
+  for (int i = 0; i < kSpLoads; ++i) {
+    const int m = (tid + i * kSpThreads) % kSpDw % 12;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      inside[i][q] = m == (10 + 3 * q) % 12 ? 0xffffu : m == (11 + 3 * q) % 12 ? 0u : ~0u;
+#if defined(__HIP_DEVICE_COMPILE__)
+      asm("" : "+v"(inside[i][q]));  // (kept in a register: derived again at each use it becomes branches)
+#endif
+    }
   }
   const int units = N * strips * chunks, nsteps = (Wp + kSpCols - 1) / kSpCols;
   for (int u = blockIdx.x; u < units; u += gridDim.x) {
@@ -133,7 +151,7 @@ __global__ __launch_bounds__(kSpThreads) void k_stem_pool_bf16(const bf16_t* __r
         if (r < kSpIn) {
 #pragma unroll
           for (int q = 0; q < 4; ++q)
-            if (d >= 3 * q) *reinterpret_cast<unsigned*>(smem + r * kSpRowB + q * kSpCopy + (d - 3 * q) * 4) = pre[i];
+            if (d >= 3 * q) *reinterpret_cast<unsigned*>(smem + r * kSpRowB + q * kSpCopy + (d - 3 * q) * 4) = pre[i] & inside[i][q];
         }
       }
     };
@@ -150,13 +168,13 @@ __global__ __launch_bounds__(kSpThreads) void k_stem_pool_bf16(const bf16_t* __r
         for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
 #pragma unroll
       for (int st = 0; st < 11; ++st) {
-        // lane half h: fragment f = 2 st + h; the last one (f = 21) has zero weights and reads fragment 20
-        const int f0 = 2 * st, f1 = 2 * st + 1 < 21 ? 2 * st + 1 : 20;
+        // lane half h: fragment f = 2 st + h; the last one (f = 21) has zero weights and reads zeros
+        const int f0 = 2 * st, f1 = 2 * st + 1;
         const unsigned o0 = (unsigned)(f0 / 3 * kSpRowB + f0 % 3 * 16), o1 = (unsigned)(f1 / 3 * kSpRowB + f1 % 3 * 16);
-        const unsigned off = lhi ? o1 : o0;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-          const uint4 a = *reinterpret_cast<const uint4*>(smem + abase[i] + off);
+          const unsigned at = !lhi ? abase[i] + o0 : f1 < 21 ? abase[i] + o1 : (unsigned)kSpZero;
+          const uint4 a = *reinterpret_cast<const uint4*>(smem + at);
           acc[i] = mma_bf16(wr[st], a, acc[i]);
         }
       }

@@ -89,3 +89,33 @@ def test_nan_stays_nan_without_output_relu(G, case):  # noqa: F811
     t.cuda.synchronize()
     got = xd.float().cpu().numpy()
     assert np.argwhere(~np.isfinite(got)).tolist() == [[N - 1, H - 2, 3, 5]] and np.isnan(got[N - 1, H - 2, 3, 5])
+
+
+@pytest.mark.parametrize("shape", [(1, 64, 80), (2, 37, 46)])
+def test_stem_infinite_pixel_stays_in_its_windows(G, shape):  # noqa: F811
+    """An infinite value of the image makes the windows that cover it infinite (or zero, behind the ReLU) and no other: not the
+    ones beside it, whose padded reduction reads the next pixel too."""
+    t, L, D = G.torch, G.L, G.D
+    N, H, W = shape
+    g = np.random.default_rng(7950 + H)
+    x = I.round_to(g.standard_normal((N, H, W, 3), dtype=np.float32), I.BF16)
+    for y, xx, c in ((5, 7, 0), (5, 30, 2), (H - 1, W - 1, 1), (20, 19, 0), (21, W - 12, 1)):
+        x[N - 1, y, xx, c] = np.inf
+    w7 = I.round_to(g.standard_normal((64, 7, 7, 3), dtype=np.float32) * np.float32(np.sqrt(2.0 / 147)), I.BF16)
+    assert np.all(w7 != 0)
+    s, b = (1 + 0.1 * g.standard_normal(64)).astype(np.float32), (0.1 * g.standard_normal(64)).astype(np.float32)
+    # a conv value is infinite where it meets an infinite value with a positive weight; -inf, and the NaN of inf - inf, end as 0
+    # behind the ReLU
+    inf = np.isinf(x).astype(np.float32)
+    plus, minus = O.conv2d(inf, np.maximum(w7, 0), 2, 3) > 0, O.conv2d(inf, np.maximum(-w7, 0), 2, 3) > 0
+    conv = O.relu(O.affine(O.conv2d(np.where(np.isinf(x), 0, x), w7, 2, 3), s, b))
+    finite = O.maxpool3x3_s2(np.where(minus, 0.0, conv))
+    want_inf = O.maxpool3x3_s2((plus & ~minus).astype(np.float32)) > 0
+    assert want_inf.any() and not want_inf.all()
+    out = t.full(finite.shape, 7.0, dtype=t.bfloat16, device="cuda")
+    L.laud_stem(D.to_device(x, I.BF16), N, H, W, I.BF16, D.to_device(w7, I.BF16), t.from_numpy(s).cuda(), t.from_numpy(b).cuda(),
+                64, out, D.workspace(L.stem_workspace(N, H, W, 64, I.BF16)))
+    t.cuda.synchronize()
+    got = D.to_host(out)
+    assert np.array_equal(np.isposinf(got), want_inf)
+    close(np.where(want_inf, 0, got), np.where(want_inf, 0, finite), TOL[I.BF16])
