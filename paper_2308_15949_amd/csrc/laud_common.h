@@ -194,10 +194,10 @@ int launch_dense_affine(int dtype, const void* A, const void* Wt, const float* s
                         long long rows, int K, int ncols, int relu, hipStream_t stream);
 
 // The SE module on the compact rows h2 [rows][C] of the active patches (pps patches per sample, SS pixels per
-// patch); see laud_se.hip.
-constexpr int kSeMaxC = 4096, kSeMaxHidden = 1024;  // widest layer / SE hidden layer the kernel keeps in LDS
+// patch, at most cap_rows rows); see laud_se.hip.  `scratch` holds N*(2*C + se_width) floats.
+constexpr int kSeMaxC = 4096, kSeMaxHidden = 1024;  // widest layer / SE hidden layer the kernels keep in LDS
 int launch_se(int dtype, int N, int pps, int SS, int C, const laud_group_se* e, void* h2, const int32_t* idx,
-              const int32_t* count, hipStream_t stream);
+              const int32_t* count, float* scratch, long long cap_rows, hipStream_t stream);
 
 // Out-of-place calls: pixels of inactive patches keep their value, so they are copied from x to out, bit for bit.  The copy
 // rides in extra workgroups of the block's last launch (nblocks of them, from workgroup id `first` on): it has nothing to

@@ -976,8 +976,8 @@ static int validate_group_se(const laud_bottleneck* p, const laud_group_se* e, c
   const int g = e->group_width;
   if (!(g == 8 || g == 16 || g == 32 || g == 64)) return LAUD_ERR_UNSUPPORTED;
   if (e->se_width > kSeMaxHidden || (e->se_width > 0 && p->c_mid > kSeMaxC)) return LAUD_ERR_UNSUPPORTED;
-  if (e->se_width > 0 && fx.N > 65535) return LAUD_ERR_UNSUPPORTED;  // one grid row of the squeeze per sample
-  // (the entry points' documented range: means, gates and hidden units fit the scratch activations of one sample)
+  if (e->se_width > 0 && fx.N > 65535) return LAUD_ERR_UNSUPPORTED;  // the means take one grid row (y) per sample
+  // the SE module's means, gates and hidden units are kept in the scratch region of h1 (N*H*W*c_mid elements)
   if (e->se_width > 0 && 4 * (2 * (size_t)p->c_mid + e->se_width) > (size_t)fx.H * fx.W * p->c_mid * elem_bytes(fx.dtype))
     return LAUD_ERR_UNSUPPORTED;
   return LAUD_OK;
@@ -1170,7 +1170,7 @@ static int run_dyn_block(const void* x, laud_fmap fx, const laud_bottleneck* p, 
   a.lda = p->c_mid; a.ldo = p->c_mid;
   if ((rc = launch_conv2(fx.dtype, a, e, npix, st)) != LAUD_OK) return rc;
   if (e && e->se_width > 0 &&
-      (rc = launch_se(fx.dtype, fx.N, Hp * Wp, S * S, p->c_mid, e, h2, idx, count, st)) != LAUD_OK)
+      (rc = launch_se(fx.dtype, fx.N, Hp * Wp, S * S, p->c_mid, e, h2, idx, count, (float*)h1, npix, st)) != LAUD_OK)
     return rc;
   // conv3: 1x1 on dense h2 with the scatter-add epilogue
   a.A = h2; a.Wt = p->w3; a.scale = p->s3; a.shift = p->t3; a.Out = out; a.Res = x;
@@ -1529,7 +1529,7 @@ static int run_dyn_projection(const void* x, laud_fmap fx, const laud_bottleneck
   a.lda = p->c_mid; a.ldo = p->c_mid;
   if ((rc = launch_conv2(fx.dtype, a, e, nout, st)) != LAUD_OK) return rc;
   if (e && e->se_width > 0 &&
-      (rc = launch_se(fx.dtype, fx.N, Hp * Wp, S * S, p->c_mid, e, h2, idx, count, st)) != LAUD_OK)
+      (rc = launch_se(fx.dtype, fx.N, Hp * Wp, S * S, p->c_mid, e, h2, idx, count, (float*)h1, nout, st)) != LAUD_OK)
     return rc;
   // conv3 added onto the shortcut already in `out`, at the active output pixels
   a.A = h2; a.Wt = p->w3; a.scale = p->s3; a.shift = p->t3; a.Out = out; a.Res = out;

@@ -58,6 +58,17 @@ CASES = [
     (2, 64, 66, 64, 16, 8, 2, I.BF16, True, 0.9),    # 132: the tiled kernel
     (2, 64, 64, 64, 16, 8, 4, I.F32, True, 0.9),
     (2, 64, 66, 64, 16, 8, 2, I.F32, True, 0.9),
+    # SE module: more than one block of 128 16-byte channel chunks (the last of one or two chunks), in one launch and in four
+    (2, 4, 4, 1032, 8, 8, 2, I.BF16, True, 0.5),
+    (2, 4, 4, 520, 8, 8, 2, I.F32, True, 0.5),
+    (3, 4, 4, 1032, 8, 64, 1, I.BF16, True, 0.5),
+    (9, 4, 4, 520, 8, 64, 2, I.F32, True, 0.5),      # nine samples: one past a group of the batched layers
+    (2, 8, 8, 32, 8, 1024, 2, I.F32, True, 0.5),     # the widest hidden layer; 256 KB of weights: the last size in one launch
+    (2, 8, 8, 64, 16, 1024, 2, I.BF16, True, 0.5),   # ... in four
+    (3, 6, 6, 392, 8, 90, 2, I.BF16, True, 0.5),     # four launches, rows of the second layer not 16-byte aligned
+    (1, 160, 160, 8, 8, 4, 4, I.BF16, True, 0.9),    # 400 KB of rows a sample: the last size in one launch ...
+    (1, 160, 162, 8, 8, 4, 2, I.BF16, True, 0.9),    # ... in four ...
+    (16, 80, 164, 8, 8, 4, 4, I.F32, True, 0.9),     # ... and from 16 samples on in one again, up to 800 KB
 ]
 
 
