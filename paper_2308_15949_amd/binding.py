@@ -169,6 +169,15 @@ def _stream():
     return _raw_stream()
 
 
+def _forget_raw_stream():
+    global _raw_stream
+    _raw_stream = None
+
+
+# a forked child goes through torch once more, which refuses a device state that was initialised in the parent
+os.register_at_fork(after_in_child=_forget_raw_stream)
+
+
 def _check(status: int, where: str) -> None:
     if status != OK:
         raise LaudError(status, where)

@@ -317,3 +317,20 @@ def test_bench_reads_traffic_from_the_committed_counter_summary():
     assert v is not None and 4e7 < v < 2e8   # tens of MB per launch at batch 128, ratio 0.5
     assert mod.traffic_from_profile("k_head") is not None
     assert mod.traffic_from_profile("no_such_kernel") is None
+
+
+def test_forked_child_asks_torch_before_it_uses_a_stream(monkeypatch):
+    """The stream comes from torch's raw getter, which checks nothing; the first call of a process goes through
+    torch.cuda.current_stream(), which raises in a child forked after the device was initialised.  That must hold in the child
+    too, not only in the parent."""
+    import torch
+    calls = []
+    monkeypatch.setattr(B, "_raw_stream", None)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 1234, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: calls.append(os.getpid()))
+    assert B._stream() == B._stream() == 1234 and calls == [os.getpid()]
+    pid = os.fork()
+    if pid == 0:
+        os._exit(0 if B._stream() == 1234 and calls[-1] == os.getpid() else 1)
+    assert os.waitpid(pid, 0)[1] == 0
