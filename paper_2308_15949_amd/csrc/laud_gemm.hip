@@ -328,7 +328,9 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
   unsigned tapbit = 1u;
   bool live = true;
   auto load_slice = [&](u32x4 (&ra)[AR], u32x4 (&rb)[BR]) __attribute__((always_inline)) -> int {
-    const int tap = ld_tap;
+    // (slices past the last tap -- the pipeline requests up to four -- read the last tap's weights: the element-wise gather
+    // below issues its loads whether they are wanted or not)
+    const int tap = min(ld_tap, NTAPS - 1);
     const int ke = ld_kc * BKE + cc * EPC;  // this thread's first (compact) K element
     const int kcb = ld_kc * BKE;
     // (with an empty reduction -- channel skipping with every group dropped -- kchunks is 0 and no chunk is inside K)

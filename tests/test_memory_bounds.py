@@ -1,0 +1,195 @@
+"""Which memory the kernels touch, checked on the CPU: their sources are built for the host (tests/host_build) and run with every
+operand, index list and workspace between two pages that nobody may touch, index lists exactly as long as their count."""
+import ctypes as C
+import os
+import re
+import subprocess
+from concurrent.futures import ThreadPoolExecutor
+
+import numpy as np
+import pytest
+
+from paper_2308_15949_amd import binding as B
+from paper_2308_15949_amd import build as build_rules
+
+HERE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "host_build")
+CXX = "/opt/rocm/llvm/bin/clang++"
+
+
+def host_source(name, s):
+    """A kernel source with dynamic LDS as pointers, generic pointers only, and its inline assembly replaced or dropped."""
+    s = re.sub(r"extern __shared__ (?:__align__\(16\) )?unsigned char (\w+)\[\];", r"unsigned char* const \1 = host::lds;", s)
+    s = re.sub(r"extern __shared__ (?:__align__\(16\) )?float (\w+)\[\];", r"float* const \1 = (float*)host::lds;", s)
+    s = re.sub(r"const __attribute__\(\(address_space\(\d\)\)\) ", "const ", s)
+    s = s.replace("#if defined(__HIP_DEVICE_COMPILE__)", "#if 1")
+    s = s.replace('asm volatile("s_waitcnt lgkmcnt(0)\\n\\ts_barrier" ::: "memory");', "host::barrier();")
+    s = s.replace('asm volatile("s_barrier" ::: "memory");', "host::barrier();")
+    if name == "laud_common.h":  # there is no kernel argument segment
+        at = s.index("prefetch_args() {") + len("prefetch_args() {")
+        s = s[:at] + s[s.index("\n}\n", at):]
+    if name == "laud_tile_util.h":
+        s = re.sub(r'asm volatile\("s_mov_b32 m0.*?;\n', "host::load_to_lds(rsrc, voff, soff, lds_base);\n", s, flags=re.S, count=1)
+        s = re.sub(r"const f32x2 v = \{lo, hi\};\s*return [^;]*;", "return (unsigned)f32_to_bf16(lo) | ((unsigned)f32_to_bf16(hi) << 16);", s)
+    return re.sub(r"\basm(?: volatile)?\s*\((?:[^()]|\((?:[^()]|\([^()]*\))*\))*\);", ";", s)
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = str(tmp_path_factory.mktemp("host_build"))
+    for name in os.listdir(build_rules.CSRC):
+        if name.endswith((".h", ".hip")):
+            with open(os.path.join(build_rules.CSRC, name)) as f:
+                text = host_source(name, f.read())
+            with open(os.path.join(d, name.replace(".hip", ".cpp")), "w") as f:
+                f.write(text)
+    flags = ["-O1", "-std=c++17", "-fPIC", "-w", "-fno-strict-aliasing", "-I", HERE, "-I", d, "-I", os.path.join(build_rules.ROOT, "include")]
+    sources = [os.path.join(d, s.replace(".hip", ".cpp")) for s in build_rules.SOURCES if s != "laud_probe.hip"]
+    sources.append(os.path.join(HERE, "host_run.cpp"))
+    objects = [os.path.join(d, os.path.basename(s) + ".o") for s in sources]
+    with ThreadPoolExecutor(8) as ex:
+        list(ex.map(lambda so: subprocess.run([CXX, *flags, "-c", so[0], "-o", so[1]], check=True, capture_output=True), zip(sources, objects)))
+    subprocess.run([CXX, "-shared", "-fPIC", *objects, "-o", os.path.join(d, "host.so")], check=True)
+    return os.path.join(d, "host.so")
+
+
+class Call:
+    """Operands of one call and the call itself; runs in a process of its own."""
+
+    def __init__(self, path, front):
+        B.LIB_PATH, B._lib, B._stream = path, None, lambda: 0
+        self.host = B.load()
+        self.host.host_alloc.restype, self.host.host_alloc.argtypes = C.c_void_p, [C.c_size_t, C.c_int]
+        self.host.host_init()
+        self.front, self.rng, self.held = front, np.random.default_rng(1), []
+
+    def buf(self, nbytes, data=None):
+        p = self.host.host_alloc(max(int(nbytes), 4), self.front)
+        if data is not None:
+            C.memmove(p, data.ctypes.data, data.nbytes)
+        return p
+
+    def values(self, n, bf16):
+        a = np.maximum(self.rng.standard_normal(n, dtype=np.float32), 0)
+        a = (a.view(np.uint32) >> 16).astype(np.uint16) if bf16 else a
+        return self.buf(a.nbytes, a)
+
+    def ws(self, nbytes):
+        w = self.buf(nbytes)
+        C.memset(w, 0x7b, int(nbytes))
+
+        class Workspace:
+            data_ptr, numel, element_size = (lambda s: w), (lambda s: int(nbytes)), (lambda s: 1)
+        return Workspace()
+
+    def block(self, ci, m, co, gw, bf16, packed):
+        t = [self.values(n, bf16) for n in (m * ci, m * 9 * (gw or m), co * m)] + [self.values(n, False) for n in (m, m, m, m, co, co)]
+        p = B.Bottleneck(ci, m, co, *t, 1)
+        nb = B.packed_weights_size(p, B.BF16 if bf16 else B.F32) if packed else 0
+        if nb:
+            p.packed = self.buf(nb)
+            B.laud_pack_weights(p, B.BF16, p.packed)
+        return p
+
+    def list(self, patches, ratio):
+        ids = np.flatnonzero(self.rng.random(patches) < ratio).astype(np.int32)
+        return self.buf(ids.nbytes, ids), self.buf(4, np.array([len(ids)], np.int32))
+
+    def se(self, m, gw, width):
+        return B.GroupSE(gw, width, *([self.values(n, False) for n in (width * m, width, m * width, m)] if width else [None] * 4))
+
+    def identity(self, kind, n, h, w, c, m, S, ratio, bf16=True, inplace=True, gw=None, se=0, packed=False, keep=False, D=0):
+        fx, x, p = B.Fmap(n, h, w, c, B.BF16 if bf16 else B.F32), self.values(n * h * w * c, bf16), self.block(c, m, c, gw, bf16, packed)
+        out, patches = x if inplace else self.buf(n * h * w * c * (2 if bf16 else 4)), n * (h // S) * (w // S)
+        ws = self.ws(B.workspace_size(B.OP_CHANNEL_SKIP if kind == "channel" else B.OP_DYN_BOTTLENECK, fx, p, S))
+        if kind == "channel":
+            mask = (self.rng.random(n * D) < 0.5).astype(np.uint8)
+            mask[:D], mask[-D:] = 1, 0
+            B.laud_channel_skip_conv(x, fx, p, self.buf(n * D, mask), D, out, ws)
+        elif kind == "masker":
+            gate = self.buf(n, (self.rng.random(n) < 0.6).astype(np.uint8)) if keep else None
+            w1 = self.rng.standard_normal(c, dtype=np.float32)
+            B.laud_masker_dyn_bottleneck(x, fx, p, S, self.buf(w1.nbytes, w1), 0.01, gate, self.buf(patches), self.buf(4 * patches),
+                                         self.buf(4), None, None if keep else self.buf(4 * patches), out, ws)
+        elif gw:
+            B.laud_dyn_group_se_bottleneck(x, fx, p, self.se(m, gw, se), S, *self.list(patches, ratio), out, ws)
+        else:
+            B.laud_dyn_bottleneck(x, fx, p, S, *self.list(patches, ratio), out, ws)
+
+    def first(self, kind, n, hi, wi, ci, m, co, stride, S, ratio, bf16=True, gw=None, se=0, packed=False):
+        h, w = (hi - 1) // stride + 1, (wi - 1) // stride + 1
+        fx, x, p = B.Fmap(n, hi, wi, ci, B.BF16 if bf16 else B.F32), self.values(n * hi * wi * ci, bf16), self.block(ci, m, co, gw, bf16, packed)
+        sc = self.values(co * ci, bf16), self.values(co, False), self.values(co, False)
+        out = self.buf(n * h * w * co * (2 if bf16 else 4))
+        if kind == "static":
+            B.laud_static_bottleneck(x, fx, p, *sc, stride, out, self.ws(B.static_bottleneck_workspace(fx, p, stride)))
+            return
+        ws, ids = self.ws(B.dyn_projection_workspace(fx, p, stride)), self.list(n * (h // S) * (w // S), ratio)
+        if gw:
+            B.laud_dyn_group_se_projection_bottleneck(x, fx, p, self.se(m, gw, se), *sc, stride, S, *ids, out, ws)
+        else:
+            B.laud_dyn_projection_bottleneck(x, fx, p, *sc, stride, S, *ids, out, ws)
+
+    def stem(self, n, h, w, co, bf16=True, k=7):
+        down = lambda v: (v - 1) // 2 + 1  # noqa: E731
+        x, wt, s, t = self.values(n * h * w * 3, bf16), self.values(co * 3 * k * k, bf16), self.values(co, False), self.values(co, False)
+        code, eb = (B.BF16, 2) if bf16 else (B.F32, 4)
+        if k == 7:
+            B.laud_stem(x, n, h, w, code, wt, s, t, co, self.buf(n * down(down(h)) * down(down(w)) * co * eb), self.ws(B.stem_workspace(n, h, w, co, code)))
+        else:
+            B.laud_stem3x3(x, n, h, w, code, wt, s, t, co, self.buf(n * down(h) * down(w) * co * eb))
+
+
+CASES = {
+    # small tiles; tiled kernels; index lists of one entry and of all
+    "few_rows": ("identity", "dyn", 1, 7, 7, 136, 72, 1, 0.5),
+    "few_rows_f32": ("identity", "dyn", 2, 5, 17, 24, 16, 1, 0.9, False, False),
+    "tiled": ("identity", "dyn", 9, 28, 28, 64, 40, 7, 0.5, True, False),
+    "tiled_f32": ("identity", "dyn", 20, 28, 28, 24, 40, 4, 0.3, False),
+    "empty_list": ("identity", "dyn", 3, 14, 14, 64, 24, 2, 0.0, True, False),
+    # 64-wide kernel, fused 3x3 -> 1x1 and register-weight first 1x1
+    "narrow": ("identity", "dyn", 5, 56, 56, 256, 64, 4, 0.3, True, False),
+    "narrow_static": ("first", "static", 1, 241, 239, 64, 64, 256, 2, 1, 1.0),
+    "narrow_projection": ("first", "dynamic", 5, 111, 112, 64, 64, 256, 2, 8, 0.4),
+    "fused": ("identity", "dyn", 22, 14, 14, 1024, 256, 2, 0.3, True, False),
+    "fused_packed": ("identity", "masker", 22, 14, 14, 1024, 256, 2, 0.5, True, True, None, 0, True, True),
+    "projection_before_fused": ("first", "dynamic", 22, 14, 14, 320, 256, 1024, 1, 2, 0.5),
+    # fused masker
+    "masker": ("identity", "masker", 3, 12, 12, 72, 24, 4, 0.5),
+    "masker_f32_gates": ("identity", "masker", 26, 14, 14, 32, 8, 1, 0.5, False, False, None, 0, False, True),
+    # first blocks
+    "static": ("first", "static", 2, 13, 9, 40, 24, 96, 2, 1, 1.0),
+    "projection_f32": ("first", "dynamic", 3, 27, 14, 8, 16, 40, 2, 7, 0.4, False),
+    # group convolution and SE, in one launch and in four
+    "group_se": ("identity", "dyn", 3, 14, 14, 144, 144, 2, 0.5, True, True, 16, 36),
+    "group_se_four_launches": ("identity", "dyn", 3, 6, 6, 392, 392, 2, 0.7, True, True, 8, 90),
+    "group_se_projection": ("first", "dynamic", 2, 27, 28, 32, 104, 104, 2, 7, 0.5, True, 8, 26),
+    # channel skipping: groups of whole 16-byte chunks, the fused kernels, and groups that are not
+    "channel": ("identity", "channel", 5, 7, 6, 64, 64, 1, 0, True, False, None, 0, False, False, 4),
+    "channel_fused": ("identity", "channel", 6, 7, 7, 1024, 256, 1, 0, True, False, None, 0, False, False, 4),
+    "channel_groups_of_9": ("identity", "channel", 6, 14, 3, 8, 72, 1, 0, True, False, None, 0, False, False, 8),
+    "channel_groups_of_18": ("identity", "channel", 4, 14, 14, 288, 72, 1, 0, True, False, None, 0, False, False, 4),
+    "channel_groups_of_33_f32": ("identity", "channel", 5, 12, 9, 264, 264, 1, 0, False, False, None, 0, False, False, 8),
+    "channel_groups_of_1": ("identity", "channel", 3, 5, 5, 16, 8, 1, 0, True, False, None, 0, False, False, 8),
+    # stems
+    "stem": ("stem", 2, 37, 45, 64),
+    "stem_f32": ("stem", 1, 17, 9, 40, False),
+    "stem3x3": ("stem", 2, 9, 66, 32, True, 3),
+    "stem3x3_odd": ("stem", 2, 9, 65, 24, True, 3),
+}
+
+
+@pytest.mark.parametrize("front", [0, 1])
+@pytest.mark.parametrize("name", CASES)
+def test_kernels_stay_inside_their_buffers(lib, name, front, capfd):
+    pid = os.fork()
+    if pid == 0:  # (a fault ends the process, with the kernel and the workgroup on stderr)
+        status = 1
+        try:
+            method, *args = CASES[name]
+            getattr(Call(lib, front), method)(*args)
+            status = 0
+        except BaseException as e:  # noqa: B902
+            os.write(2, repr(e).encode())
+        os._exit(status)
+    _, status = os.waitpid(pid, 0)
+    assert status == 0, capfd.readouterr().err
