@@ -1,5 +1,5 @@
 """GPU parity of routes through the entry points that the per-kernel files do not take: index lists that end with their last
-entry, on every kernel that reads one."""
+entry, on every kernel that reads one; values that are not finite; a mask made on the device in front of the 64-wide kernel."""
 import numpy as np
 import pytest
 
@@ -89,6 +89,33 @@ def test_nan_stays_nan_without_output_relu(G, case):  # noqa: F811
     t.cuda.synchronize()
     got = xd.float().cpu().numpy()
     assert np.argwhere(~np.isfinite(got)).tolist() == [[N - 1, H - 2, 3, 5]] and np.isnan(got[N - 1, H - 2, 3, 5])
+
+
+@pytest.mark.parametrize("use_keep", [False, True])
+@pytest.mark.parametrize("case", [(5, 56, 56, 4), (13, 40, 28, 2)])
+def test_masker_into_the_64_wide_kernel_out_of_place(G, case, use_keep):  # noqa: F811
+    """The list is made by the launch before: the 64-wide kernel's tiles and its copying workgroups both read it."""
+    t, L, D = G.torch, G.L, G.D
+    N, H, W, S = case
+    x = I.feature_map(8000 + H, N, H, W, 256, I.BF16)
+    hb = I.bottleneck_params(8100 + H, 256, 64, 256, I.BF16, relu_out=True)
+    w = I.masker_weights(8200, 256)
+    ref0 = O.mask_logits(x, S, w, 0.0)
+    bias = I.bias_for_ratio(ref0, 0.4, window=ref0.size // 8)[0]
+    keep = np.ones(N, np.uint8)
+    keep[[0, -2]] = 0
+    mask = O.threshold(ref0 + bias) * (keep[:, None, None] if use_keep else 1)
+    xd, db = D.to_device(x, I.BF16), D.DeviceBottleneck(hb)
+    fx, n = L.fmap_of(xd), mask.size
+    mk, idx, cnt = t.zeros(n, dtype=t.uint8, device="cuda"), t.zeros(n, dtype=t.int32, device="cuda"), t.zeros(1, dtype=t.int32, device="cuda")
+    out, ws = t.full_like(xd, 7.0), D.workspace(L.workspace_size(L.binding.OP_DYN_BOTTLENECK, fx, db.desc, S))
+    ws.fill_(0xFF)
+    L.laud_masker_dyn_bottleneck(xd, fx, db.desc, S, t.from_numpy(w).cuda(), bias, t.from_numpy(keep).cuda() if use_keep else None,
+                                 mk, idx, cnt, None, None, out, ws)
+    t.cuda.synchronize()
+    assert np.array_equal(mk.cpu().numpy().reshape(mask.shape), mask)
+    assert np.array_equal(D.to_host(xd), x)
+    check_dyn(D.to_host(out), x, hb, S, mask)
 
 
 @pytest.mark.parametrize("shape", [(1, 64, 80), (2, 37, 46)])

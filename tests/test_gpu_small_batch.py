@@ -21,9 +21,19 @@ CASES = [
     (3, 14, 14, 1024, 256, 2, I.BF16),   # 588 rows, 32 x 32 tiles
     (9, 14, 14, 1024, 256, 2, I.BF16),   # 1764 rows, 32 x 64 tiles
     (21, 14, 14, 1024, 256, 2, I.BF16),  # 4116 rows: past the line to the register-weight kernels
-    (1, 128, 128, 16, 8, 4, I.BF16),     # 256 tiles of 64 x 64: the last size of the split-reduction last 1x1
-    (1, 128, 132, 16, 8, 4, I.BF16),     # 264 tiles: the tiled last 1x1
+    (1, 128, 128, 16, 8, 4, I.BF16),     # 256 tiles of 64 x 64: the last size of the split-reduction first 1x1
+    (1, 128, 132, 16, 8, 4, I.BF16),     # 264 tiles: past it
     (1, 56, 64, 32, 16, 8, I.F32),
+    (1, 104, 128, 16, 8, 4, I.BF16),     # 208 tiles: the last size of the last 1x1 (a residual is read) ...
+    (1, 88, 152, 16, 8, 4, I.BF16),      # ... 209
+    (1, 112, 128, 16, 8, 4, I.BF16),     # 224 tiles: the last size of a 3x3 of nine slices ...
+    (1, 120, 120, 16, 8, 4, I.BF16),     # ... 225
+    (1, 96, 96, 16, 72, 4, I.BF16),      # 288 tiles: the last size of a 3x3 of more slices ...
+    (1, 80, 116, 16, 72, 4, I.BF16),     # ... 290
+    (1, 128, 256, 16, 8, 4, I.F32),      # 512 tiles: the last size of a float32 3x3 ...
+    (1, 108, 304, 16, 8, 4, I.F32),      # ... 513
+    (1, 104, 128, 520, 64, 4, I.BF16),   # 208 tiles: the last size of a first 1x1 of more than eight slices ...
+    (1, 88, 152, 520, 64, 4, I.BF16),    # ... 209
 ]
 
 

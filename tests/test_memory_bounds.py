@@ -129,6 +129,24 @@ class Call:
         else:
             B.laud_dyn_projection_bottleneck(x, fx, p, *sc, stride, S, *ids, out, ws)
 
+    def masks(self, n, h, w, c, S, bf16=True, keep=False, D=4):
+        """Spatial masker, compaction of its mask, gather with and without a halo, the unfused block, channel masker."""
+        fx, x, patches = B.Fmap(n, h, w, c, B.BF16 if bf16 else B.F32), self.values(n * h * w * c, bf16), n * (h // S) * (w // S)
+        w1 = self.rng.standard_normal(c, dtype=np.float32)
+        gate = self.buf(n, (self.rng.random(n) < 0.6).astype(np.uint8)) if keep else None
+        mask, idx, count = self.buf(patches), self.buf(4 * patches), self.buf(4)
+        B.laud_mask_gen(x, fx, S, self.buf(w1.nbytes, w1), 0.01, gate, mask, idx, count, self.buf(4 * (n + 1)), self.buf(4 * patches),
+                        self.ws(B.workspace_size(B.OP_MASK_GEN, fx, None, S)))
+        B.laud_layer_skip_compact(mask, patches, self.buf(4 * patches), self.buf(4), self.ws(B.workspace_size(B.OP_COMPACT, fx, None, patches)))
+        idx, count = self.list(patches, 0.4)
+        for halo in (0, 1):
+            B.laud_gather_patches(x, fx, S, halo, idx, count, self.buf(patches * (S + 2 * halo) ** 2 * c * (2 if bf16 else 4)))
+        p = self.block(c, 16, c, None, bf16, False)
+        B.laud_dyn_bottleneck_unfused(x, fx, p, S, idx, count, self.buf(n * h * w * c * (2 if bf16 else 4)), self.ws(B.dyn_bottleneck_unfused_workspace(fx, p, S)))
+        hidden = 16
+        mlp = [self.values(k, False) for k in (hidden * c, hidden, 2 * D * hidden, 2 * D)]
+        B.laud_channel_masker(x, fx, mlp[0], mlp[1], hidden, mlp[2], mlp[3], D, self.buf(n * D), self.buf(8 * n * D), self.ws(B.channel_masker_workspace(fx)))
+
     def stem(self, n, h, w, co, bf16=True, k=7):
         down = lambda v: (v - 1) // 2 + 1  # noqa: E731
         x, wt, s, t = self.values(n * h * w * 3, bf16), self.values(co * 3 * k * k, bf16), self.values(co, False), self.values(co, False)
@@ -170,6 +188,10 @@ CASES = {
     "channel_groups_of_18": ("identity", "channel", 4, 14, 14, 288, 72, 1, 0, True, False, None, 0, False, False, 4),
     "channel_groups_of_33_f32": ("identity", "channel", 5, 12, 9, 264, 264, 1, 0, False, False, None, 0, False, False, 8),
     "channel_groups_of_1": ("identity", "channel", 3, 5, 5, 16, 8, 1, 0, True, False, None, 0, False, False, 8),
+    # maskers, index lists, gather, the unfused schedule
+    "masks": ("masks", 3, 12, 20, 72, 4),
+    "masks_f32_gates": ("masks", 5, 14, 14, 8, 7, False, True),
+    "masks_long_lists": ("masks", 9, 32, 33, 8, 1),
     # stems
     "stem": ("stem", 2, 37, 45, 64),
     "stem_f32": ("stem", 1, 17, 9, 40, False),
