@@ -363,7 +363,8 @@ typedef enum {
   LAUD_STAGE_MASK_LOGITS = 0, /* pooled masker + threshold */
   LAUD_STAGE_COMPACT = 1,     /* ordered index generation */
   LAUD_STAGE_GATHER = 2,      /* stand-alone gather */
-  LAUD_STAGE_COPY_INACTIVE = 3,
+  LAUD_STAGE_COPY_INACTIVE = 3, /* unfused schedule only; elsewhere the copy of inactive patches is part of the block's last
+                                   launch and of its time (CONV3, or CONV2 where the 3x3 and the last 1x1 are one kernel) */
   LAUD_STAGE_NEED = 4,        /* dilated active pixel list for conv1 */
   LAUD_STAGE_CONV1 = 5,
   LAUD_STAGE_CONV2 = 6,

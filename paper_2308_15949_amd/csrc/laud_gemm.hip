@@ -1063,8 +1063,11 @@ static int launch_sparse_head(int dtype, const laud_bottleneck* p, const void* x
 
 // Whether a dynamic block's first 1x1 runs on every pixel of the map instead of on the dilated active set: where the small
 // tiles take it the launch is bound by its latency and not by its rows, and on narrow maps (up to kDenseConv1Bytes of input
-// and output, kDenseConv1Flops) all rows take about 16 us, of which the rows outside the dilated set (a tenth to a half) are
-// less than the launch that writes the pixel lists (7 us).
+// and output, kDenseConv1Flops) all rows take about 16 us, of which the rows outside the dilated set are less than the launch
+// that writes the pixel lists (7 us) unless few patches are active.  Blocks at activation ratios 0.05 / 0.15 / 0.5 / 0.86, dense
+// against listed: stage 1, 16 images 25 / 27 / 30 / 36 against 30 / 33 / 39 / 46 us; stage 2, 32 images 35 / 35 / 39 / 45
+// against 38 / 39 / 46 / 51 us.  Nearest the limits the sides meet at 0.15: RegNetY-800MF stage 2, 64 images 55 / 71 / 86 against
+// 51 / 74 / 91 us at 0.15 / 0.5 / 0.86, stage 1, 32 images 40 / 54 / 67 against 44 / 62 / 77 us.
 constexpr double kDenseConv1Bytes = 40e6, kDenseConv1Flops = 4e9;
 static bool dense_conv1_wanted(int dtype, const laud_bottleneck* p, long long npix) {
   GemmArgs a{};

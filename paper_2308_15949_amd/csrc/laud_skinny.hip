@@ -3,7 +3,7 @@
 //
 // With a few hundred rows a 64- or 128-row tile leaves most of the chip idle while each workgroup walks its whole reduction
 // alone, slice after slice: what bounds such a launch is that serial chain (a 3x3 over 512 channels on one 7 x 7 image:
-// 13 x 4 tiles, 72 slices each, 29 us).  Here a workgroup takes a small output tile (32*TM rows x 32*TN columns) and its
+// 13 x 4 tiles, 72 slices each, 29 us).  Here a workgroup takes a small output tile (16*TM rows x 16*TN columns) and its
 // NW waves SPLIT THE REDUCTION: wave w multiplies slices w, w+NW, ... (a slice: 128 bytes of every row of both operands) with
 // the loads of D slices in flight in registers and no barrier in the loop; the NW partial tiles meet in LDS once, are added
 // in wave order (fixed order: reproducible), and go through affine / residual / activation / rounding.
