@@ -141,6 +141,16 @@ __device__ __forceinline__ void wave_lower_bound2(const int32_t* v, int n, int k
 // error is below (n + 1) / d * 2^-23.
 __host__ __device__ __forceinline__ int fdiv(int n, float inv) { return (int)(((float)n + 0.5f) * inv); }
 
+// n / d for 0 <= n < 2^31 as a multiplication and a shift, exact: mul = ceil(2^(31+l) / d) with 2^l >= d exceeds 2^(31+l) / d by
+// less than 1, which over n < 2^31 adds less than 1 / d to the quotient.
+struct FastDiv { uint32_t mul, shift; };
+inline FastDiv make_fast_div(int d) {
+  uint32_t l = 0;
+  while ((1ull << l) < (unsigned long long)d) ++l;
+  return {(uint32_t)(((1ull << (31 + l)) + d - 1) / d), l};
+}
+__device__ __forceinline__ int fast_div(int n, FastDiv f) { return (int)(__umulhi((unsigned)n << 1, f.mul) >> f.shift); }
+
 // Entry of an index list that row `rho` of a launch over `rows` >= 1 rows (entries * S * S) belongs to.  Rows past the last one
 // repeat its entry: a caller's list may end, and its memory with it, at the last of its *count entries.
 __host__ __device__ __forceinline__ int list_entry(int rho, int rows, float inv_ss) {
@@ -216,7 +226,8 @@ struct InactiveCopy {
 constexpr int kCopyPatches = 1024;  // most patches one workgroup takes at a time
 InactiveCopy inactive_copy(const void* x, void* out, const laud_fmap& fx, int S, const int32_t* idx, const int32_t* count);
 
-// Share `part` of `nparts` of the copy; flags: kCopyPatches bytes of LDS.
+// Share `part` of `nparts` of the copy, counted in pixel rows of patches (a patch may be a whole map); flags: kCopyPatches bytes
+// of LDS.
 template <int NT>
 __device__ __forceinline__ void copy_inactive_part(const InactiveCopy& c, int part, int nparts, unsigned char* flags) {
   // (a vector type of the compiler's own: an array of the uint4 struct went to scratch memory, 80 bytes a lane that every
@@ -226,8 +237,10 @@ __device__ __forceinline__ void copy_inactive_part(const InactiveCopy& c, int pa
   chunk* const out = reinterpret_cast<chunk*>(c.out);
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int cnt = *c.count;
-  const int per = (c.npatch + nparts - 1) / nparts;
-  const int p0 = part * per, p1 = min(p0 + per, c.npatch);
+  const int rows = c.npatch * c.S, per = (rows + nparts - 1) / nparts;
+  const int r0 = part * per, r1 = min(r0 + per, rows);  // (parts behind the last row: nothing)
+  if (r0 >= r1) return;
+  const int p0 = r0 / c.S, p1 = (r1 + c.S - 1) / c.S;
   const int rowc = c.S * c.cpp;  // chunks in one pixel row of a patch
   for (int q0 = p0; q0 < p1; q0 += kCopyPatches) {
     const int n = min(kCopyPatches, p1 - q0);
@@ -239,11 +252,11 @@ __device__ __forceinline__ void copy_inactive_part(const InactiveCopy& c, int pa
       if (q < n) flags[q] = 1;
     }
     __syncthreads();
-    for (int r = wave; r < n * c.S; r += NT / kWave) {  // one wave per pixel row of a patch
-      const int k = r / c.S, q = q0 + k;
-      if (flags[k]) continue;
+    for (int r = max(r0, q0 * c.S) + wave; r < min(r1, (q0 + n) * c.S); r += NT / kWave) {  // one wave per pixel row of a patch
+      const int q = r / c.S;
+      if (flags[q - q0]) continue;
       const int s = q / (c.Hp * c.Wp), g = q - s * (c.Hp * c.Wp), py = g / c.Wp, px = g - py * c.Wp;
-      const size_t off = (((size_t)s * c.H + py * c.S + (r - k * c.S)) * c.W + px * c.S) * c.cpp;
+      const size_t off = (((size_t)s * c.H + py * c.S + (r - q * c.S)) * c.W + px * c.S) * c.cpp;
       int i = lane;
       for (; i + 3 * kWave < rowc; i += 4 * kWave) {
         chunk v[4];
@@ -273,7 +286,7 @@ struct TailArgs {
   int stride, Ho, Wo;    // spatial stride of the 3x3 and the output grid (stride 1: Ho = H, Wo = W)
   int cout;
   int relu;
-  int pb;                // tile height in blocks of 32 pixels (1..3); 0 = chosen on the device from the count
+  int pb;                // tile height in blocks of 32 pixels (1..4); 0 = chosen on the device from the count
   // channel skipping (Fig. 2(c)) on whole samples (S = H: a "patch" is a sample, `list` the samples in processing
   // order): sbits[i] = kept channel groups (bit g) of the i-th sample of the list, cs_group = channels per group (a
   // multiple of 64).  Input slices of groups no row of a tile keeps are skipped in the 3x3, and h2 is zeroed in the
@@ -282,6 +295,7 @@ struct TailArgs {
   int cs_group;
   InactiveCopy cp;       // nblocks 0: in place
   int wg_target;         // workgroups that fill the device once (its compute units; set by launch_tail)
+  FastDiv d_s, d_ss, d_wp, d_pps;  // set by launch_tail
 };
 
 bool tail_supported(int dtype, int c_mid, int c_out);

@@ -51,6 +51,16 @@ bool skinny_wanted(int mode, int dtype, const GemmArgs& a, long long cap_rows);
 int launch_skinny(int mode, int dtype, const GemmArgs& a, long long cap_rows, hipStream_t stream);
 int skinny_init_device();
 
+// Many rows (laud_pipe.h); nsamples: samples of channel skipping, groups of CONV1's pixel lists.
+int launch_pipe_a(int mode, int dtype, const GemmArgs& a, long long cap_rows, int nsamples, hipStream_t stream);
+int launch_pipe_b(int mode, int dtype, const GemmArgs& a, long long cap_rows, int nsamples, hipStream_t stream);
+int launch_pipe_c(int mode, int dtype, const GemmArgs& a, long long cap_rows, int nsamples, hipStream_t stream);
+inline int launch_pipe(int mode, int dtype, const GemmArgs& a, long long cap_rows, int nsamples, hipStream_t stream) {
+  if (mode == M_CONV1 || mode == M_DENSE1 || mode == M_SD1) return launch_pipe_a(mode, dtype, a, cap_rows, nsamples, stream);
+  if (mode == M_CONV2 || mode == M_SD2 || mode == M_G2) return launch_pipe_b(mode, dtype, a, cap_rows, nsamples, stream);
+  return launch_pipe_c(mode, dtype, a, cap_rows, nsamples, stream);
+}
+
 // ---- one 16-byte fragment pair -> MFMA ------------------------------------------------------
 template <typename ET>
 __device__ __forceinline__ void mma16(f32x16& acc, const uint4& a, const uint4& b) {

@@ -1,9 +1,8 @@
-// The three convolutions of the dynamic bottleneck as gathered implicit GEMMs on gfx950 MFMA.
+// The entry points of the blocks, and the convolutions of channel skipping whose groups are not whole 16-byte chunks.
 //
-// One kernel template, k_gemm<MODE, ET, BM, BN, WGN>, computes a BM x BN output tile with 2 x WGN
-// waves of 32x32 MFMA tiles; A (activations) and B (weights, [N][K] K-contiguous) are staged
-// through LDS in 128-byte K slices.  What differs per MODE is only where a row of A
-// comes from and where a row of the result goes:
+// The convolutions are gathered implicit GEMMs: laud_skinny.hip for few rows, laud_pipe.h for many, laud_head.hip, laud_tail.hip
+// and laud_narrow.hip for the shapes with kernels of their own.  What differs per mode is only where a row of A comes from
+// and where a row of the result goes:
 //
 //   CONV1  rows = pixels of the dilated active set (list of pixel ids): the gather is fused
 //          into the first 1x1 (Sec. 3.4 "Fusing gather and dynamic convolution"); result
@@ -31,6 +30,9 @@
 //          output channels / reduction channels gathered through the sample's kept-group list,
 //          i.e. the weight gather is fused into the conv (Sec. 3.4).
 //
+// k_gemm<MODE, ET, BM, BN, WGN> of this file: CS1..3 for group widths that do not fill 16-byte chunks, where weights are gathered
+// element by element through registers; a BM x BN tile with 2 x WGN waves of 32x32 MFMA tiles, both operands staged through LDS
+// in 128-byte K slices.
 // Accumulation is float32 (bf16: v_mfma_f32_32x32x16_bf16, fp32: v_mfma_f32_32x32x2_f32).
 #include "laud_common.h"
 #include "laud_gemm.h"
@@ -40,12 +42,6 @@
 #include <atomic>
 
 namespace laud {
-
-// 256 bytes of zeros in device memory: the source of the zero chunks of the pointer-based weight gather
-// of channel skipping (every other load gets its zeros from the buffer descriptor's range check).  Not
-// declared const on purpose: the compiler must treat a load from it like any other load (it would
-// otherwise fold the zeros in and turn the pointer select back into a branch around the load).
-__device__ uint4 g_zero_page[16];
 
 constexpr int kMaxGroups = 1024;  // channel-skip decisions per sample the kernels can hold in LDS
 
@@ -97,76 +93,29 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
   constexpr int AR = BM / RPP, BR = BN / RPP;
   constexpr int TM = BM / 64, TN = BN / (32 * WGN);
   static_assert(AR >= 1 && BR >= 1 && TN >= 1, "tile too small for this many waves");
-  constexpr bool TAPS = (MODE == M_CONV2 || MODE == M_CS2 || MODE == M_U2 || MODE == M_SD2 || MODE == M_G2);
-  constexpr bool CS = (MODE >= M_CS1 && MODE <= M_CS3);
+  constexpr bool TAPS = MODE == M_CS2;
 
   constexpr int A_BYTES = BM * LSTR, B_BYTES = BN * LSTR, STAGE_BYTES = A_BYTES + B_BYTES;
   constexpr int CSTR = BN * 4 + 32;      // epilogue staging row stride in bytes
-  // dynamic LDS = max(two pipeline stages, epilogue staging) [+ K floats of masker weights in DENSE1];
-  // the launcher sizes it the same way
-  constexpr int MAIN_BYTES = (2 * STAGE_BYTES > BM * CSTR) ? 2 * STAGE_BYTES : BM * CSTR;
+  // dynamic LDS = max(two pipeline stages, epilogue staging); the launcher sizes it the same way
   extern __shared__ __align__(16) unsigned char smem[];  // two pipeline stages, reused by the epilogue
   __shared__ int s_row[BM];
-  __shared__ unsigned char s_inact[MODE == M_SD1 ? BM : 1];  // SD1 with a patch list: row lies in an inactive patch
-  __shared__ int s_kgrp[CS ? kMaxGroups : 1];
+  __shared__ int s_kgrp[kMaxGroups];
   __shared__ int s_nkept;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if constexpr (MODE == M_CONV1 || MODE == M_DENSE1) {
-    if (a.pk_out != nullptr && (int)blockIdx.x >= a.pk_first_block) {
-      const int nextra = (int)gridDim.x - a.pk_first_block;
-      for (int idx = ((int)blockIdx.x - a.pk_first_block) * NT + tid; idx < a.pk_chunks; idx += nextra * NT)
-        tail_pack_chunk(idx, (const uint4*)a.pk_w2, (const uint4*)a.pk_w3, (uint4*)a.pk_out);
-      return;
-    }
-  }
-  if constexpr (MODE == M_CONV3) {
-    if (a.cp.nblocks && (int)blockIdx.x >= a.cp.first) {
-      copy_inactive_part<NT>(a.cp, blockIdx.x - a.cp.first, a.cp.nblocks, smem);
-      return;
-    }
-  }
   const int wm = wave / WGN, wn = wave % WGN;
-  const int HW = a.H * a.W, SS = a.S * a.S;
-  // Dynamic blocks with a spatial stride (a.stride > 1) keep their mask on the output grid Ho x Wo;
-  // everywhere else the output grid is the input grid.
-  const int oH = a.stride > 1 ? a.Ho : a.H, oW = a.stride > 1 ? a.Wo : a.W;
-  const int Hp = oH / a.S, Wp = oW / a.S;
+  const int HW = a.H * a.W;
   const ET* __restrict__ Ap = (const ET*)a.A;
   const ET* __restrict__ Wp_ = (const ET*)a.Wt;
   // ---- which tile ---------------------------------------------------------------------------
-  int rt, ct, sample = 0, M;
-  const int32_t* listp = a.list;
-  if constexpr (!CS) {
-    // XCD-aware decode: consecutive workgroup ids go round-robin over the 8 XCDs, so the column
-    // tiles of one row tile (same A rows) are given to the same XCD, one after the other.
-    const int L = blockIdx.x, xcd = L & 7, s = L >> 3;
-    rt = (s / a.col_tiles) * 8 + xcd;
-    ct = s % a.col_tiles;
-    if (rt >= a.row_tiles) return;
-    if constexpr (MODE == M_CONV1) {
-      // the dilated pixel lists are per group of samples: tile -> (group, tile within the group)
-      const int g = rt / a.tiles_per_group;
-      rt -= g * a.tiles_per_group;
-      listp += (size_t)g * a.group_rows;
-      M = a.count[g];
-    } else if constexpr (MODE == M_DENSE1 || (MODE >= M_SD1 && MODE <= M_SD3)) {
-      M = a.m_rows;
-    } else {
-      M = *a.count * (MODE == M_U1 ? (a.S + 2) * (a.S + 2) : SS);
-    }
-  } else {
-    rt = blockIdx.x % a.row_tiles;
-    ct = blockIdx.x / a.row_tiles;
-    sample = blockIdx.y;
-    M = HW;
-  }
+  const int rt = blockIdx.x % a.row_tiles, ct = blockIdx.x / a.row_tiles, sample = blockIdx.y, M = HW;
   const int row0 = rt * BM, col0 = ct * BN;
   if (row0 >= M) return;
 
   // ---- channel skipping: kept-group list of this sample (ballot + prefix, one wave) ----------
   int ncols = a.Ncols, keff = a.K;
-  if constexpr (CS) {
+  {
     if (wave == 0) {
       int base = 0;
       for (int g0 = 0; g0 < a.D; g0 += kWave) {
@@ -184,10 +133,6 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
     if (MODE != M_CS1) keff = kw;
     if (col0 >= ncols) return;
   }
-  // group convolution: the reduction runs over the input channels col0 .. col0+BN-1 (the groups of this
-  // tile's output channels; the launcher makes BN a multiple of the group width)
-  if constexpr (MODE == M_G2) keff = min(BN, a.K - col0);
-
   // ---- row descriptors ------------------------------------------------------------------------
   // Each thread keeps, for the AR activation rows and BR weight rows it loads, one 32-bit byte offset
   // that already includes its 16-byte chunk, plus (tap modes) a 9-bit mask of the taps that fall
@@ -195,26 +140,15 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
   // tail) is never masked afterwards: its load is pointed outside the operand's descriptor (below).
   const int cc = tid & 7;    // 16-byte chunk within the 128-byte K slice
   const int lr = tid >> 3;   // first row this thread loads
-  // The kept-channel weight gather of channel skipping (CS2 / CS3) still reads through pointers; its
-  // zero chunks come from a page of zeros.  Hide where that page's address comes from (knowing that it
-  // is a dereferenceable global, the compiler would split `load(ok ? row : zeros)` into two loads under
-  // a branch) but keep the fact that it is global memory, so that the loads stay global_load (vmcnt
-  // only) and not flat_load.
-  unsigned long long zaddr = reinterpret_cast<unsigned long long>(&g_zero_page[0]);
-#if defined(__HIP_DEVICE_COMPILE__)  // the constraint names a GPU register class: device pass only
-  asm volatile("" : "+s"(zaddr));
-#endif
-  const gptr16 zpage = (gptr16)zaddr;
   // Activation (and, outside the kept-channel gather of channel skipping, weight) chunks are fetched with
   // buffer loads: a resource descriptor over the operand, a per-thread 32-bit byte offset that is fixed
   // for the whole K loop, and a wave-uniform scalar offset per K slice.  A chunk that must read as zero
   // gets the offset 0x80000000, which lies outside the descriptor's 2 GiB range: the hardware returns
   // zeros for it.  A load then costs one select instead of 64-bit pointer arithmetic.
   constexpr unsigned kOob = 0x80000000u;
-  constexpr int ROWW_IS_TILE = (MODE == M_U2);
   // taps reach one row and one pixel back: the descriptor starts that far before the operand so that
   // the scalar tap offsets are never negative
-  const long long ashift = TAPS ? (long long)((ROWW_IS_TILE ? a.S + 2 : a.W) + 1) * a.lda * (long long)sizeof(ET) : 0;
+  const long long ashift = TAPS ? (long long)(a.W + 1) * a.lda * (long long)sizeof(ET) : 0;
   const __amdgpu_buffer_rsrc_t arsrc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<char*>(reinterpret_cast<const char*>(Ap)) - ashift, 0, (int)kOob, 0x00020000);
   const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -228,11 +162,9 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
     amask[i] = 0;
     if (rho < M) {
       int y, x;
-      const size_t pixrow = source_row<MODE>(a, rho, listp, sample, Hp, Wp, y, x);
-      voffA[i] = (unsigned)((pixrow * a.lda + cc * EPC + (MODE == M_G2 ? col0 : 0)) * sizeof(ET));
-      if constexpr (MODE == M_U2) {
-        amask[i] = 0x1ffu;  // every tap lies inside the gathered tile
-      } else if constexpr (TAPS) {
+      const size_t pixrow = source_row<MODE>(a, rho, nullptr, sample, 0, 0, y, x);
+      voffA[i] = (unsigned)((pixrow * a.lda + cc * EPC) * sizeof(ET));
+      if constexpr (TAPS) {
         unsigned mk = 0;
 #pragma unroll
         for (int t = 0; t < 9; ++t) {
@@ -247,27 +179,12 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
   }
   if (tid < BM) {
     const int rho = row0 + tid;
-    const int o = rho < M ? output_row<MODE>(a, rho, listp, sample, Hp, Wp) : -1;
-    s_row[tid] = o;
-    if constexpr (MODE == M_SD1) {
-      // shortcut of a dynamic first block: the activation is applied here only where the branch will
-      // not be added (inactive patches); active rows get it in the last conv's epilogue
-      bool inact = true;
-      if (a.list != nullptr && rho < M) {
-        const int n = rho / (a.Ho * a.Wo), r2 = rho - n * (a.Ho * a.Wo);
-        const int q = (n * Hp + (r2 / a.Wo) / a.S) * Wp + (r2 % a.Wo) / a.S;
-        const int cnt = *a.count;
-        const int pos = lower_bound_dev(a.list, cnt, q);
-        inact = !(pos < cnt && a.list[pos] == q);
-      }
-      s_inact[tid] = inact ? 1 : 0;
-    }
+    s_row[tid] = rho < M ? output_row<MODE>(a, rho, nullptr, sample, 0, 0) : -1;
   }
 
   // ---- weight-row descriptors -----------------------------------------------------------------
   const ET* wrow[BR];
   unsigned voffW[BR];
-  int wrel[BR];  // G2: first channel of this thread's chunk of the window's first slice, relative to the row's group
   bool cvalid[BR];
 #pragma unroll
   for (int i = 0; i < BR; ++i) {
@@ -278,28 +195,9 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
     wrow[i] = Wp_ + (size_t)wr * a.ldw;
     if constexpr (!(MODE == M_CS2 || MODE == M_CS3)) wrow[i] += cc * EPC;
     voffW[i] = (unsigned)(((size_t)wr * a.ldw + cc * EPC) * sizeof(ET));
-    wrel[i] = 0;
-    if constexpr (MODE == M_G2) {
-      voffW[i] = (unsigned)((size_t)wr * a.ldw * sizeof(ET));
-      wrel[i] = col0 + cc * EPC - (wr / a.gw) * a.gw;
-    }
   }
-  // DENSE1: the first column tile also accumulates the masker projection of its rows, on the vector
-  // ALU, from the A chunks on their way from registers to LDS (each thread: AR rows x one chunk).
-  const bool do_proj = (MODE == M_DENSE1) && ct == 0 && a.wmask != nullptr;
-  float* const s_wm = reinterpret_cast<float*>(smem + MAIN_BYTES);  // masker weights (DENSE1 only)
-  float pacc[AR];
-#pragma unroll
-  for (int i = 0; i < AR; ++i) pacc[i] = 0.f;
-  if constexpr (MODE == M_DENSE1) {
-    if (do_proj)
-      for (int k = tid; k < a.K; k += NT) s_wm[k] = a.wmask[k];
-    __syncthreads();  // the first store_slice below already reads s_wm
-  }
-
   const int kchunks = (keff + BKE - 1) / BKE;
   const int KT = (TAPS ? 9 : 1) * kchunks;
-  const bool kvec = (a.G % EPC) == 0;  // kept-channel gather can use 16-byte loads
 
   // Issues the loads of this thread's 16-byte chunks of the next K slice (A: AR rows, B: BR weight
   // rows).  All loads are unconditional and branch-free, so the compiler can count the loads in
@@ -314,14 +212,11 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
   // last tap the bit has left the masks' range and `live` is off, so null slices select nothing.
   constexpr int NTAPS = TAPS ? 9 : 1;
   constexpr int SLICE_B = BKE * (int)sizeof(ET);  // 128
-  const int rowW = ROWW_IS_TILE ? a.S + 2 : a.W;
+  const int rowW = a.W;
   const int pix_b = a.lda * (int)sizeof(ET);
   const int back_b = (kchunks - 1) * SLICE_B;     // from a tap's last slice back to its first
   const int a_pixjump = pix_b - back_b, a_rowjump = (rowW - 2) * pix_b - back_b;
-  // weights: next slice of the same tap / first slice of the next tap (G2: a tap is gw channels wide and
-  // the slice position inside it goes into the per-thread offset)
-  const int w_step = MODE == M_G2 ? 0 : SLICE_B;
-  const int w_tapjump = MODE == M_G2 ? a.gw * (int)sizeof(ET) : gK * (int)sizeof(ET) - back_b;
+  const int w_step = SLICE_B, w_tapjump = gK * (int)sizeof(ET) - back_b;  // (CS1: the only mode that reads weights by offset)
   // only a tap's last K chunk can be partial: whether this thread's chunk of it lies inside K
   const bool lastok = (kchunks - 1) * BKE + cc * EPC < keff;
   int ld_tap = 0, ld_kc = 0, ld_kx = -1, s_a = 0, s_w = 0;
@@ -358,35 +253,24 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
     int eoff[EPC];
     unsigned eok = 0;
     if constexpr (MODE == M_CS2 || MODE == M_CS3) {
-      if (!kvec) {
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-          const bool ok = kv && ke + e < keff;
-          const int kk = ok ? ke + e : 0;
-          const int g = gshift >= 0 ? kk >> gshift : kk / gG;
-          eoff[e] = (keff > 0 ? s_kgrp[g] : 0) * gG + (kk - g * gG);
-          eok |= ok ? (1u << e) : 0u;
-        }
+      for (int e = 0; e < EPC; ++e) {
+        const bool ok = kv && ke + e < keff;
+        const int kk = ok ? ke + e : 0;
+        const int g = gshift >= 0 ? kk >> gshift : kk / gG;
+        eoff[e] = (keff > 0 ? s_kgrp[g] : 0) * gG + (kk - g * gG);
+        eok |= ok ? (1u << e) : 0u;
       }
     }
 #pragma unroll
     for (int i = 0; i < BR; ++i) {
       if constexpr (MODE == M_CS2 || MODE == M_CS3) {
         const ET* wtap = wrow[i] + (long long)tap * gK;
-        if (kvec) {
-          rb[i] = *(kv ? (gptr16)(wtap + s_kgrp[ke / gG] * gG + (ke % gG)) : zpage);
-        } else {
-          // the compact K range ends on a group boundary, so a unit is inside it or outside it as a whole
-          const uint4 g = gunit == 4 ? gather_elems<ET, (EPC >= 4 ? 4 : 1)>(wtap, eoff, eok)
-                          : gunit == 2 ? gather_elems<ET, 2>(wtap, eoff, eok)
-                                       : gather_elems<ET, 1>(wtap, eoff, eok);
-          rb[i] = u32x4{g.x, g.y, g.z, g.w};
-        }
-      } else if constexpr (MODE == M_G2) {
-        const int rel = wrel[i] + kcb;  // chunk's first channel inside the row's group, if it is in it
-        const bool ing = kv && (unsigned)rel < (unsigned)a.gw;
-        rb[i] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, ing ? voffW[i] + (unsigned)rel * (unsigned)sizeof(ET) : kOob,
-                                                      wsoff, 0);
+        // the compact K range ends on a group boundary, so a unit is inside it or outside it as a whole
+        const uint4 g = gunit == 4 ? gather_elems<ET, (EPC >= 4 ? 4 : 1)>(wtap, eoff, eok)
+                        : gunit == 2 ? gather_elems<ET, 2>(wtap, eoff, eok)
+                                     : gather_elems<ET, 1>(wtap, eoff, eok);
+        rb[i] = u32x4{g.x, g.y, g.z, g.w};
       } else {
         rb[i] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, kv ? voffW[i] : kOob, wsoff, 0);
       }
@@ -401,20 +285,12 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
       u32x4 v = ra[i];
       if constexpr (MODE == M_CS2 || MODE == M_CS3) {
         // compact rows are valid up to keff only; what lies beyond in the scratch buffer is undefined
-        if (!kvec && ke + EPC > keff) {
+        if (ke + EPC > keff) {
           const uint4 t = mask_tail<ET>(make_uint4(v.x, v.y, v.z, v.w), keff - ke);
           v = u32x4{t.x, t.y, t.z, t.w};
         }
       }
       *reinterpret_cast<u32x4*>(sA + (lr + RPP * i) * LSTR + cc * 16) = v;
-      if constexpr (MODE == M_DENSE1) {
-        if (do_proj && ke < keff) {
-          ET xe[EPC];
-          __builtin_memcpy(xe, &v, 16);
-#pragma unroll
-          for (int e = 0; e < EPC; ++e) pacc[i] += elem<ET>::load(&xe[e]) * s_wm[ke + e];
-        }
-      }
     }
 #pragma unroll
     for (int i = 0; i < BR; ++i) *reinterpret_cast<u32x4*>(sB + (lr + RPP * i) * LSTR + cc * 16) = rb[i];
@@ -449,7 +325,7 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
 
   constexpr int CPR = BN / EPC;                 // 16-byte output chunks per tile row
   constexpr int EPI = (BM * CPR + NT - 1) / NT;  // epilogue chunks per thread
-  constexpr bool RES = (MODE == M_CONV3 || MODE == M_CS3 || MODE == M_SD3);
+  constexpr bool RES = MODE == M_CS3;
   // Software pipeline: PF register sets hold the slices in flight from L2 / HBM, two LDS stages.
   // Step s multiplies slice s out of stage s%2 while slice s+1 moves from its registers to the other
   // stage and slices s+2 .. s+PF are in flight: one barrier per slice, PF-1 slices of load latency
@@ -474,20 +350,6 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
       __syncthreads();
     }
   }
-  if constexpr (MODE == M_DENSE1) {
-    if (do_proj) {
-#pragma unroll
-      for (int i = 0; i < AR; ++i) {
-        float v = pacc[i];  // partial over this thread's chunk column; the row's 8 chunk columns are 8 adjacent lanes
-        v += __shfl_xor(v, 1, kWave);
-        v += __shfl_xor(v, 2, kWave);
-        v += __shfl_xor(v, 4, kWave);
-        const int rho = row0 + lr + RPP * i;
-        if (cc == 0 && rho < M) a.proj[rho] = v;
-      }
-    }
-  }
-
   // ---- epilogue ---------------------------------------------------------------------------------
   // Affine (+ReLU) in the accumulator layout (32x32 tile: lane l holds column l%32, rows
   // 8*(e/4) + 4*(l/32) + e%4), then through LDS so that global traffic is 16 bytes per lane:
@@ -511,11 +373,7 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
         for (int e = 0; e < 16; ++e) {
           const int rl = wm * (BM / 2) + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
           float v = acc[i][j][e] * sc + sh;
-          if constexpr (MODE == M_SD1) {
-            if (a.relu && s_inact[rl]) v = fmaxf(v, 0.f);
-          } else if constexpr (!(MODE == M_CONV3 || MODE == M_CS3 || MODE == M_U3 || MODE == M_SD3)) {
-            v = fmaxf(v, 0.f);
-          }
+          if constexpr (!RES) v = fmaxf(v, 0.f);
           stg[rl * (CSTR / 4) + cl] = v;
         }
       }
@@ -530,12 +388,8 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
       const int id = tid + q * NT;
       if (id >= BM * CPR) continue;
       const int rl = id / CPR, chk = id - rl * CPR;
-      int orow = s_row[rl];
+      const int orow = s_row[rl];
       const int col = col0 + chk * EPC;
-      bool zero_row = false;
-      if constexpr (MODE == M_U1) {
-        if (orow <= -2) { orow = -2 - orow; zero_row = true; }
-      }
       if (orow < 0 || col >= ncols) continue;
       const float* sp = reinterpret_cast<const float*>(smem + rl * CSTR) + chk * EPC;
       float v[EPC];
@@ -543,10 +397,6 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
       for (int u = 0; u < EPC / 4; ++u) {
         const float4 t4 = reinterpret_cast<const float4*>(sp)[u];
         v[4 * u] = t4.x; v[4 * u + 1] = t4.y; v[4 * u + 2] = t4.z; v[4 * u + 3] = t4.w;
-      }
-      if (zero_row) {
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) v[e] = 0.f;
       }
       const size_t off = (size_t)orow * a.ldo + col;
       if (col + EPC <= ncols) {
@@ -562,14 +412,7 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
             if (a.relu) v[e] = fmaxf(v[e], 0.f);
           }
         }
-        if constexpr (MODE == M_U3) {
-          // the unfused schedule's branch output stays float32 so that the stand-alone scatter adds
-          // the residual before the only rounding, like the fused epilogue does
-          float* fo = reinterpret_cast<float*>(a.Out) + off;
-#pragma unroll
-          for (int u = 0; u < EPC / 4; ++u)
-            reinterpret_cast<float4*>(fo)[u] = make_float4(v[4 * u], v[4 * u + 1], v[4 * u + 2], v[4 * u + 3]);
-        } else {
+        {
           ET ov[EPC];
 #pragma unroll
           for (int e = 0; e < EPC; ++e) elem<ET>::store(&ov[e], v[e]);
@@ -687,17 +530,8 @@ InactiveCopy inactive_copy(const void* x, void* out, const laud_fmap& fx, int S,
   c.cpp = (int)((size_t)fx.C * elem_bytes(fx.dtype) / 16);
   // about 64 KB of map per workgroup, at most four workgroups per compute unit
   const long long bytes = (long long)fx.N * fx.H * fx.W * c.cpp * 16;
-  c.nblocks = (int)std::min<long long>(std::min<long long>(c.npatch, (bytes + 65535) / 65536), 1024);
+  c.nblocks = (int)std::min<long long>(std::min<long long>((long long)c.npatch * S, (bytes + 65535) / 65536), 1024);
   return c;
-}
-
-struct Tile { int bm, bn, waves; };
-
-// Tile choice: a function of the shapes alone.
-static Tile pick_tile(int ncols, long long total_rows) {
-  if (ncols < 128) return {64, 64, 4};
-  // eight waves hide each other's LDS and load stalls; the large tile needs enough rows to fill the chip
-  return total_rows >= 8192 ? Tile{128, 128, 8} : Tile{64, 128, 8};
 }
 
 // More than 64 KB of dynamic LDS has to be requested once per kernel and device.  The request is idempotent, so
@@ -714,7 +548,7 @@ static int gemm_request_lds() {
   constexpr int kStaging = BM * (BN * 4 + 32);  // fp32 tile the epilogue transposes through
   constexpr int kLds = kStages > kStaging ? kStages : kStaging;
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm<MODE, ET, BM, BN, WGN>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, kLds + (MODE == M_DENSE1 ? 4096 * 4 : 0)) != hipSuccess)
+                          hipFuncAttributeMaxDynamicSharedMemorySize, kLds) != hipSuccess)
     return LAUD_ERR_HIP;
   done.fetch_or(bit, std::memory_order_release);
   return LAUD_OK;
@@ -722,45 +556,24 @@ static int gemm_request_lds() {
 
 template <int MODE, typename ET, int BM, int BN, int WGN>
 static int launch_gemm_t(GemmArgs a, long long cap_rows, int nsamples, hipStream_t st) {
-  constexpr bool CS = (MODE >= M_CS1 && MODE <= M_CS3);
   a.row_tiles = (int)((cap_rows + BM - 1) / BM);
-  if constexpr (MODE == M_CONV1) {  // cap_rows = rows per group of samples, nsamples = number of groups
-    a.tiles_per_group = a.row_tiles;
-    a.row_tiles *= nsamples;
-  }
   a.col_tiles = (a.Ncols + BN - 1) / BN;
-  dim3 grid;
-  if (!CS) grid = dim3((unsigned)(((a.row_tiles + 7) / 8) * 8 * a.col_tiles));
-  else grid = dim3((unsigned)(a.row_tiles * a.col_tiles), (unsigned)nsamples);
-  if constexpr (MODE == M_CONV1 || MODE == M_DENSE1) {
-    if (a.pk_out != nullptr) {  // spare workgroups for the weight re-ordering: one chunk per thread
-      a.pk_first_block = (int)grid.x;
-      grid.x += (unsigned)((a.pk_chunks + 128 * WGN - 1) / (128 * WGN));
-    }
-  } else {
-    a.pk_out = nullptr;
-  }
-  if constexpr (MODE == M_CONV3) {
-    a.cp.first = (int)grid.x;
-    grid.x += (unsigned)a.cp.nblocks;
-  }
   constexpr int kStages = 2 * (BM + BN) * 144;  // two pipeline stages of 144-byte rows
   constexpr int kStaging = BM * (BN * 4 + 32);  // fp32 tile the epilogue transposes through
   constexpr int kLds = kStages > kStaging ? kStages : kStaging;
   if (gemm_request_lds<MODE, ET, BM, BN, WGN>() != LAUD_OK) return LAUD_ERR_HIP;
-  const int lds = kLds + ((MODE == M_DENSE1 && a.wmask) ? a.K * 4 : 0);  // + masker weights
-  hipLaunchKernelGGL((k_gemm<MODE, ET, BM, BN, WGN>), grid, dim3(128 * WGN), lds, st, a);
+  hipLaunchKernelGGL((k_gemm<MODE, ET, BM, BN, WGN>), dim3((unsigned)(a.row_tiles * a.col_tiles), (unsigned)nsamples),
+                     dim3(128 * WGN), kLds, st, a);
   return check_launch();
 }
 
+// Tile choice: a function of the shapes alone.
 template <int MODE, typename ET>
 static int launch_gemm_e(const GemmArgs& a, long long cap_rows, int nsamples, hipStream_t st) {
-  const Tile t = pick_tile(a.Ncols, cap_rows * (MODE == M_CONV1 || (MODE >= M_CS1 && MODE <= M_CS3) ? nsamples : 1));
-  if (t.waves == 8) {
-    if (t.bm == 128) return launch_gemm_t<MODE, ET, 128, 128, 4>(a, cap_rows, nsamples, st);
-    return launch_gemm_t<MODE, ET, 64, 128, 4>(a, cap_rows, nsamples, st);
-  }
-  return launch_gemm_t<MODE, ET, 64, 64, 2>(a, cap_rows, nsamples, st);
+  if (a.Ncols < 128) return launch_gemm_t<MODE, ET, 64, 64, 2>(a, cap_rows, nsamples, st);
+  // eight waves hide each other's LDS and load stalls; the large tile needs enough rows to fill the chip
+  if (cap_rows * nsamples >= 8192) return launch_gemm_t<MODE, ET, 128, 128, 4>(a, cap_rows, nsamples, st);
+  return launch_gemm_t<MODE, ET, 64, 128, 4>(a, cap_rows, nsamples, st);
 }
 
 // The LDS requests of every tile a mode can be launched with, for both element types.
@@ -770,23 +583,18 @@ static int gemm_request_lds_mode() {
   auto keep = [&rc](int r) { if (r != LAUD_OK) rc = r; };
   keep(gemm_request_lds<MODE, bf16_t, 64, 64, 2>());
   keep(gemm_request_lds<MODE, float, 64, 64, 2>());
-  if constexpr (MODE != M_G2) {
-    keep(gemm_request_lds<MODE, bf16_t, 64, 128, 4>());
-    keep(gemm_request_lds<MODE, float, 64, 128, 4>());
-    keep(gemm_request_lds<MODE, bf16_t, 128, 128, 4>());
-    keep(gemm_request_lds<MODE, float, 128, 128, 4>());
-  }
-  return rc;
-}
-template <int... MODES>
-static int gemm_request_lds_modes() {
-  int rc = LAUD_OK;
-  ((rc = (gemm_request_lds_mode<MODES>() != LAUD_OK ? LAUD_ERR_HIP : rc)), ...);
+  keep(gemm_request_lds<MODE, bf16_t, 64, 128, 4>());
+  keep(gemm_request_lds<MODE, float, 64, 128, 4>());
+  keep(gemm_request_lds<MODE, bf16_t, 128, 128, 4>());
+  keep(gemm_request_lds<MODE, float, 128, 128, 4>());
   return rc;
 }
 int gemm_init_device() {
-  return gemm_request_lds_modes<M_CONV1, M_CONV2, M_CONV3, M_CS1, M_CS2, M_CS3, M_DENSE1, M_U1, M_U2, M_U3, M_SD1, M_SD2,
-                                M_SD3, M_G2>();
+  for (int mode = M_CONV1; mode <= M_G2; ++mode)
+    for (int dtype : {LAUD_BF16, LAUD_F32})
+      if (launch_pipe(mode, dtype, GemmArgs{}, -1, 1, nullptr) != LAUD_OK) return LAUD_ERR_HIP;
+  if (gemm_request_lds_mode<M_CS1>() != LAUD_OK || gemm_request_lds_mode<M_CS2>() != LAUD_OK) return LAUD_ERR_HIP;
+  return gemm_request_lds_mode<M_CS3>();
 }
 
 template <int MODE>
@@ -798,8 +606,12 @@ static int launch_gemm(int dtype, const GemmArgs& a, long long cap_rows, int nsa
   if constexpr (MODE == M_CONV2 || MODE == M_CONV3 || MODE == M_DENSE1 || (MODE >= M_SD1 && MODE <= M_SD3)) {
     if (skinny_wanted(MODE, dtype, a, cap_rows)) return launch_skinny(MODE, dtype, a, cap_rows, st);
   }
-  return dtype == LAUD_BF16 ? launch_gemm_e<MODE, bf16_t>(a, cap_rows, nsamples, st)
-                            : launch_gemm_e<MODE, float>(a, cap_rows, nsamples, st);
+  if constexpr (MODE >= M_CS1 && MODE <= M_CS3) {
+    if (a.G % (16 / (int)elem_bytes(dtype)) != 0)  // groups that are not whole 16-byte chunks
+      return dtype == LAUD_BF16 ? launch_gemm_e<MODE, bf16_t>(a, cap_rows, nsamples, st)
+                                : launch_gemm_e<MODE, float>(a, cap_rows, nsamples, st);
+  }
+  return launch_pipe(MODE, dtype, a, cap_rows, nsamples, st);
 }
 
 // The kernels address an operand through a buffer descriptor with 32-bit byte offsets and keep the upper
@@ -994,8 +806,7 @@ static int launch_conv2(int dtype, GemmArgs a, const laud_group_se* e, long long
   a.ldw = 9 * e->group_width;
   StageScope scope(LAUD_STAGE_CONV2, st);
   if (skinny_wanted(M_G2, dtype, a, cap_rows)) return launch_skinny(M_G2, dtype, a, cap_rows, st);
-  return dtype == LAUD_BF16 ? launch_gemm_t<M_G2, bf16_t, 64, 64, 2>(a, cap_rows, 1, st)
-                            : launch_gemm_t<M_G2, float, 64, 64, 2>(a, cap_rows, 1, st);
+  return launch_pipe(M_G2, dtype, a, cap_rows, 1, st);
 }
 
 // Whether conv2 -> conv3 -> residual add run as the one kernel of laud_tail.hip (h2 stays in LDS), and whether

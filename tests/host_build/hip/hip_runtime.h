@@ -66,6 +66,7 @@ typedef unsigned Chunk __attribute__((ext_vector_type(4)));
 unsigned load_dword(const Rsrc& r, unsigned voff, unsigned soff);  // zero past the descriptor's end
 Chunk load_chunk(const Rsrc& r, unsigned voff, unsigned soff);
 void load_to_lds(const Rsrc& r, unsigned voff, unsigned soff, unsigned lds_base);
+void load_dword_to_lds(const Rsrc& r, unsigned voff, unsigned soff, unsigned lds_base);
 struct Pair {
   unsigned v[2];
   unsigned operator[](int i) const { return v[i]; }

@@ -157,6 +157,12 @@ void load_to_lds(const Rsrc& r, unsigned voff, unsigned soff, unsigned lds_base)
   const Chunk c = load_chunk(r, voff, soff);
   memcpy(lds + at, &c, 16);
 }
+void load_dword_to_lds(const Rsrc& r, unsigned voff, unsigned soff, unsigned lds_base) {
+  const size_t at = lds_base + 4 * (size_t)current->lane;
+  if (at + 4 > lds_size) fail("LDS-direct load past the launch's LDS at", (void*)at);
+  const unsigned v = load_dword(r, voff, soff);
+  memcpy(lds + at, &v, 4);
+}
 }  // namespace host
 
 extern "C" void host_init() {

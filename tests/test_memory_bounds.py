@@ -29,6 +29,7 @@ def host_source(name, s):
         s = s[:at] + s[s.index("\n}\n", at):]
     if name == "laud_tile_util.h":
         s = re.sub(r'asm volatile\("s_mov_b32 m0.*?;\n', "host::load_to_lds(rsrc, voff, soff, lds_base);\n", s, flags=re.S, count=1)
+        s = re.sub(r'asm volatile\("s_mov_b32 m0.*?;\n', "host::load_dword_to_lds(rsrc, voff, soff, lds_base);\n", s, flags=re.S, count=1)
         s = re.sub(r"const f32x2 v = \{lo, hi\};\s*return [^;]*;", "return (unsigned)f32_to_bf16(lo) | ((unsigned)f32_to_bf16(hi) << 16);", s)
     return re.sub(r"\basm(?: volatile)?\s*\((?:[^()]|\((?:[^()]|\([^()]*\))*\))*\);", ";", s)
 
