@@ -151,6 +151,22 @@ inline FastDiv make_fast_div(int d) {
 }
 __device__ __forceinline__ int fast_div(int n, FastDiv f) { return (int)(__umulhi((unsigned)n << 1, f.mul) >> f.shift); }
 
+// Whether the 3x3 window (at spatial stride 1 or 2) of any active output pixel covers input pixel (y, x); pm: mask of the patches
+// [rows][Wp] of the sample.  Output rows ceil((y-1)/stride) .. floor((y+1)/stride), clipped, lie in at most three rows of
+// patches: nine look-ups that do not wait for each other.
+__device__ __forceinline__ bool window_active(const unsigned char* pm, int y, int x, int stride, int Ho, int Wo, int Wp, FastDiv d_s) {
+  const int y0 = max(stride > 1 ? y >> 1 : y - 1, 0), y2 = min(stride > 1 ? (y + 1) >> 1 : y + 1, Ho - 1), y1 = min(y0 + 1, y2);
+  const int x0 = max(stride > 1 ? x >> 1 : x - 1, 0), x2 = min(stride > 1 ? (x + 1) >> 1 : x + 1, Wo - 1), x1 = min(x0 + 1, x2);
+  const int r[3] = {fast_div(y0, d_s) * Wp, fast_div(y1, d_s) * Wp, fast_div(y2, d_s) * Wp};
+  const int c[3] = {fast_div(x0, d_s), fast_div(x1, d_s), fast_div(x2, d_s)};
+  unsigned any = 0;
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) any |= pm[r[i] + c[j]];
+  return any != 0;
+}
+
 // Entry of an index list that row `rho` of a launch over `rows` >= 1 rows (entries * S * S) belongs to.  Rows past the last one
 // repeat its entry: a caller's list may end, and its memory with it, at the last of its *count entries.
 __host__ __device__ __forceinline__ int list_entry(int rho, int rows, float inv_ss) {
@@ -319,6 +335,11 @@ struct HeadArgs {
   const int32_t* list;   // [ngroups][group_rows] ascending pixel ids of the dilated active set
   const int32_t* counts; // [ngroups] device: valid entries per group
   int group_rows;        // capacity of one group's list
+  // ... or the active patches themselves: every workgroup works out its group's list, m_rows groups of gs samples (N in all), at
+  // most kHeadGroup pixels each; patches of S x S on the output grid Ho x Wo, spatial stride `stride`, input grid H x W
+  const int32_t* idx; const int32_t* count;
+  int N, gs, S, stride, Ho, Wo, H, W;
+  FastDiv d_hw, d_w, d_s;  // set by launch_head
   // rows = the pixels of listed samples (layer gate ahead of a spatially static first 1x1): slist [scap] ascending kept
   // sample ids, *scount of them valid (device), hw pixels per sample; m_rows = scap * hw is the capacity.  Null: all rows.
   const int32_t* slist;
@@ -331,6 +352,7 @@ struct HeadArgs {
   int pb;                // tile height in blocks of 32 pixels (2 or 4); 0 = chosen by launch_head (dense rows) or on the device (lists)
   int wg_target;         // workgroups that fill the device once (its compute units; set by launch_head)
 };
+constexpr int kHeadGroup = 4096;
 bool head_supported(int dtype, int c_in, int c_mid);
 int head_init_device();
 size_t head_packed_bytes(int c_in);

@@ -444,7 +444,7 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
 constexpr int kNeedThreads = 1024;
 __global__ __launch_bounds__(kNeedThreads) void k_need(const int32_t* __restrict__ idx,
                                                        const int32_t* __restrict__ count, int N, int H, int W, int S,
-                                                       int stride, int Ho, int Wo, int gs,
+                                                       int stride, int Ho, int Wo, int gs, FastDiv d_hw, FastDiv d_w, FastDiv d_s,
                                                        int32_t* __restrict__ need_counts,
                                                        int32_t* __restrict__ pix) {
   extern __shared__ unsigned char s_pm[];  // [ns*Hp*Wp] patch masks of the group's samples
@@ -452,7 +452,7 @@ __global__ __launch_bounds__(kNeedThreads) void k_need(const int32_t* __restrict
   __shared__ int scan[2][NW];
   const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // the patch grid lives on the output grid Ho x Wo (= H x W when stride is 1); pixels are input pixels
-  const int Hp = Ho / S, Wp = Wo / S, pps = Hp * Wp, HW = H * W;
+  const int Hp = fast_div(Ho, d_s), Wp = fast_div(Wo, d_s), pps = Hp * Wp, HW = H * W;
   const int n0 = g * gs, ns = min(gs, N - n0);
   const int cnt = *count;
   for (int i = tid; i < ns * pps; i += kNeedThreads) s_pm[i] = 0;
@@ -482,15 +482,8 @@ __global__ __launch_bounds__(kNeedThreads) void k_need(const int32_t* __restrict
     const int pp = p0 + tid;
     bool need = false;
     if (pp < ns * HW) {
-      const int ln = pp / HW, q = pp - ln * HW;
-      const int y = q / W, x = q - y * W;
-      // output pixel yo reads input rows stride*yo-1 .. stride*yo+1, so input row y serves the output
-      // rows ceil((y-1)/stride) .. floor((y+1)/stride), clipped to the output grid
-      const int yo0 = max((y - 1 + stride - 1) / stride, 0), yo1 = min((y + 1) / stride, Ho - 1);
-      const int xo0 = max((x - 1 + stride - 1) / stride, 0), xo1 = min((x + 1) / stride, Wo - 1);
-      const unsigned char* pm = s_pm + ln * pps;
-      for (int py = yo0 / S; py <= yo1 / S; ++py)
-        for (int px = xo0 / S; px <= xo1 / S; ++px) need |= pm[py * Wp + px] != 0;
+      const int ln = fast_div(pp, d_hw), q = pp - ln * HW, y = fast_div(q, d_w);
+      need = window_active(s_pm + ln * pps, y, q - y * W, stride, Ho, Wo, Wp, d_s);
     }
     const unsigned long long b = __ballot(need);
     int tot;
@@ -872,6 +865,19 @@ static int launch_sparse_head(int dtype, const laud_bottleneck* p, const void* x
   return launch_head(h, st);
 }
 
+// The same with the lists worked out by that kernel's own workgroups: groups of pixels that they can hold, identity and first
+// blocks alike.
+static int launch_fused_head(const laud_fmap& fx, const laud_bottleneck* p, const void* x, void* h1, const int32_t* idx,
+                             const int32_t* count, int S, int stride, int Ho, int Wo, int gs, int ngroups, void* wpack, hipStream_t st) {
+  int rc;
+  if (!p->packed && (rc = pack_weights_into(fx.dtype, p, wpack, true, true, st)) != LAUD_OK) return rc;
+  HeadArgs h{};
+  h.x = x; h.wpacked = (const char*)(p->packed ? p->packed : wpack) + packed_layout(fx.dtype, p).head;
+  h.s1 = p->s1; h.t1 = p->t1; h.h1 = h1; h.m_rows = ngroups; h.K = p->c_in;
+  h.idx = idx; h.count = count; h.N = fx.N; h.gs = gs; h.S = S; h.stride = stride; h.Ho = Ho; h.Wo = Wo; h.H = fx.H; h.W = fx.W;
+  return launch_head(h, st);
+}
+
 // Whether a dynamic block's first 1x1 runs on every pixel of the map instead of on the dilated active set: where the small
 // tiles take it the launch is bound by its latency and not by its rows, and on narrow maps (up to kDenseConv1Bytes of input
 // and output, kDenseConv1Flops) all rows take about 16 us, of which the rows outside the dilated set are less than the launch
@@ -960,17 +966,20 @@ static int run_dyn_block(const void* x, laud_fmap fx, const laud_bottleneck* p, 
     if (gs > fx.N) gs = fx.N;
     while (gs > 1 && (size_t)gs * pps > 60000) --gs;
     const int ngroups = (fx.N + gs - 1) / gs;
-    {
+    const bool fused = !e && head_used(fx.dtype, p, npix) && gs * hw <= kHeadGroup;
+    if (!fused) {
       StageScope scope(LAUD_STAGE_NEED, st);
       hipLaunchKernelGGL(k_need, dim3(ngroups), dim3(kNeedThreads), align_up((size_t)gs * pps, 16), st, idx, count,
-                         fx.N, fx.H, fx.W, S, 1, fx.H, fx.W, gs, need_counts, pix);
+                         fx.N, fx.H, fx.W, S, 1, fx.H, fx.W, gs, make_fast_div(hw), make_fast_div(fx.W), make_fast_div(S), need_counts, pix);
     }
     if (check_launch() != LAUD_OK) return LAUD_ERR_HIP;
     // conv1: gathered 1x1 over the dilated active set -> h1 at pixel positions
     a.A = x; a.Wt = p->w1; a.scale = p->s1; a.shift = p->t1; a.Out = h1; a.Res = nullptr;
     a.count = need_counts; a.list = pix; a.group_rows = gs * hw; a.K = p->c_in; a.ldw = p->c_in; a.Ncols = p->c_mid;
     a.lda = p->c_in; a.ldo = p->c_mid; a.relu = 1;
-    if (!e && head_used(fx.dtype, p, npix)) {
+    if (fused) {
+      if ((rc = launch_fused_head(fx, p, x, h1, idx, count, S, 1, fx.H, fx.W, gs, ngroups, wsb + L.wpack, st)) != LAUD_OK) return rc;
+    } else if (!e && head_used(fx.dtype, p, npix)) {
       if ((rc = launch_sparse_head(fx.dtype, p, x, h1, pix, need_counts, gs * hw, ngroups, wsb + L.wpack, st)) != LAUD_OK) return rc;
     } else {
       attach_tail_pack(a, fx.dtype, p, e, npix, wsb + L.wpack);
@@ -1320,16 +1329,19 @@ static int run_dyn_projection(const void* x, laud_fmap fx, const laud_bottleneck
     if (gs > fx.N) gs = fx.N;
     while (gs > 1 && (size_t)gs * pps > 60000) --gs;
     const int ngroups = (fx.N + gs - 1) / gs;
-    {
+    const bool fused = !e && head_used(fx.dtype, p, npix) && gs * hw <= kHeadGroup;
+    if (!fused) {
       StageScope scope(LAUD_STAGE_NEED, st);
       hipLaunchKernelGGL(k_need, dim3(ngroups), dim3(kNeedThreads), align_up((size_t)gs * pps, 16), st, idx, count,
-                         fx.N, fx.H, fx.W, S, stride, Ho, Wo, gs, need_counts, pix);
+                         fx.N, fx.H, fx.W, S, stride, Ho, Wo, gs, make_fast_div(hw), make_fast_div(fx.W), make_fast_div(S), need_counts, pix);
     }
     if (check_launch() != LAUD_OK) return LAUD_ERR_HIP;
     // conv1 over that set -> h1 at input pixel positions
     a.Wt = p->w1; a.scale = p->s1; a.shift = p->t1; a.Out = h1; a.Res = nullptr;
     a.count = need_counts; a.list = pix; a.group_rows = gs * hw; a.Ncols = p->c_mid; a.ldo = p->c_mid; a.relu = 1;
-    if (!e && head_used(fx.dtype, p, npix)) {
+    if (fused) {
+      if ((rc = launch_fused_head(fx, p, x, h1, idx, count, S, stride, Ho, Wo, gs, ngroups, wsb + L.wpack, st)) != LAUD_OK) return rc;
+    } else if (!e && head_used(fx.dtype, p, npix)) {
       if ((rc = launch_sparse_head(fx.dtype, p, x, h1, pix, need_counts, gs * hw, ngroups, wsb + L.wpack, st)) != LAUD_OK) return rc;
     } else {
       attach_tail_pack(a, fx.dtype, p, e, nout, wsb + L.wpack);

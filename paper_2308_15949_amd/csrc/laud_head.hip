@@ -31,6 +31,8 @@ __host__ __device__ constexpr int a_stage(int pb) { return 32 * pb * 128; }  // 
 // output rows of the tile (int)
 __host__ __device__ constexpr int tab_off(int pb) { return kARing * a_stage(pb); }
 __host__ __device__ constexpr int lds_bytes(int K, int pb) { return tab_off(pb) + 2 * kMid * 4 + K * 4 + kWaves * 32 * pb * 4 + 32 * pb * 4; }
+constexpr int kListOff = tab_off(kMaxPB) + 2 * kMid * 4;
+static_assert(kHeadGroup + kHeadGroup / kWave * 4 + 128 * 4 <= 256 * 4 + kWaves * 32 * kMaxPB * 4, "the list's tables end ahead of the output rows");
 // time of one tile of 64 / 128 pixels in the same unit (measured 14-17 and 21-26 us at K = 1024): a workgroup streams
 // all of w1 whatever its height
 constexpr int kCost2 = 2, kCost4 = 3;
@@ -81,13 +83,15 @@ __device__ __forceinline__ void head_tile(const HeadArgs& a, const int row0, con
   }
 
   // ---- weight stream: four slices in registers -------------------------------------------------------------------
-  typedef const __attribute__((address_space(1))) u32x4* gptr16;
-  const gptr16 wsrc = (gptr16)a.wpacked + wave * 256 + lane;
+  // (buffer loads: see laud_tail.hip)
+  const __amdgpu_buffer_rsrc_t wrs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.wpacked), 0, NSL * (tail::kSliceChunks * 16), 0x00020000);
+  const unsigned wlane = (unsigned)(wave * 4096 + lane * 16);
   u32x4 wr[kWRing][4];
   auto load_W = [&](int buf, int b) __attribute__((always_inline)) {
     const int bb = b < NSL ? b : NSL - 1;  // past the end: the last slice again (keeps the load count uniform)
 #pragma unroll
-    for (int kg = 0; kg < 4; ++kg) wr[buf][kg] = wsrc[(size_t)bb * tail::kSliceChunks + kg * 64];
+    for (int kg = 0; kg < 4; ++kg) wr[buf][kg] = __builtin_amdgcn_raw_buffer_load_b128(wrs, wlane + kg * 1024, bb * (tail::kSliceChunks * 16), 0);
   };
 #pragma unroll
   for (int b = 0; b < kWRing; ++b) load_W(b, b);
@@ -248,6 +252,87 @@ __global__ __launch_bounds__(head::kThreads) void k_head(const HeadArgs a) {
   prefetch_args<sizeof(HeadArgs)>();
   int pb = a.pb;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, l8 = lane >> 3;
+  if constexpr (!PROJ) {
+    if (a.idx != nullptr) {
+      // The dilated pixel list of the workgroup's group of samples, made here by every workgroup of the group for itself: a chain of
+      // two memory round trips and three barriers (about 2 us), where a launch that writes the lists takes 7.  Workgroup id ->
+      // (group, tile) as for lists below.  The height goes by the group's own count: groups need not agree.
+      // (in the bytes of the masker weights and partial sums, which only the projection uses: the tile's own loads, which a faster
+      // wave may issue while another still reads here, go elsewhere)
+      extern __shared__ __align__(16) unsigned char smem[];
+      unsigned char* const s_pm = smem + kListOff;  // patch masks of the group's samples
+      int* const s_cnt = reinterpret_cast<int*>(s_pm + kHeadGroup);
+      int* const s_list = s_cnt + kHeadGroup / kWave;
+      const unsigned touched = l2_touch(a.wpacked, a.K / 64 * tail::kSliceChunks * 16, kThreads);
+      const int tid = threadIdx.x;
+      const int g = blockIdx.x % a.m_rows, tile = blockIdx.x / a.m_rows;
+      const int Wp = fast_div(a.Wo, a.d_s), pps = fast_div(a.Ho, a.d_s) * Wp, HW = a.H * a.W;
+      const int n0 = g * a.gs, ns = min(a.gs, a.N - n0), q0 = n0 * pps, nq = ns * pps, npx = ns * HW;
+      const int cnt = *a.count;
+      for (int i = tid; i < (nq + 15) / 16; i += kThreads) reinterpret_cast<uint4*>(s_pm)[i] = make_uint4(0, 0, 0, 0);
+      int lo = 0, hi = cnt;
+      constexpr int kAtOnce = 16;  // entries of a thread requested before any is used: one round trip for lists of up to 8192
+      if (cnt > kAtOnce * kThreads) wave_lower_bound2(a.idx, cnt, q0, q0 + nq, lo, hi);
+      __syncthreads();
+      for (int i0 = lo + tid; i0 < hi; i0 += kAtOnce * kThreads) {
+        int e[kAtOnce];
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u) e[u] = a.idx[min(i0 + u * kThreads, hi - 1)];
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u)
+          if (i0 + u * kThreads < hi && (unsigned)(e[u] - q0) < (unsigned)nq) s_pm[e[u] - q0] = 1;
+      }
+      __syncthreads();
+      constexpr int kSteps = kHeadGroup / kThreads;
+      unsigned need = 0;  // bit it: this thread's pixel it * kThreads + tid of the group is in the list
+      int ahead[kSteps];  // ... and the list's pixels ahead of it in its wave's 64
+#pragma unroll
+      for (int it = 0; it < kSteps; ++it) {
+        ahead[it] = 0;
+        if (it * kThreads >= npx) continue;
+        const int pp = it * kThreads + tid;
+        bool in = false;
+        if (pp < npx) {
+          const int ln = fast_div(pp, a.d_hw), q = pp - ln * HW, y = fast_div(q, a.d_w), x = q - y * a.W;
+          in = window_active(s_pm + ln * pps, y, x, a.stride, a.Ho, a.Wo, Wp, a.d_s);
+        }
+        const unsigned long long b = __ballot(in);
+        if (lane == 0) s_cnt[it * (kThreads / kWave) + wv] = __popcll(b);
+        ahead[it] = ballot_prefix(b);
+        need |= (in ? 1u : 0u) << it;
+      }
+      __syncthreads();
+      const int c = lane < (npx + kThreads - 1) / kThreads * (kThreads / kWave) ? s_cnt[lane] : 0;
+      int incl = c;
+#pragma unroll
+      for (int o = 1; o < kWave; o <<= 1) {
+        const int t = __shfl_up(incl, o, kWave);
+        if (lane >= o) incl += t;
+      }
+      const int M = __shfl(incl, kWave - 1, kWave);
+      if (pb == 0) {
+        const int t2 = (M + 63) / 64 * a.m_rows, t4 = (M + 127) / 128 * a.m_rows;
+        const int c2 = ((t2 + a.wg_target - 1) / a.wg_target) * kCost2, c4 = ((t4 + a.wg_target - 1) / a.wg_target) * kCost4;
+        pb = c2 <= c4 ? 2 : 4;
+      }
+      pb = __builtin_amdgcn_readfirstlane(pb);
+      const int row0 = tile * 32 * pb;
+      l2_touched(touched);
+      if (row0 >= M) return;
+#pragma unroll
+      for (int it = 0; it < kSteps; ++it) {
+        if (it * kThreads >= npx) continue;
+        const int r = __shfl(incl - c, it * (kThreads / kWave) + wv, kWave) + ahead[it] - row0;
+        if (((need >> it) & 1u) && (unsigned)r < 32u * pb) s_list[r] = n0 * HW + it * kThreads + tid;
+      }
+      __syncthreads();
+      const int r8 = 8 * wv + l8;
+      const int p2[1] = {s_list[r8]}, p4[2] = {s_list[r8], s_list[64 + r8]};  // (rows past the last one: not used)
+      if (pb == 2) head_tile<false, 2>(a, row0, M, true, p2);
+      else head_tile<false, 4>(a, row0, M, true, p4);
+      return;
+    }
+  }
   if (a.slist != nullptr) {
     // Rows = the pixels of the kept samples, in list order: row -> (slot = row / hw, pixel of sample slist[slot]).  The
     // count lives on the device, so the height is decided here (as for pixel lists), and the sample ids of this lane's
@@ -361,7 +446,7 @@ int launch_head(const HeadArgs& args, hipStream_t st) {
     // pixels of listed samples: capacity m_rows = scap * hw rows, the count is on the device
     if (a.pb != 2 && a.pb != 4) a.pb = 0;
     grid = (unsigned)((a.m_rows + (a.pb == 4 ? 127 : 63)) / (a.pb == 4 ? 128 : 64));
-  } else if (a.list == nullptr) {
+  } else if (a.list == nullptr && a.idx == nullptr) {
     // dense rows: the count is known here; the same rounds x tile-time cost the kernel uses for lists
     if (a.pb != 2 && a.pb != 4) {
       const long long t2 = (a.m_rows + 63) / 64, t4 = (a.m_rows + 127) / 128;
@@ -374,6 +459,10 @@ int launch_head(const HeadArgs& args, hipStream_t st) {
   } else {
     // m_rows groups, each with up to group_rows entries: enough workgroups for the smaller tile height
     if (a.pb != 2 && a.pb != 4) a.pb = 0;
+    if (a.idx) {
+      a.group_rows = a.gs * a.H * a.W;
+      a.d_hw = make_fast_div(a.H * a.W); a.d_w = make_fast_div(a.W); a.d_s = make_fast_div(a.S);
+    }
     const int h = a.pb ? 32 * a.pb : 64;
     grid = (unsigned)a.m_rows * (unsigned)((a.group_rows + h - 1) / h);
   }

@@ -137,8 +137,15 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
   }
 
   // ---- weight stream: a ring of slices in registers (one in use, the others in flight) ------------------------------
-  typedef const __attribute__((address_space(1))) u32x4* gptr16;
-  const gptr16 wsrc = (gptr16)a.wpacked + wave * 256 + lane;
+  // (Buffer loads: a 64-bit address per lane takes vector instructions and register reads from the MFMAs.  One compute unit's
+  // stream beside two MFMAs and two fragment reads a K step: 93 bytes a ns through such addresses, 119 through a descriptor; a
+  // 64-pixel tile's slice 914 -> 784 cycles.)
+  const __amdgpu_buffer_rsrc_t wrs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.wpacked), 0, kNB * kSliceChunks * 16, 0x00020000);
+  const unsigned wlane = (unsigned)(wave * 4096 + lane * 16);
+  auto fragment_W = [&](int b, int kg) __attribute__((always_inline)) -> u32x4 {  // K step kg of slice b
+    return __builtin_amdgcn_raw_buffer_load_b128(wrs, wlane + kg * 1024, b * (kSliceChunks * 16), 0);
+  };
   // Weight slices held / in flight in registers: four (every compute unit streams the same 1.7 MB at once, which keeps
   // the L2 at its bandwidth limit and its latency high: 37.3 against 38.3 us per launch with three); three with a
   // channel mask, whose slice sequences have 9, 18, 27 or 36 entries.
@@ -148,7 +155,7 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
   auto load_W = [&](int buf, int i) __attribute__((always_inline)) {  // position i of the slice sequence
     const int b = sid(i);
 #pragma unroll
-    for (int kg = 0; kg < 4; ++kg) wr[buf][kg] = wsrc[(size_t)b * kSliceChunks + kg * 64];
+    for (int kg = 0; kg < 4; ++kg) wr[buf][kg] = fragment_W(b, kg);
   };
 #pragma unroll
   for (int b = 0; b < WR; ++b) load_W(b, b);
@@ -303,8 +310,6 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
       unsigned char* row = smem + kH2Off + r * 512u;
       *reinterpret_cast<uint4*>(row + ((ch ^ (r & 15u)) << 4)) = c0;
       *reinterpret_cast<uint4*>(row + (((ch + 1u) ^ (r & 15u)) << 4)) = c1;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;  // the last 1x1 starts from zero
       __builtin_amdgcn_sched_barrier(0);              // one pixel block at a time (register pressure)
     }
   }
@@ -336,10 +341,6 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
   const __bf16* const resp = reinterpret_cast<const __bf16*>(a.res);
   __bf16* const outp = reinterpret_cast<__bf16*>(a.out);
   f32x16 acc2[DUAL ? PB : 1];  // the second accumulator set (odd column tiles)
-#pragma unroll
-  for (int t = 0; t < (DUAL ? PB : 1); ++t)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc2[t][e] = 0.f;
   uint4 res[PB][2];  // residual of the tile whose epilogue is pending: per pixel block, channels 0-7 / 8-15
 #pragma unroll
   for (int t = 0; t < PB; ++t) res[t][0] = res[t][1] = make_uint4(0, 0, 0, 0);
@@ -361,8 +362,6 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
       auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v0[i]), __float_as_uint(v1[i]), false, false);
       v0[i] = __uint_as_float(r[0]);
       v1[i] = __uint_as_float(r[1]);
-      A[4 * h + i] = 0.f;  // the set is free for the tile after next
-      A[4 * h + 8 + i] = 0.f;
     }
     const unsigned rv[4] = {res[t][h].x, res[t][h].y, res[t][h].z, res[t][h].w};
     const float x[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
@@ -396,8 +395,9 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int t = 0; t < PB; ++t) {
-        if (DUAL && (ct & 1)) acc2[t] = mma_bf16(wr[BUF][kg], fa[cur][t], acc2[t]);
-        else acc[t] = mma_bf16(wr[BUF][kg], fa[cur][t], acc[t]);
+        f32x16& A = DUAL && (ct & 1) ? acc2[t] : acc[t];
+        if (st == 0) A = mma_bf16(wr[BUF][kg], fa[cur][t], f32x16{});  // (a column tile starts from zero)
+        else A = mma_bf16(wr[BUF][kg], fa[cur][t], A);
       }
       // Odd steps 1, 3, ...: one half pixel block each.  With two accumulator sets the previous tile's epilogue piece
       // runs behind these MFMAs; the residual registers it frees are refilled at once with this tile's values, a
@@ -410,7 +410,7 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
         load_residual_half(ct, t, h);
       }
       // the weight register just used is refilled for one ring length later
-      if (b + WR < kNB) wr[BUF][kg] = wsrc[(size_t)(b + WR) * kSliceChunks + kg * 64];
+      if (b + WR < kNB) wr[BUF][kg] = fragment_W(b + WR, kg);
       __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (!DUAL) {  // one accumulator set: the epilogue follows its tile

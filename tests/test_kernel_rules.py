@@ -71,3 +71,14 @@ def test_no_inline_assembly_load_writes_a_register():
             body = text[at.end():text.index(");", at.end())]
             outputs = body.split(":")[1] if ":" in body else ""
             assert not ("load" in body and "=" in outputs), (name, body)
+
+
+def test_lds_direct_loads_meet_no_static_lds():
+    """LDS-direct loads take offsets from the start of the workgroup's LDS, where the dynamic part begins only in a kernel that
+    has no static one."""
+    for name in sorted(os.listdir(B.CSRC)):
+        if name.endswith((".h", ".hip")):
+            with open(os.path.join(B.CSRC, name)) as f:
+                text = re.sub(r"//.*", "", f.read())
+            if re.search(r"\bdma(4|16)\(", text) and name not in ("laud_tile_util.h", "laud_static.hip"):
+                assert not re.search(r"(?<!extern )__shared__", text), name
