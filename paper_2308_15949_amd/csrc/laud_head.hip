@@ -462,6 +462,8 @@ int launch_head(const HeadArgs& args, hipStream_t st) {
     if (a.idx) {
       a.group_rows = a.gs * a.H * a.W;
       a.d_hw = make_fast_div(a.H * a.W); a.d_w = make_fast_div(a.W); a.d_s = make_fast_div(a.S);
+      // a workgroup without a tile has its group's list to make before it knows: of more than two rounds of them, half as many
+      if ((long long)a.m_rows * ((a.group_rows + 63) / 64) > 2 * a.wg_target) a.pb = 4;
     }
     const int h = a.pb ? 32 * a.pb : 64;
     grid = (unsigned)a.m_rows * (unsigned)((a.group_rows + h - 1) / h);
