@@ -51,6 +51,11 @@ bool skinny_wanted(int mode, int dtype, const GemmArgs& a, long long cap_rows);
 int launch_skinny(int mode, int dtype, const GemmArgs& a, long long cap_rows, hipStream_t stream);
 int skinny_init_device();
 
+// The group 3x3 in bf16, many rows, up to kGroupMaxC channels (laud_group.hip).
+constexpr int kGroupMaxC = 4096;
+int launch_group(const GemmArgs& a, long long cap_rows, hipStream_t stream);
+int group_init_device();
+
 // Many rows (laud_pipe.h); nsamples: samples of channel skipping, groups of CONV1's pixel lists.
 int launch_pipe_a(int mode, int dtype, const GemmArgs& a, long long cap_rows, int nsamples, hipStream_t stream);
 int launch_pipe_b(int mode, int dtype, const GemmArgs& a, long long cap_rows, int nsamples, hipStream_t stream);

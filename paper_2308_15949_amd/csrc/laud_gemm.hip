@@ -799,7 +799,7 @@ static int launch_conv2(int dtype, GemmArgs a, const laud_group_se* e, long long
   a.ldw = 9 * e->group_width;
   StageScope scope(LAUD_STAGE_CONV2, st);
   if (skinny_wanted(M_G2, dtype, a, cap_rows)) return launch_skinny(M_G2, dtype, a, cap_rows, st);
-  return launch_pipe(M_G2, dtype, a, cap_rows, 1, st);
+  return dtype == LAUD_BF16 && a.Ncols <= kGroupMaxC ? launch_group(a, cap_rows, st) : launch_pipe(M_G2, dtype, a, cap_rows, 1, st);
 }
 
 // Whether conv2 -> conv3 -> residual add run as the one kernel of laud_tail.hip (h2 stays in LDS), and whether
@@ -1477,6 +1477,7 @@ extern "C" int laud_init(void) {
   rc = gemm_init_device();
   if (rc != LAUD_OK) return rc;
   if ((rc = skinny_init_device()) != LAUD_OK) return rc;
+  if ((rc = group_init_device()) != LAUD_OK) return rc;
   if ((rc = narrow_init_device()) != LAUD_OK) return rc;
   if ((rc = stem_init_device(nullptr)) != LAUD_OK) return rc;
   if ((rc = tail_init_device()) != LAUD_OK) return rc;

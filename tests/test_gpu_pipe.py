@@ -7,6 +7,7 @@ import pytest
 from oracle import laud_oracle as O
 from paper_2308_15949_amd import inputs as I
 from test_gpu_body import close, oparams, shortcut_params
+from test_gpu_group_se import check_group_se, run_group_se
 from test_gpu_parity import G, TOL, check_dyn, run_dyn  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -93,3 +94,17 @@ def test_copy_of_whole_samples(G, case):  # noqa: F811
         check_dyn(got, x, hb, H, mask)
     else:
         assert np.array_equal(got, x)
+
+
+@pytest.mark.parametrize("case", [
+    # N, H, W, C, g, S, ratio: one and several column tiles, the last with 8, 16 and 48 channels; fewer and more tiles than workgroups
+    (5, 56, 56, 64, 64, 4, 0.5), (12, 28, 28, 144, 16, 2, 0.9), (22, 14, 14, 440, 8, 7, 0.3), (9, 41, 37, 48, 8, 1, 0.5),
+    (13, 56, 56, 104, 8, 8, 1.0), (4, 28, 28, 832, 32, 28, 0.5),
+])
+def test_group_conv(G, case):  # noqa: F811
+    N, H, W, C, g, S, ratio = case
+    x = I.feature_map(9950 + C, N, H, W, C, I.BF16)
+    hb = I.bottleneck_params(9960 + C, C, C, C, I.BF16, True, group_width=g)
+    mask = I.bernoulli_mask(9970 + S, (N, H // S, W // S), ratio)
+    mask[0, 0, 0] = mask[-1, -1, -1] = 1
+    check_group_se(run_group_se(G, x, hb, g, None, S, mask, True), x, hb, g, None, S, mask)
