@@ -84,6 +84,25 @@ def test_group_se_block_bernoulli(G, case, inplace):
     check_group_se(got, x, hb, g, se, S, mask)
 
 
+@pytest.mark.parametrize("case", [
+    # H, W, C, dtype, active pixels of each sample.  One launch: lists of 64, 1024 and 8192 entries and one more; rows that the
+    # threads just keep in registers (4096 of 32 bytes, 2048 of 64, 64 of 2 KB) and one more
+    (8, 16, 16, I.BF16, (32, 32)), (8, 16, 16, I.BF16, (33, 0, 32)), (32, 20, 16, I.F32, (512, 512)),
+    (32, 20, 16, I.F32, (512, 513)), (72, 64, 16, I.BF16, (4096, 4096)), (72, 64, 16, I.BF16, (4097, 4096)),
+    (48, 44, 16, I.F32, (2048, 0, 2049)), (8, 9, 1024, I.BF16, (64, 65, 1)), (9, 9, 512, I.F32, (1, 64, 65)),
+])
+def test_group_se_list_and_row_edges(G, case):
+    H, W, C, dt, counts = case
+    x = I.feature_map(3900 + C + H, len(counts), H, W, C, dt)
+    hb = I.bottleneck_params(3910 + C, C, C, C, dt, True, group_width=8)
+    se = I.se_weights(3920 + C, C, 16)
+    mask = np.zeros((len(counts), H * W), np.uint8)
+    for n, k in enumerate(counts):
+        mask[n, np.random.default_rng(3930 + n).permutation(H * W)[:k]] = 1
+    mask = mask.reshape(-1, H, W)
+    check_group_se(run_group_se(G, x, hb, 8, se, 1, mask, True), x, hb, 8, se, 1, mask)
+
+
 @pytest.mark.parametrize("dt", [I.F32, I.BF16])
 @pytest.mark.parametrize("kind", ["ones", "zeros", "one_sample_empty", "single_patch", "layer_skip"])
 def test_group_se_block_special_masks(G, dt, kind):
