@@ -50,6 +50,9 @@ struct GemmArgs {
 bool skinny_wanted(int mode, int dtype, const GemmArgs& a, long long cap_rows);
 int launch_skinny(int mode, int dtype, const GemmArgs& a, long long cap_rows, hipStream_t stream);
 int skinny_init_device();
+// Two dense 1x1s (M_SD1) on the same input and reduction length in one launch.
+bool skinny_pair_wanted(int dtype, const GemmArgs& a, long long rows_a, const GemmArgs& b, long long rows_b);
+int launch_skinny_pair(int dtype, const GemmArgs& a, long long rows_a, const GemmArgs& b, long long rows_b, hipStream_t stream);
 
 // The group 3x3 in bf16, many rows, up to kGroupMaxC channels (laud_group.hip).
 constexpr int kGroupMaxC = 4096;

@@ -893,14 +893,28 @@ static bool dense_conv1_wanted(int dtype, const laud_bottleneck* p, long long np
   return dtype == LAUD_BF16 && (double)npix * (p->c_in + p->c_mid) * 2 <= kDenseConv1Bytes &&
          2.0 * npix * p->c_in * p->c_mid <= kDenseConv1Flops;
 }
-static int run_dense_conv1(const laud_fmap& fx, const laud_bottleneck* p, const void* x, void* h1, hipStream_t st) {
+static GemmArgs dense_conv1_args(const laud_fmap& fx, const laud_bottleneck* p, const void* x, void* h1) {
   GemmArgs a{};
   a.H = fx.H; a.W = fx.W; a.S = 1; a.D = 1; a.G = 1; a.stride = 1; a.Ho = fx.H; a.Wo = fx.W;
   a.A = x; a.Wt = p->w1; a.scale = p->s1; a.shift = p->t1; a.Out = h1; a.K = p->c_in; a.ldw = p->c_in;
   a.Ncols = p->c_mid; a.lda = p->c_in; a.ldo = p->c_mid; a.relu = 1;
-  const long long npix = (long long)fx.N * fx.H * fx.W;
-  a.m_rows = (int)npix;
-  return launch_gemm<M_SD1>(fx.dtype, a, npix, 1, st);
+  a.m_rows = (int)((long long)fx.N * fx.H * fx.W);
+  return a;
+}
+static int run_dense_conv1(const laud_fmap& fx, const laud_bottleneck* p, const void* x, void* h1, hipStream_t st) {
+  const GemmArgs a = dense_conv1_args(fx, p, x, h1);
+  return launch_gemm<M_SD1>(fx.dtype, a, a.m_rows, 1, st);
+}
+// A first block's shortcut (`a`, on `rows` output pixels) and its first 1x1 on every input pixel: one launch where both are few rows.
+static int run_shortcut_and_conv1(const GemmArgs& a, long long rows, const laud_fmap& fx, const laud_bottleneck* p, const void* x,
+                                  void* h1, hipStream_t st) {
+  const GemmArgs b = dense_conv1_args(fx, p, x, h1);
+  if (skinny_pair_wanted(fx.dtype, a, rows, b, b.m_rows)) {
+    StageScope scope(LAUD_STAGE_CONV1, st);
+    return launch_skinny_pair(fx.dtype, a, rows, b, b.m_rows, st);
+  }
+  const int rc = launch_gemm<M_SD1>(fx.dtype, a, rows, 1, st);
+  return rc != LAUD_OK ? rc : launch_gemm<M_SD1>(fx.dtype, b, b.m_rows, 1, st);
 }
 
 // conv2 -> conv3 -> residual add as one kernel where laud_tail.hip covers the shape (h2 stays in LDS).
@@ -1234,11 +1248,9 @@ extern "C" int laud_static_bottleneck(const void* x, laud_fmap fx, const laud_bo
   // shortcut: strided 1x1 + affine, straight into the output buffer
   a.A = x; a.Wt = w_sc; a.scale = s_sc; a.shift = t_sc; a.Out = out; a.K = p->c_in; a.ldw = p->c_in;
   a.Ncols = p->c_out; a.lda = p->c_in; a.ldo = p->c_out; a.relu = 0; a.stride = stride; a.m_rows = (int)nout;
-  if ((rc = launch_gemm<M_SD1>(fx.dtype, a, nout, 1, st)) != LAUD_OK) return rc;
-  // conv1 on every input pixel
-  a.Wt = p->w1; a.scale = p->s1; a.shift = p->t1; a.Out = h1; a.Ncols = p->c_mid; a.ldo = p->c_mid; a.relu = 1;
-  a.stride = 1; a.Ho = fx.H; a.Wo = fx.W; a.m_rows = (int)npix;
-  if ((rc = launch_gemm<M_SD1>(fx.dtype, a, npix, 1, st)) != LAUD_OK) return rc;
+  // ... and conv1 on every input pixel
+  if ((rc = run_shortcut_and_conv1(a, nout, fx, p, x, h1, st)) != LAUD_OK) return rc;
+  a.Ncols = p->c_mid; a.ldo = p->c_mid; a.relu = 1;
   // conv2: 3x3, pad 1, the block's stride
   a.A = h1; a.Wt = p->w2; a.scale = p->s2; a.shift = p->t2; a.Out = h2; a.K = p->c_mid; a.ldw = 9 * p->c_mid;
   a.lda = p->c_mid; a.stride = stride; a.Ho = Ho; a.Wo = Wo; a.m_rows = (int)nout;
@@ -1313,16 +1325,15 @@ static int run_dyn_projection(const void* x, laud_fmap fx, const laud_bottleneck
   a.A = x; a.Wt = w_sc; a.scale = s_sc; a.shift = t_sc; a.Out = out; a.K = p->c_in; a.ldw = p->c_in;
   a.Ncols = p->c_out; a.lda = p->c_in; a.ldo = p->c_out; a.relu = p->relu_out ? 1 : 0; a.m_rows = (int)nout;
   a.list = idx; a.count = count;
-  if ((rc = launch_gemm<M_SD1>(fx.dtype, a, nout, 1, st)) != LAUD_OK) return rc;
-
   if (dense_conv1_wanted(fx.dtype, p, npix) && !head_used(fx.dtype, p, npix)) {
     // (input widths the register-weight first 1x1 does not take, in front of the fused 3x3 -> 1x1 kernel: the dense launch
     // carries no re-ordering of its weights)
     if (tail_used(fx.dtype, p, e, nout) && !p->packed &&
         (rc = pack_weights_into(fx.dtype, p, wsb + L.wpack, false, true, st)) != LAUD_OK)
       return rc;
-    if ((rc = run_dense_conv1(fx, p, x, h1, st)) != LAUD_OK) return rc;
+    if ((rc = run_shortcut_and_conv1(a, nout, fx, p, x, h1, st)) != LAUD_OK) return rc;
   } else {
+    if ((rc = launch_gemm<M_SD1>(fx.dtype, a, nout, 1, st)) != LAUD_OK) return rc;
     // input pixels the branch reads: the 3x3 windows (at the block's stride) of the active output pixels
     const int hw = fx.H * fx.W, pps = Hp * Wp;
     int gs = (1536 + hw - 1) / hw;

@@ -53,9 +53,9 @@ __host__ __device__ constexpr int skinny_lds() {
   return part > slices ? part : slices;
 }
 
+// Workgroup L of a launch.
 template <int MODE, typename ET, int TM, int TN, int NW, int D>
-__global__ __launch_bounds__(64 * NW) void k_skinny(const SkinnyArgs ka) {
-  prefetch_args<sizeof(SkinnyArgs)>();
+__device__ __forceinline__ void skinny_tile(const SkinnyArgs& ka, const int L) {
   const GemmArgs& a = ka.g;
   constexpr int BM = 16 * TM, BN = 16 * TN, NT = 64 * NW;
   constexpr int EPC = elem<ET>::per16, ES = (int)sizeof(ET), BKE = 8 * EPC;
@@ -75,8 +75,8 @@ __global__ __launch_bounds__(64 * NW) void k_skinny(const SkinnyArgs ka) {
   const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, lq = lane >> 4, l8 = lane >> 3, l7 = lane & 7;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if constexpr (MODE == M_CONV3) {
-    if (a.cp.nblocks && (int)blockIdx.x >= a.cp.first) {
-      copy_inactive_part<NT>(a.cp, blockIdx.x - a.cp.first, a.cp.nblocks, smem);
+    if (a.cp.nblocks && L >= a.cp.first) {
+      copy_inactive_part<NT>(a.cp, L - a.cp.first, a.cp.nblocks, smem);
       return;
     }
   }
@@ -84,7 +84,6 @@ __global__ __launch_bounds__(64 * NW) void k_skinny(const SkinnyArgs ka) {
   // dealt to the XCDs as in the tiled kernel, so that the next launch finds its rows in the same L2, or column tiles
   int rt, ct;
   {
-    const int L = blockIdx.x;
     if (ka.deal == 1) {
       const int s = L >> 3, r8 = fdiv(s, ka.inv_ct);
       rt = r8 * 8 + (L & 7);
@@ -361,6 +360,23 @@ __global__ __launch_bounds__(64 * NW) void k_skinny(const SkinnyArgs ka) {
   }
 }
 
+template <int MODE, typename ET, int TM, int TN, int NW, int D>
+__global__ __launch_bounds__(64 * NW) void k_skinny(const SkinnyArgs ka) {
+  prefetch_args<sizeof(SkinnyArgs)>();
+  skinny_tile<MODE, ET, TM, TN, NW, D>(ka, blockIdx.x);
+}
+
+// Two dense 1x1s that read the same input and do not wait for each other -- the shortcut of a first block and its first 1x1 -- as
+// one launch: workgroups from `split` on take the second.  (One image, first block of stage 1 / 2 / 3 / 4 at ratio 0.15: 19.8 /
+// 17.8 / 17.1 / 23.5 -> 16.9 / 15.3 / 14.8 / 17.0 us.)
+struct SkinnyPair { SkinnyArgs p[2]; int split; };
+template <typename ET, int TM, int TN, int NW, int D>
+__global__ __launch_bounds__(64 * NW) void k_skinny_pair(const SkinnyPair ka) {
+  prefetch_args<sizeof(SkinnyPair)>();
+  const int second = (int)blockIdx.x >= ka.split;
+  skinny_tile<M_SD1, ET, TM, TN, NW, D>(ka.p[second], (int)blockIdx.x - (second ? ka.split : 0));
+}
+
 // ---- host side ------------------------------------------------------------------------------------------------------
 // More than 64 KB of dynamic LDS has to be requested once per kernel and device (idempotent; see gemm_request_lds).
 template <int MODE, typename ET, int TM, int TN, int NW, int D>
@@ -378,16 +394,14 @@ static int skinny_request_lds() {
   return LAUD_OK;
 }
 
-// rows < 0: only make the request (laud_init)
-template <int MODE, typename ET, int TM, int TN, int NW, int D>
-static int launch_skinny_t(GemmArgs a, long long cap_rows, hipStream_t st) {
-  const int rc = skinny_request_lds<MODE, ET, TM, TN, NW, D>();
-  if (rc != LAUD_OK || cap_rows < 0) return rc;
+// The arguments of a launch and its workgroups (without those that copy).
+template <int MODE, typename ET, int TM, int TN>
+static unsigned skinny_args(GemmArgs a, long long cap_rows, SkinnyArgs& k) {
   constexpr bool TAPS = (MODE == M_CONV2 || MODE == M_SD2 || MODE == M_G2);
   constexpr int BKE = 8 * elem<ET>::per16;
   a.row_tiles = (int)((cap_rows + 16 * TM - 1) / (16 * TM));
   a.col_tiles = (a.Ncols + 16 * TN - 1) / (16 * TN);
-  SkinnyArgs k{};
+  k = SkinnyArgs{};
   k.g = a;
   k.cap_rows = (int)cap_rows;
   k.kch = ((MODE == M_G2 ? 16 * TN : a.K) + BKE - 1) / BKE;
@@ -400,13 +414,42 @@ static int launch_skinny_t(GemmArgs a, long long cap_rows, hipStream_t st) {
   k.inv_rt = 1.f / a.row_tiles; k.inv_ct = 1.f / a.col_tiles;
   const bool by_row = cap_rows > (long long)a.Ncols * (TAPS ? 9 : 1) && a.row_tiles >= 64;
   k.deal = by_row ? 1 : (a.col_tiles & 7) == 0 ? 2 : 0;
+  return (unsigned)((by_row ? (a.row_tiles + 7) / 8 * 8 : a.row_tiles) * a.col_tiles);
+}
+
+// cap_rows < 0: only make the request (laud_init)
+template <int MODE, typename ET, int TM, int TN, int NW, int D>
+static int launch_skinny_t(const GemmArgs& a, long long cap_rows, hipStream_t st) {
+  const int rc = skinny_request_lds<MODE, ET, TM, TN, NW, D>();
+  if (rc != LAUD_OK || cap_rows < 0) return rc;
+  SkinnyArgs k;
+  unsigned grid = skinny_args<MODE, ET, TM, TN>(a, cap_rows, k);
   const int lds = skinny_lds<TM, TN, NW>() + (MODE == M_DENSE1 && a.wmask ? a.K * 4 : 0);
-  unsigned grid = (unsigned)((by_row ? (a.row_tiles + 7) / 8 * 8 : a.row_tiles) * a.col_tiles);
   if constexpr (MODE == M_CONV3) {
     k.g.cp.first = (int)grid;
     grid += (unsigned)a.cp.nblocks;
   }
   hipLaunchKernelGGL((k_skinny<MODE, ET, TM, TN, NW, D>), dim3(grid), dim3(64 * NW), lds, st, k);
+  return check_launch();
+}
+
+template <typename ET, int TM, int TN, int NW, int D>
+static int launch_pair_t(const GemmArgs& a, long long rows_a, const GemmArgs& b, long long rows_b, hipStream_t st) {
+  constexpr int lds = skinny_lds<TM, TN, NW>();
+  static std::atomic<unsigned> done{0};  // (as in skinny_request_lds)
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return LAUD_ERR_HIP;
+  const unsigned bit = dev >= 0 && dev < 32 ? 1u << dev : 0u;
+  if (!bit || !(done.load(std::memory_order_acquire) & bit)) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_skinny_pair<ET, TM, TN, NW, D>), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+      return LAUD_ERR_HIP;
+    done.fetch_or(bit, std::memory_order_release);
+  }
+  if (rows_a < 0) return LAUD_OK;  // only the request (laud_init)
+  SkinnyPair k;
+  k.split = (int)skinny_args<M_SD1, ET, TM, TN>(a, rows_a, k.p[0]);
+  const unsigned grid = (unsigned)k.split + skinny_args<M_SD1, ET, TM, TN>(b, rows_b, k.p[1]);
+  hipLaunchKernelGGL((k_skinny_pair<ET, TM, TN, NW, D>), dim3(grid), dim3(64 * NW), lds, st, k);
   return check_launch();
 }
 
@@ -458,6 +501,34 @@ int launch_skinny(int mode, int dtype, const GemmArgs& a, long long cap_rows, hi
   }
 }
 
+template <typename ET>
+static int launch_pair_e(const GemmArgs& a, long long rows_a, const GemmArgs& b, long long rows_b, hipStream_t st) {
+  if (rows_a < 0) {
+    int rc = launch_pair_t<ET, 1, 1, 8, 8>(a, -1, b, -1, st);
+    if (rc == LAUD_OK) rc = launch_pair_t<ET, 1, 1, 4, 4>(a, -1, b, -1, st);
+    if (rc == LAUD_OK) rc = launch_pair_t<ET, 2, 2, 8, 4>(a, -1, b, -1, st);
+    if (rc == LAUD_OK) rc = launch_pair_t<ET, 2, 2, 4, 4>(a, -1, b, -1, st);
+    if (rc == LAUD_OK) rc = launch_pair_t<ET, 2, 4, 4, 3>(a, -1, b, -1, st);
+    if (rc == LAUD_OK) rc = launch_pair_t<ET, 4, 4, 4, 2>(a, -1, b, -1, st);
+    return rc;
+  }
+  // the tile rule of launch_skinny_e for the two together (the same reduction length)
+  const int kt = (a.K + 8 * elem<ET>::per16 - 1) / (8 * elem<ET>::per16);
+  auto tiles = [&](int tm, int tn) {
+    auto of = [&](const GemmArgs& g, long long m) { return ((m + 16 * tm - 1) / (16 * tm)) * ((g.Ncols + 16 * tn - 1) / (16 * tn)); };
+    return of(a, rows_a) + of(b, rows_b);
+  };
+  constexpr int fill = sizeof(ET) == 2 ? 192 : 384;
+  if (tiles(4, 4) >= fill) return launch_pair_t<ET, 4, 4, 4, 2>(a, rows_a, b, rows_b, st);
+  if (tiles(2, 4) >= fill) return launch_pair_t<ET, 2, 4, 4, 3>(a, rows_a, b, rows_b, st);
+  const bool small = tiles(2, 2) < 192;
+  if (kt > 8) return small ? launch_pair_t<ET, 1, 1, 8, 8>(a, rows_a, b, rows_b, st) : launch_pair_t<ET, 2, 2, 8, 4>(a, rows_a, b, rows_b, st);
+  return small ? launch_pair_t<ET, 1, 1, 4, 4>(a, rows_a, b, rows_b, st) : launch_pair_t<ET, 2, 2, 4, 4>(a, rows_a, b, rows_b, st);
+}
+int launch_skinny_pair(int dtype, const GemmArgs& a, long long rows_a, const GemmArgs& b, long long rows_b, hipStream_t st) {
+  return dtype == LAUD_BF16 ? launch_pair_e<bf16_t>(a, rows_a, b, rows_b, st) : launch_pair_e<float>(a, rows_a, b, rows_b, st);
+}
+
 // The line lies where the tiled kernel of laud_gemm.hip gets the chip filled, counted in 64 x 64 output tiles: there this
 // kernel's 64 x 64 tiles stop fitting the chip in one round.  Measured on the four ResNet stages at 1 to 64 images and
 // activation ratios 0.5 and 0.86 (bf16): the 3x3 wins up to about 260 tiles with 18 slices or more (stage 4, 42 images: 25
@@ -477,11 +548,20 @@ bool skinny_wanted(int mode, int dtype, const GemmArgs& a, long long cap_rows) {
   return cap_rows < (1 << 20) && t <= most;
 }
 
+// ... and for two 1x1s in one launch: together they have to fit the chip in one round too.  (RegNetY-800MF, first block of stage 3 at
+// four images, 245 + 65 tiles: 27.8 us in two launches, 28.5 in one; ResNet stage 4 at four images, 104 + 128: 27.5 and 23.3.)
+bool skinny_pair_wanted(int dtype, const GemmArgs& a, long long rows_a, const GemmArgs& b, long long rows_b) {
+  auto tiles = [](const GemmArgs& g, long long m) { return ((m + 63) / 64) * ((g.Ncols + 63) / 64); };
+  return skinny_wanted(M_SD1, dtype, a, rows_a) && skinny_wanted(M_SD1, dtype, b, rows_b) && tiles(a, rows_a) + tiles(b, rows_b) <= 256;
+}
+
 int skinny_init_device() {
   const GemmArgs none{};
   for (int mode : {M_CONV2, M_CONV3, M_DENSE1, M_SD1, M_SD2, M_SD3, M_G2})
     for (int dtype : {LAUD_BF16, LAUD_F32})
       if (launch_skinny(mode, dtype, none, -1, nullptr) != LAUD_OK) return LAUD_ERR_HIP;
+  for (int dtype : {LAUD_BF16, LAUD_F32})
+    if (launch_skinny_pair(dtype, none, -1, none, -1, nullptr) != LAUD_OK) return LAUD_ERR_HIP;
   return LAUD_OK;
 }
 

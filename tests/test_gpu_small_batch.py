@@ -87,3 +87,26 @@ def test_dense_first_conv_before_fused_kernel(case):
     """A dynamic first block whose input width the register-weight first 1x1 does not take, with enough rows for the fused
     3x3 -> 1x1 kernel and no caller-packed weights: the call re-orders them itself, whichever way its first 1x1 runs."""
     body.test_dyn_projection_block(case)
+
+
+# shortcut and first 1x1 in one launch: N, H, W, c_in, m, c_out, stride, S, dtype
+PAIR_CASES = [
+    (1, 1, 1, 8, 8, 16, 1, 1, I.BF16),          # one row each
+    (1, 9, 7, 40, 24, 72, 2, 1, I.F32),         # 20 and 63 rows, ragged columns on both sides
+    (1, 3, 11, 520, 40, 136, 2, 1, I.BF16),     # nine slices: more than one per wave
+    (1, 14, 14, 1024, 512, 2048, 2, 1, I.BF16),  # 32 x 32 tiles
+    (3, 14, 14, 512, 256, 1024, 1, 2, I.BF16),  # 32 x 64
+    (1, 48, 64, 32, 64, 256, 1, 4, I.BF16),     # 64 x 64
+    (2, 28, 28, 96, 64, 256, 1, 4, I.F32),      # float32, 64 x 64
+    # 192 + 64 tiles of 64 x 64 in one launch, 200 + 100 in two.  In float32: over a million outputs of eight mid channels
+    # in bf16, the roundings of h2 (eight products of up to 2^-9 each, of either sign: 8 x 0.2 %), of the shortcut and of the output
+    # (2^-9 each) add up to 2 % of |ref| + rms at the worst, in one launch and in two (whose outputs are equal bit for bit).
+    (1, 64, 64, 16, 8, 192, 1, 4, I.F32), (1, 64, 100, 16, 8, 128, 1, 4, I.F32),
+]
+
+
+@pytest.mark.parametrize("case", PAIR_CASES)
+def test_few_rows_shortcut_and_first_conv(case):
+    body.test_dyn_projection_block((*case, True, "bern"))
+    N, H, W, ci, m, co, stride, _, dt = case
+    body.test_static_projection_block((N, H, W, ci, m, co, stride, dt))
