@@ -342,6 +342,7 @@ struct HeadArgs {
   FastDiv d_hw, d_w, d_s;  // set by launch_head
   // rows = the pixels of listed samples (layer gate ahead of a spatially static first 1x1): slist [scap] ascending kept
   // sample ids, *scount of them valid (device), hw pixels per sample; m_rows = scap * hw is the capacity.  Null: all rows.
+  // scap 0: a list that ends with its last valid entry (m_rows: N * hw).
   const int32_t* slist;
   const int32_t* scount;
   int scap;

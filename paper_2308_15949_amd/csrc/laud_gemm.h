@@ -34,6 +34,7 @@ struct GemmArgs {
   int D, G;              // CS: groups per sample, channels per group
   int row_tiles, col_tiles;
   int group_rows, tiles_per_group;  // CONV1: pixel lists are kept per group of samples
+  int hw;                // CONV1: pixels of a sample where `list` holds samples, whose pixels are all rows; 0: pixel lists
   int m_rows;            // DENSE1, SD1..3: number of rows (all output pixels), known on the host
   int stride, Ho, Wo;    // SD1, SD2: spatial stride and output size (H, W are the input size)
   int gw;                // G2: channels per group of the 3x3

@@ -338,9 +338,15 @@ __global__ __launch_bounds__(head::kThreads) void k_head(const HeadArgs a) {
     // count lives on the device, so the height is decided here (as for pixel lists), and the sample ids of this lane's
     // rows are requested for both candidate heights together with the count.
     const int r8 = 8 * wv + l8;
+    // A list without spare entries (scap 0) is read behind its count.
+    int last = a.scap - 1;
+    if (a.scap == 0) {
+      last = __builtin_nontemporal_load(a.scount) - 1;  // (a load of its own: the other one is not to be waited for)
+      if (last < 0) return;
+    }
     auto pix_of = [&](int row) __attribute__((always_inline)) {
       const int slot = row / a.hw;
-      return a.slist[min(slot, a.scap - 1)] * a.hw + (row - slot * a.hw);
+      return a.slist[min(slot, last)] * a.hw + (row - slot * a.hw);
     };
     const int p2[1] = {pix_of((int)blockIdx.x * 64 + r8)};
     const int p4[2] = {pix_of((int)blockIdx.x * 128 + r8), pix_of((int)blockIdx.x * 128 + 64 + r8)};

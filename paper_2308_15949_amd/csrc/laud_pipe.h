@@ -118,7 +118,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void k_pipe(const PipeArgs ka) {
       const int g = fast_div(rt, ka.tpg);
       rt -= g * a.tiles_per_group;
       listp += (size_t)g * a.group_rows;
-      M = a.count[g];
+      M = a.count[g] * (a.hw ? a.hw : 1);
     } else if constexpr (LISTED) {
       M = *a.count * (MODE == M_U1 ? (a.S + 2) * (a.S + 2) : a.S * a.S);
     } else {
@@ -278,7 +278,12 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void k_pipe(const PipeArgs ka) {
     unsigned pix = (unsigned)rho;
     if (live) {
       if constexpr (MODE == M_CONV1) {
-        o = listp[rho];
+        if (a.hw) {
+          const int p = fast_div(rho, ka.howo);
+          o = a.list[p] * a.hw + (rho - p * a.hw);
+        } else {
+          o = listp[rho];
+        }
         pix = (unsigned)o;
       } else if constexpr (MODE == M_CONV2 || MODE == M_G2 || MODE == M_CONV3) {
         const int p = fast_div(rho, ka.ss), j = rho - p * (a.S * a.S), q = a.list[p];
@@ -625,7 +630,7 @@ static int launch_pipe_t(const GemmArgs& args, long long cap_rows, int nsamples,
   k.ct = make_fast_div(a.col_tiles); k.tpg = make_fast_div(std::max(a.tiles_per_group, 1));
   k.s = make_fast_div(a.S); k.ss = make_fast_div(a.S * a.S);
   k.pps = make_fast_div(std::max((oH / a.S) * (oW / a.S), 1)); k.wp = make_fast_div(std::max(oW / a.S, 1));
-  k.howo = make_fast_div(std::max(a.Ho * a.Wo, 1)); k.wo = make_fast_div(std::max(a.Wo, 1)); k.grp = make_fast_div(std::max(a.G, 1));
+  k.howo = make_fast_div(std::max(MODE == M_CONV1 ? a.hw : a.Ho * a.Wo, 1)); k.wo = make_fast_div(std::max(a.Wo, 1)); k.grp = make_fast_div(std::max(a.G, 1));
   const int lds = pipe::lds_bytes<MODE, BM, BN, NS>() + (MODE == M_DENSE1 && a.wmask ? (a.K + BKE - 1) / BKE * BKE * 4 + 256 : 0);
   hipLaunchKernelGGL((k_pipe<MODE, ET, BM, BN, WM, WN, KS, NS>), grid, dim3(NT), lds, st, k);
   return check_launch();

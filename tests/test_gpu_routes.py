@@ -24,6 +24,9 @@ def exact_list(t, mask):
     (5, 56, 56, 256, 64, 4, I.BF16),      # 64-wide kernel
     (22, 14, 14, 1024, 256, 2, I.BF16),   # register-weight first 1x1, fused 3x3 -> 1x1
     (40, 28, 28, 512, 128, 4, I.BF16),    # tiled kernels
+    (22, 14, 14, 1024, 256, 14, I.BF16),  # patches that are whole samples, on the last two
+    (40, 28, 28, 512, 128, 28, I.BF16),
+    (22, 28, 28, 24, 40, 28, I.F32),
 ])
 @pytest.mark.parametrize("active", [1, 0.3])
 def test_list_of_exact_length(G, case, active):  # noqa: F811
@@ -44,7 +47,10 @@ def test_list_of_exact_length(G, case, active):  # noqa: F811
     check_dyn(D.to_host(xd), x, hb, S, mask)
 
 
-@pytest.mark.parametrize("case", [(3, 16, 16, 64, 64, 256, 2, 4), (8, 112, 112, 64, 64, 256, 2, 8)])
+@pytest.mark.parametrize("case", [
+    (3, 16, 16, 64, 64, 256, 2, 4), (8, 112, 112, 64, 64, 256, 2, 8),
+    (30, 56, 55, 64, 104, 104, 2, 28), (30, 28, 28, 512, 256, 1024, 2, 14),  # whole samples
+])
 def test_projection_list_of_exact_length(G, case):  # noqa: F811
     t, L, D = G.torch, G.L, G.D
     N, H, W, ci, m, co, stride, S = case

@@ -172,6 +172,11 @@ CASES = {
     "fused": ("identity", "dyn", 22, 14, 14, 1024, 256, 2, 0.3, True, False),
     "fused_packed": ("identity", "masker", 22, 14, 14, 1024, 256, 2, 0.5, True, True, None, 0, True, True),
     "projection_before_fused": ("first", "dynamic", 22, 14, 14, 320, 256, 1024, 1, 2, 0.5),
+    # patches that are whole samples
+    "samples_fused": ("identity", "dyn", 22, 14, 14, 1024, 256, 14, 0.3, True, False),
+    "samples_fused_none": ("identity", "dyn", 22, 14, 14, 1024, 256, 14, 0.0, True, False),
+    "samples_tiled_f32": ("identity", "dyn", 22, 28, 28, 24, 40, 28, 0.3, False),
+    "samples_projection_f32": ("first", "dynamic", 22, 28, 27, 24, 16, 40, 2, 14, 0.4, False),
     # fused masker
     "masker": ("identity", "masker", 3, 12, 12, 72, 24, 4, 0.5),
     "masker_f32_gates": ("identity", "masker", 26, 14, 14, 32, 8, 1, 0.5, False, False, None, 0, False, True),
