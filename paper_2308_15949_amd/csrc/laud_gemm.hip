@@ -897,11 +897,18 @@ static int launch_fused_head(const laud_fmap& fx, const laud_bottleneck* p, cons
 // against listed: stage 1, 16 images 25 / 27 / 30 / 36 against 30 / 33 / 39 / 46 us; stage 2, 32 images 35 / 35 / 39 / 45
 // against 38 / 39 / 46 / 51 us.  Nearest the limits the sides meet at 0.15: RegNetY-800MF stage 2, 64 images 55 / 71 / 86 against
 // 51 / 74 / 91 us at 0.15 / 0.5 / 0.86, stage 1, 32 images 40 / 54 / 67 against 44 / 62 / 77 us.
+// Long reductions whose 64 x 128 tiles fit the chip in one round (launch_pipe_rule) take the same time whatever their rows: stage 4,
+// 48 / 64 images at 0.05 to 0.5 dense 42 to 46 / 43 to 46, listed 46 to 50 / 47 to 51.
+// Patches that are whole samples (`whole`) need no lists: only where the small tiles take it, layer skipping runs this 1x1 on
+// every pixel (stage 1, 16 images, 0.15 / 0.4: 23.1 / 26.1 us dense, 20.5 / 24.4 on the listed samples; stage 2, 32 images 24.8 /
+// 29.0 and 19.8 / 26.5).
 constexpr double kDenseConv1Bytes = 40e6, kDenseConv1Flops = 4e9;
-static bool dense_conv1_wanted(int dtype, const laud_bottleneck* p, long long npix) {
+static bool dense_conv1_wanted(int dtype, const laud_bottleneck* p, long long npix, bool whole) {
   GemmArgs a{};
   a.K = p->c_in; a.Ncols = p->c_mid;
   if (skinny_wanted(M_SD1, dtype, a, npix)) return true;
+  if (whole) return false;
+  if (dtype == LAUD_BF16 && p->c_in >= 512 && p->c_mid > 64 && (npix + 63) / 64 * ((p->c_mid + 127) / 128) <= 256) return true;
   return dtype == LAUD_BF16 && (double)npix * (p->c_in + p->c_mid) * 2 <= kDenseConv1Bytes &&
          2.0 * npix * p->c_in * p->c_mid <= kDenseConv1Flops;
 }
@@ -982,7 +989,7 @@ static int run_dyn_block(const void* x, laud_fmap fx, const laud_bottleneck* p, 
   const InactiveCopy copy = inactive_copy(x, out, fx, S, idx, count);
   GemmArgs a{};
   a.H = fx.H; a.W = fx.W; a.S = S; a.D = 1; a.G = 1; a.cmask = nullptr;
-  if (dense_conv1_wanted(fx.dtype, p, npix) && !head_used(fx.dtype, p, npix)) {
+  if (dense_conv1_wanted(fx.dtype, p, npix, Hp * Wp == 1) && !head_used(fx.dtype, p, npix)) {
     if ((rc = run_dense_conv1(fx, p, x, h1, st)) != LAUD_OK) return rc;
   } else {
     // samples per group of the dilated pixel lists: about 1.5k pixels, so that a group's ragged last
@@ -1343,7 +1350,7 @@ static int run_dyn_projection(const void* x, laud_fmap fx, const laud_bottleneck
   a.A = x; a.Wt = w_sc; a.scale = s_sc; a.shift = t_sc; a.Out = out; a.K = p->c_in; a.ldw = p->c_in;
   a.Ncols = p->c_out; a.lda = p->c_in; a.ldo = p->c_out; a.relu = p->relu_out ? 1 : 0; a.m_rows = (int)nout;
   a.list = idx; a.count = count;
-  if (dense_conv1_wanted(fx.dtype, p, npix) && !head_used(fx.dtype, p, npix)) {
+  if (dense_conv1_wanted(fx.dtype, p, npix, Hp * Wp == 1) && !head_used(fx.dtype, p, npix)) {
     // (input widths the register-weight first 1x1 does not take, in front of the fused 3x3 -> 1x1 kernel: the dense launch
     // carries no re-ordering of its weights)
     if (tail_used(fx.dtype, p, e, nout) && !p->packed &&

@@ -696,7 +696,12 @@ static int launch_pipe_rule(const GemmArgs& a, long long cap_rows, int nsamples,
       if (tiles(m, 128, 256) >= 192 && (MODE == M_SD1 ? a.Ncols >= 256 : kt >= 8 && a.Ncols >= 1024)) return t128x256();
       return kt > 5 && MODE != M_SD1 && tiles(m, 128, 128) >= 192 ? t128x128() : t128x64();
     } else if constexpr (MODE == M_CONV1 || MODE == M_DENSE1) {
+      // (blocks of stage 4, layer skipping, 48 / 64 images at 0.15: 46.4 / 47.2 us with 128 x 128, 42.7 / 44.2 with 64 x 128)
       // 6272 rows, 2048 -> 512 channels: 128 x 64 / 128 x 128 39 / 23 us; 100352 rows, 512 -> 128: 24 / 24 us, 401408 rows, 256 -> 64: 35 / 48
+      if constexpr (MODE == M_CONV1) {
+        if (init) rc = t64x128k();
+        else if (kt >= 8 && a.Ncols > 64 && tiles(rows, 64, 128) <= 256) return t64x128k();
+      }
       if (init) return all(t128x64, t128x128);
       return kt >= 16 && a.Ncols >= 256 ? t128x128() : t128x64();
     } else {  // the unfused schedule

@@ -27,6 +27,11 @@ def exact_list(t, mask):
     (22, 14, 14, 1024, 256, 14, I.BF16),  # patches that are whole samples, on the last two
     (40, 28, 28, 512, 128, 28, I.BF16),
     (22, 28, 28, 24, 40, 28, I.F32),
+    (17, 28, 28, 64, 72, 28, I.BF16),     # whole samples on narrow maps, which other patches run the first 1x1 of densely
+    (21, 28, 28, 512, 136, 28, I.BF16),   # ... long reductions: 2 x 258 tiles of 64 x 128, one round of 128 x 64 ...
+    (9, 28, 28, 520, 136, 28, I.BF16),    # ... and 2 x 111: one round
+    (66, 7, 7, 520, 584, 1, I.BF16),      # 51 x 5 tiles: every pixel; 52 x 5: listed
+    (67, 7, 7, 520, 584, 1, I.BF16),
 ])
 @pytest.mark.parametrize("active", [1, 0.3])
 def test_list_of_exact_length(G, case, active):  # noqa: F811
