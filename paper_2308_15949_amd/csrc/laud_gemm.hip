@@ -897,6 +897,8 @@ static int launch_fused_head(const laud_fmap& fx, const laud_bottleneck* p, cons
 // against listed: stage 1, 16 images 25 / 27 / 30 / 36 against 30 / 33 / 39 / 46 us; stage 2, 32 images 35 / 35 / 39 / 45
 // against 38 / 39 / 46 / 51 us.  Nearest the limits the sides meet at 0.15: RegNetY-800MF stage 2, 64 images 55 / 71 / 86 against
 // 51 / 74 / 91 us at 0.15 / 0.5 / 0.86, stage 1, 32 images 40 / 54 / 67 against 44 / 62 / 77 us.
+// Past the limits, with k_pipe for both: stage 2, 48 images 31 / 33 / 50 against 27 / 31 / 56 us at 0.05 / 0.15 / 0.86, stage 1, 48
+// images 36 / 38 / 63 against 28 / 34 / 71.
 // Long reductions whose 64 x 128 tiles fit the chip in one round (launch_pipe_rule) take the same time whatever their rows: stage 4,
 // 48 / 64 images at 0.05 to 0.5 dense 42 to 46 / 43 to 46, listed 46 to 50 / 47 to 51.
 // Patches that are whole samples (`whole`) need no lists: only where the small tiles take it, layer skipping runs this 1x1 on

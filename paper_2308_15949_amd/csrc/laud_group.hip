@@ -5,7 +5,8 @@
 // workgroup keeps its 64 channels' weights in registers, in MFMA order, and walks over tiles of 64 rows: all nine taps' rows are
 // requested at once (72 KB of LDS, so that two workgroups share a compute unit and hide each other's waits), waited for once and
 // multiplied without a barrier.  (Loaded per tile, the weights cost more than the rows: in MFMA order a lane's 16 bytes lie in a
-// cache line of their own.)  An XCD walks over one contiguous eighth of the rows, where its taps find their neighbours in its L2.
+// cache line of their own.)  RegNetY-800MF blocks of 128 images at ratio 0.5, as a general tile / here: stage 1 93.7 / 85.0 us, stage 2 80.0 /
+// 73.6, stage 3 61.3 / 56.6.  An XCD walks over one contiguous eighth of the rows, where its taps find their neighbours in its L2.
 #include "laud_common.h"
 #include "laud_gemm.h"
 #include "laud_tile_util.h"

@@ -692,7 +692,9 @@ static int launch_pipe_rule(const GemmArgs& a, long long cap_rows, int nsamples,
       if (init) return all(t128x64, t64x128k, t128x128, t128x256);
       if (a.Ncols <= 64) return t128x64();
       const long long m = MODE == M_CONV3 ? rows / 2 : rows;
-      if (kt >= 8 && tiles(rows, 64, 128) <= 256) return t64x128k();
+      // (a tile's LDS leaves a compute unit no room for a workgroup that copies: stage 4 out of place, 16 images, 0.15 / 0.86 34.2 / 38.3 us
+      // with these, 34.9 / 36.3 with 128 x 64)
+      if (kt >= 8 && tiles(rows, 64, 128) + a.cp.nblocks <= 256) return t64x128k();
       if (tiles(m, 128, 256) >= 192 && (MODE == M_SD1 ? a.Ncols >= 256 : kt >= 8 && a.Ncols >= 1024)) return t128x256();
       return kt > 5 && MODE != M_SD1 && tiles(m, 128, 128) >= 192 ? t128x128() : t128x64();
     } else if constexpr (MODE == M_CONV1 || MODE == M_DENSE1) {
