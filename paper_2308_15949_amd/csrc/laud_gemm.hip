@@ -30,9 +30,9 @@
 //          output channels / reduction channels gathered through the sample's kept-group list,
 //          i.e. the weight gather is fused into the conv (Sec. 3.4).
 //
-// k_gemm<MODE, ET, BM, BN, WGN> of this file: CS1..3 for group widths that do not fill 16-byte chunks, where weights are gathered
-// element by element through registers; a BM x BN tile with 2 x WGN waves of 32x32 MFMA tiles, both operands staged through LDS
-// in 128-byte K slices.
+// k_gemm<MODE, ET, BM, BN, WGN> of this file: CS1..3 for group widths that do not fill 16-byte chunks, and CS2 / CS3 for
+// weights past 2 GiB.  Kept channels are gathered element by element, through 64-bit pointers and registers; a BM x BN tile with
+// 2 x WGN waves of 32x32 MFMA tiles, both operands staged through LDS in 128-byte K slices.
 // Accumulation is float32 (bf16: v_mfma_f32_32x32x16_bf16, fp32: v_mfma_f32_32x32x2_f32).
 #include "laud_common.h"
 #include "laud_gemm.h"
@@ -45,7 +45,7 @@ namespace laud {
 
 constexpr int kMaxGroups = 1024;  // channel-skip decisions per sample the kernels can hold in LDS
 
-// Element-wise form of the kept-channel gather for group widths that do not fill a 16-byte chunk: the
+// Element-wise form of the kept-channel gather, for any group width (a 16-byte chunk may straddle groups): the
 // elements at offsets eoff[] of a weight row; every load is issued (an element that must read as zero has a valid
 // offset and is dropped afterwards), so the loads of a slice stay in flight together.
 // UE = elements moved per load (1, 2 or 4: a group is a whole number of such units, so a unit never straddles two
@@ -590,6 +590,22 @@ int gemm_init_device() {
   return gemm_request_lds_mode<M_CS3>();
 }
 
+// The kernels address an operand through a buffer descriptor with 32-bit byte offsets and keep the upper
+// half of that range for "reads as zero": the activations of a layer have to stay below 2 GiB, including
+// the distance the 3x3's descriptor is moved back by (one row and one pixel, `tap_rowlen` pixels per row) and
+// the same distance a tap can reach forward.
+static bool operand_too_big(long long rows, long long row_elems, int dtype, long long tap_rowlen = 0) {
+  const unsigned long long eb = elem_bytes(dtype);
+  const unsigned long long shift = tap_rowlen > 0 ? (unsigned long long)(tap_rowlen + 1) * row_elems * eb : 0;
+  return (unsigned long long)rows * (unsigned long long)row_elems * eb + 2 * shift >= 0x7f000000ull;
+}
+
+// ... and one weight matrix at no more than 2 GiB (no tap reaches past it).  The exception are w2 and w3 in channel skipping,
+// whose larger matrices k_gemm reads through 64-bit pointers (launch_gemm).
+static bool weights_too_big(long long rows, long long row_elems, int dtype) {
+  return (unsigned long long)rows * (unsigned long long)row_elems * elem_bytes(dtype) > 0x80000000ull;
+}
+
 template <int MODE>
 static int launch_gemm(int dtype, const GemmArgs& a, long long cap_rows, int nsamples, hipStream_t st) {
   constexpr int kStage[14] = {LAUD_STAGE_CONV1, LAUD_STAGE_CONV2, LAUD_STAGE_CONV3, LAUD_STAGE_CS1, LAUD_STAGE_CS2,
@@ -600,21 +616,12 @@ static int launch_gemm(int dtype, const GemmArgs& a, long long cap_rows, int nsa
     if (skinny_wanted(MODE, dtype, a, cap_rows)) return launch_skinny(MODE, dtype, a, cap_rows, st);
   }
   if constexpr (MODE >= M_CS1 && MODE <= M_CS3) {
-    if (a.G % (16 / (int)elem_bytes(dtype)) != 0)  // groups that are not whole 16-byte chunks
+    // groups that are not whole 16-byte chunks, and matrices past 32-bit offsets (float32 from c_mid = 7728 on, bf16 from 10928)
+    if (a.G % (16 / (int)elem_bytes(dtype)) != 0 || (MODE != M_CS1 && weights_too_big(a.Ncols, a.ldw, dtype)))
       return dtype == LAUD_BF16 ? launch_gemm_e<MODE, bf16_t>(a, cap_rows, nsamples, st)
                                 : launch_gemm_e<MODE, float>(a, cap_rows, nsamples, st);
   }
   return launch_pipe(MODE, dtype, a, cap_rows, nsamples, st);
-}
-
-// The kernels address an operand through a buffer descriptor with 32-bit byte offsets and keep the upper
-// half of that range for "reads as zero": one operand (activations of a layer, its weights) has to stay
-// below 2 GiB, including the distance the 3x3's descriptor is moved back by (one row and one pixel, `tap_rowlen`
-// pixels per row) and the same distance a tap can reach forward.
-static bool operand_too_big(long long rows, long long row_elems, int dtype, long long tap_rowlen = 0) {
-  const unsigned long long eb = elem_bytes(dtype);
-  const unsigned long long shift = tap_rowlen > 0 ? (unsigned long long)(tap_rowlen + 1) * row_elems * eb : 0;
-  return (unsigned long long)rows * (unsigned long long)row_elems * eb + 2 * shift >= 0x7f000000ull;
 }
 
 // 16-byte loads and stores need 16-byte aligned bases.

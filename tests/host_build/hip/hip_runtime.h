@@ -59,7 +59,7 @@ T shuffle(int kind, T v, int arg) {
   memcpy(&v, &u, sizeof(T));
   return v;
 }
-void launch(dim3 grid, dim3 block, size_t lds_bytes, const char* kernel, const std::function<void()>& body);
+void launch(dim3 grid, dim3 block, size_t lds_bytes, const char* kernel, const void* function, const std::function<void()>& body);
 
 struct Rsrc { const char* base; unsigned bytes; };
 typedef unsigned Chunk __attribute__((ext_vector_type(4)));
@@ -113,4 +113,4 @@ static inline int hipEventSynchronize(hipEvent_t) { return 0; }
 static inline int hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0; return 0; }
 static inline int hipGetSymbolAddress(void** p, const void* s) { *p = const_cast<void*>(s); return 0; }
 #define HIP_SYMBOL(x) ((const void*)&x)
-#define hipLaunchKernelGGL(k, g, b, bytes, stream, ...) host::launch(g, b, bytes, #k, [=] { (k)(__VA_ARGS__); })
+#define hipLaunchKernelGGL(k, g, b, bytes, stream, ...) host::launch(g, b, bytes, #k, reinterpret_cast<const void*>(k), [=] { (k)(__VA_ARGS__); })

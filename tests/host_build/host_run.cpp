@@ -1,11 +1,15 @@
 // Runs the workgroups of a launch one after the other, the threads of each as fibers; see hip/hip_runtime.h.
 #include "hip/hip_runtime.h"
 
+#include <cxxabi.h>
+#include <dlfcn.h>
 #include <signal.h>
 #include <stdio.h>
 #include <sys/mman.h>
 #include <unistd.h>
 
+#include <set>
+#include <string>
 #include <vector>
 
 // Saves the callee-saved registers and the stack of one fiber, goes on with another's.
@@ -45,6 +49,7 @@ char* stacks;
 unsigned char* lds_end;
 size_t lds_size;
 std::vector<Fiber> fibers(kMaxThreads);
+std::set<std::string> launched;  // kernel instances so far
 
 void fail(const char* what, const void* at) {
   fprintf(stderr, "%s %p in %s, workgroup %u, %u of %u, %u, thread %u\n", what, at, kernel_name, block.x, block.y, grid.x, grid.y,
@@ -125,8 +130,14 @@ uint64_t wave_op(int kind, uint64_t value, int arg) {
   return current->result;
 }
 
-void launch(dim3 g, dim3 b, size_t lds_bytes, const char* kernel, const std::function<void()>& body) {
+void launch(dim3 g, dim3 b, size_t lds_bytes, const char* kernel, const void* function, const std::function<void()>& body) {
   kernel_name = kernel;
+  Dl_info info;
+  if (dladdr(function, &info) && info.dli_sname && info.dli_saddr == function)
+    if (char* const name = abi::__cxa_demangle(info.dli_sname, nullptr, nullptr, nullptr)) {
+      launched.insert(name);
+      free(name);
+    }
   kernel_body = &body;
   grid = g;
   block_size = b;
@@ -192,6 +203,14 @@ extern "C" void* host_alloc(size_t bytes, int front) {
   mprotect(p, kPage, PROT_NONE);
   mprotect(p + kPage + pages, kPage, PROT_NONE);
   return front ? p + kPage : p + kPage + pages - b;
+}
+
+// The kernel instances launched so far, a line each; returns the bytes there are.
+extern "C" size_t host_launched(char* out, size_t room) {
+  std::string all;
+  for (const std::string& k : host::launched) all += k + "\n";
+  if (room > all.size()) memcpy(out, all.c_str(), all.size() + 1);
+  return all.size();
 }
 
 extern "C" int laud_probe_mfma() { return 0; }

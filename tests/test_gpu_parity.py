@@ -408,6 +408,40 @@ def test_channel_skip(G, case, inplace):
     assert_close(got, ref, TOL[dt], "channel skipping")
 
 
+@pytest.mark.parametrize("m,dt", [(7728, I.F32), (10928, I.BF16)])
+def test_channel_skip_weights_past_2gib(G, m, dt):
+    """The smallest w2 past 32-bit byte offsets, in groups of sixteen channels: the kept groups, first and last among them, as the
+    block that has no others.  (The weights of dropped groups are zero here and are not to be read.)"""
+    t, L, D = G.torch, G.L, G.D
+    C, g, N, H, W = 8, 16, 2, 5, 3
+    groups = [0, m // g // 2, m // g - 2, m // g - 1]
+    kept = np.concatenate([np.arange(q * g, q * g + g) for q in groups])
+    x = I.feature_map(91, N, H, W, C, dt)
+    hb = I.bottleneck_params(92, C, len(kept), C, dt, True)
+    ref = O.channel_skip_bottleneck(x, oracle_params(hb), np.ones((N, len(groups)), np.uint8))
+    on = t.from_numpy(kept).cuda()
+    xd, db = D.to_device(x, dt), D.DeviceBottleneck(hb)
+    zeros = lambda *shape, dtype=xd.dtype: t.zeros(shape, dtype=dtype, device="cuda")  # noqa: E731
+    w1, w2, w3 = zeros(m, C), zeros(m, 3, 3, m), zeros(C, m)
+    assert w2.numel() * w2.element_size() > 1 << 31
+    w1[on] = db.w1
+    for i, c in enumerate(kept):
+        w2[int(c)][:, :, on] = db.w2[i]
+    w3[:, on] = db.w3
+    affine = [zeros(m, dtype=t.float32) for _ in range(4)]
+    for wide, v in zip(affine, (db.s1, db.t1, db.s2, db.t2)):
+        wide[on] = v
+    desc = L.make_bottleneck(w1, w2, w3, *affine, db.s3, db.t3, True)
+    cm = np.zeros((N, m // g), np.uint8)
+    cm[:, groups] = 1
+    out = t.full_like(xd, 123.0)
+    ws = D.workspace(L.workspace_size(L.binding.OP_CHANNEL_SKIP, L.fmap_of(xd), desc, m // g))
+    ws.fill_(0xFF)
+    L.laud_channel_skip_conv(xd, L.fmap_of(xd), desc, t.from_numpy(cm).cuda(), m // g, out, ws)
+    t.cuda.synchronize()
+    assert_close(D.to_host(out), ref, TOL[dt], "channel skipping")
+
+
 # ------------------------------------------------------------------------------------------
 # full-size workload of the benchmark (config 2), sampled images
 # ------------------------------------------------------------------------------------------
