@@ -605,6 +605,10 @@ static bool operand_too_big(long long rows, long long row_elems, int dtype, long
 static bool weights_too_big(long long rows, long long row_elems, int dtype) {
   return (unsigned long long)rows * (unsigned long long)row_elems * elem_bytes(dtype) > 0x80000000ull;
 }
+static bool block_weights_too_big(const laud_bottleneck* p, const laud_group_se* e, int dtype) {
+  return weights_too_big(p->c_mid, p->c_in, dtype) || weights_too_big(p->c_mid, 9LL * (e ? e->group_width : p->c_mid), dtype) ||
+         weights_too_big(p->c_out, p->c_mid, dtype);
+}
 
 template <int MODE>
 static int launch_gemm(int dtype, const GemmArgs& a, long long cap_rows, int nsamples, hipStream_t st) {
@@ -984,6 +988,7 @@ static int run_dyn_block(const void* x, laud_fmap fx, const laud_bottleneck* p, 
   const int Hp = fx.H / S, Wp = fx.W / S;
   if ((size_t)Hp * Wp > 60000) return LAUD_ERR_UNSUPPORTED;  // per-sample patch mask lives in LDS
   if (e && (rc = validate_group_se(p, e, fx)) != LAUD_OK) return rc;
+  if (block_weights_too_big(p, e, fx.dtype)) return LAUD_ERR_UNSUPPORTED;
   const DynWs L = dyn_ws_layout(fx, p->c_mid);
   if (!ws || ws_bytes < L.bytes) return LAUD_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
@@ -1073,6 +1078,7 @@ extern "C" int laud_masker_dyn_bottleneck(const void* x, laud_fmap fx, const lau
   if (rc != LAUD_OK) return rc;
   if (!w || !mask || !idx || !count || S <= 0 || fx.H % S || fx.W % S) return LAUD_ERR_INVALID_ARG;
   if (p->c_in > 4096) return LAUD_ERR_UNSUPPORTED;  // masker weights are held in LDS by conv1
+  if (block_weights_too_big(p, nullptr, fx.dtype)) return LAUD_ERR_UNSUPPORTED;
   const int Hp = fx.H / S, Wp = fx.W / S;
   const DynWs L = dyn_ws_layout(fx, p->c_mid);
   if (!ws || ws_bytes < L.bytes) return LAUD_ERR_WORKSPACE;
@@ -1197,6 +1203,7 @@ extern "C" int laud_dyn_bottleneck_unfused(const void* x, laud_fmap fx, const la
   const long long npatch = (long long)fx.N * Hp * Wp, npix = (long long)fx.N * fx.H * fx.W;
   if (npatch * E * E > 0x7fffffffLL / 2) return LAUD_ERR_UNSUPPORTED;
   if (operand_too_big(npatch * E * E, fx.C > p->c_mid ? fx.C : p->c_mid, fx.dtype)) return LAUD_ERR_UNSUPPORTED;
+  if (block_weights_too_big(p, nullptr, fx.dtype)) return LAUD_ERR_UNSUPPORTED;
   const UnfusedWs L = unfused_ws_layout(fx, p->c_mid, S);
   if (!ws || ws_bytes < L.bytes) return LAUD_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
@@ -1259,6 +1266,7 @@ extern "C" int laud_static_bottleneck(const void* x, laud_fmap fx, const laud_bo
   const long long npix = (long long)fx.N * fx.H * fx.W, nout = (long long)fx.N * Ho * Wo;
   if (npix > 0x7fffffffLL / 2) return LAUD_ERR_UNSUPPORTED;
   if (operand_too_big(npix, p->c_in > p->c_mid ? p->c_in : p->c_mid, fx.dtype, fx.W)) return LAUD_ERR_UNSUPPORTED;
+  if (block_weights_too_big(p, nullptr, fx.dtype) || weights_too_big(p->c_out, p->c_in, fx.dtype)) return LAUD_ERR_UNSUPPORTED;
   if (misaligned16(x) || misaligned16(out) || misaligned16(w_sc) || block_params_misaligned(p)) return LAUD_ERR_UNSUPPORTED;
   if (partial_overlap(x, out, (size_t)npix * fx.C * elem_bytes(fx.dtype), (size_t)nout * p->c_out * elem_bytes(fx.dtype)))
     return LAUD_ERR_INVALID_ARG;
@@ -1342,6 +1350,7 @@ static int run_dyn_projection(const void* x, laud_fmap fx, const laud_bottleneck
     return LAUD_ERR_INVALID_ARG;
   int rc;
   if (e && (rc = validate_group_se(p, e, fx)) != LAUD_OK) return rc;
+  if (block_weights_too_big(p, e, fx.dtype) || weights_too_big(p->c_out, p->c_in, fx.dtype)) return LAUD_ERR_UNSUPPORTED;
   const DynProjWs L = dyn_proj_ws_layout(fx, p->c_mid, p->c_out, stride);
   if (!ws || ws_bytes < L.bytes) return LAUD_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
@@ -1437,6 +1446,7 @@ extern "C" int laud_channel_skip_conv(const void* x, laud_fmap fx, const laud_bo
   if (rc != LAUD_OK) return rc;
   if (!cmask || D <= 0 || p->c_mid % D) return LAUD_ERR_INVALID_ARG;
   if (D > kMaxGroups || fx.N > 65535) return LAUD_ERR_UNSUPPORTED;
+  if (weights_too_big(p->c_mid, p->c_in, fx.dtype)) return LAUD_ERR_UNSUPPORTED;
   const CsWs L = cs_ws_layout(fx, p->c_mid);
   if (!ws || ws_bytes < L.bytes) return LAUD_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;

@@ -256,6 +256,43 @@ def test_operands_beyond_the_32_bit_offset_range_are_refused(lib):
     assert cs(vp(FAKE), big, C.byref(p), vp(FAKE), 4, vp(FAKE), vp(FAKE), 1 << 40, None) == B.ERR_UNSUPPORTED
 
 
+def test_weights_beyond_the_32_bit_offset_range_are_refused(lib):
+    """The same for one weight matrix of more than 2 GiB, in every entry point that takes a block; 2 GiB itself fits.  Channel skipping
+    takes w2 and w3 of any size."""
+    vp = C.c_void_p
+    v = [vp(FAKE)] * 5
+    far = vp(FAKE + (1 << 40))
+
+    def statuses(c_in, m, c_out, gw=None):
+        """Status of every block call with a workspace that is too small: reached only by accepted weights."""
+        p = _bn(c_in, m, c_out)
+        a, first = [vp(FAKE), B.Fmap(1, 2, 2, c_in, B.F32), C.byref(p)], [v[0], v[1], v[2], 2]
+        r = {"static": lib.laud_static_bottleneck(*a, *first, far, vp(FAKE), 0, None),
+             "projection": lib.laud_dyn_projection_bottleneck(*a, *first, 1, v[3], v[4], far, vp(FAKE), 0, None)}
+        if c_in == c_out:
+            r["channel"] = lib.laud_channel_skip_conv(*a, v[0], m // 8, vp(FAKE), vp(FAKE), 0, None)
+            r["dyn"] = lib.laud_dyn_bottleneck(*a, 1, v[0], v[1], vp(FAKE), vp(FAKE), 0, None)
+            r["unfused"] = lib.laud_dyn_bottleneck_unfused(*a, 1, v[0], v[1], vp(FAKE), vp(FAKE), 0, None)
+            if c_in <= 4096:
+                r["masker"] = lib.laud_masker_dyn_bottleneck(*a, 1, v[0], 0.0, None, v[1], v[2], v[3], None, None, vp(FAKE), vp(FAKE), 0, None)
+        if gw:
+            e = B.GroupSE(gw, 0, None, None, None, None)
+            r["group"] = lib.laud_dyn_group_se_bottleneck(*a, C.byref(e), 1, v[0], v[1], vp(FAKE), vp(FAKE), 0, None)
+            r["group_projection"] = lib.laud_dyn_group_se_projection_bottleneck(*a, C.byref(e), *first, 1, v[3], v[4], far, vp(FAKE), 0, None)
+        return r
+
+    fits, refused = {B.ERR_WORKSPACE}, {B.ERR_UNSUPPORTED}
+    assert set(statuses(64, 1024, 64, 64).values()) == fits
+    big = statuses(64, 7728, 64)                                        # w2: 2.15 GB; channel skipping takes it (966 groups)
+    assert big.pop("channel") == B.ERR_WORKSPACE and set(big.values()) == refused
+    assert set(statuses(64, 7720, 64).values()) == fits                 # ... 2.145 GB: below 2 GiB = 2.147 GB
+    grouped = statuses(64, 7744, 64, 64)                                # a group convolution's w2 is small
+    assert grouped["group"] == grouped["group_projection"] == B.ERR_WORKSPACE and grouped["dyn"] == B.ERR_UNSUPPORTED
+    wide = statuses(1 << 19, 1024, 1 << 19)                             # w1 and w3: 2 GiB; w_sc: 1 TiB
+    assert {wide.pop("static"), wide.pop("projection")} == refused and set(wide.values()) == fits
+    assert set(statuses((1 << 19) + 8, 1024, (1 << 19) + 8).values()) == refused
+
+
 def test_bench_refuses_more_than_one_gpu():
     """bench.py is a one-GPU benchmark: --gpus N with N > 1 exits with a message before touching any GPU."""
     import subprocess
