@@ -44,6 +44,11 @@ template <int MODE, int BM, int BN, int NS> __host__ __device__ constexpr int ld
   return ring_bytes<BM, BN, NS>() + 2 * BN * 4 + 3 * BM * 4 + (MODE == M_SD1 ? BM * 4 : 0) +
          (MODE >= M_CS1 && MODE <= M_CS3 ? kMaxGroups * 4 + 16 : 0);
 }
+// ... the masker's weights: K floats to whole slices, brought in pieces of 64
+constexpr int kMaxMaskerK = 4096;
+template <typename ET> __host__ __device__ constexpr int masker_bytes(int K) {
+  return ((K + 8 * elem<ET>::per16 - 1) / (8 * elem<ET>::per16) * (8 * elem<ET>::per16) + 63) / 64 * 256;
+}
 }  // namespace pipe
 
 // Waits until all but the `behind` slices requested last (0 .. MOST of them, L loads each, and RL loads more behind those) have landed.
@@ -588,7 +593,7 @@ static int pipe_request_lds() {
   if (hipGetDevice(&dev) != hipSuccess) return LAUD_ERR_HIP;
   const unsigned bit = dev >= 0 && dev < 32 ? 1u << dev : 0u;
   if (bit && (done.load(std::memory_order_acquire) & bit)) return LAUD_OK;
-  constexpr int kLds = pipe::lds_bytes<MODE, BM, BN, NS>() + (MODE == M_DENSE1 ? 4096 * 4 : 0);
+  constexpr int kLds = pipe::lds_bytes<MODE, BM, BN, NS>() + (MODE == M_DENSE1 ? pipe::masker_bytes<ET>(pipe::kMaxMaskerK) : 0);
   static_assert(kLds <= 160 * 1024, "LDS");
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pipe<MODE, ET, BM, BN, WM, WN, KS, NS>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, kLds) != hipSuccess)
@@ -603,7 +608,7 @@ static int launch_pipe_t(const GemmArgs& args, long long cap_rows, int nsamples,
   const int rc = pipe_request_lds<MODE, ET, BM, BN, WM, WN, KS, NS>();
   if (rc != LAUD_OK || cap_rows < 0) return rc;
   constexpr bool CS = (MODE >= M_CS1 && MODE <= M_CS3);
-  constexpr int NT = 64 * WM * WN * KS, BKE = 8 * elem<ET>::per16;
+  constexpr int NT = 64 * WM * WN * KS;
   PipeArgs k{};
   k.g = args;
   GemmArgs& a = k.g;
@@ -631,7 +636,7 @@ static int launch_pipe_t(const GemmArgs& args, long long cap_rows, int nsamples,
   k.s = make_fast_div(a.S); k.ss = make_fast_div(a.S * a.S);
   k.pps = make_fast_div(std::max((oH / a.S) * (oW / a.S), 1)); k.wp = make_fast_div(std::max(oW / a.S, 1));
   k.howo = make_fast_div(std::max(MODE == M_CONV1 ? a.hw : a.Ho * a.Wo, 1)); k.wo = make_fast_div(std::max(a.Wo, 1)); k.grp = make_fast_div(std::max(a.G, 1));
-  const int lds = pipe::lds_bytes<MODE, BM, BN, NS>() + (MODE == M_DENSE1 && a.wmask ? (a.K + BKE - 1) / BKE * BKE * 4 + 256 : 0);
+  const int lds = pipe::lds_bytes<MODE, BM, BN, NS>() + (MODE == M_DENSE1 && a.wmask ? pipe::masker_bytes<ET>(a.K) : 0);
   hipLaunchKernelGGL((k_pipe<MODE, ET, BM, BN, WM, WN, KS, NS>), grid, dim3(NT), lds, st, k);
   return check_launch();
 }

@@ -59,6 +59,7 @@ T shuffle(int kind, T v, int arg) {
   memcpy(&v, &u, sizeof(T));
   return v;
 }
+void request_lds(const void* function, int bytes);
 void launch(dim3 grid, dim3 block, size_t lds_bytes, const char* kernel, const void* function, const std::function<void()>& body);
 
 struct Rsrc { const char* base; unsigned bytes; };
@@ -104,7 +105,7 @@ typedef void* hipStream_t;
 typedef void* hipEvent_t;
 enum { hipSuccess = 0, hipFuncAttributeMaxDynamicSharedMemorySize, hipDeviceAttributeMultiprocessorCount };
 static inline int hipGetDevice(int* d) { *d = 0; return 0; }
-static inline int hipFuncSetAttribute(const void*, int, int) { return 0; }
+static inline int hipFuncSetAttribute(const void* f, int, int v) { host::request_lds(f, v); return 0; }
 static inline int hipDeviceGetAttribute(int* v, int, int) { *v = 256; return 0; }
 static inline int hipGetLastError() { return 0; }
 static inline int hipEventCreate(hipEvent_t* e) { *e = nullptr; return 0; }

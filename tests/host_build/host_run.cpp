@@ -8,6 +8,7 @@
 #include <sys/mman.h>
 #include <unistd.h>
 
+#include <map>
 #include <set>
 #include <string>
 #include <vector>
@@ -49,7 +50,8 @@ char* stacks;
 unsigned char* lds_end;
 size_t lds_size;
 std::vector<Fiber> fibers(kMaxThreads);
-std::set<std::string> launched;  // kernel instances so far
+std::map<const void*, int> lds_requests;  // dynamic LDS a kernel may be launched with, where more than 64 KB
+std::set<std::string> launched;           // kernel instances so far
 
 void fail(const char* what, const void* at) {
   fprintf(stderr, "%s %p in %s, workgroup %u, %u of %u, %u, thread %u\n", what, at, kernel_name, block.x, block.y, grid.x, grid.y,
@@ -130,6 +132,7 @@ uint64_t wave_op(int kind, uint64_t value, int arg) {
   return current->result;
 }
 
+void request_lds(const void* function, int bytes) { lds_requests[function] = bytes; }
 void launch(dim3 g, dim3 b, size_t lds_bytes, const char* kernel, const void* function, const std::function<void()>& body) {
   kernel_name = kernel;
   Dl_info info;
@@ -142,6 +145,9 @@ void launch(dim3 g, dim3 b, size_t lds_bytes, const char* kernel, const void* fu
   grid = g;
   block_size = b;
   if (lds_bytes > kLds || g.x == 0 || g.y == 0 || b.x > kMaxThreads) fail("launch bounds", nullptr);
+  const auto request = lds_requests.find(function);
+  if (lds_bytes > 64 * 1024 && (request == lds_requests.end() || (size_t)request->second < lds_bytes))
+    fail("more dynamic LDS than requested:", (void*)lds_bytes);
   lds_size = (lds_bytes + 15) / 16 * 16;
   lds = lds_end - lds_size;
   for (unsigned y = 0; y < g.y; ++y)

@@ -33,7 +33,7 @@ def test_dyn_block(G, case, dtype):  # noqa: F811
     check_dyn(run_dyn(G, x, hb, S, mask, False), x, hb, S, mask)
 
 
-@pytest.mark.parametrize("case", [(14, 14, 14, 1032, 264, 2), (40, 21, 21, 104, 72, 3), (23, 28, 28, 40, 56, 4)])
+@pytest.mark.parametrize("case", [(14, 14, 14, 1032, 264, 2), (40, 21, 21, 104, 72, 3), (23, 28, 28, 40, 56, 4), (3, 30, 30, 4096, 264, 2)])
 def test_masker_projection(G, case):  # noqa: F811
     """128 x 128 and 128 x 64 tiles; the first column tile takes the projection of all its rows."""
     t, L, D = G.torch, G.L, G.D

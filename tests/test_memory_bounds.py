@@ -197,6 +197,7 @@ CASES = {
     # fused masker
     "masker": ("identity", "masker", 3, 12, 12, 72, 24, 4, 0.5),
     "masker_f32_gates": ("identity", "masker", 26, 14, 14, 32, 8, 1, 0.5, False, False, None, 0, False, True),
+    "masker_widest": ("identity", "masker", 3, 30, 30, 4096, 264, 2, 0.5),
     # first blocks
     "static": ("first", "static", 2, 13, 9, 40, 24, 96, 2, 1, 1.0),
     "projection_f32": ("first", "dynamic", 3, 27, 14, 8, 16, 40, 2, 7, 0.4, False),
@@ -228,6 +229,7 @@ CASES = {
 # kernel instances that a case is about (template arguments ahead of the type and behind it): a rule that sends the case elsewhere
 # leaves them untested
 REACHES = {
+    "masker_widest": ["k_pipe<6, E, 128, 128, "],
     "channel_wide": ["k_gemm<4, E, ", "k_pipe<5, E, "], "channel_wide_f32": ["k_gemm<4, E, ", "k_pipe<5, E, "],
 }
 
