@@ -1,5 +1,5 @@
-// What the implicit-GEMM kernels of the three convolutions share (laud_gemm.hip, laud_skinny.hip): modes, arguments, and
-// where a row of the activation operand comes from and a row of the result goes to.
+// What the implicit-GEMM kernels of the three convolutions share (laud_gemm.hip, laud_pipe.h, laud_skinny.hip, laud_group.hip): modes,
+// arguments, and for the modes without lists where a row of the activation operand comes from and a row of the result goes to.
 #pragma once
 
 #include "laud_common.h"
@@ -86,55 +86,35 @@ __device__ __forceinline__ void mma16(f32x16& acc, const uint4& a, const uint4& 
   }
 }
 
-// Pixel of the input map (or row of a compact buffer) that row `rho` of the activation operand starts from; the
-// row-of-taps modes also need the centre (y, x) of the 3x3 on the input grid.
+// Row of the activation operand that row `rho` of a launch starts from, for the modes whose rows follow from their number alone
+// (the listed and strided ones are looked up in the kernels); the row-of-taps modes also need the centre (y, x) of the 3x3.
 template <int MODE>
-__device__ __forceinline__ size_t source_row(const GemmArgs& a, int rho, const int32_t* listp, int sample, int Hp, int Wp,
-                                             int& y, int& x) {
-  const int HW = a.H * a.W, SS = a.S * a.S;
-  const int sy = a.stride > 1 ? a.stride : 1;
+__device__ __forceinline__ size_t source_row(const GemmArgs& a, int rho, int sample, int& y, int& x) {
+  static_assert((MODE >= M_CS1 && MODE <= M_U3) || MODE == M_SD3, "rows of this mode are looked up in its kernel");
   y = 0; x = 0;
-  if constexpr (MODE == M_CONV1) {
-    return (size_t)listp[rho];
-  } else if constexpr (MODE == M_CONV3 || MODE == M_DENSE1 || MODE == M_U1 || MODE == M_U3 || MODE == M_SD3) {
+  if constexpr (MODE == M_DENSE1 || MODE == M_U1 || MODE == M_U3 || MODE == M_SD3) {
     return (size_t)rho;
-  } else if constexpr (MODE == M_SD1 || MODE == M_SD2) {
-    // row = output pixel (n, yo, xo); the input pixel under it (centre of the 3x3) is (yo*stride, xo*stride)
-    const int n = rho / (a.Ho * a.Wo), r2 = rho - n * (a.Ho * a.Wo);
-    y = (r2 / a.Wo) * a.stride;
-    x = (r2 % a.Wo) * a.stride;
-    return (size_t)n * HW + (size_t)y * a.W + x;
   } else if constexpr (MODE == M_U2) {
     // row = (patch p, pixel j of the patch); its centre inside the gathered (S+2) x (S+2) tile
-    const int E = a.S + 2;
+    const int E = a.S + 2, SS = a.S * a.S;
     const int p = rho / SS, j = rho - p * SS;
     return (size_t)p * E * E + (size_t)(j / a.S + 1) * E + (j % a.S + 1);
-  } else if constexpr (MODE == M_CONV2 || MODE == M_G2) {
-    const int p = rho / SS, j = rho - p * SS;
-    const int q = a.list[p];
-    const int n = q / (Hp * Wp), r2 = q - n * (Hp * Wp);
-    const int py = r2 / Wp, px = r2 - py * Wp;
-    y = (py * a.S + j / a.S) * sy;  // centre of the 3x3 on the input grid
-    x = (px * a.S + j % a.S) * sy;
-    return (size_t)n * HW + (size_t)y * a.W + x;
-  } else if constexpr (MODE == M_CS2) {
-    y = rho / a.W;
-    x = rho - y * a.W;
-    return (size_t)sample * HW + rho;
-  } else {  // CS1, CS3
-    return (size_t)sample * HW + rho;
+  } else {  // CS1, CS2, CS3
+    if constexpr (MODE == M_CS2) {
+      y = rho / a.W;
+      x = rho - y * a.W;
+    }
+    return (size_t)sample * (a.H * a.W) + rho;
   }
 }
 
-// Row of the output (and residual) buffer that row `rho` of the result belongs to; U1: -2 - row for a position outside
-// the image (stored as zeros).
+// Row of the output (and residual) buffer that row `rho` of the result belongs to, for the same modes; U1: -2 - row for a position
+// outside the image (stored as zeros).
 template <int MODE>
-__device__ __forceinline__ int output_row(const GemmArgs& a, int rho, const int32_t* listp, int sample, int Hp, int Wp) {
-  const int SS = a.S * a.S;
-  if constexpr (MODE == M_CONV1) {
-    return listp[rho];
-  } else if constexpr (MODE == M_CONV2 || MODE == M_DENSE1 || MODE == M_U2 || MODE == M_U3 || MODE >= M_SD1) {
-    return rho;  // (G2 included)
+__device__ __forceinline__ int output_row(const GemmArgs& a, int rho, int sample, int Hp, int Wp) {
+  static_assert((MODE >= M_CS1 && MODE <= M_U3) || MODE == M_SD3, "rows of this mode are looked up in its kernel");
+  if constexpr (MODE == M_DENSE1 || MODE == M_U2 || MODE == M_U3 || MODE == M_SD3) {
+    return rho;
   } else if constexpr (MODE == M_U1) {
     const int E = a.S + 2;
     const int p = rho / (E * E), e = rho - p * (E * E);
@@ -142,13 +122,6 @@ __device__ __forceinline__ int output_row(const GemmArgs& a, int rho, const int3
     const int r2 = q % (Hp * Wp);
     const int yy = (r2 / Wp) * a.S - 1 + e / E, xx = (r2 % Wp) * a.S - 1 + e % E;
     return (yy >= 0 && yy < a.H && xx >= 0 && xx < a.W) ? rho : -2 - rho;
-  } else if constexpr (MODE == M_CONV3) {
-    const int oH = a.stride > 1 ? a.Ho : a.H, oW = a.stride > 1 ? a.Wo : a.W;
-    const int p = rho / SS, j = rho - p * SS;
-    const int q = a.list[p];
-    const int n = q / (Hp * Wp), r2 = q - n * (Hp * Wp);
-    const int py = r2 / Wp, px = r2 - py * Wp;
-    return n * (oH * oW) + (py * a.S + j / a.S) * oW + (px * a.S + j % a.S);
   } else {
     return sample * a.H * a.W + rho;
   }

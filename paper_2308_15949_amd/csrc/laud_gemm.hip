@@ -162,7 +162,7 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
     amask[i] = 0;
     if (rho < M) {
       int y, x;
-      const size_t pixrow = source_row<MODE>(a, rho, nullptr, sample, 0, 0, y, x);
+      const size_t pixrow = source_row<MODE>(a, rho, sample, y, x);
       voffA[i] = (unsigned)((pixrow * a.lda + cc * EPC) * sizeof(ET));
       if constexpr (TAPS) {
         unsigned mk = 0;
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(128 * WGN) void k_gemm(const GemmArgs a) {
   }
   if (tid < BM) {
     const int rho = row0 + tid;
-    s_row[tid] = rho < M ? output_row<MODE>(a, rho, nullptr, sample, 0, 0) : -1;
+    s_row[tid] = rho < M ? output_row<MODE>(a, rho, sample, 0, 0) : -1;
   }
 
   // ---- weight-row descriptors -----------------------------------------------------------------

@@ -318,8 +318,8 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void k_pipe(const PipeArgs ka) {
           }
         }
       } else {
-        pix = (unsigned)source_row<MODE>(a, rho, listp, sample, Hp, Wp, y, x);
-        o = output_row<MODE>(a, rho, listp, sample, Hp, Wp);
+        pix = (unsigned)source_row<MODE>(a, rho, sample, y, x);
+        o = output_row<MODE>(a, rho, sample, Hp, Wp);
       }
     }
     unsigned mk = ~0u;
