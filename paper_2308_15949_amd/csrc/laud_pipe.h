@@ -694,14 +694,18 @@ static int launch_pipe_rule(const GemmArgs& a, long long cap_rows, int nsamples,
       // Dense 1x1, 128 x 64 / 128 x 128 / 128 x 256: 100352 rows, 256 -> 512 channels 67 / 66 / 57 us; 6272 rows, 1024 -> 2048
       // 48 / 43 / 36 us, 512 -> 2048 29 / 29 / 25 us; short reductions are bound by memory, where two workgroups hide each other's ends:
       // 100352 rows, 64 -> 64 channels 22 / 38 / 51 us.
-      if (init) return all(t128x64, t64x128k, t128x128, t128x256);
+      if constexpr (MODE != M_SD1)
+        if (init) rc = t128x128();
+      if (init) return all(t128x64, t64x128k, t128x256);
       if (a.Ncols <= 64) return t128x64();
       const long long m = MODE == M_CONV3 ? rows / 2 : rows;
       // (a tile's LDS leaves a compute unit no room for a workgroup that copies: stage 4 out of place, 16 images, 0.15 / 0.86 34.2 / 38.3 us
       // with these, 34.9 / 36.3 with 128 x 64)
       if (kt >= 8 && tiles(rows, 64, 128) + a.cp.nblocks <= 256) return t64x128k();
       if (tiles(m, 128, 256) >= 192 && (MODE == M_SD1 ? a.Ncols >= 256 : kt >= 8 && a.Ncols >= 1024)) return t128x256();
-      return kt > 5 && MODE != M_SD1 && tiles(m, 128, 128) >= 192 ? t128x128() : t128x64();
+      if constexpr (MODE != M_SD1)
+        if (kt > 5 && tiles(m, 128, 128) >= 192) return t128x128();
+      return t128x64();
     } else if constexpr (MODE == M_CONV1 || MODE == M_DENSE1) {
       // (blocks of stage 4, layer skipping, 48 / 64 images at 0.15: 46.4 / 47.2 us with 128 x 128, 42.7 / 44.2 with 64 x 128)
       // 6272 rows, 2048 -> 512 channels: 128 x 64 / 128 x 128 39 / 23 us; 100352 rows, 512 -> 128: 24 / 24 us, 401408 rows, 256 -> 64: 35 / 48
