@@ -147,7 +147,7 @@ class Call:
         mask[-1] = 1
         B.laud_channel_skip_conv(x, fx, p, self.buf(D, mask), D, self.buf(c * eb), self.ws(B.workspace_size(B.OP_CHANNEL_SKIP, fx, p, D)))
 
-    def masks(self, n, h, w, c, S, bf16=True, keep=False, D=4):
+    def masks(self, n, h, w, c, S, bf16=True, keep=False, D=4, m=16):
         """Spatial masker, compaction of its mask, gather with and without a halo, the unfused block, channel masker."""
         fx, x, patches = B.Fmap(n, h, w, c, B.BF16 if bf16 else B.F32), self.values(n * h * w * c, bf16), n * (h // S) * (w // S)
         w1 = self.rng.standard_normal(c, dtype=np.float32)
@@ -159,7 +159,7 @@ class Call:
         idx, count = self.list(patches, 0.4)
         for halo in (0, 1):
             B.laud_gather_patches(x, fx, S, halo, idx, count, self.buf(patches * (S + 2 * halo) ** 2 * c * (2 if bf16 else 4)))
-        p = self.block(c, 16, c, None, bf16, False)
+        p = self.block(c, m, c, None, bf16, False)
         B.laud_dyn_bottleneck_unfused(x, fx, p, S, idx, count, self.buf(n * h * w * c * (2 if bf16 else 4)), self.ws(B.dyn_bottleneck_unfused_workspace(fx, p, S)))
         hidden = 16
         mlp = [self.values(k, False) for k in (hidden * c, hidden, 2 * D * hidden, 2 * D)]
@@ -179,6 +179,16 @@ CASES = {
     # small tiles; tiled kernels; index lists of one entry and of all
     "few_rows": ("identity", "dyn", 1, 7, 7, 136, 72, 1, 0.5),
     "few_rows_f32": ("identity", "dyn", 2, 5, 17, 24, 16, 1, 0.9, False, False),
+    "tiled_128x64": ("identity", "dyn", 21, 28, 28, 72, 40, 4, 0.5, True, False),
+    "tiled_64x128_split": ("identity", "dyn", 9, 28, 28, 200, 136, 7, 0.5, True, False),
+    "tiled_128x128": ("identity", "dyn", 26, 28, 28, 80, 136, 4, 0.6, True, False),
+    "tiled_128x128_f32": ("identity", "dyn", 26, 28, 28, 80, 136, 4, 0.6, False, False),
+    "tiled_64x128_f32": ("identity", "dyn", 10, 28, 28, 264, 264, 4, 0.3, False),
+    "tiled_64x64_f32": ("identity", "dyn", 42, 28, 28, 72, 40, 4, 0.3, False),
+    "dense_first_split": ("identity", "dyn", 100, 7, 7, 520, 136, 1, 0.3, True, False),
+    "last_split": ("identity", "dyn", 100, 7, 7, 136, 520, 1, 0.3),
+    "last_128x128": ("identity", "dyn", 32, 28, 28, 136, 328, 4, 0.3),
+    "last_128x256": ("identity", "dyn", 16, 28, 28, 1032, 456, 4, 0.2),
     "tiled": ("identity", "dyn", 9, 28, 28, 64, 40, 7, 0.5, True, False),
     "tiled_f32": ("identity", "dyn", 20, 28, 28, 24, 40, 4, 0.3, False),
     "empty_list": ("identity", "dyn", 3, 14, 14, 64, 24, 2, 0.0, True, False),
@@ -192,21 +202,48 @@ CASES = {
     # patches that are whole samples
     "samples_fused": ("identity", "dyn", 22, 14, 14, 1024, 256, 14, 0.3, True, False),
     "samples_fused_none": ("identity", "dyn", 22, 14, 14, 1024, 256, 14, 0.0, True, False),
+    "samples_tiled": ("identity", "dyn", 26, 28, 28, 80, 136, 28, 0.1, True, False),
+    "samples_first_split": ("identity", "dyn", 100, 7, 7, 520, 136, 7, 0.3, True, False),
     "samples_tiled_f32": ("identity", "dyn", 22, 28, 28, 24, 40, 28, 0.3, False),
     "samples_projection_f32": ("first", "dynamic", 22, 28, 27, 24, 16, 40, 2, 14, 0.4, False),
     # fused masker
     "masker": ("identity", "masker", 3, 12, 12, 72, 24, 4, 0.5),
     "masker_f32_gates": ("identity", "masker", 26, 14, 14, 32, 8, 1, 0.5, False, False, None, 0, False, True),
+    "masker_128x64": ("identity", "masker", 40, 21, 21, 104, 72, 3, 0.5, True, False),
+    "masker_128x128_f32": ("identity", "masker", 11, 28, 28, 24, 136, 4, 0.5, False),
+    "masker_64x128_f32": ("identity", "masker", 6, 28, 28, 24, 200, 4, 0.5, False),
+    "masker_64x64_f32": ("identity", "masker", 21, 28, 28, 24, 40, 4, 0.5, False),
     "masker_widest": ("identity", "masker", 3, 30, 30, 4096, 264, 2, 0.5),
     # first blocks
     "static": ("first", "static", 2, 13, 9, 40, 24, 96, 2, 1, 1.0),
+    "static_shortcut_128x256": ("first", "static", 32, 28, 28, 8, 64, 264, 1, 1, 1.0),
+    "static_3x3_split": ("first", "static", 9, 57, 55, 72, 136, 96, 2, 1, 1.0),
+    "static_3x3_128x128": ("first", "static", 9, 129, 127, 16, 72, 80, 1, 1, 1.0),
+    "static_3x3_256x128": ("first", "static", 9, 121, 123, 16, 72, 80, 2, 1, 1.0),
+    "static_last_split": ("first", "static", 6, 28, 28, 16, 456, 136, 1, 1, 1.0),
+    "static_last_128x128": ("first", "static", 16, 28, 28, 16, 328, 136, 1, 1, 1.0),
+    "static_last_128x256": ("first", "static", 8, 28, 28, 16, 456, 1032, 1, 1, 1.0),
+    "static_64x64_f32": ("first", "static", 42, 56, 56, 24, 40, 72, 2, 1, 1.0, False),
+    "static_64x128_f32": ("first", "static", 10, 56, 56, 24, 264, 264, 2, 1, 1.0, False),
+    "static_128x128_f32": ("first", "static", 14, 56, 56, 24, 136, 136, 2, 1, 1.0, False),
     "projection_f32": ("first", "dynamic", 3, 27, 14, 8, 16, 40, 2, 7, 0.4, False),
     # group convolution and SE, in one launch and in four
     "group_se": ("identity", "dyn", 3, 14, 14, 144, 144, 2, 0.5, True, True, 16, 36),
     "group_se_four_launches": ("identity", "dyn", 3, 6, 6, 392, 392, 2, 0.7, True, True, 8, 90),
     "group_se_projection": ("first", "dynamic", 2, 27, 28, 32, 104, 104, 2, 7, 0.5, True, 8, 26),
+    "group_many_rows": ("identity", "dyn", 12, 28, 28, 144, 144, 2, 0.5, True, False, 16, 36),
+    "group_many_rows_none": ("identity", "dyn", 12, 28, 28, 144, 144, 2, 0.0, True, True, 16, 36),
+    "group_of_64": ("identity", "dyn", 5, 56, 56, 64, 64, 4, 0.5, True, True, 64),
+    "group_of_8_odd": ("identity", "dyn", 9, 41, 37, 48, 48, 1, 0.5, True, True, 8),
+    "group_many_rows_projection": ("first", "dynamic", 9, 55, 56, 32, 104, 104, 2, 7, 0.5, True, 8, 26),
+    "group_many_rows_f32": ("identity", "dyn", 12, 28, 28, 136, 136, 4, 0.5, False, True, 8),
+    "group_past_4096_channels": ("identity", "dyn", 3, 8, 8, 4104, 4104, 2, 0.5, True, True, 8),
     # channel skipping: groups of whole 16-byte chunks, the fused kernels, and groups that are not
     "channel": ("identity", "channel", 5, 7, 6, 64, 64, 1, 0, True, False, None, 0, False, False, 4),
+    "channel_128x64": ("identity", "channel", 5, 14, 14, 64, 64, 1, 0, True, False, None, 0, False, False, 4),
+    "channel_64x64_f32": ("identity", "channel", 5, 9, 14, 64, 64, 1, 0, False, False, None, 0, False, False, 16),
+    "channel_64x128_f32": ("identity", "channel", 5, 9, 14, 136, 136, 1, 0, False, False, None, 0, False, False, 17),
+    "channel_128x128_f32": ("identity", "channel", 42, 14, 14, 136, 136, 1, 0, False, False, None, 0, False, False, 17),
     "channel_fused": ("identity", "channel", 6, 7, 7, 1024, 256, 1, 0, True, False, None, 0, False, False, 4),
     "channel_groups_of_9": ("identity", "channel", 6, 14, 3, 8, 72, 1, 0, True, False, None, 0, False, False, 8),
     "channel_groups_of_18": ("identity", "channel", 4, 14, 14, 288, 72, 1, 0, True, False, None, 0, False, False, 4),
@@ -218,6 +255,10 @@ CASES = {
     "masks": ("masks", 3, 12, 20, 72, 4),
     "masks_f32_gates": ("masks", 5, 14, 14, 8, 7, False, True),
     "masks_long_lists": ("masks", 9, 32, 33, 8, 1),
+    "masks_unfused_split": ("masks", 3, 12, 20, 72, 4, True, False, 4, 136),
+    "masks_unfused_128x128": ("masks", 12, 56, 56, 8, 4, True, False, 4, 136),
+    "masks_unfused_64x128_f32": ("masks", 3, 12, 20, 136, 4, False, False, 4, 136),
+    "masks_unfused_128x128_f32": ("masks", 11, 28, 28, 136, 4, False, False, 4, 136),
     # stems
     "stem": ("stem", 2, 37, 45, 64),
     "stem_f32": ("stem", 1, 17, 9, 40, False),
@@ -226,12 +267,72 @@ CASES = {
 }
 
 
-# kernel instances that a case is about (template arguments ahead of the type and behind it): a rule that sends the case elsewhere
-# leaves them untested
+# Tiles that a case is there for (kernel, mode, type, rows x columns; "split": the K steps are shared by two groups of waves): a rule
+# that sends the case elsewhere leaves them untested.  Every tile of k_pipe and k_group is some case's.
 REACHES = {
-    "masker_widest": ["k_pipe<6, E, 128, 128, "],
-    "channel_wide": ["k_gemm<4, E, ", "k_pipe<5, E, "], "channel_wide_f32": ["k_gemm<4, E, ", "k_pipe<5, E, "],
+    "tiled_128x64": ["pipe CONV2 bf16 128x64", "pipe SD1 bf16 128x64", "pipe CONV3 bf16 128x64"],
+    "tiled_64x128_split": ["pipe CONV2 bf16 64x128 split"],
+    "tiled_128x128": ["pipe CONV2 bf16 128x128"],
+    "tiled_128x128_f32": ["pipe CONV1 float 128x128", "pipe CONV2 float 128x128", "pipe CONV3 float 64x64"],
+    "tiled_64x128_f32": ["pipe CONV1 float 64x128", "pipe CONV2 float 64x128", "pipe CONV3 float 64x128"],
+    "tiled_64x64_f32": ["pipe CONV1 float 64x64", "pipe CONV2 float 64x64"],
+    "dense_first_split": ["pipe SD1 bf16 64x128 split"],
+    "last_split": ["pipe CONV3 bf16 64x128 split"],
+    "last_128x128": ["pipe SD1 bf16 128x256", "pipe CONV3 bf16 128x128"],
+    "last_128x256": ["pipe CONV1 bf16 128x128", "pipe CONV3 bf16 128x256"],
+    "samples_tiled": ["pipe CONV1 bf16 128x64"],
+    "samples_first_split": ["pipe CONV1 bf16 64x128 split"],
+    "masker_128x64": ["pipe DENSE1 bf16 128x64"],
+    "masker_128x128_f32": ["pipe DENSE1 float 128x128"],
+    "masker_64x128_f32": ["pipe DENSE1 float 64x128"],
+    "masker_64x64_f32": ["pipe DENSE1 float 64x64"],
+    "masker_widest": ["pipe DENSE1 bf16 128x128"],
+    "static_shortcut_128x256": ["pipe SD2 bf16 128x64", "pipe SD3 bf16 128x64"],
+    "static_3x3_split": ["pipe SD2 bf16 64x128 split"],
+    "static_3x3_128x128": ["pipe SD2 bf16 128x128"],
+    "static_3x3_256x128": ["pipe SD2 bf16 256x128"],
+    "static_last_split": ["pipe SD3 bf16 64x128 split"],
+    "static_last_128x128": ["pipe SD3 bf16 128x128"],
+    "static_last_128x256": ["pipe SD3 bf16 128x256"],
+    "static_64x64_f32": ["pipe SD1 float 64x64", "pipe SD2 float 64x64", "pipe SD3 float 64x64"],
+    "static_64x128_f32": ["pipe SD1 float 128x128", "pipe SD1 float 64x128", "pipe SD2 float 64x128", "pipe SD3 float 64x128"],
+    "static_128x128_f32": ["pipe SD2 float 128x128", "pipe SD3 float 128x128"],
+    "group_many_rows": ["group 2"],
+    "group_of_64": ["group 4"],
+    "group_many_rows_f32": ["pipe G2 float 64x64", "pipe CONV3 float 128x128"],
+    "group_past_4096_channels": ["pipe G2 bf16 128x64"],
+    "channel": ["pipe CS1 bf16 64x128", "pipe CS2 bf16 64x128", "pipe CS3 bf16 64x128"],
+    "channel_128x64": ["pipe CS1 bf16 128x64", "pipe CS2 bf16 128x64", "pipe CS3 bf16 128x64"],
+    "channel_64x64_f32": ["pipe CS1 float 64x64", "pipe CS2 float 64x64", "pipe CS3 float 64x64"],
+    "channel_64x128_f32": ["pipe CS1 float 64x128", "pipe CS2 float 64x128", "pipe CS3 float 64x128"],
+    "channel_128x128_f32": ["pipe CS1 float 128x128", "pipe CS2 float 128x128", "pipe CS3 float 128x128"],
+    "channel_groups_of_9": ["gemm CS1 bf16 64x64", "gemm CS2 bf16 64x64", "gemm CS3 bf16 64x64"],
+    "channel_groups_of_18": ["gemm CS3 bf16 64x128"],
+    "channel_groups_of_33_f32": ["gemm CS1 float 64x128", "gemm CS2 float 64x128", "gemm CS3 float 64x128"],
+    "channel_wide": ["gemm CS2 bf16 64x128", "pipe CS3 bf16 64x128"],
+    "channel_wide_f32": ["gemm CS2 float 64x128", "pipe CS3 float 64x64"],
+    "masks": ["pipe U1 bf16 128x64", "pipe U2 bf16 128x64", "pipe U3 bf16 128x64"],
+    "masks_f32_gates": ["pipe U1 float 64x64", "pipe U2 float 64x64", "pipe U3 float 64x64"],
+    "masks_unfused_split": ["pipe U2 bf16 64x128 split"],
+    "masks_unfused_128x128": ["pipe U2 bf16 128x128"],
+    "masks_unfused_64x128_f32": ["pipe U1 float 64x128", "pipe U2 float 64x128", "pipe U3 float 64x128"],
+    "masks_unfused_128x128_f32": ["pipe U1 float 128x128", "pipe U2 float 128x128", "pipe U3 float 128x128"],
 }
+MODES = "CONV1 CONV2 CONV3 CS1 CS2 CS3 DENSE1 U1 U2 U3 SD1 SD2 SD3 G2".split()
+
+
+def tiles(names):
+    """The tiles among demangled kernel names, as REACHES has them."""
+    names, found = names.replace("unsigned short", "bf16"), set()
+    for kernel, mode, dtype, rows, columns, rest in re.findall(r"k_(pipe|gemm)<(\d+), (\w+), (\d+), (\d+), ([\d, ]+)>", names):
+        found.add(f"{kernel} {MODES[int(mode)]} {dtype} {rows}x{columns}" + (" split" if rest.split(", ")[2:3] == ["2"] else ""))
+    return found | {f"group {k}" for k in re.findall(r"k_group<(\d)>", names)}
+
+
+def test_every_tile_of_the_many_row_kernels_has_a_case(lib):
+    symbols = subprocess.run(["nm", "-C", lib], check=True, capture_output=True, text=True).stdout
+    built = {t for t in tiles(symbols) if not t.startswith("gemm")}
+    assert len(built) > 60 and built == {t for case in REACHES.values() for t in case if not t.startswith("gemm")}
 
 
 @pytest.mark.parametrize("front", [0, 1])
@@ -244,9 +345,8 @@ def test_kernels_stay_inside_their_buffers(lib, name, front, capfd):
             method, *args = CASES[name]
             call = Call(lib, front)
             getattr(call, method)(*args)
-            names = re.sub(r"unsigned short|float", "E", call.launched())
-            missing = [k for k in REACHES.get(name, []) if k not in names]
-            assert not missing, (missing, names)
+            missing = set(REACHES.get(name, [])) - tiles(call.launched())
+            assert not missing, (missing, call.launched())
             status = 0
         except BaseException as e:  # noqa: B902
             os.write(2, repr(e).encode())
