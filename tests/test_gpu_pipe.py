@@ -1,4 +1,5 @@
-"""GPU parity of the tiled kernel for many rows (csrc/laud_pipe.h) on each of its tiles: ragged rows, columns and reductions (not
+"""GPU parity of the tiled kernel for many rows (csrc/laud_pipe.h) on each bf16 tile of the block modes (which shapes meet which:
+REACHES in test_memory_bounds.py, whose cases have the same sizes): ragged rows, columns and reductions (not
 whole 64-channel slices), patches that straddle tiles, lists that fill a fraction of the capacity, the projection of the fused
 masker, strides.  Tolerance: that of the parity tests."""
 import numpy as np
@@ -21,6 +22,11 @@ pytestmark = pytest.mark.gpu
     (26, 28, 28, 80, 136, 4, 0.6, False),   # 128 x 128
     (26, 28, 28, 80, 136, 28, 0.1, True),   # whole samples, few of them
     (21, 28, 28, 72, 40, 14, 1.0, True),
+    (100, 7, 7, 520, 136, 1, 0.3, True),    # first 1x1 on 64 x 128, every pixel and listed samples
+    (100, 7, 7, 520, 136, 7, 0.3, False),
+    (100, 7, 7, 136, 520, 1, 0.3, True),    # last 1x1 on 64 x 128, 128 x 128 and (with listed pixels on 128 x 128 ahead) 128 x 256
+    (32, 28, 28, 136, 328, 4, 0.3, False),
+    (16, 28, 28, 1032, 456, 4, 0.2, True),
 ])
 @pytest.mark.parametrize("dtype", [I.BF16, I.F32])
 def test_dyn_block(G, case, dtype):  # noqa: F811
@@ -59,8 +65,12 @@ def test_masker_projection(G, case):  # noqa: F811
 
 
 @pytest.mark.parametrize("case", [
-    # N, H, W, c_in, m, c_out, stride: 128 x 256 shortcut with a fraction of a slice; 3x3 on 64 x 128 and 256 x 128
+    # N, H, W, c_in, m, c_out, stride: 128 x 256 shortcut with a fraction of a slice; 3x3 on the small tiles (267 of them) and 128 x 128
     (32, 28, 28, 8, 64, 264, 1), (7, 57, 55, 72, 136, 96, 2), (9, 129, 127, 16, 72, 80, 1),
+    # 3x3 on 64 x 128 (more tiles than the small ones take, one round) and 256 x 128 (two rounds of 128 x 128, one of these)
+    (9, 57, 55, 72, 136, 96, 2), (9, 121, 123, 16, 72, 80, 2),
+    # last 1x1 on 64 x 128, 128 x 128 and 128 x 256
+    (6, 28, 28, 16, 456, 136, 1), (16, 28, 28, 16, 328, 136, 1), (8, 28, 28, 16, 456, 1032, 1),
 ])
 def test_static_first_block(G, case):  # noqa: F811
     t, L, D = G.torch, G.L, G.D
