@@ -214,7 +214,7 @@ int launch_pool_compact(const float* proj, int N, int H, int W, int S, float bia
                         float* logits, int32_t* idx, int32_t* count, int32_t* sample_offsets, int32_t* block_counts,
                         hipStream_t stream);
 
-// Dense GEMM + per-column affine (+ ReLU) on the MFMA kernels of laud_gemm.hip:
+// Dense GEMM + per-column affine (+ ReLU) on the MFMA kernels of laud_pipe.h and laud_skinny.hip:
 // Out[r][c] = act(scale[c] * sum_k A[r][k] * Wt[c][k] + shift[c]), A [rows][K], Wt [ncols][K], all of `dtype`.
 int launch_dense_affine(int dtype, const void* A, const void* Wt, const float* scale, const float* shift, void* Out,
                         long long rows, int K, int ncols, int relu, hipStream_t stream);
@@ -302,7 +302,7 @@ struct TailArgs {
   int stride, Ho, Wo;    // spatial stride of the 3x3 and the output grid (stride 1: Ho = H, Wo = W)
   int cout;
   int relu;
-  int pb;                // tile height in blocks of 32 pixels (1..4); 0 = chosen on the device from the count
+  int pb;                // tile height in blocks of 32 pixels (1..3); 0 = chosen on the device from the count
   // channel skipping (Fig. 2(c)) on whole samples (S = H: a "patch" is a sample, `list` the samples in processing
   // order): sbits[i] = kept channel groups (bit g) of the i-th sample of the list, cs_group = channels per group (a
   // multiple of 64).  Input slices of groups no row of a tile keeps are skipped in the 3x3, and h2 is zeroed in the

@@ -644,7 +644,7 @@ static int launch_pipe_t(const GemmArgs& args, long long cap_rows, int nsamples,
 
 // The tiles.  A launch lasts (tiles per compute unit) x (slices x time of a slice + start and end), and a slice's time goes with
 // the bytes of its rows, so large tiles move fewer bytes for the same product and small ones fill the chip and hide each
-// other's start and end.  us a slice and start + end, measured on ResNet stages 2 to 4:
+// other's start and end.  (256 below: the compute units of an MI355X.)  us a slice and start + end, measured on ResNet stages 2 to 4:
 //   128 x  64  two workgroups a compute unit: 0.52 for both, 0.48 for one alone
 //    64 x 128  the K steps split, six slices deep: 0.285, 4.5: shortest chain, for launches that fill the chip once
 //   128 x 128  0.48, 4.5      256 x 128 and 128 x 256  0.75 (1x1) to 1.1 (3x3), 5: dense rows of large batches

@@ -1,5 +1,5 @@
 // The convolutions of a block when there are few rows (small batches, single images): same modes and arguments as the
-// tiled kernel of laud_gemm.hip, built for latency instead of throughput.
+// tiled kernel of laud_pipe.h, built for latency instead of throughput.
 //
 // With a few hundred rows a 64- or 128-row tile leaves most of the chip idle while each workgroup walks its whole reduction
 // alone, slice after slice: what bounds such a launch is that serial chain (a 3x3 over 512 channels on one 7 x 7 image:
@@ -368,7 +368,8 @@ __global__ __launch_bounds__(64 * NW) void k_skinny(const SkinnyArgs ka) {
 
 // Two dense 1x1s that read the same input and do not wait for each other -- the shortcut of a first block and its first 1x1 -- as
 // one launch: workgroups from `split` on take the second.  (One image, first block of stage 1 / 2 / 3 / 4 at ratio 0.15: 19.8 /
-// 17.8 / 17.1 / 23.5 -> 16.9 / 15.3 / 14.8 / 17.0 us.)
+// 17.8 / 17.1 / 23.5 -> 16.9 / 15.3 / 14.8 / 17.0 us.)  The second's tiles are dealt to the XCDs from `split` on: where that is not a
+// multiple of eight, the 3x3 behind finds h1 in another XCD's L2 than it would behind a launch of its own.
 struct SkinnyPair { SkinnyArgs p[2]; int split; };
 template <typename ET, int TM, int TN, int NW, int D>
 __global__ __launch_bounds__(64 * NW) void k_skinny_pair(const SkinnyPair ka) {
@@ -459,8 +460,7 @@ static int launch_skinny_e(const GemmArgs& a, long long cap_rows, hipStream_t st
   constexpr bool TAPS = (MODE == M_CONV2 || MODE == M_SD2 || MODE == M_G2);
   if constexpr (MODE == M_G2) {
     // 64-channel column tiles: they hold whole groups.  bf16: nine slices on three waves, all of a wave's under way at once, so
-    // that a compute unit holds two workgroups (on eight waves their LDS let it hold one, and a second round took 10.6 us where
-    // the tiled kernel takes 8.6).  float32: eighteen slices, MFMAs as long as loads: eight waves.
+    // that a compute unit holds two workgroups (on eight waves their LDS let it hold one, and a second round took 10.6 us).  float32: eighteen slices, MFMAs as long as loads: eight waves.
     if constexpr (sizeof(ET) == 2) return launch_skinny_t<MODE, ET, 1, 4, 3, 3>(a, cap_rows, st);
     else return launch_skinny_t<MODE, ET, 1, 4, 8, 2>(a, cap_rows, st);
   } else {
@@ -529,14 +529,20 @@ int launch_skinny_pair(int dtype, const GemmArgs& a, long long rows_a, const Gem
   return dtype == LAUD_BF16 ? launch_pair_e<bf16_t>(a, rows_a, b, rows_b, st) : launch_pair_e<float>(a, rows_a, b, rows_b, st);
 }
 
-// The line lies where the tiled kernel of laud_gemm.hip gets the chip filled, counted in 64 x 64 output tiles: there this
-// kernel's 64 x 64 tiles stop fitting the chip in one round.  Measured on the four ResNet stages at 1 to 64 images and
-// activation ratios 0.5 and 0.86 (bf16): the 3x3 wins up to about 260 tiles with 18 slices or more (stage 4, 42 images: 25
-// against 33 us) and to 220 with nine; the 1x1s meet the tiled kernel at 250 tiles with up to 8 slices, at 200 with more,
-// and at 200 where a residual is read.  In float32 the tiled kernel is bound by its MFMAs on few workgroups much longer.
-// The group 3x3 wins while its 16-row workgroups fit the chip in one round at any activation ratio, up to 128 tiles (bf16, the
-// two RegNetY backbones at ratios 0.3 / 0.95: 5.5 / 6.9 us against 8.6 / 9.0 at 112 tiles, 5.6 / 9.7 against 8.8 / 9.0 at 160;
-// float32: 8.7 / 15.7 against 16.8 / 17.5 at 112, 8.4 / 22.8 against 16.9 / 17.8 at 160).
+// The line is counted in 64 x 64 output tiles: past 256 of them this kernel's own 64 x 64 tiles are a second round.  Blocks of bf16
+// at ratios 0.15 / 0.5 / 0.86, us, with this kernel | with the one that takes the launch past the line (k_pipe, k_group):
+//   3x3, 72 slices (stage 4)   160 tiles 39.8 / 41.1 / 48.5 | 46.6 / 46.9 / 47.7     288 tiles 42.7 / 44.2 / 45.2 | 42.4 / 44.5 / 45.4
+//                              320 tiles 42.3 / 44.6 / 69.0 | 42.4 / 45.1 / 51.1
+//   3x3, 18 slices (stage 2)   172 tiles 17.7 / 18.9 / 23.5 | 19.2 / 20.3 / 22.4     294 tiles 20.3 / 22.5 / 25.4 | 19.6 / 21.7 / 24.2
+//   3x3, nine slices (stage 1)  98 tiles 13.7 / 14.6 / 15.2 | 14.9 / 15.5 / 16.1     196 tiles 17.4 / 18.6 / 21.0 | 16.6 / 17.5 / 19.8
+//   last 1x1, 512 -> 2048      192 tiles 24.2 / 30.6 / 37.3 | 25.0 / 31.5 / 38.0     224 tiles 23.7 / 24.8 / 25.4 | 24.1 / 25.5 / 26.4
+//   last 1x1, 128 -> 512       104 tiles 12.0 / 12.8 / 15.5 | 11.8 / 12.7 / 15.4     200 tiles 14.9 / 15.6 / 16.5 | 13.6 / 14.4 / 15.0
+//   first 1x1 (ratio 0.5)      2048 -> 512, 192 tiles 45.4 | 43.1     512 -> 128, 124 tiles 17.2 | 17.9, 246 tiles 22.8 | 21.9
+//   group 3x3 (RegNetY-800MF)   49 tiles 11.5 / 11.6 / 11.5 | 10.9 / 11.0 / 11.0     125 tiles 14.5 / 16.6 / 18.0 | 14.1 / 15.2 / 16.2
+// The numbers below are where the sides met before k_pipe and k_group, which are up to 2 us a block faster ahead of them: the sides meet
+// at 288 tiles with 72 slices, at about 170 with fewer, at 100 to 150 for the 1x1s of up to eight slices; the group 3x3 has no such
+// point down to 49 tiles.  In float32 the tiled kernel is bound by its MFMAs on few workgroups much longer (3x3 of stage 3 at 0.15 /
+// 0.86: 408 tiles 103 / 169 | 134 / 155, 516 tiles 140 / 210 | 232 / 256).
 bool skinny_wanted(int mode, int dtype, const GemmArgs& a, long long cap_rows) {
   const bool taps = mode == M_CONV2 || mode == M_SD2 || mode == M_G2, res = mode == M_CONV3 || mode == M_SD3;
   const int bke = dtype == LAUD_BF16 ? 64 : 32;

@@ -1,7 +1,7 @@
 // Static stem of the ResNet body (the whole-body workload): 7x7 stride-2 conv on the 3-channel image with
 // folded-BN affine and ReLU, then 3x3 stride-2 max pooling.  Outside the dynamic hot path (it runs once
 // per image and is not masked): the usual shape (bf16, 64 channels) is one kernel straight from the image to the
-// pooled map, other shapes go through an im2col kernel and the dense MFMA GEMM of laud_gemm.hip, and a plain
+// pooled map, other shapes go through an im2col kernel and the dense MFMA GEMMs (launch_dense_affine), and a plain
 // kernel pools.
 #include "laud_common.h"
 #include "laud_tile_util.h"
