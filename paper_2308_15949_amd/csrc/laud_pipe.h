@@ -31,6 +31,7 @@ namespace laud {
 
 struct PipeArgs {
   GemmArgs g;
+  int ring;  // bytes of the ring: NS slices, or all there are (1x1s only)
   FastDiv ct, tpg, s, ss, pps, wp, howo, wo, grp;
 };
 
@@ -43,6 +44,13 @@ template <int BM, int BN, int NS> __host__ __device__ constexpr int ring_bytes()
 template <int MODE, int BM, int BN, int NS> __host__ __device__ constexpr int lds_bytes() {
   return ring_bytes<BM, BN, NS>() + 2 * BN * 4 + 3 * BM * 4 + (MODE == M_SD1 ? BM * 4 : 0) +
          (MODE >= M_CS1 && MODE <= M_CS3 ? kMaxGroups * 4 + 16 : 0);
+}
+// A 1x1 of fewer than NS slices takes the LDS of those: such launches are bound by memory, and what a compute unit keeps in flight goes
+// with the workgroups it holds, tiles and copies alike.  Last 1x1 with the whole ring / here: 128 images of 56 x 56 x 64, one slice, out of
+// place at 0.15 77.7 / 49.8 us; stage 2 of 128 images, two slices, in place at 0.5 29.0 / 26.5 us; float32 stage 1 of 32 images out of
+// place at 0.86 67.8 / 54.4.
+template <int MODE, int KS> __host__ __device__ constexpr bool short_ring() {
+  return KS == 1 && (MODE == M_CONV1 || MODE == M_CONV3 || MODE == M_DENSE1 || MODE == M_SD1 || MODE == M_SD3);
 }
 // ... the masker's weights: K floats to whole slices, brought in pieces of 64
 constexpr int kMaxMaskerK = 4096;
@@ -80,15 +88,15 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void k_pipe(const PipeArgs ka) {
   constexpr bool RES = (MODE == M_CONV3 || MODE == M_CS3 || MODE == M_SD3);
   constexpr bool LISTED = (MODE == M_CONV1 || MODE == M_CONV2 || MODE == M_CONV3 || MODE == M_G2 || MODE == M_U1 || MODE == M_U2 || MODE == M_U3);
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int kTab = ring_bytes<BM, BN, NS>();
-  float* const s_scale = reinterpret_cast<float*>(smem + kTab);
+  const int tab = short_ring<MODE, KS>() ? ka.ring : ring_bytes<BM, BN, NS>();
+  float* const s_scale = reinterpret_cast<float*>(smem + tab);
   float* const s_shift = s_scale + BN;
   unsigned* const s_voff = reinterpret_cast<unsigned*>(s_shift + BN);
   unsigned* const s_bad = s_voff + BM;
   int* const s_row = reinterpret_cast<int*>(s_bad + BM);
   int* const s_extra = s_row + BM;
   float* const s_wm = reinterpret_cast<float*>(s_extra);  // DENSE1
-  constexpr int kWm = kTab + 2 * BN * 4 + 3 * BM * 4;
+  const int wm_off = tab + 2 * BN * 4 + 3 * BM * 4;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -187,13 +195,13 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void k_pipe(const PipeArgs ka) {
     if constexpr (MODE == M_CS1 || MODE == M_CS2) ch = col < ncols ? kept(col) : 0;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float*>(p < BN / 64 ? a.scale : a.shift), 0, a.Ncols * 4, 0x00020000);
-    dma4(rs, col < ncols ? (unsigned)ch * 4u : kOob, 0, (unsigned)(kTab + p * 256));
+    dma4(rs, col < ncols ? (unsigned)ch * 4u : kOob, 0, (unsigned)(tab + p * 256));
   }
   const bool do_proj = MODE == M_DENSE1 && ct == 0 && a.wmask != nullptr;
   if constexpr (MODE == M_DENSE1) {
     if (do_proj) {
       const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.wmask), 0, a.K * 4, 0x00020000);
-      for (int p = wave; p < (kchunks * BKE + 63) / 64; p += NW) dma4(rs, (unsigned)(p * 64 + lane) * 4u, 0, (unsigned)(kWm + p * 256));
+      for (int p = wave; p < (kchunks * BKE + 63) / 64; p += NW) dma4(rs, (unsigned)(p * 64 + lane) * 4u, 0, (unsigned)(wm_off + p * 256));
     }
   }
 
@@ -404,7 +412,8 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void k_pipe(const PipeArgs ka) {
   // One slice; FULL: another one is requested.
   auto slice = [&](int s, auto full) __attribute__((always_inline)) {
     constexpr bool FULL = decltype(full)::value;
-    const unsigned next = stage == (NS - 1) * STAGE ? 0u : stage + STAGE;
+    const bool wrap = stage == (NS - 1) * STAGE || (short_ring<MODE, KS>() && !FULL && s + 1 == KT);
+    const unsigned next = wrap ? 0u : stage + STAGE;
 #pragma unroll
     for (int kk = 0; kk < KG; ++kk) {
       const int buf = kk & 1;
@@ -636,7 +645,9 @@ static int launch_pipe_t(const GemmArgs& args, long long cap_rows, int nsamples,
   k.s = make_fast_div(a.S); k.ss = make_fast_div(a.S * a.S);
   k.pps = make_fast_div(std::max((oH / a.S) * (oW / a.S), 1)); k.wp = make_fast_div(std::max(oW / a.S, 1));
   k.howo = make_fast_div(std::max(MODE == M_CONV1 ? a.hw : a.Ho * a.Wo, 1)); k.wo = make_fast_div(std::max(a.Wo, 1)); k.grp = make_fast_div(std::max(a.G, 1));
-  const int lds = pipe::lds_bytes<MODE, BM, BN, NS>() + (MODE == M_DENSE1 && a.wmask ? pipe::masker_bytes<ET>(a.K) : 0);
+  constexpr int kRing = pipe::ring_bytes<BM, BN, NS>(), BKE = 8 * elem<ET>::per16;
+  k.ring = pipe::short_ring<MODE, KS>() ? std::min(NS, (a.K + BKE - 1) / BKE) * (kRing / NS) : kRing;
+  const int lds = pipe::lds_bytes<MODE, BM, BN, NS>() - kRing + k.ring + (MODE == M_DENSE1 && a.wmask ? pipe::masker_bytes<ET>(a.K) : 0);
   hipLaunchKernelGGL((k_pipe<MODE, ET, BM, BN, WM, WN, KS, NS>), grid, dim3(NT), lds, st, k);
   return check_launch();
 }
@@ -671,7 +682,7 @@ static int launch_pipe_rule(const GemmArgs& a, long long cap_rows, int nsamples,
     int rc = LAUD_OK;
     auto all = [&rc](auto... t) { ((rc = rc == LAUD_OK ? t() : rc), ...); return rc; };
     if constexpr (F32) {
-      // float32 is bound by its MFMAs (a sixteenth of the bf16 rate): the tile that wastes the fewest
+      // float32 is bound by its MFMAs (a sixteenth of the bf16 rate): the tile that wastes the fewest.
       if (init) return all(t64x64, t64x128, t128x128);
       return a.Ncols < 128 ? t64x64() : rows < 8192 ? t64x128() : t128x128();
     } else if constexpr (CS) {

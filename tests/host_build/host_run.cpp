@@ -51,7 +51,7 @@ unsigned char* lds_end;
 size_t lds_size;
 std::vector<Fiber> fibers(kMaxThreads);
 std::map<const void*, int> lds_requests;  // dynamic LDS a kernel may be launched with, where more than 64 KB
-std::set<std::string> launched;           // kernel instances so far
+std::set<std::string> launched;           // kernel instances so far, dynamic LDS and threads of a workgroup behind each
 
 void fail(const char* what, const void* at) {
   fprintf(stderr, "%s %p in %s, workgroup %u, %u of %u, %u, thread %u\n", what, at, kernel_name, block.x, block.y, grid.x, grid.y,
@@ -138,7 +138,7 @@ void launch(dim3 g, dim3 b, size_t lds_bytes, const char* kernel, const void* fu
   Dl_info info;
   if (dladdr(function, &info) && info.dli_sname && info.dli_saddr == function)
     if (char* const name = abi::__cxa_demangle(info.dli_sname, nullptr, nullptr, nullptr)) {
-      launched.insert(name);
+      launched.insert(std::string(name) + " lds " + std::to_string(lds_bytes) + " threads " + std::to_string(b.x));
       free(name);
     }
   kernel_body = &body;
@@ -211,7 +211,7 @@ extern "C" void* host_alloc(size_t bytes, int front) {
   return front ? p + kPage : p + kPage + pages - b;
 }
 
-// The kernel instances launched so far, a line each; returns the bytes there are.
+// The kernel instances launched so far with the sizes of their workgroups, a line each; returns the bytes there are.
 extern "C" size_t host_launched(char* out, size_t room) {
   std::string all;
   for (const std::string& k : host::launched) all += k + "\n";
