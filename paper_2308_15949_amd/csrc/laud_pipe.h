@@ -682,7 +682,11 @@ static int launch_pipe_rule(const GemmArgs& a, long long cap_rows, int nsamples,
     int rc = LAUD_OK;
     auto all = [&rc](auto... t) { ((rc = rc == LAUD_OK ? t() : rc), ...); return rc; };
     if constexpr (F32) {
-      // float32 is bound by its MFMAs (a sixteenth of the bf16 rate): the tile that wastes the fewest.
+      // float32 is bound by its MFMAs (a sixteenth of the bf16 rate): the tile that wastes the fewest.  Dense and last 1x1s on 64 x 128, of
+      // which a compute unit holds two or more at any K: 32 images, 64 x 128 / 128 x 128, last 1x1 in place at 0.86 of stage 1 46.5 / 53.4 us,
+      // of stage 2 37.8 / 42.5 (out of place 40.3 / 45.9), of 256 -> 1024 channels on 18 x 18 51.2 / 63.8; shortcut and first 1x1 of stage 2's
+      // first block 131 / 155.
+      if constexpr (DENSE) return init ? all(t64x64, t64x128) : a.Ncols < 128 ? t64x64() : t64x128();
       if (init) return all(t64x64, t64x128, t128x128);
       return a.Ncols < 128 ? t64x64() : rows < 8192 ? t64x128() : t128x128();
     } else if constexpr (CS) {

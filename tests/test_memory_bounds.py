@@ -187,6 +187,7 @@ CASES = {
     "tiled_64x64_f32": ("identity", "dyn", 42, 28, 28, 72, 40, 4, 0.3, False),
     "dense_first_split": ("identity", "dyn", 100, 7, 7, 520, 136, 1, 0.3, True, False),
     "last_128x64": ("identity", "dyn", 27, 28, 28, 136, 128, 4, 0.5),
+    "last_f32": ("identity", "dyn", 12, 28, 28, 264, 64, 4, 0.5, False),
     "last_split": ("identity", "dyn", 100, 7, 7, 136, 520, 1, 0.3),
     "last_128x128": ("identity", "dyn", 32, 28, 28, 136, 328, 4, 0.3),
     "last_128x256": ("identity", "dyn", 16, 28, 28, 1032, 456, 4, 0.2),
@@ -276,6 +277,7 @@ REACHES = {
     "tiled_128x128": ["pipe CONV2 bf16 128x128"],
     "tiled_128x128_f32": ["pipe CONV1 float 128x128", "pipe CONV2 float 128x128", "pipe CONV3 float 64x64"],
     "last_128x64": ["pipe CONV3 bf16 128x64"],
+    "last_f32": ["pipe CONV3 float 64x128"],
     "tiled_64x128_f32": ["pipe CONV1 float 64x128", "pipe CONV2 float 64x128", "pipe CONV3 float 64x128"],
     "tiled_64x64_f32": ["pipe CONV1 float 64x64", "pipe CONV2 float 64x64"],
     "dense_first_split": ["pipe SD1 bf16 64x128 split"],
@@ -297,11 +299,11 @@ REACHES = {
     "static_last_128x128": ["pipe SD3 bf16 128x128"],
     "static_last_128x256": ["pipe SD3 bf16 128x256"],
     "static_64x64_f32": ["pipe SD1 float 64x64", "pipe SD2 float 64x64", "pipe SD3 float 64x64"],
-    "static_64x128_f32": ["pipe SD1 float 128x128", "pipe SD1 float 64x128", "pipe SD2 float 64x128", "pipe SD3 float 64x128"],
-    "static_128x128_f32": ["pipe SD2 float 128x128", "pipe SD3 float 128x128"],
+    "static_64x128_f32": ["pipe SD1 float 64x128", "pipe SD2 float 64x128", "pipe SD3 float 64x128"],
+    "static_128x128_f32": ["pipe SD2 float 128x128"],
     "group_many_rows": ["group 2"],
     "group_of_64": ["group 4"],
-    "group_many_rows_f32": ["pipe G2 float 64x64", "pipe CONV3 float 128x128"],
+    "group_many_rows_f32": ["pipe G2 float 64x64"],
     "group_past_4096_channels": ["pipe G2 bf16 128x64"],
     "channel": ["pipe CS1 bf16 64x128", "pipe CS2 bf16 64x128", "pipe CS3 bf16 64x128"],
     "channel_128x64": ["pipe CS1 bf16 128x64", "pipe CS2 bf16 128x64", "pipe CS3 bf16 128x64"],
@@ -322,7 +324,7 @@ REACHES = {
 }
 # Threads of the last 1x1's workgroups that the LDS of a compute unit (160 KB) holds at least, where the reduction is short: its time is
 # that of memory, and the copy of inactive patches runs in workgroups of the same size.
-HELD = {"tiled_128x64": 1024, "last_128x64": 768}
+HELD = {"tiled_128x64": 1024, "last_128x64": 768, "last_f32": 768}
 MODES = "CONV1 CONV2 CONV3 CS1 CS2 CS3 DENSE1 U1 U2 U3 SD1 SD2 SD3 G2".split()
 
 
