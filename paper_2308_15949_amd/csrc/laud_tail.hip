@@ -16,10 +16,11 @@
 //     read before the current step's MFMAs are issued.
 //   * The MFMAs compute the transposed tile (weights as the first operand): a lane then holds, for one pixel,
 //     4 x 4 consecutive channels; one v_permlane32_swap per register pair turns that into 16 consecutive channels
-//     per lane, so h2 goes to LDS, and the result to memory, in 16-byte pieces without an LDS transpose.
+//     per lane, and h2 goes to LDS in 16-byte pieces.  The result passes through 4 KB of LDS a wave on its way to
+//     memory, so that four lanes together hold 64 bytes of a row (laud_tile_util.h: turn_put, turn_get).
 //   * h2 (pixels x 256 bf16) sits behind the activation ring in LDS; the last 1x1 streams w3 through the
-//     same weight ring (no barrier at all in that phase), reads the residual 32 bytes per lane and pixel, adds,
-//     applies the activation, rounds and stores.
+//     same weight ring (no barrier at all in that phase), reads the residual, adds, applies the
+//     activation, rounds and stores.
 //
 // Channel skipping (Fig. 2(c)) rides on the same kernel (template flag CS): the "patches" are whole samples in
 // mask-pattern order, the 3x3 leaves out the 64-channel input slices whose group no row of the tile keeps, and h2 is
@@ -47,7 +48,8 @@ constexpr int kWRing = 3;                     // weight slices held / in flight 
 constexpr unsigned kOob = 0x80000000u;        // offset outside every descriptor: reads as zero
 __host__ __device__ constexpr int a_stage(int pb) { return 32 * pb * 128; }        // one 128-byte K slice of every pixel row
 __host__ __device__ constexpr int h2_off(int pb) { return kARing * a_stage(pb); }  // h2 tile: 32*pb pixels x 512 bytes
-__host__ __device__ constexpr int tab_off(int pb) { return h2_off(pb) + 32 * pb * kMid * 2; }
+__host__ __device__ constexpr int turn_off(int pb) { return h2_off(pb) + 32 * pb * kMid * 2; }  // kTurnBytes of every wave
+__host__ __device__ constexpr int tab_off(int pb) { return turn_off(pb) + kWaves * kTurnBytes; }
 // float tables in LDS behind the tiles: s2, t2 [256], then s3, t3 [cout], then the tile's output rows (int)
 __host__ __device__ constexpr int lds_bytes(int pb, int cout) { return tab_off(pb) + (2 * kMid + 2 * cout) * 4 + 32 * pb * 4; }
 }  // namespace tail
@@ -76,7 +78,7 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int COUT = 256 * NCT;
   constexpr int kBM = 32 * PB;
-  constexpr int kAStage = a_stage(PB), kAOff = 0, kH2Off = h2_off(PB), kTabOff = tab_off(PB);
+  constexpr int kAStage = a_stage(PB), kAOff = 0, kH2Off = h2_off(PB), kTabOff = tab_off(PB), kTurnOff = turn_off(PB);
   constexpr int kNB = kSl2 + NCT * kKch;  // slices in the weight stream
   // LDS-direct instructions per wave and activation slice: an instruction of all eight waves covers 64 rows; with an
   // odd PB the last one is issued by waves 0-3 only
@@ -321,14 +323,13 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
   // Two accumulator sets alternate between column tiles: while tile ct is multiplied into one, the other (tile
   // ct-1) goes through its epilogue -- affine, residual add, activation, rounding, store -- in half-block pieces
   // placed behind the MFMAs of tile ct's first K steps, so the vector ALU works in the shadow of the matrix pipe.
-  int orow[PB];        // output row of this lane's pixel in block t (row 0 where the pixel does not exist: reads stay
-  unsigned exists = 0;  // in range, nothing is stored), and whether it exists
-#pragma unroll
-  for (int t = 0; t < PB; ++t) {
-    const int o = s_orow[32 * t + l31];
-    orow[t] = o < 0 ? 0 : o;
-    exists |= (o >= 0 ? 1u : 0u) << t;
-  }
+  // Results go through the wave's part of the turning buffer; then lane l holds channels 8 * (l % 4) .. +7 of row 16 q + l / 4 of a
+  // pixel block, q = 0, 1.  The row of the map is read from LDS where it is used (kept, it and its 64-bit address cost the
+  // registers that the accumulators need); negative: the pixel does not exist.
+  const int ocol = wave * 32 + (lane & 3) * 8;
+  const __bf16* const resp = reinterpret_cast<const __bf16*>(a.res);
+  __bf16* const outp = reinterpret_cast<__bf16*>(a.out);
+  unsigned char* const turn = smem + kTurnOff + wave * kTurnBytes;
   const unsigned hrow = kH2Off + (unsigned)l31 * 512u;  // h2 fragment rows: pixel block t at + t * 32 * 512
   const unsigned hx = (unsigned)(l31 & 15);
   auto read_frags3 = [&](int buf, int ks, int kg) __attribute__((always_inline)) {
@@ -338,46 +339,40 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
       fa[buf][t] = *reinterpret_cast<const uint4*>(smem + hrow + t * (32 * 512) + ((c ^ hx) << 4));
   };
   const float floor_ = act_floor(a.relu);
-  const __bf16* const resp = reinterpret_cast<const __bf16*>(a.res);
-  __bf16* const outp = reinterpret_cast<__bf16*>(a.out);
   f32x16 acc2[DUAL ? PB : 1];  // the second accumulator set (odd column tiles)
-  uint4 res[PB][2];  // residual of the tile whose epilogue is pending: per pixel block, channels 0-7 / 8-15
+  u32x4 res[PB][2];  // residual of the tile whose epilogue is pending
 #pragma unroll
-  for (int t = 0; t < PB; ++t) res[t][0] = res[t][1] = make_uint4(0, 0, 0, 0);
+  for (int t = 0; t < PB; ++t) res[t][0] = res[t][1] = u32x4{0, 0, 0, 0};
 
-  // Half a pixel block of the epilogue of column tile ct: accumulator groups h and h+2 of a lane (channels
-  // 8h + 4*(lane/32) .. +3 and 16 + 8h + 4*(lane/32) .. +3) become, after four lane swaps, eight consecutive channels.
-  auto epilogue_half = [&](int ct, int t, int h, f32x16& A) __attribute__((always_inline)) {
+  // Quarters of the epilogue of a pixel block of column tile ct: the affine of accumulator groups 2 h and 2 h + 1 into the turning
+  // buffer (twice), then residual, activation, rounding and store of 16 rows (twice).
+  auto turn_in = [&](int ct, int h, const f32x16& A) __attribute__((always_inline)) {
     const int cb = ct * 256 + wave * 32;
-    const float4 sc0 = *reinterpret_cast<const float4*>(s_s3 + cb + 8 * h + 4 * lhi);
-    const float4 sh0 = *reinterpret_cast<const float4*>(s_t3 + cb + 8 * h + 4 * lhi);
-    const float4 sc1 = *reinterpret_cast<const float4*>(s_s3 + cb + 8 * (h + 2) + 4 * lhi);
-    const float4 sh1 = *reinterpret_cast<const float4*>(s_t3 + cb + 8 * (h + 2) + 4 * lhi);
-    float v0[4] = {A[4 * h + 0] * sc0.x + sh0.x, A[4 * h + 1] * sc0.y + sh0.y, A[4 * h + 2] * sc0.z + sh0.z,
-                   A[4 * h + 3] * sc0.w + sh0.w};
-    float v1[4] = {A[4 * h + 8] * sc1.x + sh1.x, A[4 * h + 9] * sc1.y + sh1.y, A[4 * h + 10] * sc1.z + sh1.z,
-                   A[4 * h + 11] * sc1.w + sh1.w};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v0[i]), __float_as_uint(v1[i]), false, false);
-      v0[i] = __uint_as_float(r[0]);
-      v1[i] = __uint_as_float(r[1]);
+    for (int g = 2 * h; g < 2 * h + 2; ++g) {
+      const float4 sc = *reinterpret_cast<const float4*>(s_s3 + cb + 8 * g + 4 * lhi);
+      const float4 sh = *reinterpret_cast<const float4*>(s_t3 + cb + 8 * g + 4 * lhi);
+      *reinterpret_cast<float4*>(turn + turn_put(lane, g)) =
+          make_float4(A[4 * g] * sc.x + sh.x, A[4 * g + 1] * sc.y + sh.y, A[4 * g + 2] * sc.z + sh.z, A[4 * g + 3] * sc.w + sh.w);
     }
-    const unsigned rv[4] = {res[t][h].x, res[t][h].y, res[t][h].z, res[t][h].w};
-    const float x[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-    unsigned pk[4];
+  };
+  auto turn_out = [&](int ct, int t, int q) __attribute__((always_inline)) {
+    const float4 x0 = *reinterpret_cast<const float4*>(turn + turn_get(lane, q, 0));
+    const float4 x1 = *reinterpret_cast<const float4*>(turn + turn_get(lane, q, 1));
+    const float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+    u32x4 pk;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-      const float lo = fmaxf(x[2 * d] + __uint_as_float(rv[d] << 16), floor_);
-      const float hi = fmaxf(x[2 * d + 1] + __uint_as_float(rv[d] & 0xffff0000u), floor_);
+      const float lo = fmaxf(x[2 * d] + __uint_as_float(res[t][q][d] << 16), floor_);
+      const float hi = fmaxf(x[2 * d + 1] + __uint_as_float(res[t][q][d] & 0xffff0000u), floor_);
       pk[d] = pack_bf16(lo, hi);
     }
-    if ((exists >> t) & 1u)
-      *reinterpret_cast<uint4*>(outp + (size_t)orow[t] * COUT + cb + lhi * 16 + h * 8) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+    const int o = s_orow[32 * t + 16 * q + (lane >> 2)];
+    if (o >= 0) *reinterpret_cast<u32x4*>(outp + (size_t)o * COUT + (ocol + ct * 256)) = pk;
   };
-  // The 32 bytes of residual a lane needs for half a pixel block of column tile ct
-  auto load_residual_half = [&](int ct, int t, int h) __attribute__((always_inline)) {
-    res[t][h] = *reinterpret_cast<const uint4*>(resp + (size_t)orow[t] * COUT + ct * 256 + wave * 32 + lhi * 16 + h * 8);
+  auto load_residual = [&](int ct, int t, int q) __attribute__((always_inline)) {
+    const int o = max(s_orow[32 * t + 16 * q + (lane >> 2)], 0);
+    res[t][q] = *reinterpret_cast<const u32x4*>(resp + (size_t)o * COUT + (ocol + ct * 256));
   };
 
   read_frags3(0, 0, 0);
@@ -399,15 +394,21 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
         if (st == 0) A = mma_bf16(wr[BUF][kg], fa[cur][t], f32x16{});  // (a column tile starts from zero)
         else A = mma_bf16(wr[BUF][kg], fa[cur][t], A);
       }
-      // Odd steps 1, 3, ...: one half pixel block each.  With two accumulator sets the previous tile's epilogue piece
+      // Odd steps 1, 3, ...: a quarter of a pixel block each.  With two accumulator sets the previous tile's epilogue piece
       // runs behind these MFMAs; the residual registers it frees are refilled at once with this tile's values, a
       // whole tile ahead of their use.
-      if ((st & 1) && st / 2 < 2 * PB) {
-        const int pi = st / 2, t = pi / 2, h = pi % 2;
+      if ((st & 1) && st / 2 < 4 * PB) {
         if constexpr (DUAL) {
-          if (ct > 0) { if (ct & 1) epilogue_half(ct - 1, t, h, acc[t]); else epilogue_half(ct - 1, t, h, acc2[t]); }
+          const int t = st / 8, u = st / 2 % 4;
+          if (u < 2) {
+            if (ct > 0) { if (ct & 1) turn_in(ct - 1, u, acc[t]); else turn_in(ct - 1, u, acc2[t]); }
+          } else {
+            if (ct > 0) turn_out(ct - 1, t, u - 2);
+            load_residual(ct, t, u - 2);
+          }
+        } else if (st / 2 < 2 * PB) {
+          load_residual(ct, st / 4, st / 2 % 2);
         }
-        load_residual_half(ct, t, h);
       }
       // the weight register just used is refilled for one ring length later
       if (b + WR < kNB) wr[BUF][kg] = fragment_W(b + WR, kg);
@@ -415,17 +416,24 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
     }
     if constexpr (!DUAL) {  // one accumulator set: the epilogue follows its tile
 #pragma unroll
-      for (int pi = 0; pi < 2 * PB; ++pi) {
-        epilogue_half(ct, pi / 2, pi % 2, acc[pi / 2]);
+      for (int t = 0; t < PB; ++t) {
+        turn_in(ct, 0, acc[t]);
+        turn_in(ct, 1, acc[t]);
+        turn_out(ct, t, 0);
+        turn_out(ct, t, 1);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
   if constexpr (DUAL) {  // the last tile's epilogue
 #pragma unroll
-    for (int pi = 0; pi < 2 * PB; ++pi) {
-      const int t = pi / 2, h = pi % 2;
-      if ((NCT - 1) & 1) epilogue_half(NCT - 1, t, h, acc2[t]); else epilogue_half(NCT - 1, t, h, acc[t]);
+    for (int t = 0; t < PB; ++t) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if ((NCT - 1) & 1) turn_in(NCT - 1, h, acc2[t]); else turn_in(NCT - 1, h, acc[t]);
+      }
+      turn_out(NCT - 1, t, 0);
+      turn_out(NCT - 1, t, 1);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
