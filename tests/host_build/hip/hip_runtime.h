@@ -66,6 +66,7 @@ struct Rsrc { const char* base; unsigned bytes; };
 typedef unsigned Chunk __attribute__((ext_vector_type(4)));
 unsigned load_dword(const Rsrc& r, unsigned voff, unsigned soff);  // zero past the descriptor's end
 Chunk load_chunk(const Rsrc& r, unsigned voff, unsigned soff);
+void store_chunk(const Chunk& c, const Rsrc& r, unsigned voff, unsigned soff);  // dropped past the descriptor's end
 void load_to_lds(const Rsrc& r, unsigned voff, unsigned soff, unsigned lds_base);
 void load_dword_to_lds(const Rsrc& r, unsigned voff, unsigned soff, unsigned lds_base);
 struct Pair {
@@ -90,6 +91,7 @@ static inline int lanes_below(unsigned mask, int first) {  // set bits of 32 lan
 #define __amdgpu_buffer_rsrc_t host::Rsrc
 #define __builtin_amdgcn_make_buffer_rsrc(p, stride, bytes, flags) (host::Rsrc{(const char*)(p), (unsigned)(bytes)})
 #define __builtin_amdgcn_raw_buffer_load_b128(r, v, s, a) host::load_chunk(r, v, s)
+#define __builtin_amdgcn_raw_buffer_store_b128(c, r, v, s, a) host::store_chunk(c, r, v, s)
 #define __builtin_amdgcn_raw_buffer_load_b32(r, v, s, a) host::load_dword(r, v, s)
 #define __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, x, y, z) (c)
 #define __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, x, y, z) (c)

@@ -168,6 +168,12 @@ Chunk load_chunk(const Rsrc& r, unsigned voff, unsigned soff) {
     if ((uint64_t)voff + 4 * i < r.bytes) c[i] = load_dword(r, voff + 4 * i, soff);
   return c;
 }
+void store_chunk(const Chunk& c, const Rsrc& r, unsigned voff, unsigned soff) {
+  for (unsigned i = 0; i < 4; ++i) {
+    const unsigned v = c[i];
+    if ((uint64_t)voff + 4 * i + 4 <= r.bytes) memcpy(const_cast<char*>(r.base) + (size_t)voff + 4 * i + soff, &v, 4);
+  }
+}
 void load_to_lds(const Rsrc& r, unsigned voff, unsigned soff, unsigned lds_base) {
   const size_t at = lds_base + 16 * (size_t)current->lane;
   if (at + 16 > lds_size) fail("LDS-direct load past the launch's LDS at", (void*)at);

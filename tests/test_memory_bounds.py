@@ -197,6 +197,8 @@ CASES = {
     # 64-wide kernel, fused 3x3 -> 1x1 and register-weight first 1x1
     "narrow": ("identity", "dyn", 5, 56, 56, 256, 64, 4, 0.3, True, False),
     "narrow_static": ("first", "static", 1, 241, 239, 64, 64, 256, 2, 1, 1.0),
+    "one_kernel_first": ("first", "static", 2, 27, 41, 64, 64, 256, 1, 1, 1.0),
+    "one_kernel_first_one_row": ("first", "static", 1, 1, 1100, 64, 64, 256, 1, 1, 1.0),
     "narrow_projection": ("first", "dynamic", 5, 111, 112, 64, 64, 256, 2, 8, 0.4),
     "fused": ("identity", "dyn", 22, 14, 14, 1024, 256, 2, 0.3, True, False),
     "fused_packed": ("identity", "masker", 22, 14, 14, 1024, 256, 2, 0.5, True, True, None, 0, True, True),
