@@ -676,7 +676,7 @@ static int launch_pipe_rule(const GemmArgs& a, long long cap_rows, int nsamples,
     auto t256x128 = [&](auto...) { return launch_pipe_t<MODE, ET, 256, 128, 4, 2, 1, 3>(a, cap_rows, nsamples, st); };
     auto t128x256 = [&](auto...) { return launch_pipe_t<MODE, ET, 128, 256, 2, 4, 1, 3>(a, cap_rows, nsamples, st); };
     const long long rows = cap_rows * (MODE == M_CONV1 || CS ? nsamples : 1);
-    const int kt = (TAPS ? 9 : 1) * ((a.K + 8 * elem<ET>::per16 - 1) / (8 * elem<ET>::per16));
+    const int kt = (TAPS || MODE == M_CS2 ? 9 : 1) * ((a.K + 8 * elem<ET>::per16 - 1) / (8 * elem<ET>::per16));
     auto tiles = [&](long long m, int bm, int bn) { return ((m + bm - 1) / bm) * ((a.Ncols + bn - 1) / bn); };
     const bool init = cap_rows < 0;
     int rc = LAUD_OK;
@@ -690,8 +690,16 @@ static int launch_pipe_rule(const GemmArgs& a, long long cap_rows, int nsamples,
       if (init) return all(t64x64, t64x128, t128x128);
       return a.Ncols < 128 ? t64x64() : rows < 8192 ? t64x128() : t128x128();
     } else if constexpr (CS) {
+      // Of one or two tiles a sample, all of them in one round of the chip: the six-slice ring.  First 1x1 and 3x3 of stage 4, 64 samples
+      // of 7 x 7: 26.1 + 33.8 us with 64 x 128 and three slices, 15.9 + 23.1 here; the whole block 68.8 -> 54.2, one sample 43.1 ->
+      // 38.4, 19 of 9 x 9 64.9 -> 51.1.  Past one round two workgroups a compute unit are the better: 96 samples 76.9 -> 83.8, 64 of 9 x 9
+      // 83.7 -> 94.7; eight slices (512 channels on 8 x 8) 20.8 -> 21.1.
+      if constexpr (MODE != M_CS3) {
+        if (init) rc = t64x128k();
+        else if (cap_rows <= 128 && kt >= 16 && tiles(cap_rows, 64, 128) * nsamples <= 256) return t64x128k();
+      }
       if (init) return all(t64x128, t128x64);
-      return cap_rows <= 64 ? t64x128() : t128x64();  // (rows of one sample)
+      return cap_rows <= 64 ? t64x128() : t128x64();  // (cap_rows: rows of one sample)
     } else if constexpr (TAPS) {
       // Of listed rows half the capacity is taken to exist.  Stage 4, 128 images (listed, 3136 rows, 72 slices), 64 x 128 / 128 x
       // 128: 26 / 38 us; stage 2 (50176 rows, 18 slices) 36 / 26 us.  (256 x 128 there: 23, but 22 where 0.15 of the rows exist

@@ -382,6 +382,12 @@ CS_CASES = [
     (5, 14, 14, 1024, 256, 1, I.BF16, True),   # ... one group: all or nothing per sample
     (70, 7, 7, 1024, 256, 4, I.BF16, True),    # ... 49-pixel samples: several samples per tile
     (300, 7, 7, 1024, 256, 4, I.BF16, False),  # ... more samples than one round of the pattern sort
+    (5, 7, 7, 1032, 136, 17, I.BF16, True),    # few rows, long reductions: one row tile, ragged kept widths, two column tiles
+    (3, 8, 8, 1024, 512, 4, I.BF16, False),    # ... a whole row tile
+    (7, 5, 13, 1024, 200, 5, I.BF16, True),    # ... one row past it
+    (2, 8, 16, 1024, 128, 2, I.BF16, True),    # ... two whole ones, then one row more than the split ring is for
+    (2, 3, 43, 1024, 128, 2, I.BF16, True),
+    (33, 9, 13, 2048, 512, 4, I.BF16, True),   # ... more tiles than one round
 ]
 
 

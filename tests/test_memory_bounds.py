@@ -244,6 +244,7 @@ CASES = {
     "group_past_4096_channels": ("identity", "dyn", 3, 8, 8, 4104, 4104, 2, 0.5, True, True, 8),
     # channel skipping: groups of whole 16-byte chunks, the fused kernels, and groups that are not
     "channel": ("identity", "channel", 5, 7, 6, 64, 64, 1, 0, True, False, None, 0, False, False, 4),
+    "channel_split": ("identity", "channel", 5, 7, 11, 1032, 136, 1, 0, True, False, None, 0, False, False, 17),
     "channel_128x64": ("identity", "channel", 5, 14, 14, 64, 64, 1, 0, True, False, None, 0, False, False, 4),
     "channel_64x64_f32": ("identity", "channel", 5, 9, 14, 64, 64, 1, 0, False, False, None, 0, False, False, 16),
     "channel_64x128_f32": ("identity", "channel", 5, 9, 14, 136, 136, 1, 0, False, False, None, 0, False, False, 17),
@@ -308,6 +309,7 @@ REACHES = {
     "group_many_rows_f32": ["pipe G2 float 64x64"],
     "group_past_4096_channels": ["pipe G2 bf16 128x64"],
     "channel": ["pipe CS1 bf16 64x128", "pipe CS2 bf16 64x128", "pipe CS3 bf16 64x128"],
+    "channel_split": ["pipe CS1 bf16 64x128 split", "pipe CS2 bf16 64x128 split"],
     "channel_128x64": ["pipe CS1 bf16 128x64", "pipe CS2 bf16 128x64", "pipe CS3 bf16 128x64"],
     "channel_64x64_f32": ["pipe CS1 float 64x64", "pipe CS2 float 64x64", "pipe CS3 float 64x64"],
     "channel_64x128_f32": ["pipe CS1 float 64x128", "pipe CS2 float 64x128", "pipe CS3 float 64x128"],
