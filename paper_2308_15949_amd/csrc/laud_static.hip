@@ -50,8 +50,13 @@ typedef __attribute__((ext_vector_type(16))) float stem_f32x16;
 // As two kernels the conv's output (four times the image, eight times the result) makes a round trip through memory: 190 + 60
 // us at 128 images of 224 x 224.  Here it stays in LDS.
 //   * A workgroup takes strips of 7 pooled rows (16 conv rows, one of them to spare) and walks along x in steps of 16 conv
-//     columns = 8 pooled columns; the conv columns of two steps lie in LDS (slot = column mod 32), so the pooling windows
+//     columns = 8 pooled columns; the step's conv columns and the last one of the step before lie in LDS, so the pooling windows
 //     that reach one column back find it there.
+//   * Image rows, products and pooling of a step are phases between barriers, each bound by something else; two workgroups a
+//     compute unit fill each other's (71 KB of LDS, 128 registers a lane).  A wave brings whole image rows, a dword a lane, so what a
+//     row and a dword stand for is scalar or the same for all rows.  With 101 KB of LDS, one workgroup a compute unit, 32 conv columns
+//     and dwords dealt out over the threads (a division, bounds and masks for each) and copies of 240 bytes (reads in conflict): 128 / 256 images of
+//     224 x 224 85.2 / 162 us, here 62.4 / 118; two such workgroups without the rest 80.2 / 151; 8 / 32 images 14.5 / 27.0 -> 14.4 / 26.0.
 //   * Implicit GEMM per step: 256 rows (conv pixels) x 64 channels.  A window row is 21 consecutive values of the image
 //     (7 pixels x 3 channels), padded to 24 = three 16-byte fragments: K = 7 x 24 (+ 8) = 176 in eleven 32x32x16 steps.  A
 //     fragment starts 12 * column bytes into the image row, so each image row is kept in LDS four times, shifted by 0, 12,
@@ -64,13 +69,22 @@ typedef __attribute__((ext_vector_type(16))) float stem_f32x16;
 //     positions outside the conv's output count as zeros.
 constexpr int kSpRows = 7, kSpCols = 8;               // pooled rows of a strip, pooled columns of a step
 constexpr int kSpIn = 37;                             // image rows of a strip: 2 * 15 + 7
-constexpr int kSpDw = 57;                             // dwords of an image row a step reads: 12 * 15 + 48 bytes
-constexpr int kSpCopy = 240, kSpRowB = 4 * kSpCopy;   // LDS bytes of one copy / of the four copies of an image row
+constexpr int kSpCopyDw = 48;                         // dwords of a copy: four windows
+constexpr int kSpCopy = 4 * kSpCopyDw, kSpRowB = 4 * kSpCopy;  // bytes of a copy (192: the fragments of 16 conv columns meet 16 bank groups), of a row
 constexpr int kSpZero = kSpIn * kSpRowB;              // 16 bytes of zeros
 constexpr int kSpConv = (kSpZero + 16 + 255) / 256 * 256;
-constexpr int kSpLds = kSpConv + 16 * 32 * 128;       // conv values [16 rows][32 columns][64 channels]
-constexpr int kSpThreads = 512, kSpLoads = (kSpIn * kSpDw + kSpThreads - 1) / kSpThreads;
-__global__ __launch_bounds__(kSpThreads) void k_stem_pool_bf16(const bf16_t* __restrict__ x, int N, int Hin, int Win, int Hc, int Wc,
+constexpr int kSpSlots = 17;                          // conv columns in LDS: 0 .. 14 of the step, the last one of this and the previous step
+constexpr int kSpAff = kSpConv + 16 * kSpSlots * 128; // conv values [16 rows][17 columns][64 channels]
+constexpr int kSpLds = kSpAff + 2 * 64 * 4;           // scale and shift
+// Place of conv column c of a step (-1: the last one of the step before).  Columns two apart, which a pooling read takes together, lie in
+// different halves of the 256 bytes LDS serves at once; 16-byte chunk ch of a column is at ch ^ sp_swizzle(c): the sixteen columns of a
+// block's store are spread over all of them.
+__device__ __forceinline__ unsigned sp_slot(int c, int step) {
+  return c < 0 ? 15u + ((unsigned)(step - 1) & 1u) : c == 15 ? 15u + ((unsigned)step & 1u) : (unsigned)((c & 12) | ((c & 1) << 1) | ((c >> 1) & 1));
+}
+__device__ __forceinline__ unsigned sp_swizzle(int c) { return ((unsigned)c & 1u) | (((unsigned)c >> 1) & 6u); }
+constexpr int kSpThreads = 512, kSpLoads = (kSpIn + 7) / 8;  // image rows a wave brings, a dword of each per lane
+__global__ __launch_bounds__(kSpThreads, 4) void k_stem_pool_bf16(const bf16_t* __restrict__ x, int N, int Hin, int Win, int Hc, int Wc,
                                                                int Hp, int Wp, int strips, int chunks, int chunk_steps,
                                                                const bf16_t* __restrict__ w7, const float* __restrict__ s,
                                                                const float* __restrict__ t, bf16_t* __restrict__ out) {
@@ -94,33 +108,16 @@ __global__ __launch_bounds__(kSpThreads) void k_stem_pool_bf16(const bf16_t* __r
     for (int k = 0; k < 8; ++k) e[k] = ky < 7 && 8 * j + k < 21 ? (unsigned)src[k] : 0u;
     wr[st] = u32x4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
   }
-  float4 sc[4], sh[4];
+  if (tid < 128) reinterpret_cast<float*>(smem + kSpAff)[tid] = tid < 64 ? s[tid] : t[tid - 64];
+  // fragment addresses of this lane's first 32-row block (two conv rows; the second lies two rows on), without the K step's part: of lane
+  // half 1 the next fragment, which is 16 bytes on or opens the next window row
+  const unsigned abase = (unsigned)(2 * (wm * 4 + (l31 >> 4)) * kSpRowB + (l31 & 3) * kSpCopy + ((l31 & 15) >> 2) * 48);
+  const unsigned same_row = abase + lhi * 16, next_row = abase + lhi * (kSpRowB - 32);
+  // which bits of this lane's dword lie inside the window it belongs to in copy q (dwords 10 and 11 of a window's twelve: its last value
+  // and the padding)
+  unsigned inside[4];
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    __builtin_memcpy(&sc[g], s + 32 * wn + 8 * g + 4 * lhi, 16);
-    __builtin_memcpy(&sh[g], t + 32 * wn + 8 * g + 4 * lhi, 16);
-  }
-  // fragment addresses of this lane's two 32-row blocks (two conv rows each), without the K step's part
-  unsigned abase[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int rr = wm * 64 + i * 32 + l31, r = rr >> 4, xo = rr & 15;
-    abase[i] = (unsigned)(2 * r * kSpRowB + (xo & 3) * kSpCopy + (xo >> 2) * 48);
-  }
-  // which bits of this thread's dword i of a step lie inside the window it belongs to in copy q (dwords 10 and 11 of a window's
-  // twelve: its last value and the padding)
-  unsigned inside[kSpLoads][4];
-#pragma unroll
-  for (int i = 0; i < kSpLoads; ++i) {
-    const int m = (tid + i * kSpThreads) % kSpDw % 12;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      inside[i][q] = m == (10 + 3 * q) % 12 ? 0xffffu : m == (11 + 3 * q) % 12 ? 0u : ~0u;
-#if defined(__HIP_DEVICE_COMPILE__)
-      asm("" : "+v"(inside[i][q]));  // (kept in a register: derived again at each use it becomes branches)
-#endif
-    }
-  }
+  for (int q = 0; q < 4; ++q) inside[q] = lane % 12 == (10 + 3 * q) % 12 ? 0xffffu : lane % 12 == (11 + 3 * q) % 12 ? 0u : ~0u;
   const int units = N * strips * chunks, nsteps = (Wp + kSpCols - 1) / kSpCols;
   for (int u = blockIdx.x; u < units; u += gridDim.x) {
     const int c = u % chunks, ns = u / chunks, n = ns / strips, p0 = (ns - n * strips) * kSpRows;
@@ -128,37 +125,39 @@ __global__ __launch_bounds__(kSpThreads) void k_stem_pool_bf16(const bf16_t* __r
     const int iy0 = 4 * p0 - 5, cy0 = 2 * p0 - 1;  // first image row, first conv row
     const int s0 = first > 0 ? first - 1 : 0;      // the step before supplies the conv column to the left
     unsigned pre[kSpLoads];
-    // dword k of image row r: values e, e + 1 of the row's 3 Win, outside the image zero
+    // A lane brings dword `lane` of rows wave + 8 i of a step: values e, e + 1 of the row's 3 Win, outside the image zero.  The load reads the
+    // nearest two values there are; what they stand for is worked out when they are stored, a step later.
     auto request = [&](int step) __attribute__((always_inline)) {
-      const int e0 = (32 * step - 3) * 3;
+      const int e = min(max((32 * step - 3) * 3 + 2 * lane, 0), 3 * Win - 2);
 #pragma unroll
       for (int i = 0; i < kSpLoads; ++i) {
-        const int k = tid + i * kSpThreads, r = k / kSpDw, e = e0 + 2 * (k - r * kSpDw), iy = iy0 + r;
-        unsigned v = 0;
-        if (r < kSpIn && iy >= 0 && iy < Hin) {
-          const bf16_t* row = x + ((size_t)n * Hin + iy) * Win * 3;
-          if (e >= 0 && e + 1 < 3 * Win) __builtin_memcpy(&v, row + e, 4);
-          else if (e + 1 == 0) v = (unsigned)row[0] << 16;
-          else if (e + 1 == 3 * Win) v = row[e];
-        }
-        pre[i] = v;
+        const int iy = min(max(iy0 + wave + 8 * i, 0), Hin - 1);
+        __builtin_memcpy(&pre[i], x + ((size_t)n * Hin + iy) * Win * 3 + e, 4);
       }
     };
-    auto store_rows = [&]() __attribute__((always_inline)) {
+    auto store_rows = [&](int step) __attribute__((always_inline)) {
+      const int e = (32 * step - 3) * 3 + 2 * lane;
+      const int shl = e < 0 ? 16 : 0, shr = e > 3 * Win - 2 ? 16 : 0;
+      const unsigned live = e < -1 || e > 3 * Win - 1 ? 0u : ~0u;
+      unsigned v[kSpLoads];
 #pragma unroll
       for (int i = 0; i < kSpLoads; ++i) {
-        const int k = tid + i * kSpThreads, r = k / kSpDw, d = k - r * kSpDw;
-        if (r < kSpIn) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (d >= 3 * q) *reinterpret_cast<unsigned*>(smem + r * kSpRowB + q * kSpCopy + (d - 3 * q) * 4) = pre[i] & inside[i][q];
-        }
+        const int iy = iy0 + wave + 8 * i;
+        v[i] = ((pre[i] << shl) >> shr) & (iy >= 0 && iy < Hin ? live : 0u);
       }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (lane >= 3 * q && lane < 3 * q + kSpCopyDw) {
+#pragma unroll
+          for (int i = 0; i < kSpLoads; ++i)
+            if (wave + 8 * i < kSpIn)
+              *reinterpret_cast<unsigned*>(smem + (wave + 8 * i) * kSpRowB + lane * 4 + q * (kSpCopy - 12)) = v[i] & inside[q];
+        }
     };
     request(s0);
     __syncthreads();  // the weights, or the previous unit's last reads
     for (int step = s0; step < stop; ++step) {
-      store_rows();
+      store_rows(step);
       __syncthreads();
       if (step + 1 < stop) request(step + 1);
       stem_f32x16 acc[2];
@@ -166,38 +165,49 @@ __global__ __launch_bounds__(kSpThreads) void k_stem_pool_bf16(const bf16_t* __r
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
-#pragma unroll
-      for (int st = 0; st < 11; ++st) {
+      uint4 fa[2][2];  // fragments of the two blocks, read one K step ahead of their products
+      auto fragments = [&](int st) __attribute__((always_inline)) {
         // lane half h: fragment f = 2 st + h; the last one (f = 21) has zero weights and reads zeros
-        const int f0 = 2 * st, f1 = 2 * st + 1;
-        const unsigned o0 = (unsigned)(f0 / 3 * kSpRowB + f0 % 3 * 16), o1 = (unsigned)(f1 / 3 * kSpRowB + f1 % 3 * 16);
+        const int f = 2 * st;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-          const unsigned at = !lhi ? abase[i] + o0 : f1 < 21 ? abase[i] + o1 : (unsigned)kSpZero;
-          const uint4 a = *reinterpret_cast<const uint4*>(smem + at);
-          acc[i] = mma_bf16(wr[st], a, acc[i]);
+          const unsigned o = (unsigned)((f / 3 + 4 * i) * kSpRowB + f % 3 * 16);
+          const unsigned at = st == 10 ? (lhi ? (unsigned)kSpZero : abase + o) : (f % 3 == 2 ? next_row : same_row) + o;
+          fa[st & 1][i] = *reinterpret_cast<const uint4*>(smem + at);
         }
+      };
+      fragments(0);
+#pragma unroll
+      for (int st = 0; st < 11; ++st) {
+        if (st < 10) fragments(st + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) acc[i] = mma_bf16(wr[st], fa[st & 1][i], acc[i]);
+        __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const int rr = wm * 64 + i * 32 + l31, r = rr >> 4, X = 16 * step + (rr & 15), Y = cy0 + r;
+        const int rr = wm * 64 + i * 32 + l31, r = rr >> 4, C = rr & 15, X = 16 * step + C, Y = cy0 + r;
         const bool live = Y >= 0 && Y < Hc && X < Wc;
         float v[16];
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          v[4 * g + 0] = fmaxf(acc[i][4 * g + 0] * sc[g].x + sh[g].x, 0.f);
-          v[4 * g + 1] = fmaxf(acc[i][4 * g + 1] * sc[g].y + sh[g].y, 0.f);
-          v[4 * g + 2] = fmaxf(acc[i][4 * g + 2] * sc[g].z + sh[g].z, 0.f);
-          v[4 * g + 3] = fmaxf(acc[i][4 * g + 3] * sc[g].w + sh[g].w, 0.f);
+          const float4 sc = *reinterpret_cast<const float4*>(smem + kSpAff + (32 * wn + 8 * g + 4 * lhi) * 4);
+          const float4 sh = *reinterpret_cast<const float4*>(smem + kSpAff + 256 + (32 * wn + 8 * g + 4 * lhi) * 4);
+          v[4 * g + 0] = fmaxf(acc[i][4 * g + 0] * sc.x + sh.x, 0.f);
+          v[4 * g + 1] = fmaxf(acc[i][4 * g + 1] * sc.y + sh.y, 0.f);
+          v[4 * g + 2] = fmaxf(acc[i][4 * g + 2] * sc.z + sh.z, 0.f);
+          v[4 * g + 3] = fmaxf(acc[i][4 * g + 3] * sc.w + sh.w, 0.f);
         }
         to_consecutive_channels(v);
         uint4 c0 = make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[8], v[9]), pack_bf16(v[10], v[11]));
         uint4 c1 = make_uint4(pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]), pack_bf16(v[12], v[13]), pack_bf16(v[14], v[15]));
         if (!live) c0 = c1 = make_uint4(0, 0, 0, 0);
-        // 16-byte chunk ch of a conv pixel at ch ^ (column & 7)
-        const unsigned slot = (unsigned)(r * 32 + (X & 31)) * 128u, ch = wn * 4u + lhi * 2u;
-        *reinterpret_cast<uint4*>(smem + kSpConv + slot + ((ch ^ (X & 7u)) << 4)) = c0;
-        *reinterpret_cast<uint4*>(smem + kSpConv + slot + (((ch + 1u) ^ (X & 7u)) << 4)) = c1;
+        unsigned char* const at = smem + kSpConv + ((unsigned)r * kSpSlots + sp_slot(C, step)) * 128u;
+        const unsigned ch = (wn * 4u + lhi * 2u) ^ sp_swizzle(C);
+        *reinterpret_cast<uint4*>(at + (ch << 4)) = c0;
+        *reinterpret_cast<uint4*>(at + ((ch ^ 1u) << 4)) = c1;
+        __builtin_amdgcn_sched_barrier(0);
       }
       __syncthreads();
       if (step >= first && tid < kSpRows * kSpCols * 8) {
@@ -207,12 +217,12 @@ __global__ __launch_bounds__(kSpThreads) void k_stem_pool_bf16(const bf16_t* __r
         s16x8 m = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
         for (int dx = -1; dx < 2; ++dx) {
-          const int cx = 2 * X + dx;
-          if (cx < 0) continue;
+          const int c = 2 * q + dx;
+          if (c < 0 && step == 0) continue;
+          const unsigned at = kSpConv + (2 * p * kSpSlots + sp_slot(c, step)) * 128 + ((ch ^ sp_swizzle(c & 15)) << 4);
 #pragma unroll
           for (int dy = 0; dy < 3; ++dy)
-            m = __builtin_elementwise_max(m, *reinterpret_cast<const s16x8*>(smem + kSpConv + ((2 * p + dy) * 32 + (cx & 31)) * 128 +
-                                                                             ((ch ^ ((unsigned)cx & 7u)) << 4)));
+            m = __builtin_elementwise_max(m, *reinterpret_cast<const s16x8*>(smem + at + dy * kSpSlots * 128));
         }
         if (P < Hp && X < Wp) *reinterpret_cast<s16x8*>(out + (((size_t)n * Hp + P) * Wp + X) * 64 + ch * 8) = m;
       }
@@ -497,7 +507,7 @@ extern "C" int laud_stem(const void* x, int N, int Hin, int Win, int dtype, cons
     const long long ns = (long long)N * strips;
     const int chunks = (int)std::min<long long>(nsteps, std::max<long long>(1, cus / ns));
     const int chunk_steps = (nsteps + chunks - 1) / chunks;
-    hipLaunchKernelGGL(k_stem_pool_bf16, dim3((unsigned)std::min<long long>(ns * chunks, cus)), dim3(kSpThreads), kSpLds, st,
+    hipLaunchKernelGGL(k_stem_pool_bf16, dim3((unsigned)std::min<long long>(ns * chunks, 2 * cus)), dim3(kSpThreads), kSpLds, st,
                        (const bf16_t*)x, N, Hin, Win, Hc, Wc, Hp, Wp, strips, chunks, chunk_steps, (const bf16_t*)w7, s, t,
                        (bf16_t*)out);
     return check_launch();
