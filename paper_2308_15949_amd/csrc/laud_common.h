@@ -381,17 +381,17 @@ int narrow_init_device();
 int launch_narrow(const NarrowArgs& a, hipStream_t stream);
 
 // The static first block of ResNet stage 1 (64 -> 64 -> 256, no stride, bf16) in one kernel (laud_first.hip), for
-// first_supported() shapes and row counts.
+// the shapes and maps that first_plan() takes.
 struct FirstArgs {
   const void* x; void* out;        // [N][H][W][64], [N][H][W][256]
   const void* w1; const void* w2; const void* w3; const void* wsc;  // [64][64], [64][3][3][64], [256][64], [256][64]
   const float* s1; const float* t1; const float* s2; const float* t2; const float* s3; const float* t3;
   const float* ssc; const float* tsc;
   int N, H, W;
-  int th, tw, ntx, pern, ntiles;   // rectangles of th x tw outputs, ntx a row of them, pern a sample (set by launch_first)
-  FastDiv d_rw, d_tw, d_pern, d_ntx;
+  int th, tw, ntx, pern, ntiles;   // rectangles of th x tw outputs, ntx a row of them, pern a sample (set by first_plan)
+  FastDiv d_rw, d_tw, d_pern, d_ntx;  // set by launch_first
 };
-bool first_supported(int dtype, int c_in, int c_mid, int c_out, int stride, long long rows);
+bool first_plan(int dtype, int c_in, int c_mid, int c_out, int stride, FirstArgs* a);  // N, H, W given
 int first_init_device();
 int launch_first(const FirstArgs& a, hipStream_t stream);
 

@@ -337,13 +337,6 @@ __global__ __launch_bounds__(first::kThreads) void k_first(const FirstArgs a) {
 }
 
 // ---- host side ------------------------------------------------------------------------------------------------------
-bool first_supported(int dtype, int c_in, int c_mid, int c_out, int stride, long long rows) {
-  // (outputs below 1 GiB.  A workgroup has its weights to fetch, whatever the map: up to a few hundred pixels three launches of small tiles
-  // are as fast.  24 x 24 / 40 x 40 / 56 x 56 pixels: 11.7 / 15.0 / 16.8 us, here 12.6 / 13.0 / 13.4.)
-  return stride == 1 && dtype == LAUD_BF16 && c_in == first::kMid && c_mid == first::kMid && c_out == first::kOut && rows > 1024 &&
-         rows < (1 << 21);
-}
-
 static int g_first_cus[32];
 int first_init_device() {
   int dev = 0, cus = 0;
@@ -354,16 +347,29 @@ int first_init_device() {
              ? LAUD_OK : LAUD_ERR_HIP;
 }
 
-int launch_first(const FirstArgs& args, hipStream_t st) {
+// workgroups that fill the current device once; 0: no device, or one that cannot be set up
+static int first_workgroups() {
   static std::atomic<unsigned> done{0};
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 32) return LAUD_ERR_HIP;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 32) return 0;
   const unsigned bit = 1u << dev;
   if (!(done.load(std::memory_order_acquire) & bit)) {
-    if (first_init_device() != LAUD_OK) return LAUD_ERR_HIP;
+    if (first_init_device() != LAUD_OK) return 0;
     done.fetch_or(bit, std::memory_order_release);
   }
-  FirstArgs a = args;
+  return g_first_cus[dev];
+}
+
+bool first_plan(int dtype, int c_in, int c_mid, int c_out, int stride, FirstArgs* args) {
+  FirstArgs& a = *args;
+  const long long rows = (long long)a.N * a.H * a.W;
+  // (outputs below 1 GiB.  A workgroup has its weights to fetch, whatever the map: up to a few hundred pixels three launches of small tiles
+  // are as fast.  24 x 24 / 40 x 40 / 56 x 56 pixels: 11.7 / 15.0 / 16.8 us, here 12.6 / 13.0 / 13.4.)
+  if (stride != 1 || dtype != LAUD_BF16 || c_in != first::kMid || c_mid != first::kMid || c_out != first::kOut || rows <= 1024 ||
+      rows >= (1 << 21))
+    return false;
+  const int wgs = first_workgroups();
+  if (wgs <= 0) return false;
   // the rectangle: fewest of them for a map, then the smallest halo
   long long best = 1LL << 60;
   for (int tw = 1; tw <= a.W && tw <= first::kRows; ++tw) {
@@ -376,8 +382,25 @@ int launch_first(const FirstArgs& args, hipStream_t st) {
     if (cost < best) { best = cost; a.th = th; a.tw = tw; a.ntx = ntx; a.pern = nty * ntx; }
   }
   a.ntiles = a.N * a.pern;
+  // A rectangle costs about the same however full it is (about 5 us a round of them, 12 the first), and none spans two samples: what counts is
+  // the rounds against those of the other routes, whose tiles are full whatever the map.
+  //   small tiles (up to 14336 rows; 12.5 us and 0.8 a thousand rows): 1100 rows of 1 x 1 / 2 x 2 (5 / 2 rounds) 13.4 / 13.2 us there, 31 /
+  //   16.4 here; 4000 rows of 3 x 3 (2) 17.2, 16.7; 14000 of 7 x 7 / 5 x 5 / 4 x 4 (2 / 3 / 4) 24.3 / 23.7 / 24.0, 17.9 / 21.7 / 26.0.
+  //   k_narrow's rounds of 128 rows a workgroup take 8 us with the first 1x1 ahead of them: 30000 rows (1 of its rounds) of 8 x 8 / 7 x 7 (2 /
+  //   3 here) 20.1 / 19.9, 19.3 / 23.5; 100000 (4) of 12 x 12 / 8 x 8 / 4 x 4 (6 / 7 / 25) 42.5 / 42.1 / 42, 39.1 / 43.1 / 116; 400000 (13)
+  //   of 9 x 9 / 12 x 12 / 4 x 4 (20 / 22 / 98) 108 / 112 / 110, 108 / 118 / 428.
+  const long long rounds = (a.ntiles + wgs - 1) / wgs;
+  if (!narrow_supported(dtype, c_mid, c_out, rows)) return (rounds - 1) * 6144 <= rows;
+  const long long full = (rows + (long long)first::kRows * wgs - 1) / ((long long)first::kRows * wgs);
+  return 5 * rounds <= 8 * full + 2;
+}
+
+int launch_first(const FirstArgs& args, hipStream_t st) {
+  const int wgs = first_workgroups();
+  if (wgs <= 0) return LAUD_ERR_HIP;
+  FirstArgs a = args;
   a.d_rw = make_fast_div(a.tw + 2); a.d_tw = make_fast_div(a.tw); a.d_pern = make_fast_div(a.pern); a.d_ntx = make_fast_div(a.ntx);
-  const unsigned grid = (unsigned)(a.ntiles < g_first_cus[dev] ? (a.ntiles + 7) / 8 * 8 : g_first_cus[dev]);
+  const unsigned grid = (unsigned)(a.ntiles < wgs ? (a.ntiles + 7) / 8 * 8 : wgs);
   StageScope scope(LAUD_STAGE_CONV2, st);
   hipLaunchKernelGGL(k_first, dim3(grid), dim3(first::kThreads), first::kLds, st, a);
   return check_launch();

@@ -1278,11 +1278,11 @@ extern "C" int laud_static_bottleneck(const void* x, laud_fmap fx, const laud_bo
   int rc;
   GemmArgs a{};
   a.H = fx.H; a.W = fx.W; a.S = 1; a.D = 1; a.G = 1; a.Ho = Ho; a.Wo = Wo;
-  if (first_supported(fx.dtype, p->c_in, p->c_mid, p->c_out, stride, nout)) {
-    FirstArgs f{};
+  FirstArgs f{};
+  f.N = fx.N; f.H = fx.H; f.W = fx.W;
+  if (first_plan(fx.dtype, p->c_in, p->c_mid, p->c_out, stride, &f)) {
     f.x = x; f.out = out; f.w1 = p->w1; f.w2 = p->w2; f.w3 = p->w3; f.wsc = w_sc;
     f.s1 = p->s1; f.t1 = p->t1; f.s2 = p->s2; f.t2 = p->t2; f.s3 = p->s3; f.t3 = p->t3; f.ssc = s_sc; f.tsc = t_sc;
-    f.N = fx.N; f.H = fx.H; f.W = fx.W;
     return launch_first(f, st);
   }
   if (p->c_in == 64 && narrow_supported(fx.dtype, p->c_mid, p->c_out, nout)) {

@@ -346,23 +346,53 @@ def test_every_tile_of_the_many_row_kernels_has_a_case(lib):
     assert len(built) > 60 and built == {t for case in REACHES.values() for t in case if not t.startswith("gemm")}
 
 
-@pytest.mark.parametrize("front", [0, 1])
-@pytest.mark.parametrize("name", CASES)
-def test_kernels_stay_inside_their_buffers(lib, name, front, capfd):
+def in_a_process_of_its_own(body, capfd):
+    """(a fault ends the process, with the kernel and the workgroup on stderr)"""
     pid = os.fork()
-    if pid == 0:  # (a fault ends the process, with the kernel and the workgroup on stderr)
+    if pid == 0:
         status = 1
         try:
-            method, *args = CASES[name]
-            call = Call(lib, front)
-            getattr(call, method)(*args)
-            missing = set(REACHES.get(name, [])) - tiles(call.launched())
-            assert not missing, (missing, call.launched())
-            for lds, threads in re.findall(r"k_pipe<2, .*lds (\d+) threads (\d+)", call.launched()):
-                assert (160 << 10) // int(lds) * int(threads) >= HELD.get(name, 0), (lds, threads)
+            body()
             status = 0
         except BaseException as e:  # noqa: B902
             os.write(2, repr(e).encode())
         os._exit(status)
     _, status = os.waitpid(pid, 0)
     assert status == 0, capfd.readouterr().err
+
+
+@pytest.mark.parametrize("front", [0, 1])
+@pytest.mark.parametrize("name", CASES)
+def test_kernels_stay_inside_their_buffers(lib, name, front, capfd):
+    def body():
+        method, *args = CASES[name]
+        call = Call(lib, front)
+        getattr(call, method)(*args)
+        missing = set(REACHES.get(name, [])) - tiles(call.launched())
+        assert not missing, (missing, call.launched())
+        for lds, threads in re.findall(r"k_pipe<2, .*lds (\d+) threads (\d+)", call.launched()):
+            assert (160 << 10) // int(lds) * int(threads) >= HELD.get(name, 0), (lds, threads)
+    in_a_process_of_its_own(body, capfd)
+
+
+# Static blocks of 64 -> 64 -> 256 channels, bf16: the kernel of the whole block, whose rectangles are mostly empty on small and on thin
+# maps, only where it needs few rounds of them for the rows there are (256 workgroups, 128 rows each).
+ONE_KERNEL = [
+    (2, 41, 25), (128, 56, 56), (50, 72, 72), (1, 1100, 1), (65, 4, 4),       # full rectangles; at most one a workgroup
+    (384, 4, 4), (492, 5, 5), (768, 4, 4), (286, 7, 7),                       # small tiles: the second round from 6144 rows on, the third from 12288
+    (300, 7, 7), (512, 8, 8), (768, 8, 8), (694, 12, 12), (4669, 9, 9),       # ahead of the 64-wide kernel's tiles: 2 rounds for 1, 3 for 2, 6 for 4, 19 for 12
+]
+NOT_ONE_KERNEL = [
+    (1, 32, 32), (1100, 1, 1), (257, 2, 2), (383, 4, 4), (683, 3, 3), (767, 4, 4), (769, 4, 4), (13, 1100, 1),
+    (600, 5, 5), (30000, 1, 1), (1875, 4, 4), (612, 7, 7), (1024, 8, 8), (1562, 8, 8), (2778, 12, 12), (25000, 4, 4), (27, 1100, 1), (667, 300, 2),
+]
+
+
+@pytest.mark.parametrize("case", ONE_KERNEL + NOT_ONE_KERNEL)
+def test_static_block_takes_the_whole_block_kernel_where_a_map_fills_it(lib, case, capfd):
+    def body():
+        call = Call(lib, 0)
+        call.host.host_record_only()
+        call.first("static", *case, 64, 64, 256, 1, 1, 1.0)
+        assert ("k_first" in call.launched()) == (case in ONE_KERNEL), call.launched()
+    in_a_process_of_its_own(body, capfd)
