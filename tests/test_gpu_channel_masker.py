@@ -16,6 +16,8 @@ CASES = [
     (2, 56, 56, 256, 64, I.BF16),  # stage 1, G = 1
     (64, 14, 14, 1024, 4, I.BF16),  # config 4, stage 3
     (2, 4, 4, 4104, 8, I.F32),     # more chunk columns than threads
+    (2, 41, 53, 2048, 64, I.BF16),  # 33 and 34 pixels a thread: several whole batches of loads, and one or two behind them
+    (2, 41, 53, 1032, 64, I.F32),
 ]
 
 

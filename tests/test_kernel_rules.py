@@ -59,6 +59,23 @@ def test_lds_reads_have_landed_at_the_barriers_of_the_64_wide_kernel(tmp_path):
     assert barriers >= 2 * 12
 
 
+def test_pooling_loads_of_a_batch_are_under_way_together(tmp_path):
+    """The channel masker's pooling: in the generated code eight (bf16) and four (float32) 16-byte loads follow each other without
+    a wait."""
+    hipcc("--cuda-device-only", "-S", os.path.join(B.CSRC, "laud_chanmask.hip"), "-o", str(tmp_path / "chanmask.s"))
+    most = {}
+    for line in (tmp_path / "chanmask.s").read_text().splitlines():
+        if re.match(r"_ZN.*k_gap_partial.*:", line):
+            name, run = line.split(":")[0], 0
+            most[name] = 0
+        elif most and ("vmcnt(" in line or "s_endpgm" in line):
+            run = 0
+        elif most and line.split()[:1] == ["global_load_dwordx4"]:
+            run += 1
+            most[name] = max(most[name], run)
+    assert len(most) == 2 and all(v >= (8 if "ItE" in k else 4) for k, v in most.items()), most
+
+
 def test_no_inline_assembly_load_writes_a_register():
     """The compiler takes an asm statement's outputs as written when it ends and may copy or re-use them while the load is still
     under way.  Loads into registers are builtins, whose waits it places itself; asm loads go to LDS (no output operand)."""
