@@ -12,13 +12,17 @@ from test_gpu_parity import G, TOL  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("case", [
-    (1, 32, 32),                    # 1024 rows: the last size of the small tiles
-    (1, 41, 25), (2, 23, 31),       # odd in both directions, ragged rectangles
+CASES = [
+    (2, 41, 25), (2, 23, 31),       # odd in both directions, ragged rectangles
     (1, 1, 1100), (1, 1100, 1), (3, 2, 300), (2, 300, 5),   # rectangles of one row, of one column, limited by their halo and by their height
-    (1, 56, 56), (13, 56, 56),      # the shape of ResNet stage 1: fewer rectangles than compute units, more than one a workgroup
-    (9, 57, 83), (2, 150, 149),
-])
+    (1, 56, 56), (5, 56, 56), (1, 121, 119),                # the shape of ResNet stage 1: fewer rectangles than compute units
+    (13, 56, 56), (9, 57, 83), (2, 150, 149),               # two a workgroup
+    (768, 4, 4),                                            # mostly empty ones, three a workgroup: input and h2 buffers come round again
+    (20, 56, 56), (37, 56, 56), (65, 56, 56),               # up to three, five and eight a workgroup, the last eighth of them ragged
+]
+
+
+@pytest.mark.parametrize("case", [(1, 32, 32), *CASES])  # 1024 rows: the last size of the small tiles
 def test_first_block(G, case):  # noqa: F811
     t, L, D = G.torch, G.L, G.D
     N, H, W = case

@@ -55,7 +55,13 @@ def check_dyn_or_copy(got, x, hb, S, mask):
         assert np.array_equal(got, x)
 
 
-@pytest.mark.parametrize("case", [(5, 56, 56, 1), (1, 121, 119, 1), (1, 241, 239, 2), (13, 56, 56, 1)])
+STATIC_CASES = [
+    (1, 241, 239, 2), (12, 112, 112, 2), (21, 112, 112, 2),  # in front of a stride: fewer tiles than compute units, up to two and three a workgroup
+    (612, 7, 7, 1), (1400, 7, 7, 1), (20000, 1, 1, 1),       # maps too small for the rectangles of laud_first.hip
+]
+
+
+@pytest.mark.parametrize("case", STATIC_CASES)
 def test_narrow_static_first_block(G, case):  # noqa: F811
     t, L, D = G.torch, G.L, G.D
     N, H, W, stride = case

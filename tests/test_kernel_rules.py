@@ -38,13 +38,26 @@ def test_rows_past_the_end_of_an_index_list_stay_inside_it(rules, S, count):
     assert np.array_equal(out, np.minimum(rho, rows - 1) // (S * S))
 
 
-def test_lds_reads_have_landed_at_the_barriers_of_the_64_wide_kernel(tmp_path):
-    """A stage of the ring is refilled by another wave's LDS-direct loads right behind a barrier, so no wave may pass a barrier
+@pytest.fixture(scope="module")
+def assembly(tmp_path_factory):
+    """Lines of a kernel source's generated code."""
+    d, made = tmp_path_factory.mktemp("assembly"), {}
+
+    def lines(name):
+        if name not in made:
+            hipcc("--cuda-device-only", "-S", os.path.join(B.CSRC, name), "-o", str(d / (name + ".s")))
+            made[name] = (d / (name + ".s")).read_text().splitlines()
+        return made[name]
+    return lines
+
+
+@pytest.mark.parametrize("name,least", [("laud_narrow.hip", 2 * 12), ("laud_first.hip", 17)])
+def test_lds_reads_have_landed_at_the_barriers_of_the_64_wide_kernels(assembly, name, least):
+    """LDS that a wave has read is refilled by another wave's LDS-direct loads right behind a barrier, so no wave may pass a barrier
     with LDS reads under way: in the generated code every ds_read is waited for (lgkmcnt counts down in order) before the next
     s_barrier."""
-    hipcc("--cuda-device-only", "-S", os.path.join(B.CSRC, "laud_narrow.hip"), "-o", str(tmp_path / "narrow.s"))
     barriers, pending = 0, []
-    for line in (tmp_path / "narrow.s").read_text().splitlines():
+    for line in assembly(name):
         op = line.split()[:1]
         if not op:
             continue
@@ -56,15 +69,42 @@ def test_lds_reads_have_landed_at_the_barriers_of_the_64_wide_kernel(tmp_path):
         elif op[0] == "s_barrier":
             barriers += 1
             assert not pending, f"barrier {barriers} is passed with {pending} under way"
-    assert barriers >= 2 * 12
+    assert barriers >= least
 
 
-def test_pooling_loads_of_a_batch_are_under_way_together(tmp_path):
+def test_stores_behind_the_input_that_the_whole_block_kernel_waits_for(assembly):
+    """The kernel of the static first block waits for the next but one rectangle's input with "all but sixteen": in the generated code of
+    its loop six LDS-direct loads and, behind them, sixteen stores are all that counts, none of them on a branch."""
+    loop, loops, header = [], {}, None
+    for line in assembly("laud_first.hip"):  # the code of each loop, in the order it stands in
+        at = re.search(r"(?:in Loop: |=>This Inner Loop )Header[:=] ?(?:(BB\w+) )?Depth=1", line)
+        if at:
+            header = at.group(1) or line.split(":")[0].strip(". ").lstrip("L")
+        elif re.match(r"\.LBB|; %bb", line):
+            header = None
+        if header:
+            loops.setdefault(header, []).append(line.strip())
+    loop, = (v for v in loops.values() if any("vmcnt(16)" in t for t in v))
+    wait, = (i for i, t in enumerate(loop) if "vmcnt(16)" in t)
+    skipped, order = None, []
+    for t in loop[wait + 1:] + loop[:wait]:
+        branch = re.match(r"s_cbranch_\w+ \.L(BB\w+)", t)
+        if re.match(r"\.LBB", t):
+            skipped = None
+        elif branch and "=>" not in t:
+            skipped = branch.group(1)
+        memory = re.match(r"(buffer_|global_|flat_|scratch_)\w+", t)
+        if memory:
+            assert skipped is None or skipped not in " ".join(loop), (t, skipped)
+            order.append("load" if "lds" in t else "store" if "store" in t else t)
+    assert order == ["load"] * 6 + ["store"] * 16, order
+
+
+def test_pooling_loads_of_a_batch_are_under_way_together(assembly):
     """The channel masker's pooling: in the generated code eight (bf16) and four (float32) 16-byte loads follow each other without
     a wait."""
-    hipcc("--cuda-device-only", "-S", os.path.join(B.CSRC, "laud_chanmask.hip"), "-o", str(tmp_path / "chanmask.s"))
     most = {}
-    for line in (tmp_path / "chanmask.s").read_text().splitlines():
+    for line in assembly("laud_chanmask.hip"):
         if re.match(r"_ZN.*k_gap_partial.*:", line):
             name, run = line.split(":")[0], 0
             most[name] = 0

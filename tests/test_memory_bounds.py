@@ -9,6 +9,8 @@ from concurrent.futures import ThreadPoolExecutor
 import numpy as np
 import pytest
 
+import test_gpu_first
+import test_gpu_narrow
 from paper_2308_15949_amd import binding as B
 from paper_2308_15949_amd import build as build_rules
 
@@ -199,6 +201,7 @@ CASES = {
     "narrow_static": ("first", "static", 1, 241, 239, 64, 64, 256, 2, 1, 1.0),
     "one_kernel_first": ("first", "static", 2, 27, 41, 64, 64, 256, 1, 1, 1.0),
     "one_kernel_first_one_row": ("first", "static", 1, 1, 1100, 64, 64, 256, 1, 1, 1.0),
+    "one_kernel_first_walk": ("first", "static", 768, 4, 4, 64, 64, 256, 1, 1, 1.0),  # three rectangles a workgroup
     "narrow_projection": ("first", "dynamic", 5, 111, 112, 64, 64, 256, 2, 8, 0.4),
     "fused": ("identity", "dyn", 22, 14, 14, 1024, 256, 2, 0.3, True, False),
     "fused_packed": ("identity", "masker", 22, 14, 14, 1024, 256, 2, 0.5, True, True, None, 0, True, True),
@@ -273,8 +276,15 @@ CASES = {
 
 
 # Tiles that a case is there for (kernel, mode, type, rows x columns; "split": the K steps are shared by two groups of waves): a rule
-# that sends the case elsewhere leaves them untested.  Every tile of k_pipe and k_group is some case's.
+# that sends the case elsewhere leaves them untested.  Every tile of k_pipe and k_group is some case's,
+# and every instance of k_narrow and k_first.
 REACHES = {
+    "narrow": ["narrow false"],
+    "narrow_static": ["narrow true"],
+    "narrow_projection": ["narrow false"],
+    "one_kernel_first": ["first"],
+    "one_kernel_first_one_row": ["first"],
+    "one_kernel_first_walk": ["first"],
     "tiled_128x64": ["pipe CONV2 bf16 128x64", "pipe SD1 bf16 128x64", "pipe CONV3 bf16 128x64"],
     "tiled_64x128_split": ["pipe CONV2 bf16 64x128 split"],
     "tiled_128x128": ["pipe CONV2 bf16 128x128"],
@@ -337,7 +347,8 @@ def tiles(names):
     names, found = names.replace("unsigned short", "bf16"), set()
     for kernel, mode, dtype, rows, columns, rest in re.findall(r"k_(pipe|gemm)<(\d+), (\w+), (\d+), (\d+), ([\d, ]+)>", names):
         found.add(f"{kernel} {MODES[int(mode)]} {dtype} {rows}x{columns}" + (" split" if rest.split(", ")[2:3] == ["2"] else ""))
-    return found | {f"group {k}" for k in re.findall(r"k_group<(\d)>", names)}
+    found |= {"first"} if "k_first(" in names else set()
+    return found | {f"group {k}" for k in re.findall(r"k_group<(\d)>", names)} | {f"narrow {k}" for k in re.findall(r"k_narrow<(\w+)>", names)}
 
 
 def test_every_tile_of_the_many_row_kernels_has_a_case(lib):
@@ -388,11 +399,16 @@ NOT_ONE_KERNEL = [
 ]
 
 
-@pytest.mark.parametrize("case", ONE_KERNEL + NOT_ONE_KERNEL)
+@pytest.mark.parametrize("case", [(*c, 1, "first") for c in ONE_KERNEL + test_gpu_first.CASES] +
+                         [(*c, 1, None) for c in NOT_ONE_KERNEL] + [(*c, "narrow true") for c in test_gpu_narrow.STATIC_CASES])
 def test_static_block_takes_the_whole_block_kernel_where_a_map_fills_it(lib, case, capfd):
+    """(the sizes of the GPU tests of both kernels too: that they are about the kernel they name)"""
+    n, h, w, stride, kernel = case
+
     def body():
         call = Call(lib, 0)
         call.host.host_record_only()
-        call.first("static", *case, 64, 64, 256, 1, 1, 1.0)
-        assert ("k_first" in call.launched()) == (case in ONE_KERNEL), call.launched()
+        call.first("static", n, h, w, 64, 64, 256, stride, 1, 1.0)
+        found = tiles(call.launched())
+        assert kernel in found if kernel else "first" not in found, call.launched()
     in_a_process_of_its_own(body, capfd)
