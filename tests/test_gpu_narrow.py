@@ -85,6 +85,8 @@ def test_narrow_static_first_block(G, case):  # noqa: F811
     (1, 1, 1), (1, 7, 300), (1, 27, 30), (1, 29, 34),   # one pixel; one strip cut along x; one past a strip and past a step
     (300, 20, 20),                                      # more strips than compute units
     (90, 90, 46),                                       # four strips an image, the last ragged
+    # two workgroups a compute unit, 512: more strips than that, of two steps, of four strips an image; three strips a workgroup, three steps
+    (600, 20, 20), (140, 90, 46), (1100, 13, 66),
 ])
 def test_stem_one_kernel(G, case):  # noqa: F811
     t, L, D = G.torch, G.L, G.D
