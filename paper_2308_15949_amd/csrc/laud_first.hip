@@ -186,7 +186,9 @@ __device__ __forceinline__ void first_finish(const FirstArgs& a, const int tile0
   const __amdgpu_buffer_rsrc_t ors = __builtin_amdgcn_make_buffer_rsrc(a.out, 0, (int)kOob, 0x00020000);
   const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.x), 0, (int)kOob, 0x00020000);
   const unsigned chunk = ((unsigned)l7 ^ (unsigned)l8 ^ (w4 & 1u)) << 4;
-  int ld[kHalo / 32];  // the pixels this lane requests, from the first output pixel: y << 16 | x & 0xffff (far outside past the end)
+  // the pixels this lane requests, from the first output pixel: y << 16 | x & 0xffff; past the end 16384 rows up, outside maps that are not
+  // taller and any pixel of those that are (nobody uses what comes to these rows)
+  int ld[kHalo / 32];
 #pragma unroll
   for (int i = 0; i < kHalo / 32; ++i) {
     const int r = 8 * (w4 + 4 * i) + l8, y = fast_div(r, a.d_rw);
