@@ -2,7 +2,7 @@
 // kernel: first 1x1 -> 3x3 -> last 1x1 + projection shortcut, gfx950.
 //
 // What bounds it is memory at large batches: the input once, the output (four times as many channels) once, 61 us for 128 images of 56 x 56
-// at the rate of a copy.  h1 and h2 stay on the compute unit; with a first 1x1 in a launch of its own, h1 went out and came back nine-fold,
+// at the rate of a copy (272 MB of traffic measured, 257 of them input and output).  h1 and h2 stay on the compute unit; with a first 1x1 in a launch of its own, h1 went out and came back nine-fold,
 // tap by tap.  First 1x1 and k_narrow / here: 128 images 126 to 133 / 92 to 106 us (one machine and another), 32 images 44.9 / 33.8, 8
 // images 19.7 / 15.6, 50 images of 72 x 72 74.3 / 61.8.  One and four images, three and four launches / here: 16.8 / 13.4 and 24.4 / 14.1.
 //
@@ -29,7 +29,8 @@ namespace first {
 constexpr int kMid = 64, kOut = 256, kThreads = 512, kRows = 128, kHalo = 192;
 constexpr int kXBytes = kHalo * 128, kXBufs = 3;             // input: in the first waves' hands, in the others', under way
 // A pixel of h1 takes 144 bytes (nine 16-byte units: a tap is a distance that is the same for every pixel) and a rectangle's row 14 units
-// more: 32 output pixels in a row of rectangles' rows, whose inputs jump by two from one row to the next, stay free of bank conflicts.
+// more: 32 output pixels in a row of rectangles' rows jump by two inputs from one row to the next.  (Conflicts are 29 % of the kernel's LDS
+// cycles all the same, SQ_LDS_BANK_CONFLICT; an LDS instruction is under way in 4 % of a wave's time.)
 constexpr int kH1Pix = 144, kH1Pad = 224, kMaxTh = 18;
 constexpr int kH1 = kXBufs * kXBytes, kH2 = kH1 + kHalo * kH1Pix + (kMaxTh + 2) * kH1Pad;  // h2: being made, being used
 constexpr int kTab = kH2 + 2 * kRows * 128;                  // s1 t1 s2 t2 [64] | s3, s_sc, t3 + t_sc [256]

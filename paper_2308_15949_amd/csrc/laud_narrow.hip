@@ -16,6 +16,8 @@
 //     is requested ahead of the fourth tap and used after the ninth.
 //   * tiles are dealt so that an XCD works on one contiguous eighth of the rows: its taps find their neighbours in its L2.
 //
+// With a shortcut: blocks in front of a stride and maps too small for the rectangles of laud_first.hip (128 images of 112 x 112 to 56 x 56 122
+// us, 8192 maps of 7 x 7 91 us, the first 1x1 ahead of it not counted).
 // Vector-memory waits: see laud_tail.hip; the loads younger than the slice waited for are counted at each wait.
 #include "laud_common.h"
 #include "laud_tile_util.h"

@@ -53,7 +53,7 @@ typedef __attribute__((ext_vector_type(16))) float stem_f32x16;
 //     columns = 8 pooled columns; the step's conv columns and the last one of the step before lie in LDS, so the pooling windows
 //     that reach one column back find it there.
 //   * Image rows, products and pooling of a step are phases between barriers, each bound by something else; two workgroups a
-//     compute unit fill each other's (71 KB of LDS, 128 registers a lane).  A wave brings whole image rows, a dword a lane, so what a
+//     compute unit fill each other's (62.5 KB of LDS, 128 registers a lane).  A wave brings whole image rows, a dword a lane, so what a
 //     row and a dword stand for is scalar or the same for all rows.  With 101 KB of LDS, one workgroup a compute unit, 32 conv columns
 //     and dwords dealt out over the threads (a division, bounds and masks for each) and copies of 240 bytes (reads in conflict): 128 / 256 images of
 //     224 x 224 85.2 / 162 us, here 62.4 / 118; two such workgroups without the rest 80.2 / 151; 8 / 32 images 14.5 / 27.0 -> 14.4 / 26.0.

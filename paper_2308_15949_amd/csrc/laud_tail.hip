@@ -321,7 +321,7 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
 
   // ---- the last 1x1, column tile by column tile: no activation loads, no barriers ------------------------------
   // Two accumulator sets alternate between column tiles: while tile ct is multiplied into one, the other (tile
-  // ct-1) goes through its epilogue -- affine, residual add, activation, rounding, store -- in half-block pieces
+  // ct-1) goes through its epilogue -- affine, residual add, activation, rounding, store -- in quarter-block pieces
   // placed behind the MFMAs of tile ct's first K steps, so the vector ALU works in the shadow of the matrix pipe.
   // Results go through the wave's part of the turning buffer; then lane l holds channels 8 * (l % 4) .. +7 of row 16 q + l / 4 of a
   // pixel block, q = 0, 1.  The row of the map is read from LDS where it is used (kept, it and its 64-bit address cost the
