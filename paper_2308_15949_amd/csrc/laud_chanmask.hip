@@ -39,34 +39,49 @@ __global__ __launch_bounds__(kGapThreads) void k_gap_partial(const ET* __restric
 #pragma unroll
     for (int e = 0; e < EPC; ++e) acc[e] = 0.f;
     if (active) {
-      // kU pixels' chunks in flight per thread before any is added, then four, two, one (same order of additions as one by one).  None of
-      // the loads stands behind a condition of its own: the compiler puts the unpacking there too, and with it a wait for every load (bf16,
-      // one map of 61 x 67 x 4096: 55 us against 34 here).  float32 with four: 16 maps of 56 x 56 x 4096 169 us, with eight 174.
+      // kU pixels' chunks in flight per thread before any is added, then what is left of the slab in one or two steps (same order of additions
+      // as one by one).  No load has a condition of its own: the compiler puts the unpacking there too, and with it a wait for every load
+      // (bf16, one map of 61 x 67 x 4096: 55 us against 34 here); past the slab's end lanes read the first pixel left and add nothing.  How many
+      // there are is the same for all lanes, so addresses are scalar but for one offset: with eight pointers a lane (98 registers, five
+      // waves a SIMD instead of eight) narrow maps, whose blocks are one load a thread, were up to 1.4 times slower.  float32 with four:
+      // 16 maps of 56 x 56 x 4096 169 us, with eight 174.
       constexpr int kU = sizeof(ET) == 2 ? 8 : 4;
-      const ET* at = x + ((size_t)n * HW + p0 + pl) * C + (size_t)cv * EPC;
-      const size_t step = (size_t)lanes * C;
-      int left = (p1 - p0 - pl + lanes - 1) / lanes;
-      auto add = [&](auto count) __attribute__((always_inline)) {
+      const char* row = reinterpret_cast<const char*>(x + ((size_t)n * HW + p0) * C);
+      const unsigned step = (unsigned)(lanes * C * sizeof(ET)), first = (unsigned)(cv * EPC * sizeof(ET)), own = (unsigned)(pl * C * sizeof(ET));
+      int left = p1 - p0;
+      auto add = [&](auto count, auto whole) __attribute__((always_inline)) {  // count pixels of every lane, or half as many and what is left
         constexpr int U = decltype(count)::value;
+        constexpr bool kWhole = decltype(whole)::value;
+        unsigned at = first + own;
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("" : "+v"(at));  // (known from one batch to the next, it becomes a pointer a lane for every load)
+#endif
         u32x4 raw[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) raw[u] = *reinterpret_cast<const u32x4*>(at + u * step);
+        for (int u = 0; u < U; ++u)
+          raw[u] = *reinterpret_cast<const u32x4*>(kWhole || u < U / 2 ? row + (size_t)u * step + at
+                                                                       : row + (u * lanes + pl < left ? u * step + at : first));
 #if defined(__HIP_DEVICE_COMPILE__)
         asm volatile("" : "+v"(raw[U - 1]));  // (or it requests the last one behind the additions)
 #endif
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+          if (!kWhole && u >= U / 2 && u * lanes + pl >= left) raw[u] = u32x4{0, 0, 0, 0};  // (changes no sum)
           ET v[EPC];
           __builtin_memcpy(v, &raw[u], 16);
 #pragma unroll
           for (int e = 0; e < EPC; ++e) acc[e] += elem<ET>::load(&v[e]);
         }
-        at += U * step;
+        row += U * step;
+        left -= U * lanes;
       };
-      for (; left >= kU; left -= kU) add(std::integral_constant<int, kU>{});
-      if (kU > 4 && (left & 4)) add(std::integral_constant<int, 4>{});
-      if (left & 2) add(std::integral_constant<int, 2>{});
-      if (left & 1) add(std::integral_constant<int, 1>{});
+      constexpr std::true_type kAll;
+      constexpr std::false_type kSome;
+      while (left >= kU * lanes) add(std::integral_constant<int, kU>{}, kAll);
+      if (kU > 4 && left >= 4 * lanes) add(std::integral_constant<int, 4>{}, kAll);
+      if (left > 2 * lanes) add(std::integral_constant<int, 4>{}, kSome);
+      else if (left > lanes) add(std::integral_constant<int, 2>{}, kSome);
+      else if (pl < left) add(std::integral_constant<int, 1>{}, kAll);
     }
     if (lanes == 1) {  // (every thread has a chunk column's whole sum)
       if (active) __builtin_memcpy(partial + ((size_t)n * slabs + slab) * C + (size_t)cv * EPC, acc, sizeof(acc));
@@ -75,11 +90,13 @@ __global__ __launch_bounds__(kGapThreads) void k_gap_partial(const ET* __restric
 #pragma unroll
     for (int e = 0; e < EPC; ++e) red[threadIdx.x * EPC + e] = acc[e];
     __syncthreads();
-    // the pixel lanes of a chunk column are added in lane order, a channel per thread
+    // the pixel lanes of a chunk column are added in lane order, a channel per thread, eight reads at a time (up to 256 lanes: 256 maps of
+    // 28 x 28 x 8 92 us one by one, 35 here)
     const int row = cw * EPC, nc = min(row, C - cv0 * EPC);
     float* const out = partial + ((size_t)n * slabs + slab) * C + (size_t)cv0 * EPC;
     for (int c = threadIdx.x; c < nc; c += kGapThreads) {
       float s = 0.f;
+#pragma unroll 8
       for (int l = 0; l < lanes; ++l) s += red[l * row + c];
       out[c] = s;
     }

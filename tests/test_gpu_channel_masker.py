@@ -16,8 +16,9 @@ CASES = [
     (2, 56, 56, 256, 64, I.BF16),  # stage 1, G = 1
     (64, 14, 14, 1024, 4, I.BF16),  # config 4, stage 3
     (2, 4, 4, 4104, 8, I.F32),     # more chunk columns than threads
-    (2, 41, 53, 2048, 64, I.BF16),  # 33 and 34 pixels a thread: several whole batches of loads, and one or two behind them
-    (2, 41, 53, 1032, 64, I.F32),
+    # remainders of a slab behind its whole batches of loads, 1 / 2 / 8 / 32 / 256 lanes a column
+    (2, 41, 53, 2048, 64, I.BF16), (2, 41, 53, 1032, 64, I.F32), (2, 41, 59, 1024, 64, I.BF16), (3, 57, 58, 256, 64, I.BF16), (3, 41, 47, 128, 64, I.F32),
+    (2, 61, 67, 64, 64, I.BF16), (70, 13, 11, 72, 16, I.BF16), (2, 61, 67, 8, 64, I.BF16), (2, 23, 45, 8, 64, I.F32),
 ]
 
 

@@ -263,6 +263,7 @@ CASES = {
     "masks": ("masks", 3, 12, 20, 72, 4),
     "masks_f32_gates": ("masks", 5, 14, 14, 8, 7, False, True),
     "masks_long_lists": ("masks", 9, 32, 33, 8, 1),
+    "masks_wide": ("masks", 1, 14, 7, 1032, 7),  # one lane a chunk column in the channel masker's pooling
     "masks_unfused_split": ("masks", 3, 12, 20, 72, 4, True, False, 4, 136),
     "masks_unfused_128x128": ("masks", 12, 56, 56, 8, 4, True, False, 4, 136),
     "masks_unfused_64x128_f32": ("masks", 3, 12, 20, 136, 4, False, False, 4, 136),
