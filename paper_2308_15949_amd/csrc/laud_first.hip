@@ -387,13 +387,14 @@ bool first_plan(int dtype, int c_in, int c_mid, int c_out, int stride, FirstArgs
   a.ntiles = a.N * a.pern;
   // A rectangle costs about the same however full it is (about 5 us a round of them, 12 the first), and none spans two samples: what counts is
   // the rounds against those of the other routes, whose tiles are full whatever the map.
-  //   small tiles (up to 14336 rows; 12.5 us and 0.8 a thousand rows): 1100 rows of 1 x 1 / 2 x 2 (5 / 2 rounds) 13.4 / 13.2 us there, 31 /
-  //   16.4 here; 4000 rows of 3 x 3 (2) 17.2, 16.7; 14000 of 7 x 7 / 5 x 5 / 4 x 4 (2 / 3 / 4) 24.3 / 23.7 / 24.0, 17.9 / 21.7 / 26.0.
+  //   small tiles (up to 14336 rows): 1200 / 2700 / 4600 rows of 2 x 2 / 3 x 3 / 3 x 3 (2 rounds here) 13.3 / 18.3 / 18.8 us there, 16.4 / 16.5 /
+  //   16.8 here; 12272 / 12288 rows of 4 x 4 (3) 22.8 / 22.7, 23.0 / 22.1; 14000 of 7 x 7 / 5 x 5 / 4 x 4 (2 / 3 / 4) 24.3 / 23.7 / 24.0, 17.9 /
+  //   21.7 / 26.0.
   //   k_narrow's rounds of 128 rows a workgroup take 8 us with the first 1x1 ahead of them: 30000 rows (1 of its rounds) of 8 x 8 / 7 x 7 (2 /
   //   3 here) 20.1 / 19.9, 19.3 / 23.5; 100000 (4) of 12 x 12 / 8 x 8 / 4 x 4 (6 / 7 / 25) 42.5 / 42.1 / 42, 39.1 / 43.1 / 116; 400000 (13)
   //   of 9 x 9 / 12 x 12 / 4 x 4 (20 / 22 / 98) 108 / 112 / 110, 108 / 118 / 428.
   const long long rounds = (a.ntiles + wgs - 1) / wgs;
-  if (!narrow_supported(dtype, c_mid, c_out, rows)) return (rounds - 1) * 6144 <= rows;
+  if (!narrow_supported(dtype, c_mid, c_out, rows)) return rounds == 1 || (rounds - 2) * 9728 + 2560 <= rows;
   const long long full = (rows + (long long)first::kRows * wgs - 1) / ((long long)first::kRows * wgs);
   return 5 * rounds <= 8 * full + 2;
 }

@@ -391,11 +391,11 @@ def test_kernels_stay_inside_their_buffers(lib, name, front, capfd):
 # maps, only where it needs few rounds of them for the rows there are (256 workgroups, 128 rows each).
 ONE_KERNEL = [
     (2, 41, 25), (128, 56, 56), (50, 72, 72), (1, 1100, 1), (65, 4, 4),       # full rectangles; at most one a workgroup
-    (384, 4, 4), (492, 5, 5), (768, 4, 4), (286, 7, 7),                       # small tiles: the second round from 6144 rows on, the third from 12288
+    (285, 3, 3), (492, 5, 5), (768, 4, 4), (286, 7, 7),                       # small tiles: a second round from 2560 rows on, a third from 12288
     (300, 7, 7), (512, 8, 8), (768, 8, 8), (694, 12, 12), (4669, 9, 9),       # ahead of the 64-wide kernel's tiles: 2 rounds for 1, 3 for 2, 6 for 4, 19 for 12
 ]
 NOT_ONE_KERNEL = [
-    (1, 32, 32), (1100, 1, 1), (257, 2, 2), (383, 4, 4), (683, 3, 3), (767, 4, 4), (769, 4, 4), (13, 1100, 1),
+    (1, 32, 32), (1100, 1, 1), (257, 2, 2), (284, 3, 3), (683, 3, 3), (767, 4, 4), (769, 4, 4), (13, 1100, 1),
     (600, 5, 5), (30000, 1, 1), (1875, 4, 4), (612, 7, 7), (1024, 8, 8), (1562, 8, 8), (2778, 12, 12), (25000, 4, 4), (27, 1100, 1), (667, 300, 2),
 ]
 
