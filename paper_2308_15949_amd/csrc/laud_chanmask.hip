@@ -7,7 +7,7 @@
 //                   What counts is bytes in flight to a slab's end and a short finish: with four loads at a time,
 //                   the last pixels of a slab one by one and a channel's lanes added by a few threads (their
 //                   reads in bank conflict), 64 images at the four ResNet stages 30.8 / 15.8 / 11.7 / 8.5 us; now
-//                   26.8 / 16.2 / 9.9 / 5.8 (3.8 TB/s at stage 1, 2.2 at stage 4).
+//                   25.1 / 14.1 / 9.2 / 5.9 (4.1 TB/s at stage 1, 2.2 at stage 4).
 //   k_channel_mlp   one block per sample: adds the partial rows in slab order, divides by H*W, runs
 //                   the two small layers (float32) and writes the D keep/drop decisions.
 #include "laud_common.h"
