@@ -253,8 +253,10 @@ __device__ __forceinline__ void first_finish(const FirstArgs& a, const int tile0
         const u32x4 lo = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[8], v[9]), pack_bf16(v[10], v[11])};
         const u32x4 hi = {pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]), pack_bf16(v[12], v[13]), pack_bf16(v[14], v[15])};
         // (always sixteen stores a rectangle, which the wait below counts on: pixels that do not exist lie outside the descriptor)
-        __builtin_amdgcn_raw_buffer_store_b128(lo, ors, at, j * 64, 0);
-        __builtin_amdgcn_raw_buffer_store_b128(hi, ors, at, j * 64 + 16, 0);
+        // (no scalar offset: behind a 16-byte buffer store that has one the compiler leaves no wait state before a vector
+        // instruction writes the store's data registers again, and the store then takes what was written)
+        __builtin_amdgcn_raw_buffer_store_b128(lo, ors, at + j * 64, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(hi, ors, at + j * 64 + 16, 0, 0);
         __builtin_amdgcn_sched_barrier(0);  // one block at a time (registers)
       }
     }

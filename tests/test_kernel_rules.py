@@ -116,6 +116,17 @@ def test_pooling_loads_of_a_batch_are_under_way_together(assembly):
     assert len(most) == 2 and all(v >= (8 if "ItE" in k else 4) for k, v in most.items()), most
 
 
+@pytest.mark.parametrize("name", ["laud_first.hip", "laud_tail.hip"])
+def test_wide_buffer_stores_have_no_scalar_offset(assembly, name):
+    """A buffer store of more than 8 bytes reads its data registers over several cycles.  The compiler keeps the next vector instruction
+    from writing them too early, but not where the store has a scalar register for an offset: there the first register was found
+    overwritten.  In the generated code of the kernels with buffer stores none has one."""
+    stores = [t.split(",") for t in assembly(name) if re.match(r"\s*buffer_store_dwordx[34]\b", t)]
+    assert all(re.match(r"\s*(0|off|-?\d+)\b(?! *:)", t[3]) for t in stores), [t for t in stores if re.match(r"\s*s\d", t[3])]
+    named = "raw_buffer_store" in open(os.path.join(B.CSRC, name)).read()
+    assert bool(stores) == named
+
+
 def test_no_inline_assembly_load_writes_a_register():
     """The compiler takes an asm statement's outputs as written when it ends and may copy or re-use them while the load is still
     under way.  Loads into registers are builtins, whose waits it places itself; asm loads go to LDS (no output operand)."""
