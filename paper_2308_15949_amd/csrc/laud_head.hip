@@ -6,10 +6,16 @@
 //     its weight fragments in registers, streamed from the packed copy of w1 (four K slices held / in flight);
 //   * x reaches LDS with LDS-direct 16-byte loads into a four-stage ring of 128-byte K slices, swizzled on the
 //     global side; one barrier per slice, in its middle; fragments are read one K step ahead of their MFMAs;
-//   * the MFMAs compute the transposed tile, so after one lane swap per register pair a lane holds 16 consecutive
-//     channels of a pixel: h1 = relu(s1 * acc + t1) leaves in 32-byte pieces, without an LDS transpose;
-//   * the masker projection sum_c w[c] * x[pixel][c] is formed on the vector ALU from the activation fragments the
-//     waves hold anyway: K step q of the tile is taken by wave q % 8, partial sums meet in LDS at the end.
+//   * the MFMAs compute the transposed tile, so a lane holds 4 x 4 consecutive channels of a pixel: h1 = relu(s1 * acc + t1)
+//     goes through 4 KB of LDS a wave and leaves with four lanes on 64 bytes of a row;
+//   * the masker projection sum_c w[c] * x[pixel][c] is formed on the vector ALU from the same LDS slices, every wave an equal share
+//     of every slice, partial sums meet in LDS at the end.
+//
+// What bounds it (128 x 14 x 14 x 1024, 196 tiles of 128 rows): 16 slices of 1024 cycles of MFMAs between 2.5 us until the first rows
+// are there and 2 us of stores.  What is not a MFMA stands behind one each, in pieces that take no longer: the two waves of a SIMD issue
+// in step, and what both do between their MFMAs the matrix pipe waits for.  In a row ahead of the MFMAs, with the projection of a
+// K step on one wave and the rows' 16-byte stores 512 bytes apart, a slice took 1610 cycles, the stores 4200, the launch 21.8 us;
+// now 1320, 2900 and 18.4 (one input over and over; with x cold in HBM the slices wait for it, 3.3 TB/s).
 #include "laud_common.h"
 #include "laud_tail_pack.h"
 #include "laud_tile_util.h"
@@ -27,12 +33,18 @@ constexpr int kWRing = 4;                     // weight slices in registers
 constexpr unsigned kOob = 0x80000000u;
 constexpr int kMaxK = 4096;
 __host__ __device__ constexpr int a_stage(int pb) { return 32 * pb * 128; }  // one 128-byte K slice of every pixel row
-// behind the activation ring: s1, t1 [256] floats, masker weights [K] floats, partial sums [8][32*pb], then the
-// output rows of the tile (int)
+// behind the activation ring: s1, t1 [256] floats, the tile's output rows [32*pb] (int), partial sums of the projection
+// [8 / pb][32*pb], the waves' turning buffers (two pixel blocks of 32 rows x 64 bytes each), masker weights [K] floats
+constexpr int kTurn = 2 * 32 * 64;
 __host__ __device__ constexpr int tab_off(int pb) { return kARing * a_stage(pb); }
-__host__ __device__ constexpr int lds_bytes(int K, int pb) { return tab_off(pb) + 2 * kMid * 4 + K * 4 + kWaves * 32 * pb * 4 + 32 * pb * 4; }
-constexpr int kListOff = tab_off(kMaxPB) + 2 * kMid * 4;
-static_assert(kHeadGroup + kHeadGroup / kWave * 4 + 128 * 4 <= 256 * 4 + kWaves * 32 * kMaxPB * 4, "the list's tables end ahead of the output rows");
+__host__ __device__ constexpr int orow_off(int pb) { return tab_off(pb) + 2 * kMid * 4; }
+__host__ __device__ constexpr int part_off(int pb) { return orow_off(pb) + 32 * pb * 4; }
+__host__ __device__ constexpr int turn_off(int pb) { return part_off(pb) + kWaves * 32 * 4; }
+__host__ __device__ constexpr int wm_off(int pb) { return turn_off(pb) + kWaves * kTurn; }
+__host__ __device__ constexpr int lds_bytes(int K, int pb) { return wm_off(pb) + K * 4; }
+// where a workgroup makes its list (no projection then): behind everything a tile of either height writes ahead of its loop
+constexpr int kListOff = turn_off(kMaxPB);
+static_assert(wm_off(2) <= kListOff && kHeadGroup + kHeadGroup / kWave * 4 + 128 * 4 <= kWaves * kTurn, "the list's tables share their bytes");
 // time of one tile of 64 / 128 pixels in the same unit (measured 14-17 and 21-26 us at K = 1024): a workgroup streams
 // all of w1 whatever its height
 constexpr int kCost2 = 2, kCost4 = 3;
@@ -62,9 +74,9 @@ __device__ __forceinline__ void head_tile(const HeadArgs& a, const int row0, con
   static_assert(PB % 2 == 0, "an activation instruction of all eight waves covers 64 rows");
   float* const s_s1 = reinterpret_cast<float*>(smem + kTabOff);
   float* const s_t1 = s_s1 + kMid;
-  float* const s_wm = s_t1 + kMid;
-  float* const s_part = s_wm + a.K;
-  int* const s_orow = reinterpret_cast<int*>(s_part + kWaves * kBM);
+  int* const s_orow = reinterpret_cast<int*>(smem + orow_off(PB));
+  float* const s_part = reinterpret_cast<float*>(smem + part_off(PB));
+  float* const s_wm = reinterpret_cast<float*>(smem + wm_off(PB));
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -82,23 +94,27 @@ __device__ __forceinline__ void head_tile(const HeadArgs& a, const int row0, con
     }
   }
 
+  // ---- per-channel tables: requested ahead of the streams, stored to LDS behind them -------------------------------
+  static_assert(kThreads == 2 * kMid, "a thread takes one entry of s1 or t1");
+  const float tab = tid < kMid ? a.s1[tid] : a.t1[tid - kMid];
+  constexpr int kWm = PROJ ? kMaxK / kThreads : 1;
+  float wm[kWm];
+  if constexpr (PROJ) {
+#pragma unroll
+    for (int i = 0; i < kWm; ++i)
+      if (i * kThreads < K) wm[i] = a.wmask[min(i * kThreads + tid, K - 1)];
+  }
+
   // ---- weight stream: four slices in registers -------------------------------------------------------------------
   // (buffer loads: see laud_tail.hip)
   const __amdgpu_buffer_rsrc_t wrs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.wpacked), 0, NSL * (tail::kSliceChunks * 16), 0x00020000);
   const unsigned wlane = (unsigned)(wave * 4096 + lane * 16);
   u32x4 wr[kWRing][4];
-  auto load_W = [&](int buf, int b) __attribute__((always_inline)) {
+  auto load_W = [&](int buf, int b, int kg) __attribute__((always_inline)) {
     const int bb = b < NSL ? b : NSL - 1;  // past the end: the last slice again (keeps the load count uniform)
-#pragma unroll
-    for (int kg = 0; kg < 4; ++kg) wr[buf][kg] = __builtin_amdgcn_raw_buffer_load_b128(wrs, wlane + kg * 1024, bb * (tail::kSliceChunks * 16), 0);
+    wr[buf][kg] = __builtin_amdgcn_raw_buffer_load_b128(wrs, wlane + kg * 1024, bb * (tail::kSliceChunks * 16), 0);
   };
-#pragma unroll
-  for (int b = 0; b < kWRing; ++b) load_W(b, b);
-
-  for (int i = tid; i < kMid; i += kThreads) { s_s1[i] = a.s1[i]; s_t1[i] = a.t1[i]; }
-  if constexpr (PROJ)
-    for (int i = tid; i < K; i += kThreads) s_wm[i] = a.wmask[i];
 
   // ---- activation rows: instruction i of wave w loads rows 64i + 8w .. +7; row r keeps chunk c at position
   // c ^ (r&7) ^ ((r>>3)&1) ---------------------------------------------------------------------------------------
@@ -120,8 +136,21 @@ __device__ __forceinline__ void head_tile(const HeadArgs& a, const int row0, con
     for (int i = 0; i < kAI; ++i)
       dma16(xrs, s < NSL ? voffA[i] : kOob, soff, ldsA + (unsigned)(s & (kARing - 1)) * kAStage + i * 8192);
   };
+  // slice by slice, so that the first multiplications wait for the first slice only
+  static_assert(kARing == 4 && kWRing == 4, "the counts of the waits below");
 #pragma unroll
-  for (int s = 0; s < kARing - 1; ++s) issue_A(s);
+  for (int s = 0; s < kWRing; ++s) {
+    if (s < kARing - 1) issue_A(s);
+#pragma unroll
+    for (int kg = 0; kg < 4; ++kg) load_W(s, s, kg);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  s_s1[tid] = tab;  // (s1, then t1)
+  if constexpr (PROJ) {
+#pragma unroll
+    for (int i = 0; i < kWm; ++i)
+      if (i * kThreads + tid < K) s_wm[i * kThreads + tid] = wm[i];
+  }
 
   unsigned swz[4];
   {
@@ -129,115 +158,115 @@ __device__ __forceinline__ void head_tile(const HeadArgs& a, const int row0, con
 #pragma unroll
     for (int kg = 0; kg < 4; ++kg) swz[kg] = (unsigned)l31 * 128u + (((2u * kg + lhi) ^ f) << 4);
   }
+  // of the two waves of a SIMD one goes first, the other's MFMAs fill what it leaves: in step both would wait and multiply at once
+  if (wave < kWaves / 2) __builtin_amdgcn_s_setprio(1);
   f32x16 acc[PB];
-  float psum[PB];
 #pragma unroll
-  for (int t = 0; t < PB; ++t) {
-    psum[t] = 0.f;
+  for (int t = 0; t < PB; ++t)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
-  }
+  // The masker projection: wave w takes the pixel block w % PB in every kShare-th K step, the same work for every wave and slice
+  // (a wave that took one step for all blocks kept the others waiting at the slice's barrier: 1610 cycles a slice, 1024 of them
+  // MFMAs).  Four sums of a lane: as many products in a chain as the sums of sixteen lanes' steps had.
+  constexpr int kShare = kWaves / PB;
+  const int pblk = wave % PB, pshare = wave / PB;
+  float psum[4] = {0.f, 0.f, 0.f, 0.f};
+  uint4 pv = make_uint4(0, 0, 0, 0);
+  float4 pw[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
+  const unsigned swzp = (swz[0] ^ (unsigned)(pshare * 32)) + pblk * 4096;  // the chunk of K step pshare
+  const float* const wmp = s_wm + pshare * 16 + lhi * 8;
   uint4 fa[2][PB];
-  auto read_frags = [&](int buf, int s, int kg) __attribute__((always_inline)) {
-    const unsigned char* pa = smem + (unsigned)(s & (kARing - 1)) * kAStage + swz[kg];
-#pragma unroll
-    for (int t = 0; t < PB; ++t) fa[buf][t] = *reinterpret_cast<const uint4*>(pa + t * 4096);
+  auto read_frag = [&](int buf, int s, int kg, int t) __attribute__((always_inline)) {
+    fa[buf][t] = *reinterpret_cast<const uint4*>(smem + (unsigned)(s & (kARing - 1)) * kAStage + swz[kg] + t * 4096);
   };
 
-  vm_wait<0>();
+  vm_wait<16 + 2 * kAI>();  // own part of the activations of slice 0 (behind them: W(0), A(1), W(1), A(2), W(2), W(3))
   lds_wait();
   wg_barrier();
-  read_frags(0, 0, 0);
+#pragma unroll
+  for (int t = 0; t < PB; ++t) read_frag(0, 0, 0, t);
 
-  // Four slices = sixteen K steps with static register indices.  Vector-memory operations of a wave in program
-  // order, per slice s: A(s+R-1) x kAI [middle of s], W(s+4) x4 [end of s], R = kARing.  Needed at the barrier of
-  // slice s: A(s+1), issued R-2 slices earlier -- R-2 weight slices and R-3 activation slices are younger.  Loads
-  // past the last slice are issued all the same so that the count holds to the end.  (A deeper ring, R = 8, measured
-  // slower: 27.8 against 25.4 us at 128 x 14 x 14 x 1024.)
+  // Four slices = sixteen K steps with static register indices.  A weight register is refilled behind the step that
+  // used it: a wave that issues its four loads of a slice in a row stands in the queue of the compute unit's vector-memory
+  // path, which takes 64 bytes a cycle, and its MFMAs with it.  Vector-memory operations of a wave in program order, per
+  // slice s: W(s+4) K steps 0, 1; A(s+3) x kAI [middle of s]; W(s+4) K steps 2, 3.  Needed at the barrier of slice s:
+  // A(s+1), issued two slices earlier -- two steps of W, then W x 4 and A(s+2), then two steps of W are younger: 8 + kAI
+  // loads; of the slices 0 and 1, whose A(s+1) lies ahead of the loop, 14 + kAI.  Loads past the last slice are issued all
+  // the same so that the count holds to the end.
   for (int s0 = 0; s0 < NSL; s0 += 4) {
 #pragma unroll
     for (int g = 0; g < 16; ++g) {
       const int s = s0 + g / 4, kg = g % 4;
-      if (kg < 3) read_frags((g + 1) & 1, s, kg + 1);
-      else if (s + 1 < NSL) read_frags((g + 1) & 1, s + 1, 0);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int t = 0; t < PB; ++t) acc[t] = mma_bf16(wr[g / 4][kg], fa[g & 1][t], acc[t]);
-      if constexpr (PROJ) {
-        // this wave's share of the masker projection: K steps q with q % 8 == wave (s0 is a multiple of 4)
-        if ((g & 7) == wave) {
-          const float4 w0 = *reinterpret_cast<const float4*>(s_wm + s * 64 + kg * 16 + lhi * 8);
-          const float4 w1 = *reinterpret_cast<const float4*>(s_wm + s * 64 + kg * 16 + lhi * 8 + 4);
-#pragma unroll
-          for (int t = 0; t < PB; ++t) {
-            const uint4 v = fa[g & 1][t];
-            float p = psum[t];
-            p += __uint_as_float(v.x << 16) * w0.x; p += __uint_as_float(v.x & 0xffff0000u) * w0.y;
-            p += __uint_as_float(v.y << 16) * w0.z; p += __uint_as_float(v.y & 0xffff0000u) * w0.w;
-            p += __uint_as_float(v.z << 16) * w1.x; p += __uint_as_float(v.z & 0xffff0000u) * w1.y;
-            p += __uint_as_float(v.w << 16) * w1.z; p += __uint_as_float(v.w & 0xffff0000u) * w1.w;
-            psum[t] = p;
-          }
-        }
+      if (PROJ && g % kShare == 0) {
+        pv = *reinterpret_cast<const uint4*>(smem + (unsigned)(s & (kARing - 1)) * kAStage + (swzp ^ (unsigned)(kg * 32)));
+        pw[0] = *reinterpret_cast<const float4*>(wmp + s * 64 + kg * 16);
+        pw[1] = *reinterpret_cast<const float4*>(wmp + s * 64 + kg * 16 + 4);
       }
+#pragma unroll
+      for (int t = 0; t < PB; ++t) {
+        acc[t] = mma_bf16(wr[g / 4][kg], fa[g & 1][t], acc[t]);
+        __builtin_amdgcn_sched_barrier(0);
+        read_frag((g + 1) & 1, kg < 3 ? s : s + 1, (kg + 1) & 3, t);  // (behind the last slice: of a stage that nothing is done with)
+        const int m = g % kShare * PB + t;  // eight MFMAs a chunk: two of its elements behind every second one
+        if (PROJ && (m & 1)) {
+          const int d = m / 2;
+          const unsigned v = d == 0 ? pv.x : d == 1 ? pv.y : d == 2 ? pv.z : pv.w;
+          const float4 w = pw[d / 2];
+          psum[2 * (d & 1)] += __uint_as_float(v << 16) * (d & 1 ? w.z : w.x);
+          psum[2 * (d & 1) + 1] += __uint_as_float(v & 0xffff0000u) * (d & 1 ? w.w : w.y);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      load_W(g / 4, s + kWRing, kg);
       __builtin_amdgcn_sched_barrier(0);
       if (kg == 1) {
-        vm_wait<4 * (kARing - 2) + (kARing - 3) * kAI>();
+        if (s < 2) vm_wait<14 + kAI>(); else vm_wait<8 + kAI>();
         wg_barrier();
         issue_A(s + kARing - 1);
-      }
-      if (kg == 3) {
-        load_W(g / 4, s + kWRing);
-        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
 
-  // ---- h1 = relu(s1 * acc + t1), 32 bytes per lane and pixel ------------------------------------------------------
+  // ---- h1 = relu(s1 * acc + t1); through LDS, so that four lanes store 64 bytes of a row (laud_tile_util.h: row_put, row_get) ------
   {
     const int cb = wave * 32;
     __bf16* const outp = reinterpret_cast<__bf16*>(a.h1);
+    float4 sc[4], sh[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      sc[g] = *reinterpret_cast<const float4*>(s_s1 + cb + 8 * g + 4 * lhi);
+      sh[g] = *reinterpret_cast<const float4*>(s_t1 + cb + 8 * g + 4 * lhi);
+    }
 #pragma unroll
     for (int t = 0; t < PB; ++t) {
-      float v[16];
+      unsigned char* const turn = smem + turn_off(PB) + wave * kTurn + (t & 1) * 2048;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const float4 sc = *reinterpret_cast<const float4*>(s_s1 + cb + 8 * g + 4 * lhi);
-        const float4 sh = *reinterpret_cast<const float4*>(s_t1 + cb + 8 * g + 4 * lhi);
-        v[4 * g + 0] = fmaxf(acc[t][4 * g + 0] * sc.x + sh.x, 0.f);
-        v[4 * g + 1] = fmaxf(acc[t][4 * g + 1] * sc.y + sh.y, 0.f);
-        v[4 * g + 2] = fmaxf(acc[t][4 * g + 2] * sc.z + sh.z, 0.f);
-        v[4 * g + 3] = fmaxf(acc[t][4 * g + 3] * sc.w + sh.w, 0.f);
+        uint2 c = make_uint2(pack_bf16(fmaxf(acc[t][4 * g] * sc[g].x + sh[g].x, 0.f), fmaxf(acc[t][4 * g + 1] * sc[g].y + sh[g].y, 0.f)),
+                             pack_bf16(fmaxf(acc[t][4 * g + 2] * sc[g].z + sh[g].z, 0.f), fmaxf(acc[t][4 * g + 3] * sc[g].w + sh[g].w, 0.f)));
+        if (!((hkeep >> t) & 1u)) c = make_uint2(0, 0);  // channel skipping: the row's sample drops the group of this wave's channels
+        *reinterpret_cast<uint2*>(turn + row_put(lane, g)) = c;
       }
-      const int pixel = s_orow[32 * t + l31];
-      if (!((hkeep >> t) & 1u)) {  // channel skipping: the row's sample drops the group of this wave's channels
 #pragma unroll
-        for (int e = 0; e < 16; ++e) v[e] = 0.f;
-      }
-      to_consecutive_channels(v);
-      const uint4 c0 = make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[8], v[9]), pack_bf16(v[10], v[11]));
-      const uint4 c1 = make_uint4(pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]), pack_bf16(v[12], v[13]), pack_bf16(v[14], v[15]));
-      if (pixel >= 0) {
-        uint4* dst = reinterpret_cast<uint4*>(outp + (size_t)pixel * kMid + cb + lhi * 16);
-        dst[0] = c0;
-        dst[1] = c1;
+      for (int q = 0; q < 2; ++q) {
+        const uint4 c = *reinterpret_cast<const uint4*>(turn + row_get(lane, q));
+        const int pixel = s_orow[32 * t + 16 * q + (lane >> 2)];
+        if (pixel >= 0) *reinterpret_cast<uint4*>(outp + (size_t)pixel * kMid + cb + (lane & 3) * 8) = c;
       }
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  // ---- projection: the two K halves of a pixel sit in lanes l and l+32; then the eight waves' shares -------------
+  // ---- projection: the two K halves of a pixel sit in lanes l and l+32; then the shares of the block's waves --------
   if constexpr (PROJ) {
-#pragma unroll
-    for (int t = 0; t < PB; ++t) {
-      const float other = __shfl_xor(psum[t], 32, kWave);
-      if (lhi == 0) s_part[wave * kBM + 32 * t + l31] = psum[t] + other;
-    }
+    const float half = (psum[0] + psum[1]) + (psum[2] + psum[3]);
+    const float other = __shfl_xor(half, 32, kWave);
+    if (lhi == 0) s_part[pshare * kBM + 32 * pblk + l31] = half + other;
     lds_wait();
     wg_barrier();
     if (tid < kBM && s_orow[tid] >= 0) {
       float p = 0.f;
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) p += s_part[w * kBM + tid];
+      for (int w = 0; w < kShare; ++w) p += s_part[w * kBM + tid];
       a.proj[s_orow[tid]] = p;
     }
   }
@@ -257,8 +286,7 @@ __global__ __launch_bounds__(head::kThreads) void k_head(const HeadArgs a) {
       // The dilated pixel list of the workgroup's group of samples, made here by every workgroup of the group for itself: a chain of
       // two memory round trips and three barriers (about 2 us), where a launch that writes the lists takes 7.  Workgroup id ->
       // (group, tile) as for lists below.  The height goes by the group's own count: groups need not agree.
-      // (in the bytes of the masker weights and partial sums, which only the projection uses: the tile's own loads, which a faster
-      // wave may issue while another still reads here, go elsewhere)
+      // (in bytes that a tile writes behind its loop only: a faster wave may be there while another still reads here)
       extern __shared__ __align__(16) unsigned char smem[];
       unsigned char* const s_pm = smem + kListOff;  // patch masks of the group's samples
       int* const s_cnt = reinterpret_cast<int*>(s_pm + kHeadGroup);

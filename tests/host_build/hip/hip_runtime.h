@@ -25,9 +25,11 @@ struct dim3 {
 };
 struct alignas(8) float2 { float x, y; };
 struct alignas(16) float4 { float x, y, z, w; };
+struct alignas(8) uint2 { unsigned x, y; };
 struct alignas(16) uint4 { unsigned x, y, z, w; };
 static inline float4 make_float4(float a, float b, float c, float d) { return {a, b, c, d}; }
 static inline float2 make_float2(float a, float b) { return {a, b}; }
+static inline uint2 make_uint2(unsigned a, unsigned b) { return {a, b}; }
 static inline uint4 make_uint4(unsigned a, unsigned b, unsigned c, unsigned d) { return {a, b, c, d}; }
 using std::max;
 using std::min;
@@ -100,6 +102,7 @@ static inline int lanes_below(unsigned mask, int first) {  // set bits of 32 lan
 #define __builtin_amdgcn_permlane32_swap(a, b, c, d) (host::Pair{{a, b}})
 #define __builtin_amdgcn_readfirstlane(x) (x)
 #define __builtin_amdgcn_sched_barrier(x)
+#define __builtin_amdgcn_s_setprio(x)
 #define __builtin_amdgcn_mbcnt_lo(m, v) ((v) + host::lanes_below(m, 0))
 #define __builtin_amdgcn_mbcnt_hi(m, v) ((v) + host::lanes_below(m, 32))
 
