@@ -311,6 +311,7 @@ struct TailArgs {
   int cs_group;
   InactiveCopy cp;       // nblocks 0: in place
   int wg_target;         // workgroups that fill the device once (its compute units; set by launch_tail)
+  FastDiv d_s, d_ss, d_wp, d_pps;  // S, S * S, patches of a row and of a sample (set by launch_tail)
 };
 
 bool tail_supported(int dtype, int c_mid, int c_out);

@@ -15,12 +15,17 @@
 //     per slice, placed in the middle of the slice's MFMAs; fragments of the next K step (also across slices) are
 //     read before the current step's MFMAs are issued.
 //   * The MFMAs compute the transposed tile (weights as the first operand): a lane then holds, for one pixel,
-//     4 x 4 consecutive channels; one v_permlane32_swap per register pair turns that into 16 consecutive channels
-//     per lane, and h2 goes to LDS in 16-byte pieces.  The result passes through 4 KB of LDS a wave on its way to
+//     4 x 4 consecutive channels, and h2 goes to LDS in 8-byte pieces.  The result passes through 4 KB of LDS a wave on its way to
 //     memory, so that four lanes together hold 64 bytes of a row (laud_tile_util.h: turn_put, turn_get).
 //   * h2 (pixels x 256 bf16) sits behind the activation ring in LDS; the last 1x1 streams w3 through the
 //     same weight ring (no barrier at all in that phase), reads the residual, adds, applies the
 //     activation, rounds and stores.
+//
+// What bounds it: the compute unit's vector-memory path of 64 bytes a cycle.  A 64-pixel tile brings 40 KB a slice of the 3x3 and 32 KB
+// of weights, 8 KB of residual and 8 KB of results a slice of the last 1x1; measured are 690 and 900 cycles where the path alone takes
+// 640 and 768 (12544 pixels; MFMAs 512).  Ahead of it stand 2.7 us of count -> list -> rows, in whose shadow the tables and the
+// first weights come.  The launch 33.5 -> 31.0 us with tables and weights out of the rows' way, the last 1x1's epilogue in pieces of one
+// MFMA's time and results stored through a descriptor.
 //
 // Channel skipping (Fig. 2(c)) rides on the same kernel (template flag CS): the "patches" are whole samples in
 // mask-pattern order, the 3x3 leaves out the 64-channel input slices whose group no row of the tile keeps, and h2 is
@@ -101,7 +106,7 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
   const int SS = a.S * a.S;
   int qsp[(PB + 1) / 2];
 #pragma unroll
-  for (int i = 0; i < (PB + 1) / 2; ++i) qsp[i] = a.list[min(row0 + 64 * i + 8 * wave + l8, M - 1) / SS];  // (see list_entry)
+  for (int i = 0; i < (PB + 1) / 2; ++i) qsp[i] = a.list[fast_div(min(row0 + 64 * i + 8 * wave + l8, M - 1), a.d_ss)];  // (see list_entry)
   // ---- channel skipping: which input slices of the 3x3 this tile needs ---------------------------------------------
   // The tile's rows belong to the list entries (samples) row0/SS .. (row0+kBM-1)/SS; a K chunk (64 input channels) is
   // needed if any of them keeps the chunk's group.  n2 = slices of the 3x3 that are multiplied (9 taps x kept
@@ -138,6 +143,16 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
     }
   }
 
+  // ---- per-channel affine tables: requested with the list entries, stored to LDS behind the first rows' requests -------------
+  static_assert(kThreads == 2 * kMid, "a thread takes one entry of s2 or t2");
+  float tab[1 + 4 * NCT / 2];
+  tab[0] = tid < kMid ? a.s2[tid] : a.t2[tid - kMid];
+#pragma unroll
+  for (int i = 0; i < COUT / kThreads; ++i) {
+    tab[1 + 2 * i] = a.s3[i * kThreads + tid];
+    tab[2 + 2 * i] = a.t3[i * kThreads + tid];
+  }
+
   // ---- weight stream: a ring of slices in registers (one in use, the others in flight) ------------------------------
   // (Buffer loads: a 64-bit address per lane takes vector instructions and register reads from the MFMAs.  One compute unit's
   // stream beside two MFMAs and two fragment reads a K step: 93 bytes a ns through such addresses, 119 through a descriptor; a
@@ -159,18 +174,17 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
 #pragma unroll
     for (int kg = 0; kg < 4; ++kg) wr[buf][kg] = fragment_W(b, kg);
   };
+  // (two slices ahead of the rows, which wait for the list, the others behind them: what the compute unit's path of 64 bytes a cycle
+  // brings first is what the first multiplications need)
+  constexpr int kFirstW = 2;
 #pragma unroll
-  for (int b = 0; b < WR; ++b) load_W(b, b);
-
-  // ---- per-channel affine tables --------------------------------------------------------------------------------
-  for (int i = tid; i < kMid; i += kThreads) { s_s2[i] = a.s2[i]; s_t2[i] = a.t2[i]; }
-  for (int i = tid; i < COUT; i += kThreads) { s_s3[i] = a.s3[i]; s_t3[i] = a.t3[i]; }
+  for (int b = 0; b < kFirstW; ++b) load_W(b, b);
 
   // ---- activation rows: instruction i of wave w loads rows 64i + 8w .. +7, lane l the chunk position l%8 of row
   // 64i + 8w + l/8; row r keeps chunk c at position c ^ f(r), f(r) = (r&7) ^ ((r>>3)&1) (conflict-free fragment
   // reads; the swizzle is applied on the global side) -----------------------------------------------------------
   const int sy = a.stride;
-  const int Hp = a.Ho / a.S, Wp = a.Wo / a.S;
+  const int Wp = fast_div(a.Wo, a.d_s), pps = fast_div(a.Ho, a.d_s) * Wp;
   unsigned voffA[kAI], amask[kAI];
 #pragma unroll
   for (int i = 0; i < kAI; ++i) {
@@ -179,11 +193,11 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
     const int rho = row0 + r;
     if (r >= kBM) continue;
     if (rho < M) {
-      const int p = rho / SS, j = rho - p * SS;
+      const int j = rho - fast_div(rho, a.d_ss) * SS, jy = fast_div(j, a.d_s);
       const int q = qsp[i];
-      const int n = q / (Hp * Wp), r2 = q - n * (Hp * Wp);
-      const int py = r2 / Wp, px = r2 - py * Wp;
-      const int yo = py * a.S + j / a.S, xo = px * a.S + j % a.S;
+      const int n = fast_div(q, a.d_pps), r2 = q - n * pps;
+      const int py = fast_div(r2, a.d_wp), px = r2 - py * Wp;
+      const int yo = py * a.S + jy, xo = px * a.S + j - jy * a.S;
       const int y = yo * sy, x = xo * sy;  // centre of the 3x3 on the input grid
       const unsigned pix = (unsigned)(n * a.H * a.W + y * a.W + x);
       const unsigned c = (unsigned)l7 ^ ((unsigned)(l8 & 7) ^ (wave & 1u));
@@ -220,6 +234,14 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
   issue_A(0);
   issue_A(1);
   issue_A(2);
+#pragma unroll
+  for (int b = kFirstW; b < WR; ++b) load_W(b, b);
+  s_s2[tid] = tab[0];  // (s2, then t2)
+#pragma unroll
+  for (int i = 0; i < COUT / kThreads; ++i) {
+    s_s3[i * kThreads + tid] = tab[1 + 2 * i];
+    s_t3[i * kThreads + tid] = tab[2 + 2 * i];
+  }
 
   // ---- fragment addresses: row lane%32 of a 32-row block, chunk 2*kg + lane/32, swizzled ------------------------
   unsigned swz[4];
@@ -236,46 +258,49 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
     for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
 
   uint4 fa[2][PB];  // activation fragments of the pixel blocks, read one K step ahead of their MFMAs
-  auto read_frags2 = [&](int buf, int s, int kg) __attribute__((always_inline)) {
-    const unsigned char* pa = smem + kAOff + (unsigned)(s & (kARing - 1)) * kAStage + swz[kg];
-#pragma unroll
-    for (int t = 0; t < PB; ++t) fa[buf][t] = *reinterpret_cast<const uint4*>(pa + t * 4096);
+  auto read_frag2 = [&](int buf, int s, int kg, int t) __attribute__((always_inline)) {
+    fa[buf][t] = *reinterpret_cast<const uint4*>(smem + kAOff + (unsigned)(s & (kARing - 1)) * kAStage + swz[kg] + t * 4096);
   };
 
   // ---- the 3x3 -----------------------------------------------------------------------------------------------
-  vm_wait<0>();  // everything issued so far (weights 0-2, activations 0-2 of this wave) has landed
+  vm_wait<4 * (WR - kFirstW)>();  // the first weights and this wave's part of activations 0-2 have landed
   l2_touched(touched);
   lds_wait();    // the tables written above
   wg_barrier();  // ... and everybody else's
   TAIL_STAMP(1);
-  read_frags2(0, 0, 0);
+#pragma unroll
+  for (int t = 0; t < PB; ++t) read_frag2(0, 0, 0, t);
 
   // WR slices = 4 WR K steps with static register indices (weight buffer g/4, fragment buffer g%2).
   // One barrier per slice, in its middle: behind it everyone's activations of the next slice have landed and
   // everyone is done with the slice before this one, whose stage is refilled (three slices ahead).
-  // Vector-memory operations of a wave in program order, per slice s: A(s+3) x kAI [middle of s], W(s+3) x4 [end
-  // of s].  Needed at the barrier of slice s: A(s+1), issued two slices earlier -- W(s+1), A(s+2), W(s+2) are
-  // younger: 8 + (this wave's activation instructions per slice) loads.  Activation loads past the last slice are issued all the same (they read as zeros
+  // A weight register is refilled behind the step that used it (a wave that issues the four loads of a slice in a row stands in
+  // the queue of the compute unit's vector-memory path, and its MFMAs with it), a fragment read behind each MFMA.
+  // Vector-memory operations of a wave in program order, per slice s: W(s+WR) K steps 0, 1; A(s+3) x kAI [middle of s]; W(s+WR)
+  // K steps 2, 3.  Needed at the barrier of slice s: A(s+1), issued two slices earlier -- two steps of W, then W x 4 and A(s+2),
+  // then two steps of W are younger: 8 + (this wave's activation instructions per slice) loads; of the first two slices all
+  // have landed ahead of the loop.  Activation loads past the last slice are issued all the same (they read as zeros
   // into stages nobody reads any more) so that the count holds to the end.
   auto group2 = [&](int s0) __attribute__((always_inline)) {
+    int refill = 0;
 #pragma unroll
     for (int g = 0; g < 4 * WR; ++g) {
       const int s = s0 + g / 4, kg = g % 4;
       if (kg == 0) TAIL_STAMP(2 + s);
-      if (kg < 3) read_frags2((g + 1) & 1, s, kg + 1);
-      else if (s + 1 < n2) read_frags2((g + 1) & 1, s + 1, 0);
-      __builtin_amdgcn_sched_barrier(0);  // the next step's fragment reads stay ahead of this step's MFMAs
+      if (kg == 0) refill = sid(s + WR);
 #pragma unroll
-      for (int t = 0; t < PB; ++t) acc[t] = mma_bf16(wr[g / 4][kg], fa[g & 1][t], acc[t]);
+      for (int t = 0; t < PB; ++t) {
+        acc[t] = mma_bf16(wr[g / 4][kg], fa[g & 1][t], acc[t]);
+        __builtin_amdgcn_sched_barrier(0);
+        read_frag2((g + 1) & 1, kg < 3 ? s : s + 1, (kg + 1) & 3, t);  // (behind the last slice: of a stage that nothing is done with)
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      wr[g / 4][kg] = fragment_W(refill, kg);  // (the stream continues into the last 1x1)
       __builtin_amdgcn_sched_barrier(0);
       if (kg == 1) {
         if (lastA) vm_wait<8 + kAI>(); else vm_wait<8 + kAI - 1>();  // own part of the activations of slice s+1
         wg_barrier();        // everyone's; and everyone is done with slice s-1
         issue_A(s + 3);
-      }
-      if (kg == 3) {
-        load_W(g / 4, s + WR);  // (the stream continues into the last 1x1)
-        __builtin_amdgcn_sched_barrier(0);
       }
     }
   };
@@ -285,33 +310,25 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
   TAIL_STAMP(38);
   {
     const int cb = wave * 32;
+    float4 sc[4], sh[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      sc[g] = *reinterpret_cast<const float4*>(s_s2 + cb + 8 * g + 4 * lhi);
+      sh[g] = *reinterpret_cast<const float4*>(s_t2 + cb + 8 * g + 4 * lhi);
+    }
 #pragma unroll
     for (int t = 0; t < PB; ++t) {
-      float v[16];
+      // pixel row r, 512 bytes per row; 16-byte chunk c sits at position c ^ (r & 15); this lane's half of chunk 4 * wave + g
+      const unsigned r = 32u * t + l31;
+      unsigned char* row = smem + kH2Off + r * 512u + lhi * 8u;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const float4 sc = *reinterpret_cast<const float4*>(s_s2 + cb + 8 * g + 4 * lhi);
-        const float4 sh = *reinterpret_cast<const float4*>(s_t2 + cb + 8 * g + 4 * lhi);
-        v[4 * g + 0] = fmaxf(acc[t][4 * g + 0] * sc.x + sh.x, 0.f);
-        v[4 * g + 1] = fmaxf(acc[t][4 * g + 1] * sc.y + sh.y, 0.f);
-        v[4 * g + 2] = fmaxf(acc[t][4 * g + 2] * sc.z + sh.z, 0.f);
-        v[4 * g + 3] = fmaxf(acc[t][4 * g + 3] * sc.w + sh.w, 0.f);
+        uint2 c = make_uint2(pack_bf16(fmaxf(acc[t][4 * g] * sc[g].x + sh[g].x, 0.f), fmaxf(acc[t][4 * g + 1] * sc[g].y + sh[g].y, 0.f)),
+                             pack_bf16(fmaxf(acc[t][4 * g + 2] * sc[g].z + sh[g].z, 0.f), fmaxf(acc[t][4 * g + 3] * sc[g].w + sh[g].w, 0.f)));
+        // the channel mask multiplies the 3x3's output: a row that drops this wave's group stores zeros
+        if (CS && !((hkeep >> t) & 1u)) c = make_uint2(0, 0);
+        *reinterpret_cast<uint2*>(row + (((wave * 4u + g) ^ (r & 15u)) << 4)) = c;
       }
-      if constexpr (CS) {  // the mask multiplies the 3x3's output: a row that drops this wave's group stores zeros
-        if (!((hkeep >> t) & 1u)) {
-#pragma unroll
-          for (int e = 0; e < 16; ++e) v[e] = 0.f;
-        }
-      }
-      to_consecutive_channels(v);
-      const uint4 c0 = make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[8], v[9]), pack_bf16(v[10], v[11]));
-      const uint4 c1 = make_uint4(pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]), pack_bf16(v[12], v[13]), pack_bf16(v[14], v[15]));
-      // pixel row r, 512 bytes per row; 16-byte chunk c sits at position c ^ (r & 15)
-      const unsigned r = 32u * t + l31;
-      const unsigned ch = wave * 4u + lhi * 2u;
-      unsigned char* row = smem + kH2Off + r * 512u;
-      *reinterpret_cast<uint4*>(row + ((ch ^ (r & 15u)) << 4)) = c0;
-      *reinterpret_cast<uint4*>(row + (((ch + 1u) ^ (r & 15u)) << 4)) = c1;
       __builtin_amdgcn_sched_barrier(0);              // one pixel block at a time (register pressure)
     }
   }
@@ -321,22 +338,21 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
 
   // ---- the last 1x1, column tile by column tile: no activation loads, no barriers ------------------------------
   // Two accumulator sets alternate between column tiles: while tile ct is multiplied into one, the other (tile
-  // ct-1) goes through its epilogue -- affine, residual add, activation, rounding, store -- in quarter-block pieces
-  // placed behind the MFMAs of tile ct's first K steps, so the vector ALU works in the shadow of the matrix pipe.
+  // ct-1) goes through its epilogue -- affine, residual add, activation, rounding, store -- piece by piece: a quarter of a pixel
+  // block is four pieces of about eight vector instructions, each behind one MFMA, which takes as long (in larger pieces both
+  // waves of a SIMD multiplied first and then stood in line for the vector ALU: 1000 cycles a slice, 512 of them MFMAs).
   // Results go through the wave's part of the turning buffer; then lane l holds channels 8 * (l % 4) .. +7 of row 16 q + l / 4 of a
-  // pixel block, q = 0, 1.  The row of the map is read from LDS where it is used (kept, it and its 64-bit address cost the
-  // registers that the accumulators need); negative: the pixel does not exist.
-  const int ocol = wave * 32 + (lane & 3) * 8;
-  const __bf16* const resp = reinterpret_cast<const __bf16*>(a.res);
-  __bf16* const outp = reinterpret_cast<__bf16*>(a.out);
+  // pixel block, q = 0, 1.  The row of the map is read from LDS where it is used (kept, its address costs the registers that the
+  // accumulators need); a row that does not exist has an offset outside the descriptors: nothing is read or stored there.
+  const unsigned ocol = (unsigned)(wave * 32 + (lane & 3) * 8) * 2u;
+  const __amdgpu_buffer_rsrc_t resrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.res), 0, (int)kOob, 0x00020000);
+  const __amdgpu_buffer_rsrc_t outrs = __builtin_amdgcn_make_buffer_rsrc(a.out, 0, (int)kOob, 0x00020000);
   unsigned char* const turn = smem + kTurnOff + wave * kTurnBytes;
   const unsigned hrow = kH2Off + (unsigned)l31 * 512u;  // h2 fragment rows: pixel block t at + t * 32 * 512
   const unsigned hx = (unsigned)(l31 & 15);
-  auto read_frags3 = [&](int buf, int ks, int kg) __attribute__((always_inline)) {
+  auto read_frag3 = [&](int buf, int ks, int kg, int t) __attribute__((always_inline)) {
     const unsigned c = (unsigned)(ks * 8 + 2 * kg) + lhi;
-#pragma unroll
-    for (int t = 0; t < PB; ++t)
-      fa[buf][t] = *reinterpret_cast<const uint4*>(smem + hrow + t * (32 * 512) + ((c ^ hx) << 4));
+    fa[buf][t] = *reinterpret_cast<const uint4*>(smem + hrow + t * (32 * 512) + ((c ^ hx) << 4));
   };
   const float floor_ = act_floor(a.relu);
   f32x16 acc2[DUAL ? PB : 1];  // the second accumulator set (odd column tiles)
@@ -344,38 +360,49 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
 #pragma unroll
   for (int t = 0; t < PB; ++t) res[t][0] = res[t][1] = u32x4{0, 0, 0, 0};
 
-  // Quarters of the epilogue of a pixel block of column tile ct: the affine of accumulator groups 2 h and 2 h + 1 into the turning
-  // buffer (twice), then residual, activation, rounding and store of 16 rows (twice).
-  auto turn_in = [&](int ct, int h, const f32x16& A) __attribute__((always_inline)) {
-    const int cb = ct * 256 + wave * 32;
-#pragma unroll
-    for (int g = 2 * h; g < 2 * h + 2; ++g) {
-      const float4 sc = *reinterpret_cast<const float4*>(s_s3 + cb + 8 * g + 4 * lhi);
-      const float4 sh = *reinterpret_cast<const float4*>(s_t3 + cb + 8 * g + 4 * lhi);
-      *reinterpret_cast<float4*>(turn + turn_put(lane, g)) =
-          make_float4(A[4 * g] * sc.x + sh.x, A[4 * g + 1] * sc.y + sh.y, A[4 * g + 2] * sc.z + sh.z, A[4 * g + 3] * sc.w + sh.w);
+  // Piece `part` of quarter u of pixel block t.  Quarters 0, 1: the affine of accumulator groups 2 u and 2 u + 1 of column tile `from`
+  // into the turning buffer; 2, 3: residual, activation, rounding and store of 16 of its rows, then the request for the residual
+  // that column tile `next` adds there.  (from, next outside the column tiles: none)
+  float4 e0, e1;       // what a piece hands on to the next: scale and shift, or eight results
+  unsigned eoff = 0;   // byte offset of the row's channels in column tile 0
+  u32x4 epk = {0, 0, 0, 0};
+  auto piece = [&](const f32x16& A, int from, int next, int t, int u, int part) __attribute__((always_inline)) {
+    if (u < 2) {
+      if (from < 0) return;
+      const int g = 2 * u + part / 2, c = from * 256 + wave * 32 + 8 * g + 4 * lhi;
+      if (!(part & 1)) {
+        e0 = *reinterpret_cast<const float4*>(s_s3 + c);
+        e1 = *reinterpret_cast<const float4*>(s_t3 + c);
+      } else {
+        *reinterpret_cast<float4*>(turn + turn_put(lane, g)) =
+            make_float4(A[4 * g] * e0.x + e1.x, A[4 * g + 1] * e0.y + e1.y, A[4 * g + 2] * e0.z + e1.z, A[4 * g + 3] * e0.w + e1.w);
+      }
+      return;
     }
-  };
-  auto turn_out = [&](int ct, int t, int q) __attribute__((always_inline)) {
-    const float4 x0 = *reinterpret_cast<const float4*>(turn + turn_get(lane, q, 0));
-    const float4 x1 = *reinterpret_cast<const float4*>(turn + turn_get(lane, q, 1));
-    const float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-    u32x4 pk;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      const float lo = fmaxf(x[2 * d] + __uint_as_float(res[t][q][d] << 16), floor_);
-      const float hi = fmaxf(x[2 * d + 1] + __uint_as_float(res[t][q][d] & 0xffff0000u), floor_);
-      pk[d] = pack_bf16(lo, hi);
+    const int q = u - 2;
+    if (part == 0) {
+      if (from >= 0) {
+        e0 = *reinterpret_cast<const float4*>(turn + turn_get(lane, q, 0));
+        e1 = *reinterpret_cast<const float4*>(turn + turn_get(lane, q, 1));
+      }
+      const int o = s_orow[32 * t + 16 * q + (lane >> 2)];
+      eoff = o >= 0 ? (unsigned)o * (COUT * 2u) + ocol : kOob;
+    } else if (part < 3) {
+      if (from < 0) return;
+      const float4 x = part == 1 ? e0 : e1;
+      const unsigned r0 = res[t][q][2 * part - 2], r1 = res[t][q][2 * part - 1];
+      epk[2 * part - 2] = pack_bf16(fmaxf(x.x + __uint_as_float(r0 << 16), floor_), fmaxf(x.y + __uint_as_float(r0 & 0xffff0000u), floor_));
+      epk[2 * part - 1] = pack_bf16(fmaxf(x.z + __uint_as_float(r1 << 16), floor_), fmaxf(x.w + __uint_as_float(r1 & 0xffff0000u), floor_));
+    } else {
+      // (no scalar offset: behind a 16-byte buffer store that has one the compiler leaves no wait state before it writes the store's
+      // first data register again, and the store then stores what was written)
+      if (from >= 0) __builtin_amdgcn_raw_buffer_store_b128(epk, outrs, eoff + from * 512, 0, 0);
+      if (next >= 0) res[t][q] = __builtin_amdgcn_raw_buffer_load_b128(resrs, eoff, next * 512, 0);
     }
-    const int o = s_orow[32 * t + 16 * q + (lane >> 2)];
-    if (o >= 0) *reinterpret_cast<u32x4*>(outp + (size_t)o * COUT + (ocol + ct * 256)) = pk;
-  };
-  auto load_residual = [&](int ct, int t, int q) __attribute__((always_inline)) {
-    const int o = max(s_orow[32 * t + 16 * q + (lane >> 2)], 0);
-    res[t][q] = *reinterpret_cast<const u32x4*>(resp + (size_t)o * COUT + (ocol + ct * 256));
   };
 
-  read_frags3(0, 0, 0);
+#pragma unroll
+  for (int t = 0; t < PB; ++t) read_frag3(0, 0, 0, t);
 #pragma unroll
   for (int ct = 0; ct < NCT; ++ct) {
 #pragma unroll
@@ -385,56 +412,32 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
       const int BUF = b % WR;
       if (kg == 0) TAIL_STAMP(40 + ct * kKch + ks);
       const int cur = st & 1, nxt = cur ^ 1;
-      if (kg < 3) read_frags3(nxt, ks, kg + 1);
-      else if (b + 1 < kNB) read_frags3(nxt, (ks + 1) % kKch, 0);
-      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int t = 0; t < PB; ++t) {
         f32x16& A = DUAL && (ct & 1) ? acc2[t] : acc[t];
         if (st == 0) A = mma_bf16(wr[BUF][kg], fa[cur][t], f32x16{});  // (a column tile starts from zero)
         else A = mma_bf16(wr[BUF][kg], fa[cur][t], A);
-      }
-      // Odd steps 1, 3, ...: a quarter of a pixel block each.  With two accumulator sets the previous tile's epilogue piece
-      // runs behind these MFMAs; the residual registers it frees are refilled at once with this tile's values, a
-      // whole tile ahead of their use.
-      if ((st & 1) && st / 2 < 4 * PB) {
-        if constexpr (DUAL) {
-          const int t = st / 8, u = st / 2 % 4;
-          if (u < 2) {
-            if (ct > 0) { if (ct & 1) turn_in(ct - 1, u, acc[t]); else turn_in(ct - 1, u, acc2[t]); }
-          } else {
-            if (ct > 0) turn_out(ct - 1, t, u - 2);
-            load_residual(ct, t, u - 2);
-          }
-        } else if (st / 2 < 2 * PB) {
-          load_residual(ct, st / 4, st / 2 % 2);
-        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (kg < 3) read_frag3(nxt, ks, kg + 1, t);
+        else if (b + 1 < kNB) read_frag3(nxt, (ks + 1) % kKch, 0, t);
+        // 16 * PB MFMAs a column tile, four for each of the 4 * PB quarters of the tile before it; a residual register is refilled
+        // where it is used up, a whole tile ahead of its next use
+        const int m = st * PB + t, pt = m / 16, u = m / 4 % 4;
+        if constexpr (DUAL) piece(ct & 1 ? acc[pt] : acc2[pt], ct - 1, ct, pt, u, m % 4);
+        else if (u >= 2) piece(acc[pt], -1, ct, pt, u, m % 4);
+        __builtin_amdgcn_sched_barrier(0);
       }
       // the weight register just used is refilled for one ring length later
       if (b + WR < kNB) wr[BUF][kg] = fragment_W(b + WR, kg);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if constexpr (!DUAL) {  // one accumulator set: the epilogue follows its tile
+    if (!DUAL || ct == NCT - 1) {  // one accumulator set, and the last tile: the epilogue follows its tile
 #pragma unroll
       for (int t = 0; t < PB; ++t) {
-        turn_in(ct, 0, acc[t]);
-        turn_in(ct, 1, acc[t]);
-        turn_out(ct, t, 0);
-        turn_out(ct, t, 1);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) piece(DUAL && (ct & 1) ? acc2[t] : acc[t], ct, -1, t, i / 4, i % 4);
         __builtin_amdgcn_sched_barrier(0);
       }
-    }
-  }
-  if constexpr (DUAL) {  // the last tile's epilogue
-#pragma unroll
-    for (int t = 0; t < PB; ++t) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        if ((NCT - 1) & 1) turn_in(NCT - 1, h, acc2[t]); else turn_in(NCT - 1, h, acc[t]);
-      }
-      turn_out(NCT - 1, t, 0);
-      turn_out(NCT - 1, t, 1);
-      __builtin_amdgcn_sched_barrier(0);
     }
   }
   TAIL_STAMP(56);
@@ -538,6 +541,8 @@ int launch_tail(const TailArgs& args, long long cap_rows, hipStream_t st) {
   }
   TailArgs a = args;
   a.wg_target = g_tail_cus[dev];
+  a.d_s = make_fast_div(a.S); a.d_ss = make_fast_div(a.S * a.S); a.d_wp = make_fast_div(a.Wo / a.S);
+  a.d_pps = make_fast_div((a.Ho / a.S) * (a.Wo / a.S));
   // one workgroup per 32 rows of the capacity: enough for the smallest tile height; workgroups past the last tile
   // of the height chosen on the device leave at once
   unsigned grid = (unsigned)((cap_rows + 31) / 32);
