@@ -242,16 +242,16 @@ __device__ __forceinline__ void head_tile(const HeadArgs& a, const int row0, con
       unsigned char* const turn = smem + turn_off(PB) + wave * kTurn + (t & 1) * 2048;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        uint2 c = make_uint2(pack_bf16(fmaxf(acc[t][4 * g] * sc[g].x + sh[g].x, 0.f), fmaxf(acc[t][4 * g + 1] * sc[g].y + sh[g].y, 0.f)),
-                             pack_bf16(fmaxf(acc[t][4 * g + 2] * sc[g].z + sh[g].z, 0.f), fmaxf(acc[t][4 * g + 3] * sc[g].w + sh[g].w, 0.f)));
-        if (!((hkeep >> t) & 1u)) c = make_uint2(0, 0);  // channel skipping: the row's sample drops the group of this wave's channels
-        *reinterpret_cast<uint2*>(turn + row_put(lane, g)) = c;
+        u32x2 c = {pack_bf16(fmaxf(acc[t][4 * g] * sc[g].x + sh[g].x, 0.f), fmaxf(acc[t][4 * g + 1] * sc[g].y + sh[g].y, 0.f)),
+                   pack_bf16(fmaxf(acc[t][4 * g + 2] * sc[g].z + sh[g].z, 0.f), fmaxf(acc[t][4 * g + 3] * sc[g].w + sh[g].w, 0.f))};
+        if (!((hkeep >> t) & 1u)) c = u32x2{0, 0};  // channel skipping: the row's sample drops the group of this wave's channels
+        *reinterpret_cast<u32x2*>(turn + row_put(lane, g)) = c;
       }
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
-        const uint4 c = *reinterpret_cast<const uint4*>(turn + row_get(lane, q));
+        const u32x4 c = *reinterpret_cast<const u32x4*>(turn + row_get(lane, q));
         const int pixel = s_orow[32 * t + 16 * q + (lane >> 2)];
-        if (pixel >= 0) *reinterpret_cast<uint4*>(outp + (size_t)pixel * kMid + cb + (lane & 3) * 8) = c;
+        if (pixel >= 0) *reinterpret_cast<u32x4*>(outp + (size_t)pixel * kMid + cb + (lane & 3) * 8) = c;
       }
       __builtin_amdgcn_sched_barrier(0);
     }

@@ -10,7 +10,8 @@
 // wave's part of the next slice has landed and everyone is done with the slice before, whose place is refilled.  Fragments are
 // read one K step ahead of their MFMAs, across slices too.
 //   The MFMAs compute the transposed tile (weights first): a lane holds 4 x 4 consecutive channels of one row, so that after one
-// lane swap per register pair results leave, and residuals come, in 32-byte pieces without a transpose through LDS.
+// lane swap per register pair results leave, and residuals come, in 32-byte pieces without a transpose through LDS; from the large tiles
+// they go through LDS (TURN).
 //   KS = 2: the waves form two groups that share the slices and take two of a slice's four K steps each; their sums meet in LDS
 // (first group plus second, always).
 //
@@ -86,6 +87,13 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void k_pipe(const PipeArgs ka) {
   constexpr bool TAPS = (MODE == M_CONV2 || MODE == M_CS2 || MODE == M_U2 || MODE == M_SD2 || MODE == M_G2);
   constexpr bool CS = (MODE >= M_CS1 && MODE <= M_CS3);
   constexpr bool RES = (MODE == M_CONV3 || MODE == M_CS3 || MODE == M_SD3);
+  // Results of the tiles that have a compute unit to themselves pass through LDS on their way to memory, and residuals come the way they
+  // leave: four lanes on 64 bytes of a row.  Straight from the accumulators a lane holds 32 bytes of a row of its own, and the compute
+  // unit's path takes 16 bytes a cycle of those: ResNet stage 4 of 128 images, first block's 1x1s 37.6 / 36.2 -> 35.4 / 34.7 us, its 3x3
+  // 39.6 -> 37.1, last 1x1 26.3 -> 25.2, an identity block's 3x3 27.5 -> 26.0 (a dozen passes; without a pause and on changing inputs,
+  // where the clock is lower and the input cold, 45.1 / 43.2 -> 44.1 / 43.0, 42.5 -> 42.0).  Smaller tiles, several a compute unit, hide it, and
+  // the round through LDS costs them (channel skipping of stage 1, last 1x1: 54.1 -> 55.4).
+  constexpr bool TURN = ES == 2 && NT == 512 && !(MODE >= M_U1 && MODE <= M_U3);
   constexpr bool LISTED = (MODE == M_CONV1 || MODE == M_CONV2 || MODE == M_CONV3 || MODE == M_G2 || MODE == M_U1 || MODE == M_U2 || MODE == M_U3);
   extern __shared__ __align__(16) unsigned char smem[];
   const int tab = short_ring<MODE, KS>() ? ka.ring : ring_bytes<BM, BN, NS>();
@@ -357,11 +365,11 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void k_pipe(const PipeArgs ka) {
 #pragma unroll
       for (int bb = 0; bb < NBO; ++bb) {
         const int i = (ks * NBO + bb) / TN, j = (ks * NBO + bb) % TN;
-        const size_t row = (size_t)max(s_row[wm * (BM / WM) + 32 * i + l31], 0) * a.ldo;
 #pragma unroll
         for (int u = 0; u < RPB; ++u) {  // (columns past the end read valid ones; nothing is stored there)
-          const int col = col0 + wn * (BN / WN) + 32 * j + (ES == 4 ? 8 * u + 4 * lhi : 16 * lhi + 8 * u);
-          res[bb * RPB + u] = *reinterpret_cast<const uint4*>((const ET*)a.Res + row + min(col, ncols - EPC));
+          const int rl = wm * (BM / WM) + 32 * i + (TURN ? 16 * u + (lane >> 2) : l31);
+          const int col = col0 + wn * (BN / WN) + 32 * j + (TURN ? 8 * (lane & 3) : ES == 4 ? 8 * u + 4 * lhi : 16 * lhi + 8 * u);
+          res[bb * RPB + u] = *reinterpret_cast<const uint4*>((const ET*)a.Res + (size_t)max(s_row[rl], 0) * a.ldo + min(col, ncols - EPC));
         }
       }
     }
@@ -464,10 +472,14 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void k_pipe(const PipeArgs ka) {
   if (KT > NS - 1) load_res();
   for (; s < KT; ++s) slice(s, std::false_type{});
 
+  if (TURN || do_proj || KS == 2) {
+    lds_wait();
+    wg_barrier();  // everyone is done with the slices
+  }
+
   // ---- the masker projection: two K halves of a row in lanes l and l + 32, then the waves that share the rows -----------
   if constexpr (MODE == M_DENSE1) {
     if (do_proj) {
-      wg_barrier();  // everyone is done with the slices
       float* const s_part = reinterpret_cast<float*>(smem);
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
@@ -486,8 +498,6 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void k_pipe(const PipeArgs ka) {
   }
   // ---- KS = 2: each group hands the other the blocks that one finishes --------------------------------------------------
   if constexpr (KS == 2) {
-    lds_wait();
-    wg_barrier();
     uint4* const xch = reinterpret_cast<uint4*>(smem) + (size_t)wv * (NBO * 4 * 64) + lane;
     constexpr int GRP = WM * WN * NBO * 4 * 64;
 #pragma unroll
@@ -516,6 +526,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void k_pipe(const PipeArgs ka) {
   }
 
   // ---- epilogue ---------------------------------------------------------------------------------
+  const float floor_ = act_floor(a.relu);
 #pragma unroll
   for (int bb = 0; bb < NBO; ++bb) {
     const int i = (ks * NBO + bb) / TN, j = (ks * NBO + bb) % TN;
@@ -562,6 +573,39 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void k_pipe(const PipeArgs ka) {
           }
           *reinterpret_cast<float4*>((float*)a.Out + off) = o;
         }
+      }
+    } else if constexpr (TURN) {
+      // through LDS of the wave's own (its operations stay in order), in the ring's bytes: four lanes then hold 64 bytes of a row
+      constexpr int kBuf = RES ? kTurnBytes : kTurnBytes / 2;
+      constexpr int kTurnOff = KS == 2 ? 2 * WM * WN * NBO * 4096 : MODE == M_DENSE1 ? 4096 : 0;  // (behind the exchange, the partial sums)
+      static_assert(kTurnOff + NW * kBuf <= (short_ring<MODE, KS>() ? 1 : NS) * STAGE && (MODE != M_DENSE1 || WN * BM * 4 <= kTurnOff), "the turning buffers");
+      unsigned char* const turn = smem + kTurnOff + wave * kBuf;
+      const int col = col0 + cb + 8 * (lane & 3);
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        if constexpr (RES) {
+          *reinterpret_cast<float4*>(turn + turn_put(lane, g)) = make_float4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
+        } else {
+          *reinterpret_cast<u32x2*>(turn + row_put(lane, g)) = u32x2{pack_bf16(v[4 * g], v[4 * g + 1]), pack_bf16(v[4 * g + 2], v[4 * g + 3])};
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        u32x4 o;
+        if constexpr (RES) {
+          const uint4 r = res[bb * RPB + q];
+          const unsigned ru[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const float4 x = *reinterpret_cast<const float4*>(turn + turn_get(lane, q, h));
+            o[2 * h] = pack_bf16(fmaxf(x.x + __uint_as_float(ru[2 * h] << 16), floor_), fmaxf(x.y + __uint_as_float(ru[2 * h] & 0xffff0000u), floor_));
+            o[2 * h + 1] = pack_bf16(fmaxf(x.z + __uint_as_float(ru[2 * h + 1] << 16), floor_), fmaxf(x.w + __uint_as_float(ru[2 * h + 1] & 0xffff0000u), floor_));
+          }
+        } else {
+          o = *reinterpret_cast<const u32x4*>(turn + row_get(lane, q));
+        }
+        const int row = s_row[wm * (BM / WM) + 32 * i + 16 * q + (lane >> 2)];
+        if (row >= 0 && col < ncols) *reinterpret_cast<u32x4*>((ET*)a.Out + (size_t)row * a.ldo + col) = o;
       }
     } else {
       to_consecutive_channels(v);  // 0-3, 8-11, 4-7, 12-15: channels 16 lhi + 0 .. 15

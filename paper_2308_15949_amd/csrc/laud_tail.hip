@@ -323,11 +323,11 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
       unsigned char* row = smem + kH2Off + r * 512u + lhi * 8u;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        uint2 c = make_uint2(pack_bf16(fmaxf(acc[t][4 * g] * sc[g].x + sh[g].x, 0.f), fmaxf(acc[t][4 * g + 1] * sc[g].y + sh[g].y, 0.f)),
-                             pack_bf16(fmaxf(acc[t][4 * g + 2] * sc[g].z + sh[g].z, 0.f), fmaxf(acc[t][4 * g + 3] * sc[g].w + sh[g].w, 0.f)));
+        u32x2 c = {pack_bf16(fmaxf(acc[t][4 * g] * sc[g].x + sh[g].x, 0.f), fmaxf(acc[t][4 * g + 1] * sc[g].y + sh[g].y, 0.f)),
+                   pack_bf16(fmaxf(acc[t][4 * g + 2] * sc[g].z + sh[g].z, 0.f), fmaxf(acc[t][4 * g + 3] * sc[g].w + sh[g].w, 0.f))};
         // the channel mask multiplies the 3x3's output: a row that drops this wave's group stores zeros
-        if (CS && !((hkeep >> t) & 1u)) c = make_uint2(0, 0);
-        *reinterpret_cast<uint2*>(row + (((wave * 4u + g) ^ (r & 15u)) << 4)) = c;
+        if (CS && !((hkeep >> t) & 1u)) c = u32x2{0, 0};
+        *reinterpret_cast<u32x2*>(row + (((wave * 4u + g) ^ (r & 15u)) << 4)) = c;
       }
       __builtin_amdgcn_sched_barrier(0);              // one pixel block at a time (register pressure)
     }

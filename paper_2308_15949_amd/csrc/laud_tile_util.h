@@ -93,6 +93,9 @@ __device__ __forceinline__ unsigned turn_get(int lane, int q, int e) {
 // The same for a 32 x 32 block of bf16 results in 64-byte rows (2 KB): where a lane's channels 8 * g + 4 * (lane / 32) .. +3 of row
 // lane % 32 go, and where channels 8 * (lane % 4) .. +7 of row 16 * q + lane / 4 come from.  16-byte unit u of row r lies at
 // position u ^ ((r >> 1) & 3): lanes that are served together cover 128 bytes.
+// (Written as u32x2 and read as u32x4: the compiler takes vector types of its own to overlap with anything, and two different structs
+// not to.)
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ unsigned row_put(int lane, int g) {
   const unsigned r = lane & 31;
   return r * 64u + (((unsigned)g ^ (r >> 1 & 3u)) << 4) + (unsigned)(lane >> 5) * 8u;
