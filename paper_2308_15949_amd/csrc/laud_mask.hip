@@ -83,9 +83,6 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact(const uint8_t* __re
   }
 }
 
-// Small masks (a few thousand entries: one stage's patch grid, a batch of layer gates): one block
-// does the whole ordered compaction in one launch.  Each thread owns four consecutive entries per
-// pass; four ballots give the in-wave prefix (mbcnt), an LDS scan over the 16 waves the rest.
 constexpr int kSmallCompactMax = 8 * kCompactBlock;  // 32768 entries
 // Pooling of the per-pixel masker projection (Masker-Conv1x1 fusion, App. B item 1): patch logit =
 // bias + mean over the S x S patch of proj; active iff logit > 0 (and the sample's gate, if any).
@@ -128,74 +125,73 @@ __global__ __launch_bounds__(256) void k_pool_mask(PoolArgs pa, int npatch, uint
   if (q < npatch) pooled_decision(pa, q, mask);
 }
 
-__global__ __launch_bounds__(kCompactThreads) void k_compact_small(const uint8_t* __restrict__ mask, int n,
-                                                                   int32_t* __restrict__ idx,
-                                                                   int32_t* __restrict__ count,
-                                                                   int32_t* __restrict__ sample_offsets,
-                                                                   int per_sample) {
-  __shared__ int scan[2][kCompactThreads / kWave];
-  // A thread owns entries 4*tid .. 4*tid+3 of each 4096-entry pass.  All of its mask bytes (at most eight
-  // passes: n <= 32768) are requested before the first pass runs, so the kernel pays one far-memory round trip
-  // instead of one per pass.
-  constexpr int kMaxPass = kSmallCompactMax / (4 * kCompactThreads);
-  unsigned m4[kMaxPass];
-  // Every load is unconditional (clamped index, value dropped past the end): conditional loads would be waited for
-  // one by one.  Whole words when the base is word-aligned and n a multiple of four (uniform), bytes otherwise.
-  const bool words = (reinterpret_cast<unsigned long long>(mask) & 3ull) == 0 && (n & 3) == 0 && n > 0;
-  if (words) {
+// Masks of up to 32768 entries (one stage's patch grid, a batch of layer gates) in one launch: block b owns entries 4096 b .. +4095,
+// a wave 256 of them in four rounds of 64: a lane looks at one byte a round, the ballot is the order.  A block counts the set entries
+// of the blocks before it by itself, in the same way, so that none waits for another.  Such a launch is its chain of trips --
+// arguments, code, bytes, one barrier, indices --, so the code is short, every byte is requested before any is looked at (bytes
+// past the end read as zero and need no alignment), counts are scalar, and a wave adds the sixteen waves' counts itself.
+// (Words of four entries in a block of their own, with a scan of the counts by shuffles: single images 2.8 to 3.7 us, here 1.3 to 1.6;
+// 648 patches behind their masker 3.9 / 2.8.  Behind a launch that has just written much, any launch of this size takes 4.7.)
+constexpr int kCompactRounds = kCompactBlock / kCompactThreads;  // of 64 entries a wave
+constexpr int kCompactWaves = kCompactThreads / kWave;
+__global__ __launch_bounds__(kCompactThreads) void k_compact_ballot(const uint8_t* __restrict__ mask, int n, int32_t* __restrict__ idx,
+                                                                    int32_t* __restrict__ count, int32_t* __restrict__ sample_offsets,
+                                                                    int per_sample) {
+  __shared__ __align__(16) int2 s_cnt[kCompactWaves];  // of a wave: set entries of its own, of earlier blocks
+  prefetch_args<48>();
+  const int lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  const int i0 = (int)blockIdx.x * kCompactBlock + wave * (kCompactRounds * kWave);
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(mask), 0, n, 0x00020000);
+  uint8_t own[kCompactRounds];
 #pragma unroll
-    for (int p = 0; p < kMaxPass; ++p) {
-      const int i0 = p * 4 * kCompactThreads + 4 * (int)threadIdx.x;
-      const unsigned v = *reinterpret_cast<const unsigned*>(mask + min(i0, n - 4));
-      m4[p] = i0 < n ? v : 0u;
-    }
-  } else if (n > 0) {
+  for (int r = 0; r < kCompactRounds; ++r) own[r] = __builtin_amdgcn_raw_buffer_load_b8(rs, i0 + lane + r * kWave, 0, 0);
+  int before = 0;
+  for (int p = 0; p < (int)blockIdx.x; p += 2) {  // two earlier blocks at a time: this wave's 256 entries of each
+    uint8_t v[2 * kCompactRounds];
+    const int at = p * kCompactBlock + wave * (kCompactRounds * kWave), next = p + 1 < (int)blockIdx.x ? at + kCompactBlock : n;
 #pragma unroll
-    for (int p = 0; p < kMaxPass; ++p) {
-      const int i0 = p * 4 * kCompactThreads + 4 * (int)threadIdx.x;
-      unsigned v = 0;
+    for (int r = 0; r < 2 * kCompactRounds; ++r)
+      v[r] = __builtin_amdgcn_raw_buffer_load_b8(rs, (r < kCompactRounds ? at : next) + lane + r % kCompactRounds * kWave, 0, 0);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const unsigned byte = mask[min(i0 + j, n - 1)];
-        v |= (i0 + j < n ? byte : 0u) << (8 * j);
-      }
-      m4[p] = v;
-    }
-  } else {
-#pragma unroll
-    for (int p = 0; p < kMaxPass; ++p) m4[p] = 0u;
+    for (int r = 0; r < 2 * kCompactRounds; ++r) before += __popcll(__ballot(v[r] != 0));
   }
-  int running = 0;
+  unsigned long long b[kCompactRounds];
+  int mine = 0;
 #pragma unroll
-  for (int p = 0; p < kMaxPass; ++p) {
-    const int base = p * 4 * kCompactThreads;
-    if (base >= n) break;  // uniform
-    const int i0 = base + 4 * (int)threadIdx.x;
-    bool f[4];
-    unsigned long long b[4];
-    int before = 0, mine = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      f[j] = ((m4[p] >> (8 * j)) & 0xffu) != 0;  // entries past n were read as 0
-      b[j] = __ballot(f[j]);
-      before += ballot_prefix(b[j]);  // set entries of lower lanes at position j
-    }
-    int wtot = 0, tot;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) wtot += __popcll(b[j]);
-    const int wo = scan_wave_counts(wtot, kCompactThreads / kWave, scan[p & 1], &tot);
-    int pos = running + wo + before;  // set entries before (this thread, position 0)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int i = i0 + j;
-      if (sample_offsets && i < n && (i % per_sample) == 0) sample_offsets[i / per_sample] = pos + mine;
-      if (f[j]) { idx[pos + mine] = i; ++mine; }
-    }
-    running += tot;
+  for (int r = 0; r < kCompactRounds; ++r) {
+    b[r] = __ballot(own[r] != 0);
+    mine += __popcll(b[r]);
   }
-  if (threadIdx.x == 0) {
-    *count = running;
-    if (sample_offsets) sample_offsets[n / per_sample] = running;
+  int first = before, total = before + mine;
+  if (blockDim.x > kWave) {  // (one wave or all of them)
+    if (lane == 0) s_cnt[wave] = make_int2(mine, before);
+    __syncthreads();
+    first = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < kCompactWaves; ++w) {
+      const int2 c = s_cnt[w];
+      first += c.y + (w < wave ? c.x : 0);
+      total += c.y + c.x;
+    }
+  }
+  int pos = first;
+#pragma unroll
+  for (int r = 0; r < kCompactRounds; ++r) {
+    if (own[r] != 0) idx[pos + ballot_prefix(b[r])] = i0 + r * kWave + lane;
+    pos += __popcll(b[r]);
+  }
+  const bool last = blockIdx.x == gridDim.x - 1 && threadIdx.x == 0;
+  if (last) *count = total;
+  if (sample_offsets) {
+    for (int r = 0; r < kCompactRounds; ++r) {
+      const int i = i0 + r * kWave + lane;
+      const unsigned long long br = __ballot(own[r] != 0);
+      if (i < n && i % per_sample == 0) sample_offsets[i / per_sample] = first + ballot_prefix(br);
+      first += __popcll(br);
+    }
+    if (last) sample_offsets[n / per_sample] = total;
   }
 }
 
@@ -285,7 +281,7 @@ __global__ __launch_bounds__(kCompactThreads) void k_pool_compact_one_block(Pool
   }
 }
 
-// Ordered compaction of up to 64 x 4096 entries in ONE launch of several blocks: block b owns entries
+// Ordered compaction of 32769 to 64 x 4096 entries in ONE launch of several blocks: block b owns entries
 // [4096 b, 4096 b + 4096) and first counts the set entries of all blocks before it by itself (one 4-byte load
 // per thread and preceding block, eight in flight) instead of waiting for anybody: no second launch, no
 // inter-block dependency, and each block's own pass runs on a CU of its own.  Needs a word-aligned mask and n a
@@ -318,7 +314,7 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_blocks(const uint8_
   }
   int base;
   (void)scan_wave_counts(wave_sum_int(before_blocks), kCompactThreads / kWave, scan[0], &base);
-  // own pass, as in k_compact_small
+  // own pass: four ballots, a thread's entries are consecutive
   const unsigned m4 = i0 < n ? own : 0u;
   bool f[4];
   unsigned long long bal[4];
@@ -356,15 +352,15 @@ int launch_compact(const uint8_t* mask, int n, int32_t* idx, int32_t* count, int
     hipLaunchKernelGGL(k_write_zero_count, dim3(1), dim3(1), 0, stream, count, sample_offsets);
     return check_launch();
   }
-  if (n > kCompactBlock && n <= kCompactOneLaunchMax && (n & 3) == 0 &&
-      (reinterpret_cast<unsigned long long>(mask) & 3ull) == 0) {
-    hipLaunchKernelGGL(k_compact_blocks, dim3((n + kCompactBlock - 1) / kCompactBlock), dim3(kCompactThreads), 0, stream,
-                       mask, n, idx, count, sample_offsets, per_sample > 0 ? per_sample : 1);
+  if (n <= kSmallCompactMax) {
+    hipLaunchKernelGGL(k_compact_ballot, dim3((n + kCompactBlock - 1) / kCompactBlock),
+                       dim3(n <= kCompactRounds * kWave ? kWave : kCompactThreads), 0, stream, mask, n, idx, count, sample_offsets,
+                       per_sample > 0 ? per_sample : 1);
     return check_launch();
   }
-  if (n <= kSmallCompactMax) {
-    hipLaunchKernelGGL(k_compact_small, dim3(1), dim3(kCompactThreads), 0, stream, mask, n, idx, count,
-                       sample_offsets, per_sample > 0 ? per_sample : 1);
+  if (n <= kCompactOneLaunchMax && (n & 3) == 0 && (reinterpret_cast<unsigned long long>(mask) & 3ull) == 0) {
+    hipLaunchKernelGGL(k_compact_blocks, dim3((n + kCompactBlock - 1) / kCompactBlock), dim3(kCompactThreads), 0, stream,
+                       mask, n, idx, count, sample_offsets, per_sample > 0 ? per_sample : 1);
     return check_launch();
   }
   const int nb = (n + kCompactBlock - 1) / kCompactBlock;

@@ -25,10 +25,12 @@ struct dim3 {
 };
 struct alignas(8) float2 { float x, y; };
 struct alignas(16) float4 { float x, y, z, w; };
+struct alignas(8) int2 { int x, y; };
 struct alignas(8) uint2 { unsigned x, y; };
 struct alignas(16) uint4 { unsigned x, y, z, w; };
 static inline float4 make_float4(float a, float b, float c, float d) { return {a, b, c, d}; }
 static inline float2 make_float2(float a, float b) { return {a, b}; }
+static inline int2 make_int2(int a, int b) { return {a, b}; }
 static inline uint2 make_uint2(unsigned a, unsigned b) { return {a, b}; }
 static inline uint4 make_uint4(unsigned a, unsigned b, unsigned c, unsigned d) { return {a, b, c, d}; }
 using std::max;
@@ -67,6 +69,7 @@ void launch(dim3 grid, dim3 block, size_t lds_bytes, const char* kernel, const v
 struct Rsrc { const char* base; unsigned bytes; };
 typedef unsigned Chunk __attribute__((ext_vector_type(4)));
 unsigned load_dword(const Rsrc& r, unsigned voff, unsigned soff);  // zero past the descriptor's end
+uint8_t load_byte(const Rsrc& r, unsigned voff, unsigned soff);
 Chunk load_chunk(const Rsrc& r, unsigned voff, unsigned soff);
 void store_chunk(const Chunk& c, const Rsrc& r, unsigned voff, unsigned soff);  // dropped past the descriptor's end
 void load_to_lds(const Rsrc& r, unsigned voff, unsigned soff, unsigned lds_base);
@@ -94,6 +97,7 @@ static inline int lanes_below(unsigned mask, int first) {  // set bits of 32 lan
 #define __builtin_amdgcn_make_buffer_rsrc(p, stride, bytes, flags) (host::Rsrc{(const char*)(p), (unsigned)(bytes)})
 #define __builtin_amdgcn_raw_buffer_load_b128(r, v, s, a) host::load_chunk(r, v, s)
 #define __builtin_amdgcn_raw_buffer_store_b128(c, r, v, s, a) host::store_chunk(c, r, v, s)
+#define __builtin_amdgcn_raw_buffer_load_b8(r, v, s, a) host::load_byte(r, v, s)
 #define __builtin_amdgcn_raw_buffer_load_b32(r, v, s, a) host::load_dword(r, v, s)
 #define __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, x, y, z) (c)
 #define __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, x, y, z) (c)

@@ -159,6 +159,9 @@ void launch(dim3 g, dim3 b, size_t lds_bytes, const char* kernel, const void* fu
     }
 }
 
+uint8_t load_byte(const Rsrc& r, unsigned voff, unsigned soff) {
+  return (uint64_t)voff < r.bytes ? *reinterpret_cast<const volatile uint8_t*>(r.base + voff + soff) : 0;
+}
 unsigned load_dword(const Rsrc& r, unsigned voff, unsigned soff) {
   unsigned v = 0;
   if ((uint64_t)voff + 4 <= r.bytes) memcpy(&v, r.base + (size_t)voff + soff, 4);

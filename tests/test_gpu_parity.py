@@ -71,6 +71,19 @@ def test_compact_bit_exact(G, n, p):
     assert np.all(idx[c:] == -7)  # nothing written past count
 
 
+@pytest.mark.parametrize("n", [255, 256, 257, 1023, 3841, 8191, 8193, 12289, 28673, 32767, 32768, 32769])
+def test_compact_at_the_edges_of_waves_and_blocks(G, n):
+    """Sizes either side of one wave, of a block's waves, of a block and of the one-launch path; masks at an odd address."""
+    t, L, D = G.torch, G.L, G.D
+    mask = I.bernoulli_mask(n, (n,), 0.5) * np.uint8(5)
+    md = t.from_numpy(np.concatenate([np.full(1, 9, np.uint8), mask, np.full(7, 9, np.uint8)])).cuda()[1:n + 1]
+    idx, cnt = t.full((n + 8,), -7, dtype=t.int32, device="cuda"), t.zeros(1, dtype=t.int32, device="cuda")
+    L.laud_layer_skip_compact(md, n, idx, cnt, D.workspace(1 << 12))
+    ref = O.compact(mask)
+    assert int(cnt.item()) == len(ref)
+    assert np.array_equal(idx.cpu().numpy()[:len(ref)], ref) and bool((idx[len(ref):] == -7).all())
+
+
 @pytest.mark.parametrize("n", [4100, 8192, 25088, 65536, 262144, 262148])
 def test_compact_any_nonzero_byte_counts_as_set(G, n):
     """Byte values with a single bit anywhere (0x01 .. 0x80) and 0xff among zeros, at sizes on both sides of the
