@@ -17,7 +17,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "liblaud.so")
-SOURCES = ["laud_api.hip", "laud_mask.hip", "laud_chanmask.hip", "laud_static.hip", "laud_se.hip", "laud_gemm.hip", "laud_pipe_a.hip", "laud_pipe_b.hip", "laud_pipe_c.hip", "laud_group.hip", "laud_skinny.hip", "laud_narrow.hip", "laud_first.hip",
+SOURCES = ["laud_api.hip", "laud_mask.hip", "laud_chanmask.hip", "laud_static.hip", "laud_se.hip", "laud_gemm.hip", "laud_pipe_a.hip", "laud_pipe_b.hip", "laud_pipe_c.hip", "laud_group.hip", "laud_group_fused.hip", "laud_skinny.hip", "laud_narrow.hip", "laud_first.hip",
            "laud_probe.hip", "laud_tail.hip", "laud_head.hip"]
 # packed-fp32 code generation is switched off for device code (the host pass warns that it
 # does not know the feature; that is harmless).

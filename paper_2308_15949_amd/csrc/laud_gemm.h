@@ -59,6 +59,10 @@ int launch_skinny_pair(int dtype, const GemmArgs& a, long long rows_a, const Gem
 constexpr int kGroupMaxC = 4096;
 int launch_group(const GemmArgs& a, long long cap_rows, hipStream_t stream);
 int group_init_device();
+// First 1x1 and group 3x3 in one launch (laud_group_fused.hip; `whole`: a patch is a whole sample): `a` as for the 3x3 on the listed patches, but A = x, K = c_in.
+bool group_fused_wanted(int dtype, int c_in, int c_mid, int group_width, int S, int stride, bool whole, long long cap_rows);
+int launch_group_fused(const GemmArgs& a, const void* w1, const float* s1, const float* t1, long long cap_rows, hipStream_t stream);
+int group_fused_init_device();
 
 // Many rows (laud_pipe.h); nsamples: samples of channel skipping, groups of CONV1's pixel lists.
 int launch_pipe_a(int mode, int dtype, const GemmArgs& a, long long cap_rows, int nsamples, hipStream_t stream);

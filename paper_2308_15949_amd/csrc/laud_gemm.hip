@@ -813,6 +813,17 @@ static int launch_conv2(int dtype, GemmArgs a, const laud_group_se* e, long long
   return dtype == LAUD_BF16 && a.Ncols <= kGroupMaxC ? launch_group(a, cap_rows, st) : launch_pipe(M_G2, dtype, a, cap_rows, 1, st);
 }
 
+// First 1x1 and group 3x3 in one launch where laud_group_fused.hip takes them (1: launched, *rc its status).  `a`: the map's geometry.
+static int try_group_fused(int dtype, GemmArgs a, const laud_bottleneck* p, const laud_group_se* e, const void* x, void* h2, const int32_t* idx,
+                           const int32_t* count, bool whole, long long cap_rows, hipStream_t st, int* rc) {
+  if (!e || !group_fused_wanted(dtype, p->c_in, p->c_mid, e->group_width, a.S, a.stride > 1 ? a.stride : 1, whole, cap_rows)) return 0;
+  a.A = x; a.Wt = p->w2; a.scale = p->s2; a.shift = p->t2; a.Out = h2; a.count = count; a.list = idx; a.K = p->c_in; a.lda = p->c_in;
+  a.Ncols = p->c_mid; a.ldo = p->c_mid; a.gw = e->group_width;
+  StageScope scope(LAUD_STAGE_CONV2, st);
+  *rc = launch_group_fused(a, p->w1, p->s1, p->t1, cap_rows, st);
+  return 1;
+}
+
 // Whether conv2 -> conv3 -> residual add run as the one kernel of laud_tail.hip (h2 stays in LDS), and whether
 // the dense first 1x1 (+ masker projection) runs as the kernel of laud_head.hip.
 static bool tail_wanted(int dtype, const laud_bottleneck* p, const laud_group_se* e) {
@@ -1003,7 +1014,10 @@ static int run_dyn_block(const void* x, laud_fmap fx, const laud_bottleneck* p, 
   const InactiveCopy copy = inactive_copy(x, out, fx, S, idx, count);
   GemmArgs a{};
   a.H = fx.H; a.W = fx.W; a.S = S; a.D = 1; a.G = 1; a.cmask = nullptr;
-  if (dense_conv1_wanted(fx.dtype, p, npix, Hp * Wp == 1) && !head_used(fx.dtype, p, npix)) {
+  const bool fused_conv2 = try_group_fused(fx.dtype, a, p, e, x, h2, idx, count, Hp * Wp == 1, npix, st, &rc) != 0;
+  if (fused_conv2) {
+    if (rc != LAUD_OK) return rc;
+  } else if (dense_conv1_wanted(fx.dtype, p, npix, Hp * Wp == 1) && !head_used(fx.dtype, p, npix)) {
     if ((rc = run_dense_conv1(fx, p, x, h1, st)) != LAUD_OK) return rc;
   } else {
     // samples per group of the dilated pixel lists: about 1.5k pixels, so that a group's ragged last
@@ -1046,7 +1060,7 @@ static int run_dyn_block(const void* x, laud_fmap fx, const laud_bottleneck* p, 
   a.A = h1; a.Wt = p->w2; a.scale = p->s2; a.shift = p->t2; a.Out = h2;
   a.count = count; a.list = idx; a.K = p->c_mid; a.ldw = 9 * p->c_mid; a.Ncols = p->c_mid;
   a.lda = p->c_mid; a.ldo = p->c_mid;
-  if ((rc = launch_conv2(fx.dtype, a, e, npix, st)) != LAUD_OK) return rc;
+  if (!fused_conv2 && (rc = launch_conv2(fx.dtype, a, e, npix, st)) != LAUD_OK) return rc;
   if (e && e->se_width > 0 &&
       (rc = launch_se(fx.dtype, fx.N, Hp * Wp, S * S, p->c_mid, e, h2, idx, count, (float*)h1, npix, st)) != LAUD_OK)
     return rc;
@@ -1375,7 +1389,12 @@ static int run_dyn_projection(const void* x, laud_fmap fx, const laud_bottleneck
   a.A = x; a.Wt = w_sc; a.scale = s_sc; a.shift = t_sc; a.Out = out; a.K = p->c_in; a.ldw = p->c_in;
   a.Ncols = p->c_out; a.lda = p->c_in; a.ldo = p->c_out; a.relu = p->relu_out ? 1 : 0; a.m_rows = (int)nout;
   a.list = idx; a.count = count;
-  if (dense_conv1_wanted(fx.dtype, p, npix, Hp * Wp == 1) && !head_used(fx.dtype, p, npix)) {
+  GemmArgs g{};
+  g.H = fx.H; g.W = fx.W; g.S = S; g.Ho = Ho; g.Wo = Wo; g.stride = stride;
+  const bool fused_conv2 = try_group_fused(fx.dtype, g, p, e, x, h2, idx, count, Hp * Wp == 1, nout, st, &rc) != 0;
+  if (fused_conv2) {
+    if (rc != LAUD_OK || (rc = launch_gemm<M_SD1>(fx.dtype, a, nout, 1, st)) != LAUD_OK) return rc;
+  } else if (dense_conv1_wanted(fx.dtype, p, npix, Hp * Wp == 1) && !head_used(fx.dtype, p, npix)) {
     // (input widths the register-weight first 1x1 does not take, in front of the fused 3x3 -> 1x1 kernel: the dense launch
     // carries no re-ordering of its weights)
     if (tail_used(fx.dtype, p, e, nout) && !p->packed &&
@@ -1420,7 +1439,7 @@ static int run_dyn_projection(const void* x, laud_fmap fx, const laud_bottleneck
   a.A = h1; a.Wt = p->w2; a.scale = p->s2; a.shift = p->t2; a.Out = h2;
   a.count = count; a.list = idx; a.K = p->c_mid; a.ldw = 9 * p->c_mid; a.Ncols = p->c_mid;
   a.lda = p->c_mid; a.ldo = p->c_mid;
-  if ((rc = launch_conv2(fx.dtype, a, e, nout, st)) != LAUD_OK) return rc;
+  if (!fused_conv2 && (rc = launch_conv2(fx.dtype, a, e, nout, st)) != LAUD_OK) return rc;
   if (e && e->se_width > 0 &&
       (rc = launch_se(fx.dtype, fx.N, Hp * Wp, S * S, p->c_mid, e, h2, idx, count, (float*)h1, nout, st)) != LAUD_OK)
     return rc;
@@ -1544,6 +1563,7 @@ extern "C" int laud_init(void) {
   if (rc != LAUD_OK) return rc;
   if ((rc = skinny_init_device()) != LAUD_OK) return rc;
   if ((rc = group_init_device()) != LAUD_OK) return rc;
+  if ((rc = group_fused_init_device()) != LAUD_OK) return rc;
   if ((rc = narrow_init_device()) != LAUD_OK) return rc;
   if ((rc = first_init_device()) != LAUD_OK) return rc;
   if ((rc = stem_init_device(nullptr)) != LAUD_OK) return rc;

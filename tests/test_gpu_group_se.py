@@ -236,6 +236,28 @@ def test_group_se_projection_block(G, case):
     assert_close(D.to_host(out), ref, TOL[dt], "group/SE first block")
 
 
+# First 1x1 and group 3x3 in one launch: tiles of whole patches (a last one of fewer) and of rows of a patch (a last strip of fewer),
+# reductions of part of a slice, of one, of several with a ragged end; part of a column tile; workgroups that take two tiles.
+FUSED = [
+    (3, 28, 28, 24, 8, 8, 4, I.BF16, True, 0.6), (2, 16, 24, 64, 16, 16, 8, I.BF16, True, 0.7), (3, 14, 14, 72, 8, 0, 7, I.BF16, False, 0.5),
+    (2, 28, 42, 136, 8, 20, 14, I.BF16, True, 0.9), (2, 28, 28, 200, 8, 20, 28, I.BF16, True, 0.6), (3, 10, 14, 104, 8, 26, 2, I.BF16, True, 0.5),
+    (1, 9, 7, 256, 16, 26, 1, I.BF16, True, 0.5), (57, 24, 24, 40, 8, 0, 4, I.BF16, True, 0.95),
+]
+FUSED_PROJ = [
+    (2, 31, 30, 24, 40, 8, 0, 2, 1, I.BF16, "bern"), (3, 15, 28, 72, 136, 8, 26, 2, 2, I.BF16, "bern"), (2, 55, 56, 64, 104, 8, 26, 2, 7, I.BF16, "ones"),
+    (2, 31, 32, 96, 48, 16, 8, 2, 8, I.BF16, "bern"), (3, 27, 28, 200, 80, 16, 26, 2, 14, I.BF16, "ones"), (2, 56, 111, 40, 64, 16, 8, 2, 28, I.BF16, "one_sample_empty"),
+    (3, 28, 28, 264, 320, 16, 36, 2, 2, I.BF16, "bern"), (12, 62, 61, 32, 24, 8, 0, 2, 1, I.BF16, "ones"),
+]
+
+
+@pytest.mark.parametrize("case", FUSED + FUSED_PROJ)
+def test_first_1x1_and_group_3x3_in_one_launch(G, case):
+    if len(case) == 10:
+        test_group_se_block_bernoulli(G, case, True)
+    else:
+        test_group_se_projection_block(G, case)
+
+
 @pytest.mark.parametrize("stage", [1, 3, 4])
 def test_group_se_block_full_batch_sampled(G, stage):
     """The bench shapes (RegNetY-800MF stage blocks, batch 128, bf16, masker-calibrated ratio 0.5 replaced by a

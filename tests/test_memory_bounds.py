@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 
 import test_gpu_first
+import test_gpu_group_se
 import test_gpu_narrow
 from paper_2308_15949_amd import binding as B
 from paper_2308_15949_amd import build as build_rules
@@ -243,6 +244,13 @@ CASES = {
     "group_of_64": ("identity", "dyn", 5, 56, 56, 64, 64, 4, 0.5, True, True, 64),
     "group_of_8_odd": ("identity", "dyn", 9, 41, 37, 48, 48, 1, 0.5, True, True, 8),
     "group_many_rows_projection": ("first", "dynamic", 9, 55, 56, 32, 104, 104, 2, 7, 0.5, True, 8, 26),
+    "group_fused": ("identity", "dyn", 3, 28, 28, 72, 72, 4, 0.6, True, False, 8, 20),
+    "group_fused_strips": ("identity", "dyn", 3, 28, 42, 136, 136, 14, 0.6, True, True, 8, 20),
+    "group_fused_walk": ("identity", "dyn", 57, 24, 24, 40, 40, 4, 1.0, True, True, 8),  # two tiles a workgroup
+    "group_fused_none": ("identity", "dyn", 3, 28, 28, 72, 72, 4, 0.0, True, False, 8, 20),
+    "group_fused_projection": ("first", "dynamic", 4, 27, 28, 104, 208, 208, 2, 2, 0.5, True, 16, 26),
+    "group_fused_projection_strips": ("first", "dynamic", 2, 55, 56, 40, 104, 104, 2, 28, 0.9, True, 8),
+    "group_fused_projection_walk": ("first", "dynamic", 12, 62, 61, 32, 24, 24, 2, 1, 0.9, True, 8),
     "group_many_rows_f32": ("identity", "dyn", 12, 28, 28, 136, 136, 4, 0.5, False, True, 8),
     "group_past_4096_channels": ("identity", "dyn", 3, 8, 8, 4104, 4104, 2, 0.5, True, True, 8),
     # channel skipping: groups of whole 16-byte chunks, the fused kernels, and groups that are not
@@ -277,7 +285,7 @@ CASES = {
 
 
 # Tiles that a case is there for (kernel, mode, type, rows x columns; "split": the K steps are shared by two groups of waves): a rule
-# that sends the case elsewhere leaves them untested.  Every tile of k_pipe and k_group is some case's,
+# that sends the case elsewhere leaves them untested.  Every tile of k_pipe, k_group and k_group_fused is some case's,
 # and every instance of k_narrow and k_first.
 REACHES = {
     "narrow": ["narrow false"],
@@ -316,6 +324,12 @@ REACHES = {
     "static_64x128_f32": ["pipe SD1 float 64x128", "pipe SD2 float 64x128", "pipe SD3 float 64x128"],
     "static_128x128_f32": ["pipe SD2 float 128x128"],
     "group_many_rows": ["group 2"],
+    "group_fused": ["group_fused 2"],
+    "group_fused_strips": ["group_fused 2"],
+    "group_fused_walk": ["group_fused 2"],
+    "group_fused_projection": ["group_fused 1"],
+    "group_fused_projection_strips": ["group_fused 1"],
+    "group_fused_projection_walk": ["group_fused 1"],
     "group_of_64": ["group 4"],
     "group_many_rows_f32": ["pipe G2 float 64x64"],
     "group_past_4096_channels": ["pipe G2 bf16 128x64"],
@@ -349,6 +363,7 @@ def tiles(names):
     for kernel, mode, dtype, rows, columns, rest in re.findall(r"k_(pipe|gemm)<(\d+), (\w+), (\d+), (\d+), ([\d, ]+)>", names):
         found.add(f"{kernel} {MODES[int(mode)]} {dtype} {rows}x{columns}" + (" split" if rest.split(", ")[2:3] == ["2"] else ""))
     found |= {"first"} if "k_first(" in names else set()
+    found |= {f"group_fused {k}" for k in re.findall(r"k_group_fused<(\d)>", names)}
     return found | {f"group {k}" for k in re.findall(r"k_group<(\d)>", names)} | {f"narrow {k}" for k in re.findall(r"k_narrow<(\w+)>", names)}
 
 
@@ -412,4 +427,20 @@ def test_static_block_takes_the_whole_block_kernel_where_a_map_fills_it(lib, cas
         call.first("static", n, h, w, 64, 64, 256, stride, 1, 1.0)
         found = tiles(call.launched())
         assert kernel in found if kernel else "first" not in found, call.launched()
+    in_a_process_of_its_own(body, capfd)
+
+
+@pytest.mark.parametrize("case", test_gpu_group_se.FUSED + test_gpu_group_se.FUSED_PROJ)
+def test_group_blocks_take_first_1x1_and_3x3_in_one_launch(lib, case, capfd):
+    """(the sizes of the GPU test of that kernel: that they are about it)"""
+    def body():
+        call = Call(lib, 0)
+        call.host.host_record_only()
+        if len(case) == 10:
+            n, h, w, c, g, se, S = case[:7]
+            call.identity("dyn", n, h, w, c, c, S, 0.5, gw=g, se=se)
+        else:
+            n, h, w, ci, co, g, se, stride, S = case[:9]
+            call.first("dynamic", n, h, w, ci, co, co, stride, S, 0.5, gw=g, se=se)
+        assert f"group_fused {2 if len(case) == 10 else 1}" in tiles(call.launched()), call.launched()
     in_a_process_of_its_own(body, capfd)
