@@ -195,70 +195,97 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_ballot(const uint8_
   }
 }
 
-// Pooling, threshold and ordered compaction in ONE launch for S = 2 and at most 8192 patches (a stage-3
-// batch of 128 images): the two dependent kernels cost two launch-plus-far-latency chains for a few kilobytes
-// of work.  One patch per thread, up to eight blocks of 1024; a block needs the number of active patches
-// before its own and gets it by deciding those patches itself (at most seven more per thread: four adds and a
-// compare each), so the blocks neither wait for each other nor share anything, and no block runs more than one
-// compaction pass (a single block doing all passes is bound by instruction issue on its one CU).  Every
-// projection read of a thread (two 8-byte loads per patch) is requested before any is used.  Same summation
-// order as pooled_decision, hence the same decisions in every block.
-constexpr int kPoolFusedMax = 2 * kCompactBlock;
-constexpr int kPoolFusedBlocks = kPoolFusedMax / kCompactThreads;
-__global__ __launch_bounds__(kCompactThreads) void k_pool_compact_s2(PoolArgs pa, int n, uint8_t* __restrict__ mask,
-                                                                     int32_t* __restrict__ idx,
-                                                                     int32_t* __restrict__ count,
-                                                                     int32_t* __restrict__ sample_offsets,
-                                                                     int per_sample) {
-  __shared__ int scan[2][kCompactThreads / kWave];
-  prefetch_args<sizeof(PoolArgs) + 48>();
-  const int Hp = pa.H / 2, Wp = pa.W / 2;
-  const int b = blockIdx.x, tid = threadIdx.x;
-  float2 top[kPoolFusedBlocks], bot[kPoolFusedBlocks];
-  int kept[kPoolFusedBlocks];
+// Pooling, threshold and ordered compaction in one launch for S = 1, 2 and 4.  As in k_compact_ballot, of which it is the same chain of trips,
+// a block decides the patches of the blocks before its own 1024 by itself, in pooled_decision's summation order and hence alike, CH blocks
+// at a time, so that none waits for another.  A block reads up to all projections for that, from one compute unit (0.13 MB in
+// a microsecond): up to 256 KB of them the second launch, 4.7 us behind one that has just written much, costs more.
+// (6272 patches of one pixel, stage 4 of 128 images, in two launches 9.5 us, here 5.1; of 2 x 2, with scans of the counts by shuffles and
+// three barriers 6.2, here 4.8; 49 of them, one image, 1.9 and 1.35.)
+struct PoolCompactArgs {
+  PoolArgs pa;
+  FastDiv d_pps, d_wp;  // patches of a sample, of a row
+  int n, pps, Wp;
+  uint8_t* mask;
+  int32_t* idx; int32_t* count; int32_t* sample_offsets;
+};
+constexpr int pool_fused_max(int S) { return S == 1 ? 32768 : S == 2 ? 16384 : S == 4 ? 4096 : 0; }
+template <int S>
+struct Pooled {
+  float v[S * S];
+  int kept;
+  __device__ __forceinline__ void load(const PoolCompactArgs& a, int q) {
+    const int s = fast_div(q, a.d_pps), r = q - s * a.pps, py = fast_div(r, a.d_wp), px = r - py * a.Wp;
+    const float* const base = a.pa.proj + ((size_t)s * a.pa.H + py * S) * a.pa.W + px * S;
 #pragma unroll
-  for (int u = 0; u < kPoolFusedBlocks; ++u) {
-    // slot u < b: the patch of block u at this thread's position; slots from b on: the thread's own patch
-    const int q = min(min(u, b) * kCompactThreads + tid, n - 1);  // past the end: the last patch, result unused
-    const int s = q / (Hp * Wp), r = q - s * (Hp * Wp);
-    const int py = r / Wp, px = r - py * Wp;
-    const float* base = pa.proj + ((size_t)s * pa.H + py * 2) * pa.W + px * 2;
-    top[u] = *reinterpret_cast<const float2*>(base);
-    bot[u] = *reinterpret_cast<const float2*>(base + pa.W);
-    kept[u] = pa.keep ? (int)pa.keep[s] : 1;
+    for (int y = 0; y < S; ++y) {  // (a map's width is a multiple of S: rows of a patch are aligned to their size)
+      if constexpr (S == 1) {
+        v[0] = base[0];
+      } else if constexpr (S == 2) {
+        const float2 t = *reinterpret_cast<const float2*>(base + y * a.pa.W);
+        v[2 * y] = t.x; v[2 * y + 1] = t.y;
+      } else {
+        const float4 t = *reinterpret_cast<const float4*>(base + y * a.pa.W);
+        v[4 * y] = t.x; v[4 * y + 1] = t.y; v[4 * y + 2] = t.z; v[4 * y + 3] = t.w;
+      }
+    }
+    kept = a.pa.keep ? (int)a.pa.keep[s] : 1;
   }
-  int before_blocks = 0;
-  bool own_on = false;
-  float own_logit = 0.f;
+  __device__ __forceinline__ float logit(float bias) const {
+    float acc = v[0];
 #pragma unroll
-  for (int u = 0; u < kPoolFusedBlocks; ++u) {
-    const float acc = ((top[u].x + top[u].y) + bot[u].x) + bot[u].y;
-    const float logit = acc / 4.0f + pa.bias;
-    const bool on = logit > 0.f && kept[u] != 0;  // false for NaN
-    before_blocks += (u < b && on) ? 1 : 0;         // blocks before this one are full: every slot is a patch
-    if (u == b) { own_on = on; own_logit = logit; }
+    for (int k = 1; k < S * S; ++k) acc += v[k];
+    return acc / (float)(S * S) + bias;
   }
-  int base_cnt;
-  (void)scan_wave_counts(wave_sum_int(before_blocks), kCompactThreads / kWave, scan[0], &base_cnt);
-  const int q = b * kCompactThreads + tid;
-  const bool f = q < n && own_on;
-  if (q < n) {
-    mask[q] = own_on ? 1 : 0;
-    if (pa.logits) pa.logits[q] = own_logit;
+  __device__ __forceinline__ bool on(float bias) const { return logit(bias) > 0.f && kept != 0; }  // (not for NaN)
+};
+template <int S, int CH>
+__global__ __launch_bounds__(kCompactThreads) void k_pool_compact(const PoolCompactArgs a) {
+  __shared__ __align__(16) int2 s_cnt[kCompactWaves];  // of a wave: active patches of its own, of earlier blocks
+  prefetch_args<sizeof(PoolCompactArgs)>();
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), waves = (int)blockDim.x / kWave;
+  const int q = (int)blockIdx.x * kCompactThreads + tid;
+  Pooled<S> own;
+  own.load(a, min(q, a.n - 1));
+  int before = 0;
+  for (int b = 0; b < (int)blockIdx.x; b += CH) {
+    Pooled<S> e[CH];
+#pragma unroll
+    for (int u = 0; u < CH; ++u) e[u].load(a, min(b + u, (int)blockIdx.x - 1) * kCompactThreads + tid);
+#pragma unroll
+    for (int u = 0; u < CH; ++u) before += b + u < (int)blockIdx.x ? __popcll(__ballot(e[u].on(a.pa.bias))) : 0;
+  }
+  const bool f = q < a.n && own.on(a.pa.bias);
+  if (q < a.n) {
+    a.mask[q] = f ? 1 : 0;
+    if (a.pa.logits) a.pa.logits[q] = own.logit(a.pa.bias);
   }
   const unsigned long long bal = __ballot(f);
-  int tot;
-  const int wo = scan_wave_counts(__popcll(bal), kCompactThreads / kWave, scan[1], &tot);
-  const int pos = base_cnt + wo + ballot_prefix(bal);
-  if (sample_offsets && q < n && (q % per_sample) == 0) sample_offsets[q / per_sample] = pos;
-  if (f) idx[pos] = q;
-  if (b == (int)gridDim.x - 1 && tid == 0) {
-    *count = base_cnt + tot;
-    if (sample_offsets) sample_offsets[n / per_sample] = base_cnt + tot;
+  int pos = before, total = before + __popcll(bal);
+  if (waves > 1) {
+    if ((tid & (kWave - 1)) == 0) s_cnt[wave] = make_int2(__popcll(bal), before);
+    __syncthreads();
+    pos = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < kCompactWaves; ++w) {
+      const int2 c = s_cnt[min(w, waves - 1)];
+      pos += w < waves ? c.y + (w < wave ? c.x : 0) : 0;
+      total += w < waves ? c.y + c.x : 0;
+    }
+  }
+  pos += ballot_prefix(bal);
+  if (a.sample_offsets && q < a.n) {
+    const int s = fast_div(q, a.d_pps);
+    if (q == s * a.pps) a.sample_offsets[s] = pos;
+  }
+  if (f) a.idx[pos] = q;
+  if (blockIdx.x == gridDim.x - 1 && tid == 0) {
+    *a.count = total;
+    if (a.sample_offsets) a.sample_offsets[fast_div(a.n, a.d_pps)] = total;
   }
 }
 
-// The same in one launch for any S when one block holds all patches (coarse granularities: S = 7 on a 14 x 14 map
+// The same for any other S when one block holds all patches (coarse granularities: S = 7 on a 14 x 14 map
 // gives 512 patches for 128 images): one patch per thread, decision by pooled_decision (so the masks are those of
 // the two-launch path, bit for bit), ordered compaction with one ballot and one scan of the wave counts.
 __global__ __launch_bounds__(kCompactThreads) void k_pool_compact_one_block(PoolArgs pa, int n, uint8_t* __restrict__ mask,
@@ -378,10 +405,13 @@ int launch_pool_compact(const float* proj, int N, int H, int W, int S, float bia
                         hipStream_t stream) {
   const int pps = (H / S) * (W / S), npatch = N * pps;
   PoolArgs pa{proj, keep, logits, H, W, S, bias};
-  if (S == 2 && npatch > kCompactThreads && npatch <= kPoolFusedMax) {
+  if (npatch > 0 && npatch <= pool_fused_max(S)) {
     StageScope scope(LAUD_STAGE_COMPACT, stream);
-    hipLaunchKernelGGL(k_pool_compact_s2, dim3((npatch + kCompactThreads - 1) / kCompactThreads), dim3(kCompactThreads), 0,
-                       stream, pa, npatch, mask, idx, count, sample_offsets, pps);
+    const PoolCompactArgs k{pa, make_fast_div(pps), make_fast_div(W / S), npatch, pps, W / S, mask, idx, count, sample_offsets};
+    const dim3 grid((npatch + kCompactThreads - 1) / kCompactThreads), block(std::min(kCompactThreads, (npatch + kWave - 1) / kWave * kWave));
+    if (S == 1) hipLaunchKernelGGL((k_pool_compact<1, 8>), grid, block, 0, stream, k);
+    else if (S == 2) hipLaunchKernelGGL((k_pool_compact<2, 8>), grid, block, 0, stream, k);
+    else hipLaunchKernelGGL((k_pool_compact<4, 3>), grid, block, 0, stream, k);
     return check_launch();
   }
   if (npatch > 0 && npatch <= kCompactThreads) {

@@ -619,6 +619,19 @@ def test_masker_dyn_bottleneck(G, case, inplace, use_keep):
     assert_close(got[up], ref[up], TOL[dt], "fused masker block")
 
 
+# Pooling and list in one launch: one wave, part of a block, blocks either side of 1024 patches, the last size of each granularity and the
+# first of the two launches past it.
+POOLED = [(1, 7, 7, 1), (3, 19, 18, 1), (32, 32, 32, 1), (33, 32, 32, 1), (1, 16, 14, 2), (4, 32, 32, 2), (5, 30, 30, 2), (64, 32, 32, 2), (65, 32, 32, 2),
+          (1, 8, 8, 4), (1, 32, 36, 4), (9, 44, 44, 4), (64, 32, 32, 4), (65, 32, 32, 4)]
+
+
+@pytest.mark.parametrize("size", POOLED)
+@pytest.mark.parametrize("use_keep", [False, True])
+def test_pooled_masks_at_the_edges_of_blocks(G, size, use_keep):
+    n, h, w, S = size
+    test_masker_dyn_bottleneck(G, (n, h, w, 16, 8, S, I.F32 if n & 1 else I.BF16, True), True, use_keep)
+
+
 def test_masker_dyn_bottleneck_equals_two_call_path(G):
     """Same mask, same indices, same output bits as laud_mask_gen + laud_dyn_bottleneck on config-2 geometry."""
     t, L, D = G.torch, G.L, G.D
