@@ -18,66 +18,82 @@ constexpr int kSeThreads = 1024, kSeChunks = 128, kSeLanes = 16;
 
 // dst[o] = f(w[o] . v + b[o]), o < n, for vectors of length len in LDS: sixteen lanes per output, 64 outputs at a time.  A
 // thread's share of the weights is a sequence of items (pass over the outputs, 16-byte step along the row); the first kSePre
-// of them are loaded before anything else the kernel does (they depend on nothing), the rest four at a time.
+// of them are loaded before anything else the kernel does (they depend on nothing), the rest four at a time.  Loads return in
+// order, so that the list and the rows wait for them: a pass or a step that there is not is not loaded, nor a lane past the last one.
+// The biases are in LDS: from memory every pass waited for its own.
 // (Positions are counted up instead of divided out: sixteen waves share four SIMDs, and a division per item and wave cost more
 // than the loads.)
 constexpr int kSePre = 8, kSeOutputs = kSeThreads / kSeLanes;
 struct SeItems {
   int l, o0, n, q4, ks, passes;
-  const float4* w;
+  __amdgpu_buffer_rsrc_t w;
   int p, k;  // position of the next load
   __device__ __forceinline__ SeItems(const float* wt, int n_, int len)
       : l((int)threadIdx.x & (kSeLanes - 1)), o0((int)threadIdx.x / kSeLanes), n(n_), q4(len / 4), ks((len / 4 + kSeLanes - 1) / kSeLanes),
-        passes((n_ + kSeOutputs - 1) / kSeOutputs), w(reinterpret_cast<const float4*>(wt)), p(0), k(0) {}
-  __device__ __forceinline__ float4 next() {  // items past the end re-read a valid row; never used
-    const float4 r = w[(size_t)min(p * kSeOutputs + o0, n - 1) * q4 + min(k * kSeLanes + l, q4 - 1)];
-    if (++k == ks) { k = 0; ++p; }
+        passes((n_ + kSeOutputs - 1) / kSeOutputs),
+        w(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(wt), 0, n_ * len * 4, 0x00020000)), p(0), k(0) {}
+  __device__ __forceinline__ u32x4 next() {
+    u32x4 r = {0, 0, 0, 0};
+    if (p < passes) {
+      const int o = p * kSeOutputs + o0, c = k * kSeLanes + l;
+      r = __builtin_amdgcn_raw_buffer_load_b128(w, o < n && c < q4 ? (unsigned)(o * q4 + c) * 16u : 0x80000000u, 0, 0);
+      if (++k == ks) { k = 0; ++p; }
+    }
     return r;
   }
 };
-// Item (p, k) with weights r; steps (p, k) on.
+// Sum over a row of sixteen lanes, the lanes 8, 4, 2 and 1 apart (rotations: what they add has that period).
+template <int N>
+__device__ __forceinline__ float add_rotated(float v) {
+  return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x120 + N, 0xf, 0xf, true));
+}
+// Four items with weights r; steps (p, k) on.
 template <bool SIGMOID>
-__device__ __forceinline__ void se_item(const SeItems& it, int& p, int& k, const float4& r, const float* v,
-                                        const float* __restrict__ b, float& acc, float* dst) {
-  const int c = k * kSeLanes + it.l;
-  if (c < it.q4) {
-    const float4 x = reinterpret_cast<const float4*>(v)[c];
-    acc += r.x * x.x + r.y * x.y + r.z * x.z + r.w * x.w;
-  }
-  if (++k == it.ks) {  // the output is complete
+__device__ __forceinline__ void se_items(const SeItems& it, int& p, int& k, const u32x4* r, const float* v, const float* b, float& acc, float* dst) {
+  float4 x[4];
+  float bias[4];
+  int pp = p, kk = k;
 #pragma unroll
-    for (int d = kSeLanes / 2; d > 0; d >>= 1) acc += __shfl_xor(acc, d, kWave);
-    const int o = p * kSeOutputs + it.o0;
-    if (it.l == 0 && o < it.n) {
-      const float s = acc + b[o];
-      dst[o] = SIGMOID ? 1.f / (1.f + __expf(-s)) : fmaxf(s, 0.f);
+  for (int u = 0; u < 4; ++u) {  // (what lies in LDS is under way together)
+    x[u] = reinterpret_cast<const float4*>(v)[min(kk * kSeLanes + it.l, it.q4 - 1)];
+    bias[u] = b[min(pp * kSeOutputs + it.o0, it.n - 1)];
+    if (++kk == it.ks) { kk = 0; ++pp; }
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if (p >= it.passes) return;
+    if (k * kSeLanes + it.l < it.q4)
+      acc += __uint_as_float(r[u].x) * x[u].x + __uint_as_float(r[u].y) * x[u].y + __uint_as_float(r[u].z) * x[u].z + __uint_as_float(r[u].w) * x[u].w;
+    if (++k == it.ks) {  // the output is complete
+      acc = add_rotated<1>(add_rotated<2>(add_rotated<4>(add_rotated<8>(acc))));
+      const int o = p * kSeOutputs + it.o0;
+      if (it.l == 0 && o < it.n) {
+        const float s = acc + bias[u];
+        dst[o] = SIGMOID ? 1.f / (1.f + __expf(-s)) : fmaxf(s, 0.f);
+      }
+      acc = 0.f;
+      k = 0;
+      ++p;
     }
-    acc = 0.f;
-    k = 0;
-    ++p;
   }
 }
 template <bool SIGMOID>
-__device__ __forceinline__ void se_layer(SeItems& it, const float4 (&pre)[kSePre], const float* v, const float* __restrict__ b,
-                                         float* dst) {
+__device__ __forceinline__ void se_layer(SeItems& it, const u32x4 (&pre)[kSePre], const float* v, const float* b, float* dst) {
   float acc = 0.f;
   int p = 0, k = 0;
 #pragma unroll
-  for (int t = 0; t < kSePre; ++t)
-    if (p < it.passes) se_item<SIGMOID>(it, p, k, pre[t], v, b, acc, dst);
+  for (int t = 0; t < kSePre; t += 4) se_items<SIGMOID>(it, p, k, pre + t, v, b, acc, dst);
   while (p < it.passes) {
-    float4 r[4];
+    u32x4 r[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) r[u] = it.next();
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (p < it.passes) se_item<SIGMOID>(it, p, k, r[u], v, b, acc, dst);
+    se_items<SIGMOID>(it, p, k, r, v, b, acc, dst);
   }
 }
 // rows of w whose length is no multiple of four (not 16-byte aligned)
 template <bool SIGMOID>
 __device__ __forceinline__ void se_layer_any(const float* __restrict__ w, const float* v, int n, int len,
-                                             const float* __restrict__ b, float* dst) {
+                                             const float* b, float* dst) {
   const int l = threadIdx.x % kSeLanes, o0 = threadIdx.x / kSeLanes;
   for (int o1 = 0; o1 < n; o1 += kSeThreads / kSeLanes) {
     const int o = min(o1 + o0, n - 1);
@@ -177,10 +193,12 @@ __global__ __launch_bounds__(kSeThreads) void k_se(ET* __restrict__ h2, const in
   __shared__ __align__(16) float s_z[kSeMaxC];              // means, then gates
   __shared__ __align__(16) float s_h[kSeMaxHidden];
   __shared__ float s_sums[kSeThreads];
+  __shared__ float s_b1[kSeMaxHidden], s_b2[kSeMaxC];
   __shared__ int s_below[2][NW];
   const int n = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   SeItems it1(w1, se_w, C), it2(w2, C, se_w);
-  float4 pre1[kSePre], pre2[kSePre];
+  const float bias1 = tid < se_w ? b1[tid] : 0.f, bias2 = tid < C ? b2[tid] : 0.f;
+  u32x4 pre1[kSePre], pre2[kSePre];
   const bool vec2 = (se_w & 3) == 0;  // (C is a multiple of eight)
 #pragma unroll
   for (int t = 0; t < kSePre; ++t) {
@@ -214,6 +232,9 @@ __global__ __launch_bounds__(kSeThreads) void k_se(ET* __restrict__ h2, const in
   }
   const int rows = (hi - lo) * SS;
   if (rows == 0) return;
+  s_b1[tid] = bias1;  // (read behind the means' barriers)
+  s_b2[tid] = bias2;
+  for (int i = tid + kSeThreads; i < C; i += kSeThreads) s_b2[i] = b2[i];
   const int cpr = C / EPC;  // 16-byte chunks per row
   uint4* const base = reinterpret_cast<uint4*>(h2 + (long long)lo * SS * C);
   const float inv = 1.f / (float)rows;
@@ -245,6 +266,7 @@ __global__ __launch_bounds__(kSeThreads) void k_se(ET* __restrict__ h2, const in
     const int G = fdiv(kSeThreads, inv_c), g = fdiv(tid, inv_c), c = tid - g * C;
     if (g < G) {
       float t = 0.f;
+#pragma unroll 4
       for (int q = g; q < RP; q += G) t += s_part[q * C + c];
       if (G > 1) s_sums[g * C + c] = t;
       else s_z[c] = t * inv;
@@ -262,10 +284,10 @@ __global__ __launch_bounds__(kSeThreads) void k_se(ET* __restrict__ h2, const in
       __syncthreads();
     }
   }
-  se_layer<false>(it1, pre1, s_z, b1, s_h);
+  se_layer<false>(it1, pre1, s_z, s_b1, s_h);
   __syncthreads();
-  if (vec2) se_layer<true>(it2, pre2, s_h, b2, s_z);
-  else se_layer_any<true>(w2, s_h, C, se_w, b2, s_z);
+  if (vec2) se_layer<true>(it2, pre2, s_h, s_b2, s_z);
+  else se_layer_any<true>(w2, s_h, C, se_w, s_b2, s_z);
   __syncthreads();
   // h2[row][:] *= gate, rounded to the storage type
   if (keep) {

@@ -37,6 +37,8 @@ using std::max;
 using std::min;
 static inline unsigned __float_as_uint(float f) { unsigned u; memcpy(&u, &f, 4); return u; }
 static inline float __uint_as_float(unsigned u) { float f; memcpy(&f, &u, 4); return f; }
+static inline int __float_as_int(float v) { int u; memcpy(&u, &v, 4); return u; }
+static inline float __int_as_float(int u) { float v; memcpy(&v, &u, 4); return v; }
 static inline int __popcll(unsigned long long v) { return __builtin_popcountll(v); }
 static inline int __popc(unsigned v) { return __builtin_popcount(v); }
 static inline unsigned __umulhi(unsigned a, unsigned b) { return (unsigned)(((unsigned long long)a * b) >> 32); }
@@ -93,6 +95,8 @@ static inline int lanes_below(unsigned mask, int first) {  // set bits of 32 lan
 #define __shfl_xor(v, o, w) host::shuffle(host::XOR, v, o)
 #define __shfl_up(v, o, w) host::shuffle(host::UP, v, o)
 #define __shfl(v, l, w) host::shuffle(host::FROM, v, l)
+// (rotations of the rows of sixteen lanes only)
+#define __builtin_amdgcn_mov_dpp(v, c, r, b, z) host::shuffle(host::FROM, v, (host::current->lane & 48) | ((host::current->lane - ((c) - 0x120)) & 15))
 #define __amdgpu_buffer_rsrc_t host::Rsrc
 #define __builtin_amdgcn_make_buffer_rsrc(p, stride, bytes, flags) (host::Rsrc{(const char*)(p), (unsigned)(bytes)})
 #define __builtin_amdgcn_raw_buffer_load_b128(r, v, s, a) host::load_chunk(r, v, s)
