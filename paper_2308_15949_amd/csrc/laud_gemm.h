@@ -12,7 +12,8 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(1))) u32x4* gptr16;  // 16-byte chunk in global memory
 
 enum { M_CONV1 = 0, M_CONV2 = 1, M_CONV3 = 2, M_CS1 = 3, M_CS2 = 4, M_CS3 = 5, M_DENSE1 = 6, M_U1 = 7, M_U2 = 8, M_U3 = 9,
-       M_SD1 = 10, M_SD2 = 11, M_SD3 = 12, M_G2 = 13 };
+       M_SD1 = 10, M_SD2 = 11, M_SD3 = 12, M_G2 = 13,
+       M_CONV2P = 14 };  // CONV2 that decides the patches itself (PoolList; laud_skinny.hip only)
 
 struct GemmArgs {
   const void* A;         // activations the rows are gathered from
@@ -46,10 +47,20 @@ struct GemmArgs {
   InactiveCopy cp;       // CONV3: copy of the inactive patches in extra workgroups (nblocks 0: none)
 };
 
+// The masker's decision of a map's patches from the per-pixel projection, made by every workgroup of the 3x3 that runs on them.
+constexpr int kPoolListMax = 1024;
+struct PoolList {
+  const float* proj; const uint8_t* keep;  // [N*H*W]; [N] or null
+  uint8_t* mask; float* logits;            // [n]; logits or null
+  int32_t* sample_offsets;                 // [N + 1] or null
+  float bias;
+  int n;                                   // patches, up to kPoolListMax
+};
+
 // Few rows: small tiles, the reduction split over the waves of a workgroup (laud_skinny.hip).  cap_rows: number of rows, or
 // its upper bound where the count is on the device.
 bool skinny_wanted(int mode, int dtype, const GemmArgs& a, long long cap_rows);
-int launch_skinny(int mode, int dtype, const GemmArgs& a, long long cap_rows, hipStream_t stream);
+int launch_skinny(int mode, int dtype, const GemmArgs& a, long long cap_rows, hipStream_t stream, const PoolList* pool = nullptr);
 int skinny_init_device();
 // Two dense 1x1s (M_SD1) on the same input and reduction length in one launch.
 bool skinny_pair_wanted(int dtype, const GemmArgs& a, long long rows_a, const GemmArgs& b, long long rows_b);

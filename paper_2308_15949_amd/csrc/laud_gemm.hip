@@ -1130,19 +1130,32 @@ extern "C" int laud_masker_dyn_bottleneck(const void* x, laud_fmap fx, const lau
     if ((rc = launch_gemm<M_DENSE1>(fx.dtype, a, npix, 1, st)) != LAUD_OK) return rc;
     a.pk_out = nullptr;
   }
-  // pooled logits -> threshold -> ascending index list (device-side count)
-  if ((rc = launch_pool_compact(proj, fx.N, fx.H, fx.W, S, bias, keep, mask, logits, idx, count, sample_offsets,
-                                (int32_t*)(wsb + L.blocks), st)) != LAUD_OK)
-    return rc;
+  // pooled logits -> threshold -> ascending index list (device-side count): a launch of its own, or, with few patches and the small
+  // tiles behind it, part of the 3x3 (whose workgroups all read `keep`: not where the mask is written over it)
   a.wmask = nullptr; a.proj = nullptr;
+  GemmArgs b = a;
+  b.A = h1; b.Wt = p->w2; b.scale = p->s2; b.shift = p->t2; b.Out = h2;
+  b.count = count; b.list = idx; b.K = p->c_mid; b.ldw = 9 * p->c_mid; b.Ncols = p->c_mid;
+  b.lda = p->c_mid; b.ldo = p->c_mid;
+  const int npatch = fx.N * Hp * Wp;
+  const bool own_list = npatch <= kPoolListMax && (S == 1 || S == 2 || S == 4) && skinny_wanted(M_CONV2, fx.dtype, b, npix) &&
+                        !tail_used(fx.dtype, p, nullptr, npix) && !narrow_supported(fx.dtype, p->c_mid, p->c_out, npix) &&
+                        !(keep && keep < mask + npatch && mask < keep + fx.N);
+  if (!own_list && (rc = launch_pool_compact(proj, fx.N, fx.H, fx.W, S, bias, keep, mask, logits, idx, count, sample_offsets,
+                                             (int32_t*)(wsb + L.blocks), st)) != LAUD_OK)
+    return rc;
   const InactiveCopy copy = inactive_copy(x, out, fx, S, idx, count);
   if (try_tail(fx.dtype, p, nullptr, h1, x, out, idx, count, fx.H, fx.W, S, 1, fx.H, fx.W, npix, wsb + L.wpack, copy, st, &rc)) return rc;
   if (try_narrow(fx.dtype, p, nullptr, h1, x, out, idx, count, fx.H, fx.W, S, 1, fx.H, fx.W, npix, copy, st, &rc)) return rc;
   // conv2 and conv3 exactly as in laud_dyn_bottleneck
-  a.A = h1; a.Wt = p->w2; a.scale = p->s2; a.shift = p->t2; a.Out = h2;
-  a.count = count; a.list = idx; a.K = p->c_mid; a.ldw = 9 * p->c_mid; a.Ncols = p->c_mid;
-  a.lda = p->c_mid; a.ldo = p->c_mid;
-  if ((rc = launch_gemm<M_CONV2>(fx.dtype, a, npix, 1, st)) != LAUD_OK) return rc;
+  if (own_list) {
+    StageScope scope(LAUD_STAGE_CONV2, st);
+    const PoolList pool{proj, keep, mask, logits, sample_offsets, bias, npatch};
+    if ((rc = launch_skinny(M_CONV2P, fx.dtype, b, npix, st, &pool)) != LAUD_OK) return rc;
+  } else if ((rc = launch_gemm<M_CONV2>(fx.dtype, b, npix, 1, st)) != LAUD_OK) {
+    return rc;
+  }
+  a = b;
   a.A = h2; a.Wt = p->w3; a.scale = p->s3; a.shift = p->t3; a.Out = out; a.Res = x;
   a.K = p->c_mid; a.ldw = p->c_mid; a.Ncols = p->c_out; a.lda = p->c_mid; a.ldo = p->c_out;
   a.relu = p->relu_out ? 1 : 0;

@@ -16,10 +16,18 @@
 #include "laud_gemm.h"
 
 #include <atomic>
+#include <type_traits>
 
 namespace laud {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+// (LDS only: the weight loads stay in flight across this barrier)
+__device__ __forceinline__ void lds_barrier() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#endif
+}
 
 // One 16-byte fragment pair: 16x16x32 bf16, or four k-steps of the 16x16x4 fp32 MFMA (lane group l/16 holds k-slots
 // 4q .. 4q+3 of the 16-wide K group for both operands, so their pairing is consistent).
@@ -45,6 +53,110 @@ struct SkinnyArgs {
   unsigned kmul;              // ceil(2^32 / kch), 0 for kch = 1
   int deal;                   // tiles to XCDs: 1 by row tile, 2 by column tile (a multiple of eight of them), 0 as they come
   float inv_ss, inv_s, inv_pps, inv_wp, inv_howo, inv_wo, inv_rt, inv_ct;
+  PoolList pool;              // CONV2P
+};
+
+// CONV2P: with few patches every workgroup of the 3x3 decides all of them from the masker's projection -- one trip of loads, a ballot --
+// instead of waiting for a launch that does (1.35 us and the gap behind it) and then for its count and list, two trips.  The first
+// workgroup leaves mask, list and count for the last 1x1 and the caller.  Up to kPoolListMax patches, up to four a thread, of 1, 2 x 2 or 4 x 4 pixels.
+// Summation order and decision as in laud_mask.hip.  (Blocks with their masker, before / here: one image of stage 1 / 2 / 3 / 4 18.1 / 15.2 / 15.6 /
+// 19.5 -> 16.5 / 14.6 / 14.4 / 18.0 us, 16 images of stage 3 35.9 -> 34.5.  Decided ahead of the early exit, so that workgroups past the active
+// rows load no weights: behind it four images of stage 4 took 25.7 instead of 23.8.)
+template <int U>
+struct PoolDecision {
+  float v[U][16];
+  int kept[U];
+  __device__ __forceinline__ const float* base(const SkinnyArgs& ka, int q, int& n) const {
+    const GemmArgs& a = ka.g;
+    const int Wp = fdiv(a.W, ka.inv_s), pps = fdiv(a.H, ka.inv_s) * Wp;
+    n = fdiv(q, ka.inv_pps);
+    const int r = q - n * pps, py = fdiv(r, ka.inv_wp), px = r - py * Wp;
+    return ka.pool.proj + ((size_t)n * a.H + py * a.S) * a.W + px * a.S;
+  }
+  template <int NT>
+  __device__ __forceinline__ void load(const SkinnyArgs& ka, int tid) {
+    const GemmArgs& a = ka.g;
+    const float* b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (u * NT >= ka.pool.n) break;  // (uniform, here and below)
+      int n;
+      b[u] = base(ka, min(tid + u * NT, ka.pool.n - 1), n);
+      kept[u] = ka.pool.keep ? (int)ka.pool.keep[n] : 1;
+    }
+    const auto rows = [&](auto S) __attribute__((always_inline)) {  // (a map's width is a multiple of S: rows of a patch are aligned to their size)
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (u * NT < ka.pool.n)
+#pragma unroll
+          for (int y = 0; y < S; ++y) __builtin_memcpy(&v[u][S * y], __builtin_assume_aligned(b[u] + y * a.W, 4 * S), 4 * S);
+    };
+    if (a.S == 1) rows(std::integral_constant<int, 1>{});
+    else if (a.S == 2) rows(std::integral_constant<int, 2>{});
+    else rows(std::integral_constant<int, 4>{});
+  }
+  __device__ __forceinline__ float logit(const SkinnyArgs& ka, int u) const {
+    const int S = ka.g.S;
+    float acc = v[u][0];
+    if (S > 1) {
+#pragma unroll
+      for (int k = 1; k < 4; ++k) acc += v[u][k];
+    }
+    if (S == 4) {
+#pragma unroll
+      for (int k = 4; k < 16; ++k) acc += v[u][k];
+    }
+    return acc / (float)(S * S) + ka.pool.bias;
+  }
+  // List and number of the active patches; s_cnt: counts of the waves, for every u.  `first`: the workgroup that leaves the results.
+  template <int NT>
+  __device__ __forceinline__ int list(const SkinnyArgs& ka, int tid, bool first, int* s_list, int* s_cnt) const {
+    constexpr int NW = NT / kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    float lg[U];
+    bool on[U];
+    unsigned long long bal[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (u * NT >= ka.pool.n) break;
+      lg[u] = logit(ka, u);
+      on[u] = tid + u * NT < ka.pool.n && lg[u] > 0.f && kept[u] != 0;  // (not for NaN)
+      bal[u] = __ballot(on[u]);
+      if ((tid & (kWave - 1)) == 0) s_cnt[u * NW + wave] = __popcll(bal[u]);
+    }
+    lds_barrier();
+    int pos[U], total = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (u * NT >= ka.pool.n) break;
+      pos[u] = 0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        if (w == wave) pos[u] = total + ballot_prefix(bal[u]);
+        total += s_cnt[u * NW + w];
+      }
+      if (on[u]) s_list[pos[u]] = tid + u * NT;
+    }
+    lds_barrier();
+    if (first) {
+      const int Wp = fdiv(ka.g.W, ka.inv_s), pps = fdiv(ka.g.H, ka.inv_s) * Wp;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int q = tid + u * NT;
+        if (q >= ka.pool.n) continue;
+        ka.pool.mask[q] = on[u] ? 1 : 0;
+        if (ka.pool.logits) ka.pool.logits[q] = lg[u];
+        if (on[u]) const_cast<int32_t*>(ka.g.list)[pos[u]] = q;
+        const int n = fdiv(q, ka.inv_pps);
+        if (ka.pool.sample_offsets && q == n * pps) ka.pool.sample_offsets[n] = pos[u];
+      }
+      if (tid == 0) {
+        *const_cast<int32_t*>(ka.g.count) = total;
+        if (ka.pool.sample_offsets) ka.pool.sample_offsets[fdiv(ka.pool.n, ka.inv_pps)] = total;
+      }
+    }
+    return total;
+  }
 };
 
 template <int TM, int TN, int NW>
@@ -59,9 +171,9 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& ka, const int L) {
   const GemmArgs& a = ka.g;
   constexpr int BM = 16 * TM, BN = 16 * TN, NT = 64 * NW;
   constexpr int EPC = elem<ET>::per16, ES = (int)sizeof(ET), BKE = 8 * EPC;
-  constexpr bool TAPS = (MODE == M_CONV2 || MODE == M_SD2 || MODE == M_G2);
+  constexpr bool POOL = MODE == M_CONV2P, TAPS = (MODE == M_CONV2 || POOL || MODE == M_SD2 || MODE == M_G2);
   constexpr bool RES = (MODE == M_CONV3 || MODE == M_SD3);
-  constexpr bool LISTED = (MODE == M_CONV2 || MODE == M_CONV3 || MODE == M_G2);
+  constexpr bool LISTED = (MODE == M_CONV2 || POOL || MODE == M_CONV3 || MODE == M_G2);
   constexpr int PSTR = BN + 4;  // floats per row of a partial tile
   extern __shared__ __align__(16) unsigned char smem[];
   // partial tiles [NW][BM][PSTR]; during the loop the same bytes are the waves' private slices [NW][(BM + BN) * 128 bytes]
@@ -71,6 +183,8 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& ka, const int L) {
   __shared__ int s_row[BM];
   __shared__ unsigned char s_inact[MODE == M_SD1 ? BM : 1];
   __shared__ float s_proj[MODE == M_DENSE1 ? NW * BM : 1];
+  constexpr int PU = POOL ? kPoolListMax / NT : 1;  // patches a thread decides
+  __shared__ int s_list[POOL ? kPoolListMax : 1], s_cnt[POOL ? kPoolListMax / kWave : 1];
 
   const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, lq = lane >> 4, l8 = lane >> 3, l7 = lane & 7;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -100,7 +214,14 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& ka, const int L) {
   }
   const int row0 = rt * BM, col0 = ct * BN;
   const int SS = a.S * a.S;
-  const int M = LISTED ? *a.count * SS : ka.cap_rows;
+  int M;
+  if constexpr (POOL) {
+    PoolDecision<PU> decision;
+    decision.template load<NT>(ka, tid);
+    M = decision.template list<NT>(ka, tid, L == 0, s_list, s_cnt) * SS;
+  } else {
+    M = LISTED ? *a.count * SS : ka.cap_rows;
+  }
   if (row0 >= M) return;
 
   constexpr unsigned kOob = 0x80000000u;
@@ -113,7 +234,8 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& ka, const int L) {
   // ---- the row this thread looks up for the workgroup (first BM threads); its list entry is requested first -------------
   const int rrow = row0 + min(tid, BM - 1);
   int entry = 0;
-  if constexpr (LISTED) entry = a.list[list_entry(rrow, M, ka.inv_ss)];
+  if constexpr (POOL) entry = s_list[list_entry(rrow, M, ka.inv_ss)];
+  else if constexpr (LISTED) entry = a.list[list_entry(rrow, M, ka.inv_ss)];
 
   // ---- the weights of the first D slices: they depend on nothing but the tile ------------------------------------------
   // Every load is unconditional; a chunk that must read as zero (past K, past the wave's last slice, outside the image) gets
@@ -218,10 +340,7 @@ __device__ __forceinline__ void skinny_tile(const SkinnyArgs& ka, const int L) {
   const bool do_proj = MODE == M_DENSE1 && ct == 0 && a.wmask != nullptr;
   if (do_proj)
     for (int k = tid; k < a.K; k += NT) s_wm[k] = a.wmask[k];
-  // (LDS only: the weight loads stay in flight across this barrier)
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-#endif
+  lds_barrier();
 #pragma unroll
   for (int t = 0; t < 2 * TM; ++t) {
     voffA[t] = s_voff[8 * t + l8] + (unsigned)(l7 * 16);
@@ -398,7 +517,7 @@ static int skinny_request_lds() {
 // The arguments of a launch and its workgroups (without those that copy).
 template <int MODE, typename ET, int TM, int TN>
 static unsigned skinny_args(GemmArgs a, long long cap_rows, SkinnyArgs& k) {
-  constexpr bool TAPS = (MODE == M_CONV2 || MODE == M_SD2 || MODE == M_G2);
+  constexpr bool TAPS = (MODE == M_CONV2 || MODE == M_CONV2P || MODE == M_SD2 || MODE == M_G2);
   constexpr int BKE = 8 * elem<ET>::per16;
   a.row_tiles = (int)((cap_rows + 16 * TM - 1) / (16 * TM));
   a.col_tiles = (a.Ncols + 16 * TN - 1) / (16 * TN);
@@ -420,12 +539,13 @@ static unsigned skinny_args(GemmArgs a, long long cap_rows, SkinnyArgs& k) {
 
 // cap_rows < 0: only make the request (laud_init)
 template <int MODE, typename ET, int TM, int TN, int NW, int D>
-static int launch_skinny_t(const GemmArgs& a, long long cap_rows, hipStream_t st) {
+static int launch_skinny_t(const GemmArgs& a, long long cap_rows, hipStream_t st, const PoolList* pool = nullptr) {
   const int rc = skinny_request_lds<MODE, ET, TM, TN, NW, D>();
   if (rc != LAUD_OK || cap_rows < 0) return rc;
   SkinnyArgs k;
   unsigned grid = skinny_args<MODE, ET, TM, TN>(a, cap_rows, k);
   const int lds = skinny_lds<TM, TN, NW>() + (MODE == M_DENSE1 && a.wmask ? a.K * 4 : 0);
+  if constexpr (MODE == M_CONV2P) k.pool = *pool;
   if constexpr (MODE == M_CONV3) {
     k.g.cp.first = (int)grid;
     grid += (unsigned)a.cp.nblocks;
@@ -455,14 +575,14 @@ static int launch_pair_t(const GemmArgs& a, long long rows_a, const GemmArgs& b,
 }
 
 template <int MODE, typename ET>
-static int launch_skinny_e(const GemmArgs& a, long long cap_rows, hipStream_t st) {
+static int launch_skinny_e(const GemmArgs& a, long long cap_rows, hipStream_t st, const PoolList* pool) {
   constexpr int BKE = 8 * elem<ET>::per16;
-  constexpr bool TAPS = (MODE == M_CONV2 || MODE == M_SD2 || MODE == M_G2);
+  constexpr bool TAPS = (MODE == M_CONV2 || MODE == M_CONV2P || MODE == M_SD2 || MODE == M_G2);
   if constexpr (MODE == M_G2) {
     // 64-channel column tiles: they hold whole groups.  bf16: nine slices on three waves, all of a wave's under way at once, so
     // that a compute unit holds two workgroups (on eight waves their LDS let it hold one, and a second round took 10.6 us).  float32: eighteen slices, MFMAs as long as loads: eight waves.
-    if constexpr (sizeof(ET) == 2) return launch_skinny_t<MODE, ET, 1, 4, 3, 3>(a, cap_rows, st);
-    else return launch_skinny_t<MODE, ET, 1, 4, 8, 2>(a, cap_rows, st);
+    if constexpr (sizeof(ET) == 2) return launch_skinny_t<MODE, ET, 1, 4, 3, 3>(a, cap_rows, st, pool);
+    else return launch_skinny_t<MODE, ET, 1, 4, 8, 2>(a, cap_rows, st, pool);
   } else {
     if (cap_rows < 0) {
       int rc = launch_skinny_t<MODE, ET, 1, 1, 8, 8>(a, -1, st);
@@ -478,18 +598,19 @@ static int launch_skinny_e(const GemmArgs& a, long long cap_rows, hipStream_t st
     const int kt = (TAPS ? 9 : 1) * ((a.K + BKE - 1) / BKE);
     auto tiles = [&](int tm, int tn) { return ((cap_rows + 16 * tm - 1) / (16 * tm)) * ((a.Ncols + 16 * tn - 1) / (16 * tn)); };
     constexpr int fill = sizeof(ET) == 2 ? 192 : 384;
-    if (tiles(4, 4) >= fill) return launch_skinny_t<MODE, ET, 4, 4, 4, 2>(a, cap_rows, st);
-    if (tiles(2, 4) >= fill) return launch_skinny_t<MODE, ET, 2, 4, 4, 3>(a, cap_rows, st);
+    if (tiles(4, 4) >= fill) return launch_skinny_t<MODE, ET, 4, 4, 4, 2>(a, cap_rows, st, pool);
+    if (tiles(2, 4) >= fill) return launch_skinny_t<MODE, ET, 2, 4, 4, 3>(a, cap_rows, st, pool);
     const bool small = tiles(2, 2) < 192;
-    if (kt > 8) return small ? launch_skinny_t<MODE, ET, 1, 1, 8, 8>(a, cap_rows, st) : launch_skinny_t<MODE, ET, 2, 2, 8, 4>(a, cap_rows, st);
-    return small ? launch_skinny_t<MODE, ET, 1, 1, 4, 4>(a, cap_rows, st) : launch_skinny_t<MODE, ET, 2, 2, 4, 4>(a, cap_rows, st);
+    if (kt > 8) return small ? launch_skinny_t<MODE, ET, 1, 1, 8, 8>(a, cap_rows, st, pool) : launch_skinny_t<MODE, ET, 2, 2, 8, 4>(a, cap_rows, st, pool);
+    return small ? launch_skinny_t<MODE, ET, 1, 1, 4, 4>(a, cap_rows, st, pool) : launch_skinny_t<MODE, ET, 2, 2, 4, 4>(a, cap_rows, st, pool);
   }
 }
 
-int launch_skinny(int mode, int dtype, const GemmArgs& a, long long cap_rows, hipStream_t st) {
+int launch_skinny(int mode, int dtype, const GemmArgs& a, long long cap_rows, hipStream_t st, const PoolList* pool) {
   switch (mode) {
-#define LAUD_SKINNY_MODE(M) case M: return dtype == LAUD_BF16 ? launch_skinny_e<M, bf16_t>(a, cap_rows, st) : launch_skinny_e<M, float>(a, cap_rows, st)
+#define LAUD_SKINNY_MODE(M) case M: return dtype == LAUD_BF16 ? launch_skinny_e<M, bf16_t>(a, cap_rows, st, pool) : launch_skinny_e<M, float>(a, cap_rows, st, pool)
     LAUD_SKINNY_MODE(M_CONV2);
+    LAUD_SKINNY_MODE(M_CONV2P);
     LAUD_SKINNY_MODE(M_CONV3);
     LAUD_SKINNY_MODE(M_DENSE1);
     LAUD_SKINNY_MODE(M_SD1);
@@ -563,7 +684,7 @@ bool skinny_pair_wanted(int dtype, const GemmArgs& a, long long rows_a, const Ge
 
 int skinny_init_device() {
   const GemmArgs none{};
-  for (int mode : {M_CONV2, M_CONV3, M_DENSE1, M_SD1, M_SD2, M_SD3, M_G2})
+  for (int mode : {M_CONV2, M_CONV2P, M_CONV3, M_DENSE1, M_SD1, M_SD2, M_SD3, M_G2})
     for (int dtype : {LAUD_BF16, LAUD_F32})
       if (launch_skinny(mode, dtype, none, -1, nullptr) != LAUD_OK) return LAUD_ERR_HIP;
   for (int dtype : {LAUD_BF16, LAUD_F32})
