@@ -77,7 +77,7 @@ __device__ __forceinline__ void to_consecutive_channels(float (&v)[16]) {
 // operations of a wave stay in order: no barrier, no wait) a lane gets eight consecutive channels, four lanes 64 bytes of a row, and
 // residuals are read the same way: k_tail on 12544 / 18816 / 25088 pixels (128 images of 14 x 14 at 0.5, 0.75, 1) 35.6 / 47.8 / 65.0 ->
 // 33.2 / 45.0 / 61.8 us.  16-byte unit u of row r lies at position u ^ ((r >> 1) & 7) of the row's eight: four cycles of bank
-// conflicts an instruction on average (SQ_LDS_BANK_CONFLICT), 9 % of k_tail's LDS cycles.
+// conflicts an instruction on average (SQ_LDS_BANK_CONFLICT), 11 % of k_tail's LDS cycles.
 constexpr int kTurnBytes = 4096;
 // where a lane's channels 8 g + 4 * (lane / 32) .. +3 of row lane % 32 go
 __device__ __forceinline__ unsigned turn_put(int lane, int g) {
