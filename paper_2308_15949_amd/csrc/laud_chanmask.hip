@@ -127,7 +127,15 @@ __global__ __launch_bounds__(kMlpThreads) void k_channel_mlp(const float* __rest
 #pragma unroll
       for (int u = 0; u < 8; ++u) s += v[u];
     }
-    for (; k < slabs; ++k) s += pc[(size_t)k * C];
+    // ... and what is left four at a time, past the end the last row again, not added (one by one each was a trip of its own: 7 x 7 x 2048,
+    // twelve slabs, the masker of 1 / 24 / 64 images 9.2 / 10.4 / 12.7 -> 7.8 / 9.0 / 11.4 us)
+    for (; k < slabs; k += 4) {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = pc[(size_t)min(k + u, slabs - 1) * C];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) s += k + u < slabs ? v[u] : 0.f;
+    }
     g[c] = s * inv;
   }
   __syncthreads();
