@@ -319,7 +319,7 @@ int tail_init_device();
 size_t tail_packed_bytes(int c_mid, int c_out);
 // re-orders w2 [c_mid][3][3][c_mid] and w3 [c_out][c_mid] into the order the fused kernel streams them
 int launch_tail_pack(const void* w2, const void* w3, int c_out, void* packed, hipStream_t stream);
-// cap_rows: upper bound of the number of active pixels (grid size); the count itself stays on the device
+// cap_rows: pixels of the output map, the upper bound of the active ones (grid size); the count itself stays on the device
 int launch_tail(const TailArgs& a, long long cap_rows, hipStream_t stream);
 
 // conv1 on every pixel (+ masker projection) with register-resident weights (laud_head.hip), for head_supported() shapes.

@@ -77,7 +77,8 @@ __device__ long long g_tail_fine[8 * 64];
 #endif
 
 // One tile: rows row0 .. row0 + 32*PB - 1 of the compact list of active pixels (M rows exist).
-template <int NCT, int PB, bool CS>  // NCT column tiles of 256 output channels (cout = 256 * NCT); CS: channel mask
+// NCT column tiles of 256 output channels (cout = 256 * NCT); CS: channel mask; WIDE: the output map has more than 2 GiB
+template <int NCT, int PB, bool CS, bool WIDE>
 __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, const int M, const unsigned touched) {
   using namespace tail;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -364,7 +365,7 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
   // into the turning buffer; 2, 3: residual, activation, rounding and store of 16 of its rows, then the request for the residual
   // that column tile `next` adds there.  (from, next outside the column tiles: none)
   float4 e0, e1;       // what a piece hands on to the next: scale and shift, or eight results
-  unsigned eoff = 0;   // byte offset of the row's channels in column tile 0
+  unsigned eoff = 0;   // byte offset of the row's channels in column tile 0; WIDE: the row itself
   u32x4 epk = {0, 0, 0, 0};
   auto piece = [&](const f32x16& A, int from, int next, int t, int u, int part) __attribute__((always_inline)) {
     if (u < 2) {
@@ -386,13 +387,18 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
         e1 = *reinterpret_cast<const float4*>(turn + turn_get(lane, q, 1));
       }
       const int o = s_orow[32 * t + 16 * q + (lane >> 2)];
-      eoff = o >= 0 ? (unsigned)o * (COUT * 2u) + ocol : kOob;
+      eoff = WIDE ? (unsigned)o : o >= 0 ? (unsigned)o * (COUT * 2u) + ocol : kOob;
     } else if (part < 3) {
       if (from < 0) return;
       const float4 x = part == 1 ? e0 : e1;
       const unsigned r0 = res[t][q][2 * part - 2], r1 = res[t][q][2 * part - 1];
       epk[2 * part - 2] = pack_bf16(fmaxf(x.x + __uint_as_float(r0 << 16), floor_), fmaxf(x.y + __uint_as_float(r0 & 0xffff0000u), floor_));
       epk[2 * part - 1] = pack_bf16(fmaxf(x.z + __uint_as_float(r1 << 16), floor_), fmaxf(x.w + __uint_as_float(r1 & 0xffff0000u), floor_));
+    } else if constexpr (WIDE) {
+      const int o = (int)eoff;
+      const size_t at = (size_t)max(o, 0) * (COUT * 2) + ocol;
+      if (from >= 0 && o >= 0) *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(a.out) + at + from * 512) = epk;
+      if (next >= 0) res[t][q] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(a.res) + at + next * 512);
     } else {
       // (no scalar offset: behind a 16-byte buffer store that has one the compiler leaves no wait state before it writes the store's
       // first data register again, and the store then stores what was written)
@@ -449,7 +455,7 @@ __device__ __forceinline__ void tail_tile(const TailArgs& a, const int row0, con
 // units (measured; a small tile is bound by its weight stream, a large one by LDS fragment reads + MFMAs).  Every
 // workgroup evaluates the same three candidates and takes the cheapest: a small active set spreads over the whole
 // chip, a large one does not leave a nearly empty last round.
-template <int NCT, bool CS>
+template <int NCT, bool CS, bool WIDE>
 __global__ __launch_bounds__(tail::kThreads) void k_tail(const TailArgs a) {
   using namespace tail;
   prefetch_args<sizeof(TailArgs)>();
@@ -485,9 +491,9 @@ __global__ __launch_bounds__(tail::kThreads) void k_tail(const TailArgs a) {
     return;
   }
   switch (pb) {
-    case 1: tail_tile<NCT, 1, CS>(a, row0, M, touched); break;
-    case 2: tail_tile<NCT, 2, CS>(a, row0, M, touched); break;
-    default: tail_tile<NCT, 3, CS>(a, row0, M, touched); break;
+    case 1: tail_tile<NCT, 1, CS, WIDE>(a, row0, M, touched); break;
+    case 2: tail_tile<NCT, 2, CS, WIDE>(a, row0, M, touched); break;
+    default: tail_tile<NCT, 3, CS, WIDE>(a, row0, M, touched); break;
   }
 }
 
@@ -515,11 +521,11 @@ int tail_init_device() {
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 32) return LAUD_ERR_HIP;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return LAUD_ERR_HIP;
   g_tail_cus[dev] = cus;
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tail<4, false>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          tail::lds_bytes(tail::kMaxPB, 1024)) != hipSuccess)
-    return LAUD_ERR_HIP;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tail<4, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             tail::lds_bytes(tail::kMaxPB, 1024)) == hipSuccess ? LAUD_OK : LAUD_ERR_HIP;
+  const auto request = [](const void* kernel) {
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, tail::lds_bytes(tail::kMaxPB, 1024)) == hipSuccess;
+  };
+  return request(reinterpret_cast<const void*>(&k_tail<4, false, false>)) && request(reinterpret_cast<const void*>(&k_tail<4, false, true>)) &&
+                 request(reinterpret_cast<const void*>(&k_tail<4, true, false>)) ? LAUD_OK : LAUD_ERR_HIP;
 }
 
 int launch_tail_pack(const void* w2, const void* w3, int c_out, void* packed, hipStream_t st) {
@@ -548,10 +554,15 @@ int launch_tail(const TailArgs& args, long long cap_rows, hipStream_t st) {
   unsigned grid = (unsigned)((cap_rows + 31) / 32);
   if (a.cp.nblocks) grid += tail::kCopyExtra;
   StageScope scope(LAUD_STAGE_CONV2, st);
-  if (a.sbits)
-    hipLaunchKernelGGL((k_tail<4, true>), dim3(grid), dim3(tail::kThreads), tail::lds_bytes(tail::kMaxPB, 1024), st, a);
-  else
-    hipLaunchKernelGGL((k_tail<4, false>), dim3(grid), dim3(tail::kThreads), tail::lds_bytes(tail::kMaxPB, 1024), st, a);
+  // results past a descriptor's 2 GiB (first blocks: c_out = 1024 is more than what bounds x and h1) go through 64-bit addresses, as
+  // does the residual (channel skipping: c_out = c_in, which is bounded)
+  const bool wide = cap_rows * a.cout * 2 > (long long)tail::kOob;
+  if (a.sbits && wide) return LAUD_ERR_UNSUPPORTED;
+  const dim3 block(tail::kThreads);
+  const int lds = tail::lds_bytes(tail::kMaxPB, 1024);
+  if (a.sbits) hipLaunchKernelGGL((k_tail<4, true, false>), dim3(grid), block, lds, st, a);
+  else if (wide) hipLaunchKernelGGL((k_tail<4, false, true>), dim3(grid), block, lds, st, a);
+  else hipLaunchKernelGGL((k_tail<4, false, false>), dim3(grid), block, lds, st, a);
   return check_launch();
 }
 

@@ -5,6 +5,7 @@
 #include <dlfcn.h>
 #include <signal.h>
 #include <stdio.h>
+#include <string.h>
 #include <sys/mman.h>
 #include <unistd.h>
 
@@ -53,6 +54,7 @@ std::vector<Fiber> fibers(kMaxThreads);
 std::map<const void*, int> lds_requests;  // dynamic LDS a kernel may be launched with, where more than 64 KB
 std::set<std::string> launched;           // kernel instances so far, dynamic LDS and threads of a workgroup behind each
 bool record_only;                         // note launches, run none
+std::string only;                         // ... or run only kernels whose name holds this (empty: all)
 
 void fail(const char* what, const void* at) {
   fprintf(stderr, "%s %p in %s, workgroup %u, %u of %u, %u, thread %u\n", what, at, kernel_name, block.x, block.y, grid.x, grid.y,
@@ -149,7 +151,7 @@ void launch(dim3 g, dim3 b, size_t lds_bytes, const char* kernel, const void* fu
   const auto request = lds_requests.find(function);
   if (lds_bytes > 64 * 1024 && (request == lds_requests.end() || (size_t)request->second < lds_bytes))
     fail("more dynamic LDS than requested:", (void*)lds_bytes);
-  if (record_only) return;
+  if (record_only || !strstr(kernel, only.c_str())) return;
   lds_size = (lds_bytes + 15) / 16 * 16;
   lds = lds_end - lds_size;
   for (unsigned y = 0; y < g.y; ++y)
@@ -232,6 +234,9 @@ extern "C" size_t host_launched(char* out, size_t room) {
 
 // From now on launches are noted only: which kernels a call takes, at sizes that would run for long here.
 extern "C" void host_record_only() { host::record_only = true; }
+
+// From now on only launches of this kernel run: one kernel of a call whose others would run for long.
+extern "C" void host_run_only(const char* kernel) { host::only = kernel; }
 
 extern "C" int laud_probe_mfma() { return 0; }
 extern "C" int laud_probe_read() { return 0; }

@@ -444,3 +444,56 @@ def test_group_blocks_take_first_1x1_and_3x3_in_one_launch(lib, case, capfd):
             call.first("dynamic", n, h, w, ci, co, co, stride, S, 0.5, gw=g, se=se)
         assert f"group_fused {2 if len(case) == 10 else 1}" in tiles(call.launched()), call.launched()
     in_a_process_of_its_own(body, capfd)
+
+
+class Untouched:
+    """A workspace of zeros whose pages stay untouched."""
+
+    def __init__(self, call, nbytes):
+        p = call.buf(nbytes)
+        self.data_ptr, self.numel, self.element_size = (lambda: p), (lambda: int(nbytes)), (lambda: 1)
+
+
+def bf16(a):
+    return (np.asarray(a, np.float32).view(np.uint32) >> 16).astype(np.uint16)
+
+
+def wide_projection(call, n, h, w, ids):
+    """The fused 3x3 -> last 1x1 kernel of a first block of 256 -> 256 -> 1024 channels (stride 1, S = 1), weights and h1 zero: onto the
+    shortcut, which is not run, it adds the last 1x1's shift.  The shortcut is 256 (i + 1) in the i-th listed pixel; returns `out`."""
+    call.host.host_run_only.argtypes = [C.c_char_p]
+    call.host.host_run_only(b"k_tail")
+    ci, m, co = 256, 256, 1024
+    weights = [call.buf(k * 2) for k in (m * ci, 9 * m * m, co * m)]
+    affine = [call.buf(4 * k, np.full(k, v, np.float32)) for k, v in ((m, 1), (m, 0), (m, 1), (m, 0), (co, 1), (co, 64))]
+    p = B.Bottleneck(ci, m, co, *weights, *affine, 1)
+    p.packed = call.buf(B.packed_weights_size(p, B.BF16))
+    fx, out, ids = B.Fmap(n, h, w, ci, B.BF16), call.buf(n * h * w * co * 2), np.array(ids, np.int32)
+    for i, pixel in enumerate(ids):
+        row = bf16(np.full(co, 256 * (i + 1)))
+        C.memmove(out + int(pixel) * co * 2, row.ctypes.data, co * 2)
+    B.laud_dyn_projection_bottleneck(call.buf(n * h * w * ci * 2), fx, p, call.buf(co * ci * 2), affine[4], affine[5], 1, 1, call.buf(ids.nbytes, ids),
+                                     call.buf(4, np.array([len(ids)], np.int32)), out, Untouched(call, B.dyn_projection_workspace(fx, p, 1)))
+    return out
+
+
+@pytest.mark.parametrize("n", [64, 65, 129])
+def test_outputs_of_the_fused_kernel_past_2_gib(lib, n, capfd):
+    """First blocks whose output is wider than what the size rule counts (c_in, c_mid): 64 samples of 128 x 128 are 2 GiB of output, 65
+    more, the last of 129 lies past 4 GiB.  (The threads of a wave run one after the other here: of what they hand each other through LDS
+    some values come late, so that a result is the shortcut plus the shift or, where it came late, plus nothing.)"""
+    pixels = n * 128 * 128
+    ids = sorted({0, 1, 16383, 777777, (1 << 20) - 1, pixels - 16384, pixels - 2, pixels - 1} | ({1 << 20, (1 << 20) + 5} if n > 64 else set()) |
+                 ({1 << 21} if n > 128 else set()))
+
+    def body():
+        call = Call(lib, 0)
+        out = wide_projection(call, n, 128, 128, ids)
+        rows = lambda pixel: np.ctypeslib.as_array((C.c_uint16 * 1024).from_address(out + pixel * 2048))  # noqa: E731
+        assert "k_tail" in call.launched()
+        for i, pixel in enumerate(ids):
+            got = set(rows(pixel).tolist())
+            assert got <= set(bf16([256 * (i + 1), 256 * (i + 1) + 64]).tolist()) and len(got) > 1, (pixel, got)
+        for pixel in {2, 3, 5, 8, 4096, 16384, 16386, 32768} - set(ids):  # (an offset that wraps lands in the first samples)
+            assert not rows(pixel).any(), pixel
+    in_a_process_of_its_own(body, capfd)
