@@ -960,6 +960,21 @@ static int run_shortcut_and_conv1(const GemmArgs& a, long long rows, const laud_
   return rc != LAUD_OK ? rc : launch_gemm<M_SD1>(fx.dtype, b, b.m_rows, 1, st);
 }
 
+// A first block of few rows, whose shortcut and first 1x1 go in one launch: first 1x1 and group 3x3 in one launch, with the shortcut in
+// one of its own, save none, and are the longer pair unless the first 1x1 fills the chip (64 x 64 tiles of its rows; more of them for
+// longer reductions, which k_group_fused takes slice by slice where the small tiles split them).  3000 blocks of up to 12000 outputs, 8 to 480
+// channels, groups of 8 and 16, fused against that pair, medians of the whole block's time.  No stride, 1 / 2 / 3 / 4 slices of c_in: below 64 tiles
+// 1.04 / 1.09 / 1.15 / 1.20, 64 to 95 0.98 / 1.03 / 1.08 / 1.12, from 96 on 0.93 / 0.94 / 1.02 / 0.99.  Stride two, where four pixels of h1 for
+// an output stay off memory: 1.00 / 1.04 / 1.08 / 1.12 below 64 tiles, 0.94 / 1.01 / 1.03 / 1.07 to 95, 0.9 / 0.9 / 0.99 / 1.04 from 96 on (two slices
+// by outputs: 1.04 up to 256, 1.02 up to 1024, 0.93 past them); five and six slices 1.2 below 64 tiles, 1.04 to 159, 0.97 from there on.
+static bool shortcut_pair_faster(const GemmArgs& shortcut, long long nout, const laud_fmap& fx, const laud_bottleneck* p, const void* x, void* h1, int stride) {
+  const GemmArgs b = dense_conv1_args(fx, p, x, h1);
+  if (!skinny_pair_wanted(fx.dtype, shortcut, nout, b, b.m_rows)) return false;
+  const long long slices = (p->c_in + 63) / 64, tiles = ((long long)b.m_rows + 63) / 64 * ((p->c_mid + 63) / 64);
+  if (stride > 1) return nout <= 256 ? slices > 1 : slices > 2 && tiles < (slices > 4 ? 160 : 64);
+  return tiles < 32 + 32 * slices;
+}
+
 // conv2 -> conv3 -> residual add as one kernel where laud_tail.hip covers the shape (h2 stays in LDS).
 // Returns 1 when that kernel was launched (*rc = its status), 0 when the caller has to run the two GEMMs.
 static int try_tail(int dtype, const laud_bottleneck* p, const laud_group_se* e, const void* h1, const void* res,
@@ -1404,7 +1419,8 @@ static int run_dyn_projection(const void* x, laud_fmap fx, const laud_bottleneck
   a.list = idx; a.count = count;
   GemmArgs g{};
   g.H = fx.H; g.W = fx.W; g.S = S; g.Ho = Ho; g.Wo = Wo; g.stride = stride;
-  const bool fused_conv2 = try_group_fused(fx.dtype, g, p, e, x, h2, idx, count, Hp * Wp == 1, nout, st, &rc) != 0;
+  const bool fused_conv2 = e && !shortcut_pair_faster(a, nout, fx, p, x, h1, stride) &&
+                           try_group_fused(fx.dtype, g, p, e, x, h2, idx, count, Hp * Wp == 1, nout, st, &rc) != 0;
   if (fused_conv2) {
     if (rc != LAUD_OK || (rc = launch_gemm<M_SD1>(fx.dtype, a, nout, 1, st)) != LAUD_OK) return rc;
   } else if (dense_conv1_wanted(fx.dtype, p, npix, Hp * Wp == 1) && !head_used(fx.dtype, p, npix)) {

@@ -497,3 +497,25 @@ def test_outputs_of_the_fused_kernel_past_2_gib(lib, n, capfd):
         for pixel in {2, 3, 5, 8, 4096, 16384, 16386, 32768} - set(ids):  # (an offset that wraps lands in the first samples)
             assert not rows(pixel).any(), pixel
     in_a_process_of_its_own(body, capfd)
+
+
+# First blocks of few rows with groups (n, h, w, c_in, c, group width, stride, S): those whose shortcut and first 1x1 are faster in one launch
+# than the 3x3 with the first 1x1, and the nearest ones that are not.
+SHORTCUT_PAIR = [(1, 4, 4, 112, 16, 8, 1, 2), (2, 14, 14, 144, 320, 16, 1, 1), (4, 7, 7, 208, 440, 8, 1, 1), (33, 4, 4, 64, 288, 16, 1, 2),
+                 (63, 8, 8, 64, 16, 16, 1, 4), (95, 8, 8, 128, 16, 16, 1, 4), (1, 7, 7, 8, 8, 8, 1, 7), (4, 16, 16, 96, 48, 16, 2, 2), (63, 8, 8, 136, 16, 16, 2, 2),
+                 (159, 8, 8, 328, 16, 16, 2, 4)]
+NOT_SHORTCUT_PAIR = [(64, 8, 8, 64, 16, 16, 1, 4), (96, 8, 8, 128, 16, 16, 1, 4), (4, 16, 16, 64, 48, 16, 2, 2), (5, 16, 16, 96, 48, 16, 2, 2), (64, 8, 8, 136, 16, 16, 2, 2), (160, 8, 8, 328, 16, 16, 2, 4),
+                     (1, 112, 112, 32, 64, 16, 2, 4), (1, 56, 56, 64, 144, 16, 2, 2), (3, 28, 28, 144, 320, 16, 2, 2)]
+
+
+@pytest.mark.parametrize("case", SHORTCUT_PAIR + NOT_SHORTCUT_PAIR)
+def test_small_first_blocks_keep_shortcut_and_first_1x1_in_one_launch(lib, case, capfd):
+    n, h, w, ci, c, g, stride, S = case
+
+    def body():
+        call = Call(lib, 0)
+        call.host.host_record_only()
+        call.first("dynamic", n, h, w, ci, c, c, stride, S, 0.5, gw=g, se=0)
+        names = call.launched()
+        assert ("k_skinny_pair" in names, "k_group_fused" in names) == (case in SHORTCUT_PAIR, case in NOT_SHORTCUT_PAIR), names
+    in_a_process_of_its_own(body, capfd)
