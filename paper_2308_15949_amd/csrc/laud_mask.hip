@@ -198,8 +198,10 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_ballot(const uint8_
 // Pooling, threshold and ordered compaction in one launch for S = 1, 2 and 4.  As in k_compact_ballot, of which it is the same chain of trips,
 // a block decides the patches of the blocks before its own 1024 by itself, in pooled_decision's summation order and hence alike, CH blocks
 // at a time, so that none waits for another.  The last block reads all projections for that, from one compute unit: up to about 128 KB, or
-// twelve blocks' trips, the second launch costs more (blocks of stage 1 to 3, two launches / one: 7840 patches of one pixel 31.7 / 30.0 us, 12544
-// 30.1 / 29.8, 18816 36.8 / 38.1; of 2 x 2, 7840 28.2 / 26.9, 12544 34.0 / 34.7; of 4 x 4, 1960 27.4 / 26.9, 3136 31.0 / 31.0).
+// twelve blocks' trips, the second launch costs more (blocks of stage 1 to 3, two launches / one: 7840 patches of one pixel 31.7 / 30.0 us,
+// 12544 30.1 / 29.8, 18816 36.8 / 38.1; of 2 x 2, 7840 28.2 / 26.9, 12544 34.0 / 34.7; of 4 x 4, 1960 27.4 / 26.9, 3136 31.0 / 31.0).  Where a
+// sample's gate stands behind each patch's projection a trip is twice as long: eight blocks, one trip, of one pixel (7840 of stage 2 even,
+// 9408 of stage 1 / 2 28.4 / 30.6 and 32.3 / 34.5).
 // (6272 patches of one pixel, stage 4 of 128 images, in two launches 9.5 us, here 5.1; of 2 x 2, with scans of the counts by shuffles and
 // three barriers 6.2, here 4.8; 49 of them, one image, 1.9 and 1.35.)
 struct PoolCompactArgs {
@@ -209,7 +211,7 @@ struct PoolCompactArgs {
   uint8_t* mask;
   int32_t* idx; int32_t* count; int32_t* sample_offsets;
 };
-constexpr int pool_fused_max(int S) { return S == 1 ? 12288 : S == 2 ? 8192 : S == 4 ? 2048 : 0; }
+constexpr int pool_fused_max(int S, bool gates) { return S == 1 ? (gates ? 8192 : 12288) : S == 2 ? 8192 : S == 4 ? 2048 : 0; }
 template <int S>
 struct Pooled {
   float v[S * S];
@@ -408,7 +410,7 @@ int launch_pool_compact(const float* proj, int N, int H, int W, int S, float bia
   PoolArgs pa{proj, keep, logits, H, W, S, bias};
   // (blocks read the gates of earlier ones': not where the mask is written over them)
   const bool over = keep && keep < mask + npatch && mask < keep + N;
-  if (npatch > 0 && npatch <= pool_fused_max(S) && (!over || npatch <= kCompactThreads)) {
+  if (npatch > 0 && npatch <= pool_fused_max(S, keep != nullptr) && (!over || npatch <= kCompactThreads)) {
     StageScope scope(LAUD_STAGE_COMPACT, stream);
     const PoolCompactArgs k{pa, make_fast_div(pps), make_fast_div(W / S), npatch, pps, W / S, mask, idx, count, sample_offsets};
     const dim3 grid((npatch + kCompactThreads - 1) / kCompactThreads), block(std::min(kCompactThreads, (npatch + kWave - 1) / kWave * kWave));

@@ -519,3 +519,26 @@ def test_small_first_blocks_keep_shortcut_and_first_1x1_in_one_launch(lib, case,
         names = call.launched()
         assert ("k_skinny_pair" in names, "k_group_fused" in names) == (case in SHORTCUT_PAIR, case in NOT_SHORTCUT_PAIR), names
     in_a_process_of_its_own(body, capfd)
+
+
+# Where the masker's decision of the patches and their list are made (n, h, w, S, with gates): in one launch up to a number of patches (less with
+# gates where a patch is one pixel), in two past it.
+POOL_ROUTES = [
+    ((8, 32, 32, 1, True), "k_pool_compact<1, 8>"), ((9, 32, 32, 1, True), "k_pool_mask"), ((12, 32, 32, 1, True), "k_pool_mask"),
+    ((12, 32, 32, 1, False), "k_pool_compact<1, 8>"), ((13, 32, 32, 1, False), "k_pool_mask"),
+    ((32, 32, 32, 2, True), "k_pool_compact<2, 8>"), ((33, 32, 32, 2, True), "k_pool_mask"), ((32, 32, 32, 4, True), "k_pool_compact<4, 1>"),
+    ((33, 32, 32, 4, False), "k_pool_mask"),
+]
+
+
+@pytest.mark.parametrize("case,kernel", POOL_ROUTES)
+def test_masker_decides_its_patches_in(lib, case, kernel, capfd):
+    n, h, w, S, keep = case
+
+    def body():
+        call = Call(lib, 0)
+        call.host.host_record_only()
+        call.identity("masker", n, h, w, 16, 8, S, 0.5, keep=keep)
+        found = set(re.findall(r"k_pool_\w+(?:<\d, \d>)?", call.launched())) | set(re.findall(r"k_skinny<14", call.launched()))
+        assert found == {kernel}, call.launched()
+    in_a_process_of_its_own(body, capfd)
