@@ -84,6 +84,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void k_pipe(const PipeArgs ka) {
   constexpr int STAGE = (BM + BN) * 128;
   static_assert(NW % 2 == 0 && LA >= 1 && LB >= 1 && TM >= 1 && TN >= 1 && NT >= BM && NS >= 3, "tile and waves do not fit");
   static_assert(KS == 1 || (KS == 2 && NB % 2 == 0), "the two K groups share the result blocks");
+  static_assert(MODE != M_DENSE1 || KS == 1, "the K groups' exchange would overwrite the projection's partial sums while other waves read them");
   constexpr bool TAPS = (MODE == M_CONV2 || MODE == M_CS2 || MODE == M_U2 || MODE == M_SD2 || MODE == M_G2);
   constexpr bool CS = (MODE >= M_CS1 && MODE <= M_CS3);
   constexpr bool RES = (MODE == M_CONV3 || MODE == M_CS3 || MODE == M_SD3);

@@ -150,3 +150,15 @@ def test_lds_direct_loads_meet_no_static_lds():
                 text = re.sub(r"//.*", "", f.read())
             if re.search(r"\bdma(4|16)\(", text) and name not in ("laud_tile_util.h", "laud_static.hip"):
                 assert not re.search(r"(?<!extern )__shared__", text), name
+
+
+@pytest.mark.parametrize("mode,builds", [("M_SD1", True), ("M_DENSE1", False)])
+def test_masker_projection_and_two_k_groups_do_not_build_together(tmp_path, mode, builds):
+    """The exchange between two groups of waves that share the K steps lies over the partial sums of the masker projection, with no barrier
+    between: the tiled kernel refuses the combination."""
+    (tmp_path / "tile.hip").write_text('#include "laud_pipe.h"\n'
+                                       f"template __global__ void laud::k_pipe<laud::{mode}, laud::bf16_t, 64, 128, 2, 2, 2, 6>(const laud::PipeArgs);\n")
+    made = subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *B.FLAGS, "--cuda-device-only", "-fsyntax-only", str(tmp_path / "tile.hip")],
+                          capture_output=True, text=True)
+    assert (made.returncode == 0) == builds, made.stderr
+    assert builds or "partial sums" in made.stderr, made.stderr
