@@ -619,8 +619,8 @@ def test_masker_dyn_bottleneck(G, case, inplace, use_keep):
     assert_close(got[up], ref[up], TOL[dt], "fused masker block")
 
 
-# Pooling and list in one launch: one wave, part of a block, blocks either side of 1024 patches, the last size of each granularity and the
-# first of the two launches past it.
+# Pooling and list without a launch of the decision's own: up to 1024 patches in the small 3x3 (one wave, part of a block, a whole one), past
+# them in one launch, up to the last size of each granularity, and the first of the two launches past it.
 POOLED = [(1, 7, 7, 1), (3, 19, 18, 1), (12, 32, 32, 1), (13, 32, 32, 1), (1, 16, 14, 2), (4, 32, 32, 2), (5, 30, 30, 2), (32, 32, 32, 2), (33, 32, 32, 2), (2, 32, 32, 2),
           (1, 8, 8, 4), (1, 32, 36, 4), (9, 44, 44, 4), (32, 32, 32, 4), (33, 32, 32, 4), (8, 32, 32, 4), (4, 16, 16, 1), (16, 32, 32, 4), (5, 20, 20, 2)]
 

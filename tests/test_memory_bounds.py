@@ -12,6 +12,7 @@ import pytest
 import test_gpu_first
 import test_gpu_group_se
 import test_gpu_narrow
+import test_gpu_pooled_lists
 from paper_2308_15949_amd import binding as B
 from paper_2308_15949_amd import build as build_rules
 
@@ -222,6 +223,8 @@ CASES = {
     "masker_64x128_f32": ("identity", "masker", 6, 28, 28, 24, 200, 4, 0.5, False),
     "masker_64x64_f32": ("identity", "masker", 21, 28, 28, 24, 40, 4, 0.5, False),
     "masker_widest": ("identity", "masker", 3, 30, 30, 4096, 264, 2, 0.5),
+    "masker_four_patches_a_thread": ("identity", "masker", 13, 32, 32, 16, 8, 4, 0.5, True, False, None, 0, False, True),
+    "masker_two_blocks_of_patches": ("identity", "masker", 9, 24, 24, 16, 8, 2, 0.5),
     # first blocks
     "static": ("first", "static", 2, 13, 9, 40, 24, 96, 2, 1, 1.0),
     "static_shortcut_128x256": ("first", "static", 32, 28, 28, 8, 64, 264, 1, 1, 1.0),
@@ -541,4 +544,45 @@ def test_masker_decides_its_patches_in(lib, case, kernel, capfd):
         call.identity("masker", n, h, w, 16, 8, S, 0.5, keep=keep)
         found = set(re.findall(r"k_pool_\w+(?:<\d, \d>)?", call.launched())) | set(re.findall(r"k_skinny<14", call.launched()))
         assert found == {kernel}, call.launched()
+    in_a_process_of_its_own(body, capfd)
+
+
+@pytest.mark.parametrize("case,threads", test_gpu_pooled_lists.PARTIAL)
+def test_lists_of_less_than_a_block_are_launched_in_fewer_waves(lib, case, threads, capfd):
+    """(the sizes of the GPU test of that launch: that they are about it)"""
+    def body():
+        n, h, w, c, m, S = case[:6]
+        call = Call(lib, 0)
+        call.host.host_record_only()
+        call.identity("masker", n, h, w, c, m, S, 0.5)
+        assert re.findall(r"k_pool_compact<(\d), \d>.* threads (\d+)", call.launched()) == [(str(S), str(threads))], call.launched()
+    in_a_process_of_its_own(body, capfd)
+
+
+@pytest.mark.parametrize("case,threads", test_gpu_pooled_lists.IN_3X3)
+def test_few_patches_are_decided_in_the_3x3(lib, case, threads, capfd):
+    def body():
+        n, h, w, c, m, S, dtype = case[:7]
+        call = Call(lib, 0)
+        call.host.host_record_only()
+        call.identity("masker", n, h, w, c, m, S, 0.5, dtype == B.BF16)
+        assert re.findall(r"k_skinny<14, .* threads (\d+)", call.launched()) == [str(threads)] and "k_pool" not in call.launched(), call.launched()
+    in_a_process_of_its_own(body, capfd)
+
+
+@pytest.mark.parametrize("apart,kernel", [(-40, "k_skinny<14"), (40, "k_skinny<14"), (0, "k_pool_compact<4, 1>"), (39, "k_pool_compact<4, 1>"), (-39, "k_pool_compact<4, 1>")])
+@pytest.mark.parametrize("n", [40, 1100])
+def test_masks_over_their_gates_are_decided_by_one_reader_a_gate(lib, n, apart, kernel, capfd):
+    """Every workgroup of the 3x3, and every later block of the list's launch, reads the gates again: not where the mask is written over
+    them (gates `apart` of n bytes from the mask's)."""
+    def body():
+        call = Call(lib, 0)
+        call.host.host_record_only()
+        fx, x, p = B.Fmap(n, 4, 4, 16, B.BF16), call.values(n * 256, True), call.block(16, 8, 16, None, True, False)
+        both = call.buf(3 * n)
+        mask, gates = both + n, both + n + (apart if abs(apart) < 40 else n if apart > 0 else -n)
+        B.laud_masker_dyn_bottleneck(x, fx, p, 4, call.values(16, False), 0.01, gates, mask, call.buf(4 * n), call.buf(4), None, None, x,
+                                     call.ws(B.workspace_size(B.OP_DYN_BOTTLENECK, fx, p, 4)))
+        found = set(re.findall(r"k_pool_\w+(?:<\d, \d>)?", call.launched())) | set(re.findall(r"k_skinny<14", call.launched()))
+        assert found == {kernel if n == 40 else "k_pool_compact<4, 1>" if abs(apart) == 40 else "k_pool_mask"}, call.launched()
     in_a_process_of_its_own(body, capfd)
