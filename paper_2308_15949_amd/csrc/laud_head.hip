@@ -11,11 +11,12 @@
 //   * the masker projection sum_c w[c] * x[pixel][c] is formed on the vector ALU from the same LDS slices, every wave an equal share
 //     of every slice, partial sums meet in LDS at the end.
 //
-// What bounds it (128 x 14 x 14 x 1024, 196 tiles of 128 rows): 16 slices of 1024 cycles of MFMAs between 2.5 us until the first rows
-// are there and 2 us of stores.  What is not a MFMA stands behind one each, in pieces that take no longer: the two waves of a SIMD issue
-// in step, and what both do between their MFMAs the matrix pipe waits for.  In a row ahead of the MFMAs, with the projection of a
-// K step on one wave and the rows' 16-byte stores 512 bytes apart, a slice took 1610 cycles, the stores 4200, the launch 21.8 us;
-// now 1320, 2900 and 18.4 (one input over and over; with x cold in HBM the slices wait for it, 3.3 TB/s).
+// What bounds it (128 x 14 x 14 x 1024, 196 tiles of 128 rows): 16 slices of 1024 cycles of MFMAs, beside 768 of the vector-memory path, at 1.9 GHz.
+// What is not a MFMA stands behind one each, in pieces that take no longer: the two waves of a SIMD issue in step, and what both do between
+// their MFMAs the matrix pipe waits for.  In a row ahead of the MFMAs, with the projection of a K step on one wave and the rows' 16-byte stores
+// 512 bytes apart, a slice took 1610 cycles, the stores 4200, the launch 21.8 us.  Now (stamps, one input over and over): 5518 cycles until the
+// first rows are there, 16 x 1268, stores 2708, projection 1276: 15.6 us at 1.91 GHz, 0.6 between the workgroups, 2.6 of the launch around
+// them.  With x cold in HBM a slice takes 1664 (3.3 TB/s) and the launch 24.7.
 #include "laud_common.h"
 #include "laud_tail_pack.h"
 #include "laud_tile_util.h"

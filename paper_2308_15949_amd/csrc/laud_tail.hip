@@ -21,11 +21,12 @@
 //     same weight ring (no barrier at all in that phase), reads the residual, adds, applies the
 //     activation, rounds and stores.
 //
-// What bounds it: the compute unit's vector-memory path of 64 bytes a cycle.  A 64-pixel tile brings 40 KB a slice of the 3x3 and 32 KB
-// of weights, 8 KB of residual and 8 KB of results a slice of the last 1x1; measured are 690 and 900 cycles where the path alone takes
-// 640 and 768 (12544 pixels; MFMAs 512).  Ahead of it stand 2.7 us of count -> list -> rows, in whose shadow the tables and the
-// first weights come.  The launch 33.5 -> 31.0 us with tables and weights out of the rows' way, the last 1x1's epilogue in pieces of one
-// MFMA's time and results stored through a descriptor.
+// What bounds it: the compute unit's vector-memory path of 64 bytes a cycle, at the clock this load leaves.  A 64-pixel tile brings 40 KB a slice
+// of the 3x3 and 32 KB of weights, 8 KB of residual and 8 KB of results a slice of the last 1x1: 640 and 768 cycles of the path (MFMAs 512).
+// Stamps, 12544 pixels in place, inputs in turn, 1.71 GHz: 1818 cycles until the count is there, 6514 list -> rows (in whose shadow the
+// tables and the first weights come), 36 x 675, 1284 for h2, 16 x 931 with the last epilogue: 28.5 us, 1.2 more between the first and the last
+// workgroup, 4.7 of the launch around them.  The launch 33.5 -> 31.0 us with tables and weights out of the rows' way, the last 1x1's
+// epilogue in pieces of one MFMA's time and results stored through a descriptor (maps past its 2 GiB: WIDE).
 //
 // Channel skipping (Fig. 2(c)) rides on the same kernel (template flag CS): the "patches" are whole samples in
 // mask-pattern order, the 3x3 leaves out the 64-channel input slices whose group no row of the tile keeps, and h2 is
